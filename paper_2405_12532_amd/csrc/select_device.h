@@ -1,25 +1,39 @@
 // Device code of the segmented top-k (Algorithm 1, TopP(A_e, p) with the retention ratio turned
 // into a count, followed by the recent window that is always kept), written for a workgroup of
-// any multiple of 64 lanes; the selection kernel (select.hip) runs it with 1024 lanes per sequence.
+// any multiple of 64 lanes; the selection kernel (select.hip) runs it, one workgroup per sequence.
 //
 // The paper names the sort inside TopP as the one extra cost of the method that matters
 // (Appendix A.1).  Nothing is sorted here: the workgroup finds the value of the need-th largest
-// context score with a most-significant-digit-first radix select on the fp32 bit patterns
-// (4 passes of 8 bits, histogram in LDS), then emits the survivors with wavefront ballots and
-// prefix counts, which yields ascending positions for free.  Ties at the threshold go to the
-// lower positions.
+// context score with a most-significant-digit-first radix select on the fp32 bit patterns, then
+// emits the survivors with wavefront ballots and prefix counts, which yields ascending positions
+// for free.  Ties at the threshold go to the lower positions.
+//
+// Bound: latency (a few KB per sequence, one workgroup): barriers and passes over the keys.  The radix
+// select therefore skips the leading bits that all keys share (minimum and maximum are known from
+// staging them), takes digits of 11 bits, and stops as soon as the digit's bin holds at most
+// kCandidates keys, which are then ranked against each other directly: at the score distributions of
+// the method that is one pass instead of the four that fixed 8-bit digits take (us per launch, before / now: one
+// sequence of 256 tokens 6.4 / 4.9, of 2048 9.5 / 6.3, of 8192 27 / 10.4, four of 32768 64 / 25).
 #pragma once
 
 #include "pyr_internal.h"
 
 namespace pyr {
 
+constexpr int kDigitBits = 11;
+constexpr int kBins = 1 << kDigitBits;
+constexpr int kCandidates = 256;
+
 // LDS the selection needs besides the staged keys
 struct SelectShared {
-    uint32_t hist[256];
+    uint32_t hist[kBins];
+    uint32_t cand[kCandidates];
     int wave_cnt[2 * 16];
-    int bcast[2];
     int red[16];
+    uint32_t wave_min[16], wave_max[16];
+    int n_cand;
+    int bcast[3];
+    uint32_t tau;
 };
 
 // Monotone map float -> uint32 (larger float, larger key); -0 is folded onto +0 so that
@@ -41,84 +55,136 @@ __device__ __forceinline__ uint32_t get_key(const uint32_t* lds_keys, const floa
     return ordered_key(g[i]);
 }
 
-// The body after the keys are reachable through get_key<kStaged>; kT lanes (a multiple of 64, at most 1024).
+// The body after the keys are reachable through get_key<kStaged> and their minimum and maximum are known
+// (sh->hist zeroed, both behind a barrier); kT lanes (a multiple of 64, at most 1024).
 template <bool kStaged, int kT>
-__device__ void select_body(const uint32_t* lds_keys, const float* __restrict__ sc, int C, int need,
+__device__ void select_body(const uint32_t* lds_keys, const float* __restrict__ sc, int C, int need, uint32_t kmin, uint32_t kmax,
                             int32_t row0, int32_t* __restrict__ out, SelectShared* sh) {
     constexpr int kW = kT / 64;
+    constexpr int kPer = kBins / kT;            // bins a lane scans
+    constexpr int kAhead = 4;                   // keys a lane fetches before it uses the first
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c_round = (C + kT - 1) / kT * kT;
-    uint32_t* hist = sh->hist;
 
-    // ---- radix select: threshold key `prefix` and the number of ties still to admit
-    uint32_t prefix = 0, mask = 0;
-    int remaining = need;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        for (int i = tid; i < 256; i += kT) hist[i] = 0;
-        __syncthreads();
-        for (int i = tid; i < c_round; i += kT) {
-            const bool valid = i < C;
-            const uint32_t key = valid ? get_key<kStaged>(lds_keys, sc, i) : 0u;
-            bool match = valid && ((key & mask) == prefix);
-            const uint32_t digit = (key >> shift) & 255u;
-            // Scores of one sequence share their leading bits, so most lanes of a wavefront
-            // hit the same bin: peel the two most common digits with ballots first.
-            uint64_t active = __ballot(match);
-#pragma unroll 1
-            for (int round = 0; round < 2 && active != 0; ++round) {
-                const int leader = __ffsll((unsigned long long)active) - 1;
-                const uint32_t dl = __builtin_amdgcn_readlane(digit, leader);
-                const uint64_t same = __ballot(match && digit == dl);
-                if (lane == leader) atomicAdd(&hist[dl], (uint32_t)__popcll(same));
-                match = match && digit != dl;
-                active &= ~same;
+    // ---- radix select: threshold key tau and the number of ties still to admit
+    uint32_t tau = kmin;
+    int ties = need;                            // (all keys equal: the first `need` of them)
+    if (kmin != kmax) {
+        int bits_left = 32 - __clz((int)(kmin ^ kmax));        // the keys differ in their low bits_left bits only
+        int remaining = need;
+        uint64_t prefix = (uint64_t)kmin >> bits_left;
+        while (true) {
+            const int nbits = min(kDigitBits, bits_left), shift = bits_left - nbits;
+            for (int i0 = tid - lane; i0 < C; i0 += kAhead * kT) {      // (whole wavefronts: the ballots below)
+                uint32_t keys[kAhead];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const int i = i0 + u * kT + lane;
+                    keys[u] = i < C ? get_key<kStaged>(lds_keys, sc, i) : 0u;
+                }
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const bool match = i0 + u * kT + lane < C && ((uint64_t)keys[u] >> bits_left) == prefix;
+                    const uint32_t digit = (keys[u] >> shift) & ((1u << nbits) - 1);
+                    // equal digits throughout a wavefront (many equal scores) are counted by one lane
+                    const uint64_t active = __ballot(match);
+                    if (active == 0) continue;
+                    const int leader = __ffsll((unsigned long long)active) - 1;
+                    const uint32_t dl = __builtin_amdgcn_readlane(digit, leader);
+                    if (__ballot(match && digit == dl) == active) {
+                        if (lane == leader) atomicAdd(&sh->hist[dl], (uint32_t)__popcll(active));
+                    } else if (match) {
+                        atomicAdd(&sh->hist[digit], 1u);
+                    }
+                }
             }
-            if (match) atomicAdd(&hist[digit], 1u);
-        }
-        __syncthreads();
-        if (wave == 0) {
-            // lane l owns bins 255-4l .. 252-4l (descending order of value)
-            const int top = 255 - 4 * lane;
-            const uint32_t h0 = hist[top], h1 = hist[top - 1], h2 = hist[top - 2], h3 = hist[top - 3];
-            const int mine = (int)(h0 + h1 + h2 + h3);
+            __syncthreads();
+            // lane t owns bins kBins-1 - kPer*t downwards (descending order of value)
+            const int top = kBins - 1 - kPer * tid;
+            uint32_t h[kPer];
+            int mine = 0;
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                h[u] = sh->hist[top - u];
+                mine += (int)h[u];
+            }
             int incl = mine;
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1) {
                 const int up = __shfl_up(incl, d);
                 if (lane >= d) incl += up;
             }
-            const int excl = incl - mine;
-            if (excl < remaining && remaining <= incl) {
-                int run = excl, sel = top - 3;
-                const uint32_t hh[4] = {h0, h1, h2, h3};
+            if (lane == 63) sh->red[wave] = incl;
+            if (tid == 0) sh->n_cand = 0;
+            __syncthreads();
+            int run = incl - mine;
+            for (int u = 0; u < wave; ++u) run += sh->red[u];
+            if (run < remaining && remaining <= run + mine) {
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    if (run + (int)hh[b] >= remaining) { sel = top - b; break; }
-                    run += (int)hh[b];
+                for (int u = 0; u < kPer; ++u) {
+                    if (run < remaining && remaining <= run + (int)h[u]) {
+                        sh->bcast[0] = top - u;
+                        sh->bcast[1] = remaining - run;
+                        sh->bcast[2] = (int)h[u];
+                    }
+                    run += (int)h[u];
                 }
-                sh->bcast[0] = sel;
-                sh->bcast[1] = remaining - run;
             }
+            __syncthreads();
+            prefix = (prefix << nbits) | (uint32_t)sh->bcast[0];
+            remaining = sh->bcast[1];
+            const int in_bin = sh->bcast[2];
+            bits_left = shift;
+            if (bits_left == 0) {                              // every bit decided: the bin's keys are equal
+                tau = (uint32_t)prefix;
+                ties = remaining;
+                break;
+            }
+            if (in_bin <= kCandidates) {
+#pragma unroll 4
+                for (int i = tid; i < C; i += kT) {
+                    const uint32_t key = get_key<kStaged>(lds_keys, sc, i);
+                    if (((uint64_t)key >> bits_left) == prefix) sh->cand[atomicAdd(&sh->n_cand, 1)] = key;
+                }
+                __syncthreads();
+                if (tid < in_bin) {
+                    const uint32_t my = sh->cand[tid];
+                    int gt = 0, eq = 0;
+                    for (int u = 0; u < in_bin; ++u) {
+                        const uint32_t o = sh->cand[u];
+                        gt += o > my;
+                        eq += o == my;
+                    }
+                    if (gt < remaining && remaining <= gt + eq) {      // (equal candidates all write the same)
+                        sh->tau = my;
+                        sh->bcast[0] = remaining - gt;
+                    }
+                }
+                __syncthreads();
+                tau = sh->tau;
+                ties = sh->bcast[0];
+                break;
+            }
+            for (int i = tid; i < kBins; i += kT) sh->hist[i] = 0;
+            __syncthreads();
         }
-        __syncthreads();
-        prefix |= (uint32_t)sh->bcast[0] << shift;
-        mask |= 255u << shift;
-        remaining = sh->bcast[1];
-        // (the next pass starts with a barrier after clearing hist, which also orders these reads)
     }
-    const uint32_t tau = prefix;
-    const int ties = remaining;                 // >= 1 ties at tau are admitted, lowest positions first
+    // ties >= 1 keys equal to tau are admitted, lowest positions first
 
     // ---- ordered emission: wavefront `wave` owns positions [wave*seg, (wave+1)*seg)
     const int seg = (C + kW * 64 - 1) / (kW * 64) * 64;
     const int lo = wave * seg;
     const int hi = min(C, lo + seg);
     int n_gt = 0, n_eq = 0;
-    for (int i0 = lo; i0 < hi; i0 += 64) {
-        const int i = i0 + lane;
-        const uint32_t key = i < hi ? get_key<kStaged>(lds_keys, sc, i) : 0u;
-        n_gt += __popcll(__ballot(i < hi && key > tau));
-        n_eq += __popcll(__ballot(i < hi && key == tau));
+#pragma unroll 4
+    for (int i = lo + lane; i < hi; i += 64) {
+        const uint32_t key = get_key<kStaged>(lds_keys, sc, i);
+        n_gt += key > tau;
+        n_eq += key == tau;
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        n_gt += __shfl_xor(n_gt, d);
+        n_eq += __shfl_xor(n_eq, d);
     }
     if (lane == 0) { sh->wave_cnt[2 * wave] = n_gt; sh->wave_cnt[2 * wave + 1] = n_eq; }
     __syncthreads();
@@ -126,18 +192,26 @@ __device__ void select_body(const uint32_t* lds_keys, const float* __restrict__ 
     for (int u = 0; u < wave; ++u) { gt_before += sh->wave_cnt[2 * u]; eq_before += sh->wave_cnt[2 * u + 1]; }
     int kept_cnt = gt_before + min(eq_before, ties);
     const uint64_t lt = lanemask_lt();
-    for (int i0 = lo; i0 < hi; i0 += 64) {
-        const int i = i0 + lane;
-        const uint32_t key = i < hi ? get_key<kStaged>(lds_keys, sc, i) : 0u;
-        const bool gt = i < hi && key > tau;
-        const bool eq = i < hi && key == tau;
-        const uint64_t eq_mask = __ballot(eq);
-        const int eq_rank = eq_before + __popcll(eq_mask & lt);
-        const bool keep = gt || (eq && eq_rank < ties);
-        const uint64_t keep_mask = __ballot(keep);
-        if (keep) out[kept_cnt + __popcll(keep_mask & lt)] = row0 + i;
-        kept_cnt += __popcll(keep_mask);
-        eq_before += __popcll(eq_mask);
+    for (int i0 = lo; i0 < hi; i0 += 64 * kAhead) {
+        uint32_t keys[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int i = i0 + 64 * u + lane;
+            keys[u] = i < hi ? get_key<kStaged>(lds_keys, sc, i) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int i = i0 + 64 * u + lane;
+            const bool gt = i < hi && keys[u] > tau;
+            const bool eq = i < hi && keys[u] == tau;
+            const uint64_t eq_mask = __ballot(eq);
+            const int eq_rank = eq_before + __popcll(eq_mask & lt);
+            const bool keep = gt || (eq && eq_rank < ties);
+            const uint64_t keep_mask = __ballot(keep);
+            if (keep) out[kept_cnt + __popcll(keep_mask & lt)] = row0 + i;
+            kept_cnt += __popcll(keep_mask);
+            eq_before += __popcll(eq_mask);
+        }
     }
 }
 
@@ -150,24 +224,59 @@ __device__ void select_sequence(int b, const float* __restrict__ scores, const i
                                 SelectShared* sh, int32_t* __restrict__ kept_idx, int32_t* __restrict__ out_offsets) {
     constexpr int kW = kT / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-
-    // packed position of this sequence's output: sum of the keep counts before it
-    int part = 0;
-    for (int u = tid; u < b; u += kT) part += keep_len[u];
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) part += __shfl_xor(part, d);
-    if (lane == 0) sh->red[wave] = part;
-    __syncthreads();
-    int out_base = 0;
-#pragma unroll
-    for (int u = 0; u < kW; ++u) out_base += sh->red[u];
-
     const int32_t row0 = seq_offsets[b];
     const int S = seq_offsets[b + 1] - row0;
     const int L = min(w, S);
     const int k = min(max(keep_len[b], L), S);
     const int C = S - L;                        // context positions, the candidates
     const int need = k - L;                     // how many of them survive
+    const float* __restrict__ sc = scores + row0;
+
+    // packed position of this sequence's output: sum of the keep counts before it
+    int part = 0;
+    for (int u = tid; u < b; u += kT) part += keep_len[u];
+
+    // keys to LDS (if they fit), their minimum and maximum
+    const bool staged = C <= lds_cap;
+    const bool ranked = need > 0 && need < C;   // else there is nothing to decide
+    uint32_t kmin = 0xffffffffu, kmax = 0u;
+    if (ranked) {
+        constexpr int kAhead = 8;               // scores a lane has in flight
+        for (int i0 = tid; i0 < C; i0 += kAhead * kT) {
+            float x[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) x[u] = i0 + u * kT < C ? sc[i0 + u * kT] : 0.f;
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int i = i0 + u * kT;
+                if (i >= C) break;
+                const uint32_t key = ordered_key(x[u]);
+                if (staged) lds_keys[i] = key;
+                kmin = min(kmin, key);
+                kmax = max(kmax, key);
+            }
+        }
+        for (int i = tid; i < kBins; i += kT) sh->hist[i] = 0;
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        part += __shfl_xor(part, d);
+        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, d));
+        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, d));
+    }
+    if (lane == 0) {
+        sh->red[wave] = part;
+        sh->wave_min[wave] = kmin;
+        sh->wave_max[wave] = kmax;
+    }
+    __syncthreads();
+    int out_base = 0;
+#pragma unroll
+    for (int u = 0; u < kW; ++u) {
+        out_base += sh->red[u];
+        kmin = min(kmin, sh->wave_min[u]);
+        kmax = max(kmax, sh->wave_max[u]);
+    }
     if (tid == 0) {
         out_offsets[b + 1] = out_base + k;
         if (b == 0) out_offsets[0] = 0;
@@ -181,14 +290,9 @@ __device__ void select_sequence(int b, const float* __restrict__ scores, const i
         for (int i = tid; i < C; i += kT) out[i] = row0 + i;
         return;
     }
-    const float* __restrict__ sc = scores + row0;
-    if (C <= lds_cap) {
-        for (int i = tid; i < C; i += kT) lds_keys[i] = ordered_key(sc[i]);
-        __syncthreads();
-        select_body<true, kT>(lds_keys, sc, C, need, row0, out, sh);
-    } else {
-        select_body<false, kT>(lds_keys, sc, C, need, row0, out, sh);
-    }
+    __syncthreads();                            // (red is used again below)
+    if (staged) select_body<true, kT>(lds_keys, sc, C, need, kmin, kmax, row0, out, sh);
+    else select_body<false, kT>(lds_keys, sc, C, need, kmin, kmax, row0, out, sh);
 }
 
 }  // namespace pyr

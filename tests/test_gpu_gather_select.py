@@ -122,6 +122,31 @@ def test_select_tiny_and_denormal_scores(lib):
     _select_case(lib, [4096], 64, [2000], scores.astype(np.float32))
 
 
+def _ulps_above(base, steps):
+    return (np.float32(base).view(np.uint32) + np.asarray(steps, dtype=np.uint32)).astype(np.uint32).view(np.float32)
+
+
+@pytest.mark.parametrize("n", [300, 4096, 4097])                     # 512 lanes up to 4096 tokens, 1024 beyond
+@pytest.mark.parametrize("spread", ["few_ulps", "digit_edge", "outlier", "two_digits", "bin_256", "bin_257"])
+def test_select_radix_passes(lib, n, spread):
+    """Score distributions that end the radix select in its different ways: every bit decided in one digit, keys that
+    differ in exactly 11 and 12 bits, one pass and a crowded bin, two and three digits, a bin of 256 keys (ranked
+    directly) and of 257 (another pass)."""
+    rng = np.random.default_rng(n)
+    steps = {
+        "few_ulps": lambda: rng.integers(0, 40, n),
+        "digit_edge": lambda: rng.integers(0, 1 << int(rng.integers(11, 13)), n),
+        "outlier": lambda: np.where(np.arange(n) == n // 2, 0x08000000, rng.integers(0, 3000, n)),
+        "two_digits": lambda: rng.integers(0, 4, n) * 0x00400000 + rng.integers(0, 1 << 20, n),
+        "bin_256": lambda: np.where(np.arange(n) < 256, rng.integers(0, 1 << 12, n), 0x00800000 + np.arange(n) * 8192),
+        "bin_257": lambda: np.where(np.arange(n) < 257, rng.integers(0, 1 << 12, n), 0x00800000 + np.arange(n) * 8192),
+    }[spread]()
+    scores = _ulps_above(1e-4, steps)
+    w = 16
+    for keep in (w + 1, n - 100, n // 2, n - 1):
+        _select_case(lib, [n], w, [keep], scores)
+
+
 @pytest.mark.parametrize("n_src,n_kept", [(1, 1), (1000, 777), (3_000_000, 2_500_001)])
 def test_gather_positions_bit_exact(lib, n_src, n_kept):
     rng = np.random.default_rng(n_kept)
