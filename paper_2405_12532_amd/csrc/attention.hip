@@ -580,10 +580,24 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
             if (next.kind != 0) F[j - NS] = frag(next, j - NS);
         }
     };
+    // One wait for the LDS reads of half a group's fragments in front of their first MFMA (own fragments up to i + NS/2 - 1;
+    // the `reads` youngest reads may be outstanding) instead of the compiler's own in front of every MFMA: a wait is an
+    // instruction like any other to the issue port (4 x 32768, 64/8 heads: 57.98 -> 57.34 ms; 64 x 359: 189.4 -> 188.5 us).
+    // At d = 64 half a group is two fragments just asked for, and with one wavefront per SIMD nothing covers the longer
+    // wait (one 2048-token prompt: 47.3 -> 47.8 us): there the compiler's single waits stay.
+    auto half_group_wait = [&](const Frags& own, const Frags& next, int i) __attribute__((always_inline)) {
+        if (NS != 8 || kNW != 8 || i % (NS / 2) != 0) return;
+        const Frags& young = i == 0 ? own : next;             // reads of own fragments 4, 5, or of the next group's 0, 1
+        if (young.kind == 2) __builtin_amdgcn_s_waitcnt(0xC07F | (4 << 8));
+        else if (young.kind == 1) __builtin_amdgcn_s_waitcnt(0xC07F | (2 << 8));
+        else __builtin_amdgcn_s_waitcnt(0xC07F);
+        fence();
+    };
     // QK group: sd = K_half Q^T
     auto qk_group = [&](f32x16& sd, const Chunk& e, const Frags& own, const Frags& next) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
+            half_group_wait(own, next, i);
             if (i == 0) {
                 f32x16 z;
 #pragma unroll
@@ -603,6 +617,7 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
                         __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
+            half_group_wait(own, next, i);
             oacc[i % kDTiles] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                 F[i], __builtin_bit_cast(bf16x8, pp[i / kDTiles]), oacc[i % kDTiles], 0, 0, 0);
             if (e.on) e_slice(*e.se, e.base, i, *e.pe, *e.lsum);
