@@ -117,7 +117,7 @@ int pyr_workspace_bytes(const pyr_shape* shape, int32_t w, size_t* bytes_out) {
     if (rc != PYR_OK) return rc;
     if (w < 1) return PYR_ERR_SHAPE;
     *bytes_out = align_up((size_t)shape->total_tokens * shape->n_q_heads * sizeof(float)) +
-                 align_up(((size_t)shape->n_seqs + 1) * sizeof(int32_t)) + align_up(pyr::score_tail_bytes(*shape));
+                 align_up(((size_t)shape->n_seqs + 1) * sizeof(int32_t)) + align_up(pyr::score_parts_bytes(*shape));
     return PYR_OK;
 }
 
@@ -165,8 +165,7 @@ int pyr_attention(const void* q, const void* k, const void* v,
     if (rc != PYR_OK) return rc;
     if (info.uniform_len == 0 && shape->total_tokens > 0 && tile_map == nullptr) return PYR_ERR_WORKSPACE;
     return pyr::launch_attention(q, k, v, seq_offsets_dev, seq_offsets_host, *shape, info.uniform_len,
-                                 scale_log2(softmax_scale, shape->head_dim), out, lse, tile_map, nullptr, 0,
-                                 (hipStream_t)stream);
+                                 scale_log2(softmax_scale, shape->head_dim), out, lse, tile_map, (hipStream_t)stream);
 }
 
 int pyr_score_weighted(const void* q, const void* k, const float* lse,
@@ -209,8 +208,8 @@ int pyr_select(const float* scores,
     if (rc != PYR_OK) return rc;
     rc = check_keep_len(keep_len_host, seq_offsets_host, n_seqs, w, nullptr);
     if (rc != PYR_OK) return rc;
-    return pyr::launch_select(scores, seq_offsets_dev, keep_len_dev, n_seqs, info.max_len, w, kept_idx,
-                              out_offsets_dev, (hipStream_t)stream);
+    return pyr::launch_select(nullptr, 1, 0, const_cast<float*>(scores), seq_offsets_dev, keep_len_dev, n_seqs, info.max_len, w,
+                              kept_idx, out_offsets_dev, (hipStream_t)stream);
 }
 
 int pyr_compact2(const void* src0, void* dst0, const void* src1, void* dst1, size_t row_bytes,
@@ -298,25 +297,27 @@ int pyr_prefill_layer_fused(const void* q, const void* k, const void* v,
     if (rc != PYR_OK) return rc;
     if (workspace == nullptr || ((uintptr_t)workspace % kAlign) != 0 || workspace_bytes < need) return PYR_ERR_WORKSPACE;
 
-    // workspace: row statistics | tile map | the score pass's counters and partial sums
+    // workspace: row statistics | tile map | partial sums of the score pass
     float* lse = (float*)workspace;
     char* at = (char*)workspace + align_up((size_t)shape->total_tokens * shape->n_q_heads * sizeof(float));
     int32_t* tile_map = (int32_t*)at;
     at += align_up(((size_t)shape->n_seqs + 1) * sizeof(int32_t));
-    void* tail_ws = at;
+    float* parts = (float*)at;
     hipStream_t st = (hipStream_t)stream;
     const float c = scale_log2(softmax_scale, shape->head_dim);
+    if (pyr::score_parts_bytes(*shape) == 0) parts = nullptr;      // (no room in the workspace: the score pass is not split)
     pyr_shape s = *shape;
     s.max_seqlen = info.max_len;
 
-    // four launches (five for a ragged batch: the tile map): attention, which also clears the counters of the
-    // next one; the score pass; the selection; one gather for everything
-    rc = pyr::launch_attention(q, k, v, seq_offsets_dev, seq_offsets_host, s, info.uniform_len, c, out, lse, tile_map,
-                               (int32_t*)tail_ws, pyr::score_tail_counters(s), st);
+    // four launches (five for a ragged batch: the tile map): attention; the score pass; the selection, which also adds
+    // the partial sums of a score pass that was split; one gather for everything
+    rc = pyr::launch_attention(q, k, v, seq_offsets_dev, seq_offsets_host, s, info.uniform_len, c, out, lse, tile_map, st);
     if (rc != PYR_OK) return rc;
-    rc = pyr::launch_score_groups(q, k, lse, seq_offsets_dev, s, info.min_len, w, c, row_weights_dev, scores, tail_ws, st);
+    int groups = 1;
+    rc = pyr::launch_score_groups(q, k, lse, seq_offsets_dev, s, info.min_len, w, c, row_weights_dev, scores, parts, &groups, st);
     if (rc != PYR_OK) return rc;
-    rc = pyr::launch_select(scores, seq_offsets_dev, keep_len_dev, s.n_seqs, info.max_len, w, kept_idx, out_offsets_dev, st);
+    rc = pyr::launch_select(parts, groups, s.total_tokens, scores, seq_offsets_dev, keep_len_dev, s.n_seqs, info.max_len, w, kept_idx,
+                            out_offsets_dev, st);
     if (rc != PYR_OK) return rc;
     if (total_kept > 0) {
         const void* srcs[3];
@@ -396,11 +397,12 @@ int pyr_decode_update(const void* q_win, const void* k, const void* v,
     hipStream_t st = (hipStream_t)stream;
     pyr_shape s = *shape;
     s.max_seqlen = info.max_len;
+    int groups = 1;
     rc = pyr::launch_window_score(q_win, k, seq_offsets_dev, s, info.min_len, w, scale_log2(softmax_scale, shape->head_dim),
-                                  row_weights_dev, lse_win, part, scores, st);
+                                  row_weights_dev, lse_win, part, scores, &groups, st);
     if (rc != PYR_OK) return rc;
-    rc = pyr::launch_select(scores, seq_offsets_dev, keep_len_dev, s.n_seqs, info.max_len, w, kept_idx,
-                            out_offsets_dev, st);
+    rc = pyr::launch_select((const float*)part, groups, s.total_tokens, scores, seq_offsets_dev, keep_len_dev, s.n_seqs, info.max_len,
+                            w, kept_idx, out_offsets_dev, st);
     if (rc != PYR_OK) return rc;
     if (total_kept > 0) {                             // K, V and the position ids in one launch
         const size_t row_bytes = (size_t)shape->n_kv_heads * shape->head_dim * 2;

@@ -27,36 +27,38 @@ int launch_gather(const void* src0, void* dst0, const void* src1, void* dst1, si
 int launch_gather_multi(int n, const void* const* srcs, void* const* dsts, const size_t* row_bytes, const int32_t* pos,
                         int32_t* pos_out, const int32_t* kept_idx, int64_t n_kept, hipStream_t stream);
 
-int launch_select(const float* scores, const int32_t* seq_offsets_dev, const int32_t* keep_len_dev,
-                  int32_t n_seqs, int32_t max_seqlen, int32_t w, int32_t* kept_idx, int32_t* out_offsets_dev,
-                  hipStream_t stream);
+// groups > 1: parts holds `groups` rows of total_tokens partial scores, whose sums the kernel writes to `scores` and ranks;
+// else `scores` is only read.
+int launch_select(const float* parts, int groups, int32_t total_tokens, float* scores, const int32_t* seq_offsets_dev,
+                  const int32_t* keep_len_dev, int32_t n_seqs, int32_t max_seqlen, int32_t w, int32_t* kept_idx,
+                  int32_t* out_offsets_dev, hipStream_t stream);
 
 int launch_attention(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev,
                      const int32_t* seq_offsets_host, const pyr_shape& shape, int32_t uniform_len, float scale_log2,
-                     void* out, float* lse, int32_t* item_map, int32_t* zero_ptr, int32_t zero_count,
-                     hipStream_t stream);     // zero_ptr[0 .. zero_count) is cleared by the kernel (may be nullptr, 0)
+                     void* out, float* lse, int32_t* item_map, hipStream_t stream);
 
 // row_weights: device [w] or nullptr (uniform); min_seqlen: the shortest sequence (0 if not known)
 int launch_score(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev,
                  const pyr_shape& shape, int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights,
                  float* scores, hipStream_t stream);
 
-// The score pass with its small-batch extra (see score.hip): the KV heads split over several workgroups per key
-// block when the grid is small.  tail_ws: score_tail_bytes() bytes whose first score_tail_counters() int32 are zero
-// at launch (the kernel leaves them zero).
-size_t score_tail_bytes(const pyr_shape& shape);
-int32_t score_tail_counters(const pyr_shape& shape);
+// The score pass with its small-batch extra (see score.hip): the tasks of a range split over several workgroups when the
+// grid is small.  *groups > 1 afterwards: `parts` (score_parts_bytes()) holds that many rows of total_tokens partial
+// sums and `scores` is not written yet (launch_select does it); *groups == 1: `scores` is complete.
+// parts == nullptr: never split.
+constexpr int kMaxScoreGroups = 16;
+size_t score_parts_bytes(const pyr_shape& shape);
 int launch_score_groups(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev,
                         const pyr_shape& shape, int32_t min_seqlen, int32_t w, float scale_log2,
-                        const float* row_weights, float* scores, void* tail_ws, hipStream_t stream);
+                        const float* row_weights, float* scores, float* parts, int* groups, hipStream_t stream);
 
 // Generation phase: the same scores from the window's own query buffer q_win [B, w, Hq, d]
-// (right-aligned), three launches: per-block row statistics -> part, folded into lse_win
-// [B, w, Hq], then the score pass.  part holds window_score_part_bytes() bytes.
+// (right-aligned), three launches: row statistics per range of keys -> part, folded into lse_win
+// [B, w, Hq], then the score pass.  part holds window_score_part_bytes() bytes; *groups as above, the partial sums in part.
 size_t window_score_part_bytes(const pyr_shape& shape, int32_t w);
 int launch_window_score(const void* q_win, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& shape,
                         int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights, float* lse_win, void* part,
-                        float* scores, hipStream_t stream);
+                        float* scores, int* groups, hipStream_t stream);
 
 int launch_gather_positions(const int32_t* pos, const int32_t* kept_idx, int64_t n_kept, int32_t* pos_out,
                             hipStream_t stream);

@@ -8,59 +8,65 @@
 // The weights of the last L' rows are rebuilt from the logits and the row denominators the
 // attention kernel saved (log2 domain), so the S x S matrix is never stored:
 //   A_h[i,t] = 2^(c * q_i.k_t - lse_h[i]);  a weight enters as  - log2(omega_i)  next to lse_h[i].
-// One workgroup owns 64 consecutive key positions of one sequence; its two wavefronts share
-// out the KV heads (so a small batch still fills the chip) and each walks over its heads and,
-// per head, over "steps": one query head x one 32-row block of the window.  With
-// S^T = K Q^T in the MFMA accumulator a lane holds 16 keys of one window row, adds its
-// probabilities into 2x16 per-lane sums, and only at the very end the 32 lanes of each half
-// and the two wavefronts are added up through LDS in a fixed order.  No atomics: the result
-// is bit-reproducible.  All S columns are written, the window's own columns too (so each
-// sequence's scores sum to one).
 //
-// Every byte of K (once, from HBM) and of the window's Q rows (once per 64 keys, from L2)
-// passes the CU's vector L1, and loads into registers get through it at roughly a quarter of
-// the rate of loads that write LDS directly - with them this kernel ran at the pace of that
-// L1, not of HBM.  So all operands take the direct path: a wavefront keeps a private 64 x d K
-// tile, a 32 x d Q tile and 32 row denominators in LDS, fills them with global_load_lds
-// (fully coalesced: 16 lanes per 256-byte row, 16-byte chunks XOR-swizzled against bank
-// conflicts), copies the fragments into registers and at once requests the next tile into
-// the same LDS space, which then arrives while the MFMAs and exponentials of this one run.
+// Bound: reading K once from HBM.  So the window's queries stand still and K streams past them.  A
+// wavefront owns a RANGE of consecutive keys and a list of TASKS: one KV head times up to two 32-row blocks of
+// the window (of one query head, or of two of the head's group).  Per task the queries go into registers once
+// and the range's keys follow in tiles of 32; with S = Q K^T in the MFMA accumulator a lane holds 16 window
+// rows of ONE key, so the sum over the rows is a sum of registers, and a key's running sum over the tasks is
+// one LDS word per half-wavefront.  Queries and keys are elements of one stream of 32-row tiles, loaded
+// straight into a private ring of two LDS slots (global_load_lds, 16-byte chunks XOR-swizzled against bank
+// conflicts), copied into registers, and the slot is requested again at once: no barrier until the end, where
+// the wavefronts of a workgroup (they share out the tasks of one range) add their sums in a fixed order.
+// No atomics: the result is bit-reproducible.  All S columns are written, the window's own columns too (so
+// each sequence's scores sum to one).
+// (Loads into registers pass the vector L1 at a quarter of the rate of LDS-direct loads, hence the ring.)
+// Measured against the walk this one replaced (a workgroup per 64 keys with the keys standing still and every window
+// row read once per 64 keys), us per launch: 64 x 2048, 32 heads 253 -> 188 (5.7 TB/s of K), 64 x 359 103 -> 49, 8 x 2048
+// 45 -> 31, 4 x 32768 with 64/8 heads and w = 128 493 -> 370, one 2048-token prompt 20 -> 10, statistics of a
+// 1537-row cache 49 -> 9.
 //
 // The same walk serves the generation-phase update of the cache (Algorithm 1 with a non-empty
 // cache; Section 4.1): there the queries of the recent rows come in a buffer of their own
 // ([B, w, Hq, d], right-aligned) and no attention pass has left row denominators behind, so a
-// first pass (kStats) writes, per 64-key workgroup, every window row's maximum and sum of
-// exponentials, a small kernel folds them into denominators, and the score pass runs as above.
+// first pass (kStats; S^T = K Q^T there, a lane follows one window row over its keys) writes, per range, every
+// window row's maximum and sum of exponentials, a small kernel folds them into denominators, and the score pass
+// runs as above.
 //
-// Small batches.  With one workgroup per 64 keys a single 2048-token prompt gives 32 workgroups to 256
-// compute units, and the step then spends a third of its time here (Appendix A.1 of the paper: the
-// selection overhead eats the gain at small batch).  The launcher may therefore split the KV heads over
-// gridDim.y workgroups per key block; each writes its partial sums, and the workgroup that arrives last at
-// the block's counter adds them up in head-group order (so the result does not depend on who was last).
-// (Letting the workgroup that completes a sequence's scores run the top-k selection as well was built and
-// measured: it replaces a launch that costs as much as the selection it carries, and was slower at every
-// shape - 27.8 against 26.5 us per step at one 256-token prompt, 40.0 against 39.5 ms over the 32-layer
-// pyramid at batch 64 - so the selection stays a kernel of its own.)  The counters live in the caller's
-// workspace, start at zero and are put back to zero by their last arrival.
+// Small batches.  When ranges times wavefronts leave the chip idle, the tasks of a range are also split over
+// gridDim.y workgroups that write partial sums, one row of `sums` each; the selection kernel, which reads
+// every score anyway, adds the rows up in order.
+#include <math.h>
+
 #include "pyr_internal.h"
 
 namespace pyr {
 namespace {
 
-constexpr int kWavesPerBlock = 2;    // wavefronts sharing out a workgroup's KV heads
+constexpr int kMaxWaves = 8;         // wavefronts of a workgroup
+constexpr int kMaxRangeTiles = 12;   // 32-key tiles of a range: eight wavefronts then fill the 160 KB of LDS at d = 128
+constexpr int kRowArea = 512;        // LDS of one row block's denominators and weights, 64 floats each (32 used)
+constexpr int kSlots = 2;            // tiles of a wavefront's ring
+
 enum Mode { kScores = 0, kScoresWeighted = 1, kStats = 2 };
-constexpr int kKeysPerBlock = 64;
 
 typedef __attribute__((address_space(3))) char* lptr_t;
+typedef __attribute__((address_space(3))) float* lfloat_t;
 
-constexpr int kMaxHeadGroups = 16;
-
-// What the last-arriving workgroup of a key block does when the KV heads are split over gridDim.y workgroups
-// (all pointers device; counters == nullptr: no split).
-struct ScoreTail {
-    int32_t* counters;            // [n_seqs * blocks_per_seq] one per key block; zero at launch
-    float* part_sums;             // [gridDim.y, total_tokens] partial scores
+struct StripArgs {
+    const uint16_t* q;
+    const uint16_t* k;
+    const float* lse;
+    const int32_t* seq_offsets;
+    int32_t n_seqs, n_q_heads, n_kv_heads, w;
+    int32_t range_tiles, ranges_per_seq;      // tiles of a range; ranges of the longest sequence
+    int32_t chunk_ranges, xcds, head_step;    // order of the ranges over the XCDs, of the heads over the ranges
+    int32_t q_window;                         // 0: q and lse by packed row; else by (sequence, window slot)
+    float c;
+    const float* row_weights;
+    float* sums;                              // [gridDim.y, total_tokens]
     int32_t total_tokens;
+    float2* part;                             // kStats: [range, sequence, query head, window slot]
 };
 
 // 64 lanes x 16 bytes (or x 4 bytes) from base + voff[lane] to LDS at lds_addr + 16 (4) * lane.
@@ -84,220 +90,314 @@ __device__ __forceinline__ void wait_loads() {      // until at most N of this w
 }
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-// q_window == 0: q and lse are indexed by packed row like k ([T, Hq, d], [T, Hq]);
-// q_window != 0: by (sequence, window slot): [B, w, Hq, d], [B, w, Hq], the last row in slot w-1.
-// kStats writes part[((key block * B + b) * Hq + h) * w + slot] = (max, sum of 2^(x - max)) over the
-// block's visible keys, x = c * q.k, and touches neither lse nor scores.
+template <int D>
+constexpr int wave_lds_bytes(int range_tiles) { return kSlots * 32 * D * 2 + 2 * kRowArea + 256 * range_tiles; }
+
+// A position in a wavefront's stream of tiles.  All fields wave-uniform.
+struct Cursor {
+    int left;        // tasks left, this one included
+    int hd, pair;    // KV head (before the rotation) and row-block pair of the task
+    int e;           // element of the task: its row blocks, then its key tiles
+};
+
+// Accumulator register r of a lane: row 8*(r >> 2) + 4*gl + (r & 3) of the A operand, column li of the B operand.
+
+// Score pass (rows: window rows, column: key): the key's probabilities over the 16 rows the lane holds, added up.
+// nl: minus the rows' denominators.  Without kPlain, rows before the key are masked (q0: position of the lane's row 0).
+template <bool kPlain>
+__device__ __forceinline__ float tile_sum(const f32x16& s, float c, const float (&nl)[16], int key, int q0) {
+    float p4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, nl[r]));
+        if (!kPlain) p = key <= q0 + 8 * (r >> 2) + (r & 3) ? p : 0.f;
+        p4[r & 3] += p;
+    }
+    return (p4[0] + p4[1]) + (p4[2] + p4[3]);
+}
+
+// Statistics pass (rows: keys, column: window row): the row's running maximum and sum of exponentials.  Without kPlain
+// keys past the row, and rows past the sequence, are masked (key0: position of the lane's key 0).
+template <bool kPlain>
+__device__ __forceinline__ void tile_stats(f32x16& s, float c, int key0, int qpos, int S, float& m_run, float& l_run) {
+    float mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        s[r] *= c;
+        if (!kPlain) s[r] = key0 + 8 * (r >> 2) + (r & 3) <= qpos && qpos < S ? s[r] : -INFINITY;
+        mx = fmaxf(mx, s[r]);
+    }
+    if (!(mx > -INFINITY)) return;
+    const float m_new = fmaxf(m_run, mx);
+    float l4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < 16; ++r) l4[r & 3] += __builtin_amdgcn_exp2f(s[r] - m_new);
+    l_run = l_run * __builtin_amdgcn_exp2f(m_run - m_new) + ((l4[0] + l4[1]) + (l4[2] + l4[3]));
+    m_run = m_new;
+}
+
+// kStats writes part[((range * B + b) * Hq + h) * w + slot] = (max, sum of 2^(x - max)) over the
+// range's visible keys, x = c * q.k, and touches neither lse nor sums.
 template <int D, int kMode>
-__global__ __launch_bounds__(kWavesPerBlock * 64, 2) void score_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const float* __restrict__ lse,
-    const int32_t* __restrict__ seq_offsets, int32_t n_seqs, int32_t n_q_heads, int32_t n_kv_heads, int32_t w,
-    int32_t blocks_per_seq, int32_t chunk_blocks, int32_t xcds, int32_t head_step, int32_t q_window, float c,
-    const float* __restrict__ row_weights, float* __restrict__ scores, float2* __restrict__ part, ScoreTail tail) {
+__global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(StripArgs a) {
     constexpr bool kWeighted = kMode == kScoresWeighted;
-    constexpr int kKSteps = D / 16;
+    constexpr int kSteps = D / 16;
     constexpr int kChunks = D / 8;                  // 16-byte chunks per row
     constexpr int kRowBytes = D * 2;
     constexpr int kRowsPerLoad = 64 / kChunks;      // rows one load instruction covers
-    constexpr int kKBytes = 64 * kRowBytes, kQBytes = 32 * kRowBytes, kLseBytes = 256;
-    constexpr int kNK = kKBytes / 1024, kNQ = kQBytes / 1024;       // load instructions per K tile, per Q tile
-    constexpr int kStepLoads = kNQ + (kMode == kStats ? 0 : kWeighted ? 2 : 1);   // ... per step: Q tile, denominators, weights
-    constexpr int kRedBytes = kWavesPerBlock * 2 * 64 * 17 * 4;     // +1 column: conflict-free column sums
-    constexpr int kSmemBytes = kWavesPerBlock * (kKBytes + kQBytes + 2 * kLseBytes);
-    static_assert(kSmemBytes >= kRedBytes, "the final reduction reuses the tiles' space");
-    __shared__ __align__(1024) char smem[kSmemBytes];
+    constexpr int kTileBytes = 32 * kRowBytes;
+    constexpr int kTileLoads = kTileBytes / 1024;   // load instructions of a tile
+    constexpr int kRowLoads = kMode == kStats ? 0 : kWeighted ? 2 : 1;      // ... of a task's denominators and weights
+    extern __shared__ __align__(1024) char smem[];
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, waves = (int)(blockDim.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int li = lane & 31, gl = lane >> 5;
-    // Workgroup -> (sequence, key block).  Consecutive workgroup ids go to consecutive XCDs; a chunk of
-    // chunk_blocks key blocks of one sequence stays on one XCD, so that the window's Q rows, which every key
-    // block of the sequence re-reads, are found in that XCD's L2.
-    const int wg_slot = (int)blockIdx.x / xcds;
-    const int chunk = (wg_slot / chunk_blocks) * xcds + (int)blockIdx.x % xcds;
-    const int chunks_per_seq = (blocks_per_seq + chunk_blocks - 1) / chunk_blocks;
+    // Workgroup -> (sequence, range).  Consecutive workgroup ids go to consecutive XCDs; a chunk of
+    // chunk_ranges ranges of one sequence stays on one XCD, so that the window's Q rows, which every
+    // range of the sequence re-reads, are found in that XCD's L2.
+    const int wg_slot = (int)blockIdx.x / a.xcds;
+    const int chunk = (wg_slot / a.chunk_ranges) * a.xcds + (int)blockIdx.x % a.xcds;
+    const int chunks_per_seq = (a.ranges_per_seq + a.chunk_ranges - 1) / a.chunk_ranges;
     const int b = chunk / chunks_per_seq;
-    const int key_block = (chunk % chunks_per_seq) * chunk_blocks + wg_slot % chunk_blocks;
-    if (b >= n_seqs || key_block >= blocks_per_seq) return;      // (uniform over the workgroup, like the next one)
-    const int row0 = seq_offsets[b];
-    const int S = seq_offsets[b + 1] - row0;
-    const int key_base = key_block * kKeysPerBlock;
+    const int range = (chunk % chunks_per_seq) * a.chunk_ranges + wg_slot % a.chunk_ranges;
+    if (b >= a.n_seqs || range >= a.ranges_per_seq) return;      // (uniform over the workgroup, like the next one)
+    const int row0 = a.seq_offsets[b];
+    const int S = a.seq_offsets[b + 1] - row0;
+    const int key_base = range * a.range_tiles * 32;
     if (key_base >= S) return;
-    const int L = min(w, S);
+    const int n_tiles = min(a.range_tiles, (S - key_base + 31) / 32);
+    const int L = min(a.w, S);
     const int first_row = S - L;                      // local position of the first window row
-    const int q_row_base = q_window ? b * w + (w - L) : row0 + first_row;   // row of q / lse holding the first window row
-    const int n_row_blocks = (L + 31) / 32;
-    const int group = n_q_heads / n_kv_heads;
-    const int n_steps = group * n_row_blocks;         // per KV head
-    // this workgroup's share of the KV heads (all of them unless the launcher split them over gridDim.y), halved
-    // between the two wavefronts
-    const int wg_heads = n_kv_heads / (int)gridDim.y, wg_first = (int)blockIdx.y * wg_heads;
-    // Each wavefront takes half of the workgroup's heads, and, where the launcher asks for it (head_step != 0), every
-    // key block starts its walk at another head: workgroups that run side by side then read different 256-byte
-    // columns of their token rows, which spreads them over the memory channels when the rows are a power of two
-    // apart (a read-only stream over 8 KB rows: 5.5 -> 5.9 TB/s with steps of 7; 1 and 8 are worse than none).
-    const int head_rot = (key_block * head_step) % wg_heads;
-    auto head_at = [&](int i) { const int r = i + head_rot; return wg_first + (r >= wg_heads ? r - wg_heads : r); };   // i < wg_heads
-
-    float acc[2][16];
-#pragma unroll
-    for (int sk = 0; sk < 2; ++sk)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[sk][r] = 0.f;
+    const int q_row_base = a.q_window ? b * a.w + (a.w - L) : row0 + first_row;   // row of q / lse holding the first window row
+    const int n_rb = (L + 31) / 32;
+    const int group = a.n_q_heads / a.n_kv_heads;
+    const int blocks = group * n_rb;                  // row blocks per KV head
+    const int pairs = (blocks + 1) / 2;
+    // this workgroup's share of the tasks, dealt to its wavefronts one by one
+    const int64_t n_tasks = (int64_t)a.n_kv_heads * pairs;
+    const int t_begin = (int)(n_tasks * blockIdx.y / gridDim.y), t_end = (int)(n_tasks * (blockIdx.y + 1) / gridDim.y);
+    const int n_my = max(0, (t_end - t_begin - wave + waves - 1) / waves);
+    // Where the launcher asks for it (head_step != 0), every range starts its walk at another head: workgroups
+    // that run side by side then read different columns of their token rows, which spreads them over the memory
+    // channels when the rows are a power of two apart.
+    const int head_rot = (range * a.head_step) % a.n_kv_heads;
 
     // sum of the weights in use (fixed order: every lane strides over them, then a butterfly).
     // These are the only ordinary loads of the kernel and they are complete before the first
-    // LDS-direct load is issued: the wait counts below assume nothing else is in flight.
+    // LDS-direct load is issued: the wait counts below assume no other load is in flight.
     float weight_sum = (float)L;
     if (kWeighted) {
         float part = 0.f;
-        for (int j = lane; j < L; j += 64) part += row_weights[w - L + j];
+        for (int j = lane; j < L; j += 64) part += a.row_weights[a.w - L + j];
 #pragma unroll
         for (int m = 32; m >= 1; m >>= 1) part += __shfl_xor(part, m, 64);
         asm volatile("s_waitcnt vmcnt(0)" : "+v"(part) : : "memory");
         weight_sum = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, part)));   // uniform: a scalar register
     }
 
-    // ---- this wavefront's LDS: K tile, Q tile (1 KB aligned), then the row denominators
+    // ---- this wavefront's LDS: ring, two row areas (denominators, then weights), key sums
+    const int wave_bytes = wave_lds_bytes<D>(a.range_tiles);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
-    const uint32_t kt = lds0 + wave * (kKBytes + kQBytes), qt = kt + kKBytes;
-    const uint32_t lt = lds0 + kWavesPerBlock * (kKBytes + kQBytes) + wave * 2 * kLseBytes;   // denominators, then weights
-    const uint32_t wt = lt + kLseBytes;
+    const uint32_t ring = lds0 + wave * wave_bytes;
+    const uint32_t rows_at = ring + kSlots * kTileBytes;
+    const uint32_t sums_at = rows_at + 2 * kRowArea;
 
     // ---- load side: lane -> (row inside an instruction's row group, physical chunk).  The LDS
     // slot of a lane is fixed by the instruction, so the swizzle picks the global chunk.
     const int ld_row = lane / kChunks, ld_chunk = lane % kChunks;
-    const uint32_t k_row_bytes = (uint32_t)n_kv_heads * kRowBytes, q_row_bytes = (uint32_t)n_q_heads * kRowBytes;
-    const int last_key = S - 1 - key_base;            // rows past the end of the sequence re-read its last row
-    // (the offsets are recomputed at every use - a few VALU operations per load; kept live they
-    //  would push the kernel past the registers of two wavefronts per SIMD)
-    auto issue_k = [&](int kvh) {
-        const char* base = (const char*)(k + ((size_t)(row0 + key_base) * n_kv_heads + kvh) * D);
-        int lim = last_key;
-        asm volatile("" : "+v"(lim));
+    const uint32_t k_row_bytes = (uint32_t)a.n_kv_heads * kRowBytes, q_row_bytes = (uint32_t)a.n_q_heads * kRowBytes;
+    auto load_tile = [&](const char* base, uint32_t row_bytes, int last_row, uint32_t to) {      // rows past the last re-read it
 #pragma unroll
-        for (int i = 0; i < kNK; ++i) {
+        for (int i = 0; i < kTileLoads; ++i) {
             const int row = kRowsPerLoad * i + ld_row;
             // (24-bit multiply: full rate, where the 32-bit one takes four times as long; rows and strides are far below 2^24)
-            lds_dma(base, __umul24((uint32_t)min(row, lim), k_row_bytes) + 16 * (ld_chunk ^ (row & (kChunks - 1))), kt + 1024 * i,
+            lds_dma(base, __umul24((uint32_t)min(row, last_row), row_bytes) + 16 * (ld_chunk ^ (row & (kChunks - 1))), to + 1024 * i,
                     false);
         }
     };
-    auto issue_q = [&](int kvh, int st) {             // kStepLoads instructions
-        const int h = kvh * group + st / n_row_blocks, rb = st % n_row_blocks;
-        const int rb_row0 = first_row + 32 * rb;
-        int last_row = L - 1 - 32 * rb;
-        asm volatile("" : "+v"(last_row));
-        const char* base = (const char*)(q + ((size_t)(q_row_base + 32 * rb) * n_q_heads + h) * D);
+    // a full key tile's offsets stay in registers: the loop over the keys issues nothing but its loads
+    uint32_t k_off[kTileLoads];
 #pragma unroll
-        for (int i = 0; i < kNQ; ++i) {
-            const int row = kRowsPerLoad * i + ld_row;
-            lds_dma(base, __umul24((uint32_t)min(row, last_row), q_row_bytes) + 16 * (ld_chunk ^ (row & (kChunks - 1))),
-                    qt + 1024 * i, false);
+    for (int i = 0; i < kTileLoads; ++i) {
+        const int row = kRowsPerLoad * i + ld_row;
+        k_off[i] = __umul24((uint32_t)row, k_row_bytes) + 16 * (ld_chunk ^ (row & (kChunks - 1)));
+    }
+    auto kv_head = [&](const Cursor& cu) { const int h = cu.hd + head_rot; return h >= a.n_kv_heads ? h - a.n_kv_heads : h; };
+    auto n_blk = [&](const Cursor& cu) { return min(2, blocks - 2 * cu.pair); };
+    auto next_task = [&](Cursor& cu) {
+        --cu.left;
+        cu.pair += waves;
+        while (cu.pair >= pairs) {
+            cu.pair -= pairs;
+            ++cu.hd;
         }
-        if (kMode != kStats)
-            lds_dma((const char*)(lse + (size_t)(q_row_base + 32 * rb) * n_q_heads + h),
-                    __umul24((uint32_t)min(li, last_row), (uint32_t)n_q_heads * 4), lt, true);
-        if (kWeighted) lds_dma((const char*)(row_weights + (w - L) + 32 * rb), (uint32_t)min(li, last_row) * 4, wt, true);
+    };
+    // Request the element at the cursor into ring slot `slot` and move on; returns the number of load
+    // instructions issued (0: the stream has ended).
+    auto request = [&](Cursor& cu, int slot) -> int {
+        if (cu.left <= 0) return 0;
+        const uint32_t to = ring + slot * kTileBytes;
+        const int kvh = kv_head(cu), nb = n_blk(cu);
+        int n = kTileLoads;
+        if (cu.e < nb) {
+            const int blk = 2 * cu.pair + cu.e;
+            const int h = kvh * group + blk / n_rb, rb = blk % n_rb;
+            if (kMode != kStats) {
+                const uint32_t row = (uint32_t)min(li, L - 1 - 32 * rb), area = rows_at + cu.e * kRowArea;
+                lds_dma((const char*)(a.lse + (size_t)(q_row_base + 32 * rb) * a.n_q_heads + h), __umul24(row, (uint32_t)a.n_q_heads * 4), area, true);
+                if (kWeighted) lds_dma((const char*)(a.row_weights + (a.w - L) + 32 * rb), row * 4, area + 256, true);
+                n += kRowLoads;
+            }
+            load_tile((const char*)(a.q + ((size_t)(q_row_base + 32 * rb) * a.n_q_heads + h) * D), q_row_bytes, L - 1 - 32 * rb, to);
+        } else {
+            const int key = key_base + 32 * (cu.e - nb);
+            const char* base = (const char*)(a.k + ((size_t)(row0 + key) * a.n_kv_heads + kvh) * D);
+            if (key + 32 <= S) {
+#pragma unroll
+                for (int i = 0; i < kTileLoads; ++i) lds_dma(base, k_off[i], to + 1024 * i, false);
+            } else {
+                load_tile(base, k_row_bytes, S - 1 - key, to);
+            }
+        }
+        if (++cu.e == nb + n_tiles) {
+            cu.e = 0;
+            next_task(cu);
+        }
+        return n;
+    };
+    // wait until the element in front of the one requested last (`behind` instructions) has landed
+    auto wait_front = [&](int behind) {
+        if (behind == 0) wait_loads<0>();
+        else if (kRowLoads == 0 || behind == kTileLoads) wait_loads<kTileLoads>();
+        else wait_loads<kTileLoads + kRowLoads>();
     };
 
     // ---- fragment side: operand row li, logical chunk 2*ks + gl
-    auto frag = [&](uint32_t tile, int row, int ks) {
-        const uint32_t a = tile + row * kRowBytes + (((2 * ks + gl) ^ (row & (kChunks - 1))) << 4);
-        return *(const bf16x8 __attribute__((address_space(3)))*)(uintptr_t)a;
+    auto copy_tile = [&](bf16x8 (&f)[kSteps], int slot) {
+#pragma unroll
+        for (int ks = 0; ks < kSteps; ++ks) {
+            const uint32_t p = ring + slot * kTileBytes + li * kRowBytes + (((2 * ks + gl) ^ (li & (kChunks - 1))) << 4);
+            f[ks] = *(const bf16x8 __attribute__((address_space(3)))*)(uintptr_t)p;
+        }
     };
 
-    const int hi_begin = wave * wg_heads / kWavesPerBlock, hi_end = (wave + 1) * wg_heads / kWavesPerBlock;
-    if (hi_begin < hi_end) {
-        issue_k(head_at(hi_begin));
-        issue_q(head_at(hi_begin), 0);
-    }
-    // Outstanding loads at the top of a head: its K tile (oldest), then its first step's rows.
-    for (int hi = hi_begin; hi < hi_end; ++hi) {
-        const bool has_next = hi + 1 < hi_end;
-        const int kvh = head_at(hi), kvh_next = has_next ? head_at(hi + 1) : kvh;
-        wait_loads<kStepLoads>();                     // the K tile has landed
-        bf16x8 kf[2][kKSteps];
+    // minus the denominators of row block rb (accumulator order), weights included
+    auto copy_rows = [&](float (&nl)[16], int j, int rb) {
+        if (kMode == kStats) return;
 #pragma unroll
-        for (int sk = 0; sk < 2; ++sk)
+        for (int a4 = 0; a4 < 4; ++a4) {
+            const uint32_t p = rows_at + j * kRowArea + 4 * (8 * a4 + 4 * gl);
+            const f32x4 d4 = *(const f32x4 __attribute__((address_space(3)))*)(uintptr_t)p;
+            f32x4 w4 = {1.f, 1.f, 1.f, 1.f};
+            if (kWeighted) w4 = *(const f32x4 __attribute__((address_space(3)))*)(uintptr_t)(p + 256);
 #pragma unroll
-            for (int ks = 0; ks < kKSteps; ++ks) kf[sk][ks] = frag(kt, 32 * sk + li, ks);
-        wait_lds();                                   // fragments are in registers: the tile's space is free
-        if (has_next) issue_k(kvh_next);
-        for (int st = 0; st < n_steps; ++st) {
-            // the step's rows are older than the next K tile only in the head's first step
-            if (st == 0 && has_next) wait_loads<kNK>(); else wait_loads<0>();
-            bf16x8 qf[kKSteps];
-#pragma unroll
-            for (int ks = 0; ks < kKSteps; ++ks) qf[ks] = frag(qt, li, ks);
-            float lse_row = 0.f;
-            if (kMode != kStats) lse_row = *(const float __attribute__((address_space(3)))*)(uintptr_t)(lt + 4 * li);
-            if (kWeighted)      // omega * 2^x = 2^(x + log2 omega); a zero weight gives 2^-inf = 0
-                lse_row -= __builtin_amdgcn_logf(*(const float __attribute__((address_space(3)))*)(uintptr_t)(wt + 4 * li));
-            wait_lds();
-            if (st + 1 < n_steps) issue_q(kvh, st + 1);
-            else if (has_next) issue_q(kvh_next, 0);
-
-            const int rb = st % n_row_blocks;
-            const int qpos = first_row + 32 * rb + li;              // this lane's window row
-            if (first_row + 32 * rb + 31 < key_base) continue;      // whole row block precedes the keys
-            // masks are only needed where the keys reach into the window or the row block is ragged
-            const bool plain = key_base + 63 <= first_row + 32 * rb && first_row + 32 * rb + 31 < S;   // uniform
-            if (kMode == kStats) {
-                // this row's maximum and sum of exponentials over the 32 keys the lane holds, then
-                // over the 32 the other half-wavefront holds
-                f32x16 x[2];
-                float mx = -INFINITY;
-#pragma unroll
-                for (int sk = 0; sk < 2; ++sk) {
-                    f32x16 s;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) s[r] = 0.f;
-#pragma unroll
-                    for (int ks = 0; ks < kKSteps; ++ks)
-                        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[sk][ks], qf[ks], s, 0, 0, 0);
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int key = key_base + 32 * sk + 8 * (r >> 2) + 4 * gl + (r & 3);
-                        const bool visible = plain || (key <= qpos && qpos < S);
-                        x[sk][r] = visible ? s[r] * c : -INFINITY;
-                        mx = fmaxf(mx, x[sk][r]);
-                    }
-                }
-                float sum = 0.f;
-                if (mx > -INFINITY) {
-#pragma unroll
-                    for (int sk = 0; sk < 2; ++sk)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(x[sk][r] - mx);
-                }
-                const float mo = __shfl_xor(mx, 32, 64), so = __shfl_xor(sum, 32, 64);
-                const float m_all = fmaxf(mx, mo);
-                if (gl == 0 && m_all > -INFINITY && 32 * rb + li < L) {
-                    const float total = (mx > -INFINITY ? sum * __builtin_amdgcn_exp2f(mx - m_all) : 0.f) +
-                                        (mo > -INFINITY ? so * __builtin_amdgcn_exp2f(mo - m_all) : 0.f);
-                    const int h = kvh * group + st / n_row_blocks, slot = (w - L) + 32 * rb + li;
-                    part[(((size_t)key_block * n_seqs + b) * n_q_heads + h) * w + slot] = make_float2(m_all, total);   // 32 rows: 256 consecutive bytes
-                }
-                continue;
+            for (int i = 0; i < 4; ++i) {
+                float x = -d4[i];
+                if (kWeighted) x += __builtin_amdgcn_logf(w4[i]);      // omega * 2^x = 2^(x + log2 omega); a zero weight gives 2^-inf = 0
+                nl[4 * a4 + i] = 32 * rb + 8 * a4 + 4 * gl + i < L ? x : -INFINITY;      // a row past the window adds nothing
             }
+        }
+    };
+
+    auto product = [&](const bf16x8& qv, const bf16x8& kv, const f32x16& acc) {
+        return kMode == kStats ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(kv, qv, acc, 0, 0, 0)
+                               : __builtin_amdgcn_mfma_f32_32x32x16_bf16(qv, kv, acc, 0, 0, 0);
+    };
+
+    if (n_my == 0) {
+        for (int t = 0; t < n_tiles; ++t) *(lfloat_t)(uintptr_t)(sums_at + 256 * t + 4 * lane) = 0.f;
+    } else {
+        Cursor now{n_my, 0, 0, 0};
+        {
+            const int first = t_begin + wave;
+            now.hd = first / pairs;
+            now.pair = first % pairs;
+        }
+        Cursor ahead = now;
+        request(ahead, 0);
+        int behind = request(ahead, 1);
+        int slot = 0;
+        bool first_task = true;
+        for (; now.left > 0; next_task(now)) {
+            const int kvh = kv_head(now), nb = n_blk(now);
+            bf16x8 qf[2][kSteps];
+            float nl[2][16];                          // minus the rows' denominators (log2 domain), weights included
+            int q_lo[2];                              // sequence positions of the row blocks' first rows
+            const int rb0 = (2 * now.pair) % n_rb, rb1 = (2 * now.pair + 1) % n_rb;
+            q_lo[0] = first_row + 32 * rb0;
+            q_lo[1] = first_row + 32 * rb1;
+            wait_front(behind);
+            copy_tile(qf[0], slot);
+            copy_rows(nl[0], 0, rb0);
+            wait_lds();                               // in registers: the slot is free
+            behind = request(ahead, slot);
+            slot ^= 1;
+            if (nb == 2) {
+                wait_front(behind);
+                copy_tile(qf[1], slot);
+                copy_rows(nl[1], 1, rb1);
+                wait_lds();
+                behind = request(ahead, slot);
+                slot ^= 1;
+            }
+            float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};       // kStats: this lane's window rows
+            for (int t = 0; t < n_tiles; ++t) {
+                bf16x8 kf[kSteps];
+                wait_front(behind);
+                copy_tile(kf, slot);
+                wait_lds();
+                behind = request(ahead, slot);
+                slot ^= 1;
+                const int key0 = key_base + 32 * t;
+                float v = 0.f;
+                if (nb == 2 && key0 + 31 <= q_lo[0] && key0 + 31 <= q_lo[1]) {
+                    // the common tile: two row blocks, every row sees every key; their chains of products side by side
+                    f32x16 s[2];
 #pragma unroll
-            for (int sk = 0; sk < 2; ++sk) {
-                f32x16 s;
+                    for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s[r] = 0.f;
+                        for (int r = 0; r < 16; ++r) s[j][r] = 0.f;
 #pragma unroll
-                for (int ks = 0; ks < kKSteps; ++ks)
-                    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[sk][ks], qf[ks], s, 0, 0, 0);
-                if (plain) {
+                    for (int ks = 0; ks < kSteps; ++ks)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[sk][r] += __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -lse_row));
+                        for (int j = 0; j < 2; ++j) s[j] = product(qf[j][ks], kf[ks], s[j]);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        if (kMode == kStats) tile_stats<true>(s[j], a.c, 0, 0, 0, m_run[j], l_run[j]);
+                        else v += tile_sum<true>(s[j], a.c, nl[j], 0, 0);
                 } else {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int key = key_base + 32 * sk + 8 * (r >> 2) + 4 * gl + (r & 3);
-                        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -lse_row));
-                        const bool visible = key <= qpos && qpos < S;   // causal, and the row exists
-                        acc[sk][r] += visible ? p : 0.f;
+                    for (int j = 0; j < 2; ++j) {
+                        if ((j == 1 && nb < 2) || key0 > q_lo[j] + 31) continue;      // (the block precedes the keys)
+                        f32x16 s;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+                        for (int ks = 0; ks < kSteps; ++ks) s = product(qf[j][ks], kf[ks], s);
+                        if (kMode == kStats) tile_stats<false>(s, a.c, key0 + 4 * gl, q_lo[j] + li, S, m_run[j], l_run[j]);
+                        else v += tile_sum<false>(s, a.c, nl[j], key0 + li, q_lo[j] + 4 * gl);
+                    }
+                }
+                if (kMode != kStats) {
+                    lfloat_t at = (lfloat_t)(uintptr_t)(sums_at + 256 * t + 4 * lane);
+                    *at = first_task ? v : *at + v;
+                }
+            }
+            first_task = false;
+            if (kMode == kStats) {
+                // this half-wavefront's keys and the other's
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    if (j == 1 && nb < 2) continue;
+                    const float mo = __shfl_xor(m_run[j], 32, 64), so = __shfl_xor(l_run[j], 32, 64);
+                    const float m_all = fmaxf(m_run[j], mo);
+                    const int rb = j ? rb1 : rb0;
+                    if (gl == 0 && m_all > -INFINITY && 32 * rb + li < L) {
+                        const float total = (m_run[j] > -INFINITY ? l_run[j] * __builtin_amdgcn_exp2f(m_run[j] - m_all) : 0.f) +
+                                            (mo > -INFINITY ? so * __builtin_amdgcn_exp2f(mo - m_all) : 0.f);
+                        const int h = kvh * group + (2 * now.pair + j) / n_rb, at = (a.w - L) + 32 * rb + li;
+                        a.part[(((size_t)range * a.n_seqs + b) * a.n_q_heads + h) * a.w + at] = make_float2(m_all, total);   // 32 rows: 256 consecutive bytes
                     }
                 }
             }
@@ -306,189 +406,234 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void score_kernel(
     // every load issued above has been waited for: nothing is in flight towards LDS here
     if (kMode == kStats) return;
 
-    // ---- add the 32 window-row lanes of each half and the two head groups, fixed order
-    const float norm = 1.0f / ((float)n_q_heads * weight_sum);
-    float (*red)[2][64][17] = (float (*)[2][64][17])smem;
-    __syncthreads();                                  // both wavefronts are done with their tiles
-#pragma unroll
-    for (int sk = 0; sk < 2; ++sk)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) red[wave][sk][lane][r] = acc[sk][r];
+    // ---- the sums of the two half-wavefronts (16 window rows of a block each) and of the wavefronts, fixed order
+    const float norm = 1.0f / ((float)a.n_q_heads * weight_sum);
     __syncthreads();
-    if (lane < 32) {
-        const int sk = wave;                          // wavefront 0 sums the first 32 keys, wavefront 1 the rest
-        // key offset `lane` inside the sub-tile lives in half (lane>>2)&1, register 4*(lane>>3)+(lane&3)
-        const int half = (lane >> 2) & 1, r = 4 * (lane >> 3) + (lane & 3);
+    float* dst = a.sums + (size_t)blockIdx.y * a.total_tokens + row0 + key_base;
+    for (int x = threadIdx.x; x < 32 * n_tiles && key_base + x < S; x += blockDim.x) {
+        const uint32_t at = lds0 + kSlots * kTileBytes + 2 * kRowArea + 256 * (x >> 5) + 4 * (x & 31);
         float sum = 0.f;
-        for (int v = 0; v < kWavesPerBlock; ++v)
-            for (int j = 0; j < 32; ++j) sum += red[v][sk][32 * half + j][r];
-        const int key = key_base + 32 * sk + lane;
-        float* dst = gridDim.y > 1 ? tail.part_sums + (size_t)blockIdx.y * tail.total_tokens : scores;
-        if (key < S) dst[row0 + key] = sum * norm;
-    }
-    if (gridDim.y == 1) return;
-
-    // ---- the last of this key block's head groups to arrive adds up the partial sums, in head-group order.
-    // (Uniform over the workgroup from here on.)
-    int* flag = (int*)smem;                           // (past the reduction's reads: behind a barrier)
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();                              // this workgroup's partial sums are visible before its count is
-        int* cnt = tail.counters + b * blocks_per_seq + key_block;
-        const int old = atomicAdd(cnt, 1);
-        *flag = old == (int)gridDim.y - 1;
-        if (*flag) *cnt = 0;                          // back to zero for the next launch
-    }
-    __syncthreads();
-    if (*flag == 0) return;
-    __threadfence();                                  // the other head groups' partial sums are visible now
-    const int key = key_base + (int)threadIdx.x;
-    if (threadIdx.x < 64 && key < S) {
-        float sum = 0.f;
-        for (int hg = 0; hg < (int)gridDim.y; ++hg) sum += tail.part_sums[(size_t)hg * tail.total_tokens + row0 + key];
-        scores[row0 + key] = sum;
+        for (int wv = 0; wv < waves; ++wv) {
+            const uint32_t p = at + wv * wave_bytes;
+            sum += *(const lfloat_t)(uintptr_t)p + *(const lfloat_t)(uintptr_t)(p + 128);
+        }
+        dst[x] = sum * norm;
     }
 }
 
-// Row denominators of the window rows from the per-block statistics: for every (sequence,
-// window slot, head) fold (max, sum) over the key blocks the row can see, in block order:
-//   lse = M + log2(sum_kb sum_kb * 2^(m_kb - M)),  M = max_kb m_kb.
-__global__ __launch_bounds__(256) void fold_stats_kernel(const float2* __restrict__ part,
-                                                         const int32_t* __restrict__ seq_offsets, int32_t n_seqs,
-                                                         int32_t n_q_heads, int32_t w, float* __restrict__ lse_win) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;        // (b, h, slot), slot fastest, as in part
-    if (idx >= (int64_t)n_seqs * w * n_q_heads) return;
-    const int slot = (int)(idx % w), h = (int)((idx / w) % n_q_heads), b = (int)(idx / ((int64_t)n_q_heads * w));
-    float* dst = lse_win + ((size_t)b * w + slot) * n_q_heads + h;
-    const int S = seq_offsets[b + 1] - seq_offsets[b];
-    const int L = min(w, S), i = slot - (w - L);
-    if (i < 0) {                                      // slot not in use (sequence shorter than the window)
-        *dst = 0.f;
-        return;
+// Row denominators of the window rows from the per-range statistics: for every (sequence,
+// window slot, head) fold (max, sum) over the ranges the row can see, in a fixed order:
+//   lse = M + log2(sum_r sum_r * 2^(m_r - M)),  M = max_r m_r.
+// Bound: the latency of the loads, so eight lanes share a row (lane u takes ranges u, u + 8, ..., four of them in flight)
+// and their eight results are folded through LDS.
+constexpr int kFoldRows = 32, kFoldLanes = 8;
+
+__device__ __forceinline__ void fold_one(float& m_run, float& s_run, float m, float s) {
+    const float m_new = fmaxf(m_run, m);
+    if (m_new > -INFINITY) {      // (2^-inf = 0 for the side that is still empty)
+        s_run = s_run * __builtin_amdgcn_exp2f(m_run - m_new) + s * __builtin_amdgcn_exp2f(m - m_new);
+        m_run = m_new;
     }
-    const int n_blocks = (S - L + i) / kKeysPerBlock + 1;        // key blocks row S-L+i can see
-    const size_t stride = (size_t)n_seqs * w * n_q_heads;
+}
+
+__global__ __launch_bounds__(kFoldRows * kFoldLanes) void fold_stats_kernel(const float2* __restrict__ part,
+                                                         const int32_t* __restrict__ seq_offsets, int32_t n_seqs,
+                                                         int32_t n_q_heads, int32_t w, int32_t range_keys, float* __restrict__ lse_win) {
+    __shared__ float2 folded[kFoldLanes][kFoldRows + 1];
+    const int row = threadIdx.x % kFoldRows, u = threadIdx.x / kFoldRows;
+    const int64_t idx = (int64_t)blockIdx.x * kFoldRows + row;          // (b, h, slot), slot fastest, as in part
+    const int64_t n_rows = (int64_t)n_seqs * w * n_q_heads;
+    int slot = 0, h = 0, b = 0, n_ranges = 0;
+    if (idx < n_rows) {
+        slot = (int)(idx % w);
+        h = (int)((idx / w) % n_q_heads);
+        b = (int)(idx / ((int64_t)n_q_heads * w));
+        const int S = seq_offsets[b + 1] - seq_offsets[b];
+        const int L = min(w, S), i = slot - (w - L);
+        if (i >= 0) n_ranges = (S - L + i) / range_keys + 1;            // ranges row S-L+i can see (0: slot not in use)
+    }
     float m_run = -INFINITY, s_run = 0.f;
-    for (int kb = 0; kb < n_blocks; ++kb) {
-        const float2 p = part[kb * stride + idx];
-        if (p.x > m_run) {
-            s_run = s_run * __builtin_amdgcn_exp2f(m_run - p.x) + p.y;      // (2^-inf = 0 the first time)
-            m_run = p.x;
-        } else {
-            s_run += p.y * __builtin_amdgcn_exp2f(p.x - m_run);
+    constexpr int kAhead = 4;
+    for (int r0 = u; r0 < n_ranges; r0 += kFoldLanes * kAhead) {
+        float2 p[kAhead];
+#pragma unroll
+        for (int v = 0; v < kAhead; ++v) p[v] = part[(size_t)min(r0 + kFoldLanes * v, n_ranges - 1) * n_rows + idx];
+#pragma unroll
+        for (int v = 0; v < kAhead; ++v)
+            if (r0 + kFoldLanes * v < n_ranges) fold_one(m_run, s_run, p[v].x, p[v].y);
+    }
+    folded[u][row] = make_float2(m_run, s_run);
+    __syncthreads();
+    if (u != 0 || idx >= n_rows) return;
+    for (int v = 1; v < kFoldLanes; ++v) fold_one(m_run, s_run, folded[v][row].x, folded[v][row].y);
+    lse_win[((size_t)b * w + slot) * n_q_heads + h] = n_ranges > 0 ? m_run + __builtin_amdgcn_logf(s_run) : 0.f;
+}
+
+// How a walk over K is cut up.
+struct StripPlan {
+    int range_tiles, waves, groups;
+};
+
+// Two limits, in microseconds as measured at d = 128.  The chain: a wavefront takes 0.82 per tile of its stream alone on its
+// SIMD (wait, copy, products, exponentials) and 1.0 beside a second one, and a compute unit runs its workgroups in rounds
+// (a grid that fits exactly does not always start at once: nine tenths are counted on).  The stream: a compute unit's
+// share of the memory system delivers a tile of K from HBM in 0.35 and one of Q from L2 in 0.08; a last round that is
+// not full costs half of what it leaves idle.  The cut with the smallest larger one wins.
+// (Predicted / measured: 64 x 2048, ranges of 256 keys, 189 / 187 us, of 352 keys 218 / 224; 4 x 32768 with 64/8 heads
+// and w = 128, 256 keys, 326 / 378, of 384 keys 454 / 460; 8 x 2048, 64 keys, 28 / 30, of 256 keys 46 / 49.)
+StripPlan plan_strip(const pyr_shape& s, int32_t min_seqlen, int32_t w, int compute_units, int min_range_tiles, int max_groups) {
+    const int L = w < s.max_seqlen ? w : s.max_seqlen;
+    const int64_t n_rb = (L + 31) / 32, pairs = (s.n_q_heads / s.n_kv_heads * n_rb + 1) / 2, tasks = s.n_kv_heads * pairs;
+    const int64_t max_tiles = (s.max_seqlen + 31) / 32;
+    const double tiles = min_seqlen == s.max_seqlen ? (double)s.n_seqs * max_tiles : s.total_tokens / 32.0 + 0.5 * s.n_seqs;
+    const double spill = min_seqlen == s.max_seqlen ? 0.0 : 0.4;       // (ragged: the XCDs' shares of a round differ)
+    StripPlan best{1, 1, 1};
+    double best_cost = 1e300;
+    for (int nt = kMaxRangeTiles; nt >= 1; --nt) {
+        if (nt < min_range_tiles && nt < max_tiles) continue;
+        const int64_t ranges_per_seq = (max_tiles + nt - 1) / nt;
+        if (nt > min_range_tiles && ranges_per_seq == (max_tiles + nt - 2) / (nt - 1)) continue;   // the same number of ranges, more evenly
+        const double ranges = min_seqlen == s.max_seqlen ? (double)s.n_seqs * ranges_per_seq : tiles / nt + 0.5 * s.n_seqs;
+        const double size = s.head_dim / 128.0, stream = tasks * (tiles * 0.35 + ranges * 2 * 0.08) * size / compute_units;
+        for (int waves = kMaxWaves; waves >= 1; waves /= 2) {
+            if (waves > tasks && waves > 1) continue;
+            // workgroups a compute unit holds: 8 wavefronts at d = 128 and 12 at d = 64 by registers, 160 KB of LDS
+            const int bytes = s.head_dim == 64 ? wave_lds_bytes<64>(nt) : wave_lds_bytes<128>(nt);
+            int wgs_per_cu = 160 * 1024 / (waves * bytes);
+            if (wgs_per_cu > (s.head_dim == 64 ? 12 : 8) / waves) wgs_per_cu = (s.head_dim == 64 ? 12 : 8) / waves;
+            for (int g = 1; g <= max_groups && (g == 1 || (int64_t)g * waves < 2 * tasks); g *= 2) {
+                const int64_t tpw = (tasks + (int64_t)g * waves - 1) / ((int64_t)g * waves);
+                const double wgs = ranges * g, rounds = wgs / ((double)compute_units * wgs_per_cu), whole = ceil(rounds + spill);
+                const double tile = (wgs * waves > 4.0 * compute_units ? 1.0 : 0.82) * (0.4 + 0.6 * size);
+                const double chain = ceil(rounds / 0.9) * tpw * (nt + 2) * tile;
+                const double idle = 1.0 + 0.5 * (whole / rounds - 1.0);
+                const double cost = (chain + 6.0 > stream * idle ? chain + 6.0 : stream * idle) + 0.25 * (g - 1);
+                if (cost < best_cost * 0.999) {
+                    best_cost = cost;
+                    best = StripPlan{nt, waves, g};
+                }
+            }
         }
     }
-    *dst = m_run + __builtin_amdgcn_logf(s_run);
+    return best;
 }
 
-}  // namespace
-
-namespace {
-template <int kMode>
-int launch_walk(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev, const pyr_shape& s,
-                int32_t min_seqlen, int32_t w, int32_t q_window, float scale_log2, const float* row_weights, float* scores,
-                float2* part, hipStream_t stream,
-                const ScoreTail& tail = ScoreTail{nullptr, nullptr, 0}, int head_groups = 1) {
-    const int32_t blocks_per_seq = (s.max_seqlen + kKeysPerBlock - 1) / kKeysPerBlock;
-    DeviceInfo dev;
-    if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
-    // A whole sequence per XCD where that spreads the work evenly by construction (equal lengths, a multiple of the XCD
-    // count); otherwise the plain order, key block after key block over the XCDs: with ragged lengths the sequences
-    // of one XCD can be much longer than another's (measured: 32 sequences of 512...8192 tokens, 0.35 -> 0.51 ms).
-    const int32_t xcds = dev.xccs;
-    const int32_t chunk_blocks = min_seqlen == s.max_seqlen && s.n_seqs % xcds == 0 ? blocks_per_seq : 1;
-    // (rows of 10 KB - 40 heads - are spread well as they are, and lose 4 % to the rotation: neighbouring key blocks then
-    //  no longer share the window's Q rows of one head in L2)
-    const size_t k_row_bytes = (size_t)s.n_kv_heads * s.head_dim * 2;
-    const int32_t head_step = (k_row_bytes & (k_row_bytes - 1)) == 0 ? 7 : 0;
-    const int64_t chunks = (int64_t)s.n_seqs * ((blocks_per_seq + chunk_blocks - 1) / chunk_blocks);
-    const int64_t n_blocks = (chunks + xcds - 1) / xcds * xcds * chunk_blocks;
-    if (n_blocks >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
-    dim3 grid((unsigned)n_blocks, (unsigned)head_groups, 1), block(kWavesPerBlock * 64);
-    if (s.head_dim == 128)
-        hipLaunchKernelGGL((score_kernel<128, kMode>), grid, block, 0, stream, (const uint16_t*)q, (const uint16_t*)k, lse,
-                           seq_offsets_dev, s.n_seqs, s.n_q_heads, s.n_kv_heads, w, blocks_per_seq, chunk_blocks, xcds, head_step,
-                           q_window, scale_log2, row_weights, scores, part, tail);
-    else
-        hipLaunchKernelGGL((score_kernel<64, kMode>), grid, block, 0, stream, (const uint16_t*)q, (const uint16_t*)k, lse,
-                           seq_offsets_dev, s.n_seqs, s.n_q_heads, s.n_kv_heads, w, blocks_per_seq, chunk_blocks, xcds, head_step,
-                           q_window, scale_log2, row_weights, scores, part, tail);
+template <int D, int kMode>
+int launch_strip_d(const StripArgs& a, dim3 grid, int waves, hipStream_t stream) {
+    static std::atomic<uint64_t> lds_set{0};
+    if (ensure_dynamic_lds((const void*)strip_kernel<D, kMode>, kMaxWaves * wave_lds_bytes<D>(kMaxRangeTiles), &lds_set) != PYR_OK)
+        return PYR_ERR_LAUNCH;
+    hipLaunchKernelGGL((strip_kernel<D, kMode>), grid, dim3(64 * waves), waves * wave_lds_bytes<D>(a.range_tiles), stream, a);
     return check_launch();
 }
+
+template <int kMode>
+int launch_strip(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev, const pyr_shape& s,
+                 int32_t min_seqlen, int32_t w, int32_t q_window, float scale_log2, const float* row_weights, float* sums,
+                 float2* part, const StripPlan& plan, const DeviceInfo& dev, hipStream_t stream) {
+    StripArgs a{};
+    a.q = (const uint16_t*)q;
+    a.k = (const uint16_t*)k;
+    a.lse = lse;
+    a.seq_offsets = seq_offsets_dev;
+    a.n_seqs = s.n_seqs;
+    a.n_q_heads = s.n_q_heads;
+    a.n_kv_heads = s.n_kv_heads;
+    a.w = w;
+    a.range_tiles = plan.range_tiles;
+    a.ranges_per_seq = ((s.max_seqlen + 31) / 32 + plan.range_tiles - 1) / plan.range_tiles;
+    // A whole sequence per XCD where that spreads the work evenly by construction (equal lengths, a multiple of the XCD
+    // count: 64 x 2048 216 -> 196 us); otherwise the plain order, range after range over the XCDs: with ragged lengths the
+    // sequences of one XCD can be much longer than another's.  An odd number of ranges per sequence (the last one may be
+    // empty) keeps range r of all sequences from meeting on one XCD (32 sequences of 512...8192 tokens, ranges of 256
+    // keys: 326 us with 32 ranges per sequence).
+    a.xcds = dev.xccs;
+    const bool seq_per_xcd = min_seqlen == s.max_seqlen && s.n_seqs % dev.xccs == 0;
+    if (!seq_per_xcd && s.n_seqs > 1) a.ranges_per_seq |= 1;
+    a.chunk_ranges = seq_per_xcd ? a.ranges_per_seq : 1;
+    // (rows a power of two apart: 64 x 2048 in ranges of 256 keys 210 us without, 188 with steps of 8, 196 with 7, 8 x 2048
+    //  in ranges of 64 keys 31.8, 36.7 and 29.8; rows of 10 KB: no difference)
+    const size_t k_row_bytes = (size_t)s.n_kv_heads * s.head_dim * 2;
+    a.head_step = (k_row_bytes & (k_row_bytes - 1)) != 0 ? 0 : plan.range_tiles >= 8 ? 8 : 7;
+    a.q_window = q_window;
+    a.c = scale_log2;
+    a.row_weights = row_weights;
+    a.sums = sums;
+    a.total_tokens = s.total_tokens;
+    a.part = part;
+    const int64_t chunks = (int64_t)s.n_seqs * ((a.ranges_per_seq + a.chunk_ranges - 1) / a.chunk_ranges);
+    const int64_t n = (chunks + a.xcds - 1) / a.xcds * a.xcds * a.chunk_ranges;
+    if (n >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)n, (unsigned)plan.groups, 1);
+    return s.head_dim == 128 ? launch_strip_d<128, kMode>(a, grid, plan.waves, stream)
+                             : launch_strip_d<64, kMode>(a, grid, plan.waves, stream);
+}
+
+int launch_scores(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev, const pyr_shape& s,
+                  int32_t min_seqlen, int32_t w, int32_t q_window, float scale_log2, const float* row_weights, float* scores,
+                  float* parts, int max_groups, int* groups, hipStream_t stream) {
+    DeviceInfo dev;
+    if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
+    const StripPlan plan = plan_strip(s, min_seqlen, w, dev.compute_units, 1, max_groups);
+    *groups = plan.groups;
+    float* sums = plan.groups > 1 ? parts : scores;
+    return row_weights ? launch_strip<kScoresWeighted>(q, k, lse, seq_offsets_dev, s, min_seqlen, w, q_window, scale_log2, row_weights,
+                                                       sums, nullptr, plan, dev, stream)
+                       : launch_strip<kScores>(q, k, lse, seq_offsets_dev, s, min_seqlen, w, q_window, scale_log2, nullptr, sums,
+                                               nullptr, plan, dev, stream);
+}
+
 }  // namespace
 
 int launch_score(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev,
                  const pyr_shape& s, int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights,
                  float* scores, hipStream_t stream) {
     if (s.n_seqs == 0 || s.max_seqlen == 0) return PYR_OK;
-    return row_weights ? launch_walk<kScoresWeighted>(q, k, lse, seq_offsets_dev, s, min_seqlen, w, 0, scale_log2, row_weights, scores,
-                                                      nullptr, stream)
-                       : launch_walk<kScores>(q, k, lse, seq_offsets_dev, s, min_seqlen, w, 0, scale_log2, nullptr, scores, nullptr,
-                                              stream);
+    int groups = 1;
+    return launch_scores(q, k, lse, seq_offsets_dev, s, min_seqlen, w, 0, scale_log2, row_weights, scores, nullptr, 1, &groups, stream);
 }
 
-// Head groups for a grid of n_blocks key blocks: enough workgroups for two per compute unit, every group at least
-// two KV heads (one per wavefront) where there are two, an even split.
-static int pick_head_groups(int64_t n_blocks, int n_kv_heads, int compute_units) {
-    int g = 1;
-    while (g < kMaxHeadGroups && n_blocks * g < 2 * (int64_t)compute_units && n_kv_heads % (2 * g) == 0 &&
-           n_kv_heads / (2 * g) >= 2)
-        g *= 2;
-    return g;
-}
-
-size_t score_tail_bytes(const pyr_shape& s) {
-    const size_t blocks_per_seq = ((size_t)s.max_seqlen + kKeysPerBlock - 1) / kKeysPerBlock;
-    const size_t counters = ((size_t)s.n_seqs * blocks_per_seq * sizeof(int32_t) + 255) / 256 * 256;
-    // partial sums are only ever used by grids of fewer than 2 x 256 key blocks
-    const size_t parts = (size_t)s.n_seqs * blocks_per_seq < 1024 ? (size_t)kMaxHeadGroups * s.total_tokens * sizeof(float) : 0;
-    return counters + (parts + 255) / 256 * 256;
-}
-
-int32_t score_tail_counters(const pyr_shape& s) {
-    const int32_t blocks_per_seq = (s.max_seqlen + kKeysPerBlock - 1) / kKeysPerBlock;
-    return s.n_seqs * blocks_per_seq;
+// (Only batches of fewer than 1024 blocks of 64 keys are ever split: beyond that the ranges alone fill the chip.)
+size_t score_parts_bytes(const pyr_shape& s) {
+    const size_t blocks = (size_t)s.n_seqs * (((size_t)s.max_seqlen + 63) / 64);
+    return blocks < 1024 ? (size_t)kMaxScoreGroups * s.total_tokens * sizeof(float) : 0;
 }
 
 int launch_score_groups(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev,
                         const pyr_shape& s, int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights,
-                        float* scores, void* tail_ws, hipStream_t stream) {
+                        float* scores, float* parts, int* groups, hipStream_t stream) {
+    *groups = 1;
     if (s.n_seqs == 0 || s.max_seqlen == 0) return PYR_OK;
-    DeviceInfo dev;
-    if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
-    const int64_t blocks_per_seq = (s.max_seqlen + kKeysPerBlock - 1) / kKeysPerBlock;
-    const int64_t n_blocks = blocks_per_seq * s.n_seqs;
-    const int g = n_blocks < 1024 ? pick_head_groups(n_blocks, s.n_kv_heads, dev.compute_units) : 1;
-    if (g == 1) return launch_score(q, k, lse, seq_offsets_dev, s, min_seqlen, w, scale_log2, row_weights, scores, stream);
-    const size_t counter_bytes = ((size_t)s.n_seqs * blocks_per_seq * sizeof(int32_t) + 255) / 256 * 256;
-    ScoreTail tail{(int32_t*)tail_ws, (float*)((char*)tail_ws + counter_bytes), s.total_tokens};
-    return row_weights ? launch_walk<kScoresWeighted>(q, k, lse, seq_offsets_dev, s, min_seqlen, w, 0, scale_log2, row_weights, scores,
-                                                      nullptr, stream, tail, g)
-                       : launch_walk<kScores>(q, k, lse, seq_offsets_dev, s, min_seqlen, w, 0, scale_log2, nullptr, scores, nullptr,
-                                              stream, tail, g);
+    return launch_scores(q, k, lse, seq_offsets_dev, s, min_seqlen, w, 0, scale_log2, row_weights, scores, parts,
+                         parts != nullptr ? kMaxScoreGroups : 1, groups, stream);
 }
 
 size_t window_score_part_bytes(const pyr_shape& s, int32_t w) {
-    const size_t blocks_per_seq = ((size_t)s.max_seqlen + kKeysPerBlock - 1) / kKeysPerBlock;
-    return blocks_per_seq * (size_t)s.n_seqs * (size_t)w * (size_t)s.n_q_heads * sizeof(float2);
+    const size_t ranges = ((size_t)s.max_seqlen + 63) / 64;           // (statistics ranges are at least 64 keys)
+    return ranges * (size_t)s.n_seqs * (size_t)w * (size_t)s.n_q_heads * sizeof(float2);
 }
 
 int launch_window_score(const void* q_win, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& s,
                         int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights, float* lse_win, void* part, float* scores,
-                        hipStream_t stream) {
+                        int* groups, hipStream_t stream) {
+    *groups = 1;
     if (s.n_seqs == 0 || s.max_seqlen == 0) return PYR_OK;
-    int rc = launch_walk<kStats>(q_win, k, nullptr, seq_offsets_dev, s, min_seqlen, w, 1, scale_log2, nullptr, nullptr, (float2*)part,
-                                 stream);
+    DeviceInfo dev;
+    if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
+    const StripPlan stats = plan_strip(s, min_seqlen, w, dev.compute_units, 2, kMaxScoreGroups);
+    int rc = launch_strip<kStats>(q_win, k, nullptr, seq_offsets_dev, s, min_seqlen, w, 1, scale_log2, nullptr, nullptr, (float2*)part,
+                                  stats, dev, stream);
     if (rc != PYR_OK) return rc;
     const int64_t n = (int64_t)s.n_seqs * w * s.n_q_heads;
-    if ((n + 255) / 256 >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(fold_stats_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, (const float2*)part,
-                       seq_offsets_dev, s.n_seqs, s.n_q_heads, w, lse_win);
+    if ((n + kFoldRows - 1) / kFoldRows >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(fold_stats_kernel, dim3((unsigned)((n + kFoldRows - 1) / kFoldRows)), dim3(kFoldRows * kFoldLanes), 0, stream, (const float2*)part,
+                       seq_offsets_dev, s.n_seqs, s.n_q_heads, w, (int32_t)(32 * stats.range_tiles), lse_win);
     if (check_launch() != PYR_OK) return PYR_ERR_LAUNCH;
-    return row_weights ? launch_walk<kScoresWeighted>(q_win, k, lse_win, seq_offsets_dev, s, min_seqlen, w, 1, scale_log2, row_weights,
-                                                      scores, nullptr, stream)
-                       : launch_walk<kScores>(q_win, k, lse_win, seq_offsets_dev, s, min_seqlen, w, 1, scale_log2, nullptr, scores,
-                                              nullptr, stream);
+    // the statistics are dead once folded: their space takes the partial sums, as many as fit
+    int most = 1;
+    while (most < kMaxScoreGroups && 2 * (size_t)most * s.total_tokens * sizeof(float) <= window_score_part_bytes(s, w)) most *= 2;
+    return launch_scores(q_win, k, lse_win, seq_offsets_dev, s, min_seqlen, w, 1, scale_log2, row_weights, scores, (float*)part, most,
+                         groups, stream);
 }
 
 }  // namespace pyr

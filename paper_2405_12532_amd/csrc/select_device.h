@@ -216,11 +216,12 @@ __device__ void select_body(const uint32_t* lds_keys, const float* __restrict__ 
 }
 
 // The selection of sequence b by the calling workgroup (all kT lanes take part; uniform control
-// flow).  lds_keys: room for lds_cap keys; scores of longer contexts are re-read from memory in
+// flow).  groups > 1: the scores are first added up from parts[groups][total_tokens], in order, and written.
+// lds_keys: room for lds_cap keys; scores of longer contexts are re-read from memory in
 // every pass.  Also writes out_offsets[b + 1] (and out_offsets[0] for b == 0).
 template <int kT>
-__device__ void select_sequence(int b, const float* __restrict__ scores, const int32_t* __restrict__ seq_offsets,
-                                const int32_t* __restrict__ keep_len, int32_t w, uint32_t* lds_keys, int32_t lds_cap,
+__device__ void select_sequence(int b, const float* __restrict__ parts, int groups, int32_t total_tokens, float* scores,
+                                const int32_t* __restrict__ seq_offsets, const int32_t* __restrict__ keep_len, int32_t w, uint32_t* lds_keys, int32_t lds_cap,
                                 SelectShared* sh, int32_t* __restrict__ kept_idx, int32_t* __restrict__ out_offsets) {
     constexpr int kW = kT / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -230,7 +231,7 @@ __device__ void select_sequence(int b, const float* __restrict__ scores, const i
     const int k = min(max(keep_len[b], L), S);
     const int C = S - L;                        // context positions, the candidates
     const int need = k - L;                     // how many of them survive
-    const float* __restrict__ sc = scores + row0;
+    float* sc = scores + row0;
 
     // packed position of this sequence's output: sum of the keep counts before it
     int part = 0;
@@ -240,15 +241,24 @@ __device__ void select_sequence(int b, const float* __restrict__ scores, const i
     const bool staged = C <= lds_cap;
     const bool ranked = need > 0 && need < C;   // else there is nothing to decide
     uint32_t kmin = 0xffffffffu, kmax = 0u;
-    if (ranked) {
+    if (ranked || groups > 1) {
         constexpr int kAhead = 8;               // scores a lane has in flight
-        for (int i0 = tid; i0 < C; i0 += kAhead * kT) {
+        const float* __restrict__ from = groups > 1 ? parts + row0 : sc;
+        const int n = groups > 1 ? S : C;
+        for (int i0 = tid; i0 < n; i0 += kAhead * kT) {
             float x[kAhead];
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) x[u] = i0 + u * kT < C ? sc[i0 + u * kT] : 0.f;
+            for (int u = 0; u < kAhead; ++u) x[u] = i0 + u * kT < n ? from[i0 + u * kT] : 0.f;
+            for (int g = 1; g < groups; ++g) {
+                const float* __restrict__ more = from + (size_t)g * total_tokens;
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) x[u] += i0 + u * kT < n ? more[i0 + u * kT] : 0.f;
+            }
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
                 const int i = i0 + u * kT;
+                if (i >= n) break;
+                if (groups > 1) sc[i] = x[u];
                 if (i >= C) break;
                 const uint32_t key = ordered_key(x[u]);
                 if (staged) lds_keys[i] = key;
@@ -269,7 +279,7 @@ __device__ void select_sequence(int b, const float* __restrict__ scores, const i
         sh->wave_min[wave] = kmin;
         sh->wave_max[wave] = kmax;
     }
-    __syncthreads();
+    __syncthreads();                            // (also: the scores written above are visible to the workgroup)
     int out_base = 0;
 #pragma unroll
     for (int u = 0; u < kW; ++u) {

@@ -1,0 +1,75 @@
+"""The score and statistics walks (stationary window queries, keys streamed in ranges) at the edges of their cut: tiles of
+32 keys, ranges of 1 to 12 tiles, row blocks of 32 window rows paired within a KV head's group, tasks split over
+wavefronts and workgroups.  Against the float64 oracle; the scores tighter than the parity tolerance: a logit of magnitude x
+carries at most 130 roundings of the fp32 accumulation and its row's denominator as many, so x = 8 bounds the
+relative error of a probability by 260 * 2^-24 * 8 ~ 1.3e-4 and in the mean (rounding errors of either sign) far below it."""
+import numpy as np
+import pytest
+
+from paper_2405_12532_amd import synth
+from tests import parity, test_gpu_decode, test_gpu_layer
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+SCORE_RTOL = 1.3e-4
+
+
+def _wl(lens, Hq, Hkv, d, w):
+    return synth.shrunk(synth.workload("cfg2"), lens, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, w=w, hidden_dim=0)
+
+
+SHAPES = [
+    ((31, 32, 33, 63, 64, 65, 96, 97), 4, 4, 128, 32),          # one row block per head, tiles and their remainders
+    ((383, 384, 385, 767, 768, 769), 2, 2, 128, 33),            # around ranges of 12 tiles; a row block of one row
+    ((200, 1, 90), 6, 2, 128, 20),                              # group of 3: pairs span query heads, one row block is left over
+    ((500, 130), 12, 4, 64, 96),                                # nine row blocks per KV head
+    ((260,), 40, 40, 128, 64),                                  # rows not a power of two apart; tasks split over workgroups
+    ((1300,), 5, 5, 64, 100),                                   # fewer tasks than wavefronts; four row blocks, the last of four rows
+    ((150,) * 16, 8, 8, 128, 64),                               # a sequence per XCD
+]
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w", SHAPES)
+@pytest.mark.parametrize("weighted", [False, True])
+def test_prefill_scores(lib, lens, Hq, Hkv, d, w, weighted):
+    rw = np.linspace(0.0, 1.0, w, dtype=np.float32) if weighted and w > 1 else None      # (the first weight is zero)
+    res, ref, _ = test_gpu_layer.run_and_check(lib, _wl(lens, Hq, Hkv, d, w), row_weights=rw)
+    np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w", SHAPES)
+def test_decode_scores(lib, lens, Hq, Hkv, d, w):
+    res, ref, _ = test_gpu_decode.run_and_check(lib, _wl(lens, Hq, Hkv, d, w), with_pos=True)
+    np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
+
+
+def test_decode_long_cache(lib):
+    """More ranges than the fold keeps in flight, and a context the selection cannot stage in LDS."""
+    res, ref, _ = test_gpu_decode.run_and_check(lib, _wl((40000,), 8, 2, 64, 40))
+    np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
+
+
+def test_loose_max_seqlen(lib):
+    """A caller whose max_seqlen is far above the longest sequence gets no more workspace than it asked for: the score pass may not
+    split itself into partial sums there.  The guard behind the workspace stays as it was."""
+    lens, H, d, w = (64,) * 64, 8, 64, 16
+    wl = _wl(lens, H, H, d, w)
+    x = parity.inputs(wl, lib, want_hidden=False)
+    q, k, v = (lib.to_device_bf16(x[n]) for n in ("q", "k", "v"))
+    T = sum(lens)
+    off_h = torch.from_numpy(np.ascontiguousarray(x["seq_offsets"], dtype=np.int32))
+    keep_h = torch.from_numpy(np.ascontiguousarray(x["keep_len"], dtype=np.int32))
+    off_d, keep_d = off_h.cuda(), keep_h.cuda()
+    n_kept = int(keep_h.sum())
+    results = []
+    for claimed in (64, T):
+        shape = lib.make_shape(len(lens), T, claimed, H, H, d)
+        ws_bytes = lib.workspace_bytes(shape, w)
+        ws = torch.full((ws_bytes + 4 * 16 * T,), 0x5A, dtype=torch.uint8, device="cuda")
+        out, scores = torch.empty_like(q), torch.empty(T, dtype=torch.float32, device="cuda")
+        kept, out_off = torch.empty(n_kept, dtype=torch.int32, device="cuda"), torch.empty(len(lens) + 1, dtype=torch.int32, device="cuda")
+        lib.prefill_layer(q, k, v, off_d, off_h, shape, w, 0.0, keep_d, keep_h, out, scores, kept, out_off, None, None, ws, ws_bytes)
+        torch.cuda.synchronize()
+        assert bool((ws[ws_bytes:] == 0x5A).all())
+        results.append(scores.cpu().numpy())
+    np.testing.assert_allclose(results[0], results[1], rtol=2e-6, atol=1e-12)
