@@ -1,9 +1,11 @@
 // Causal softmax attention over packed, ragged sequences (Algorithm 1, "compute attention
 // weights of KV", applied to V), flash style: the S x S weight matrix never exists.
 //
-// Work split.  The unit of work is a SEGMENT: kAttnBlockRows (256) consecutive query
-// positions of one (sequence, query head); each of the 8 wavefronts of a workgroup owns 32 of
-// them.  Segments are paired into ITEMS - query tile j of a sequence together with tile
+// Two kernels.  This file: d = 128 and enough long query tiles to keep every compute unit at work.  attention_tile.hip: one
+// tile per workgroup, for d = 64, short sequences and small batches.  pick_kernel() below says where the line lies.
+//
+// Work split.  The unit of work is a SEGMENT: 256 consecutive query positions of one
+// (sequence, query head); each of the 8 wavefronts of a workgroup owns 32 of them.  Segments are paired into ITEMS - query tile j of a sequence together with tile
 // n-1-j - so every item of a sequence sweeps the same number of causal key tiles.  Workgroups
 // are persistent, one per compute unit (two wavefronts per SIMD), each walking items with a
 // fixed stride.  The 32-row blocks are dealt to the wavefronts so that the two wavefronts of a
@@ -50,13 +52,18 @@
 // reference by more than 2^16 (probabilities stay exact in fp32 and as precise in bf16 as at
 // any other magnitude).  The common tile therefore takes no row maximum, no cross-lane
 // exchange and no rescale of the output.
-#include <type_traits>
+#include <math.h>
 
-#include "pyr_internal.h"
+#include <numeric>
+
+#include "attention_device.h"
 
 namespace pyr {
 namespace {
 
+constexpr int D = 128;                     // head dimension
+constexpr int kNW = 8;                     // wavefronts of a workgroup, 32 query rows each
+constexpr int kBM = kNW * 32;              // query positions per segment
 constexpr int kBN = 64;                    // key positions per LDS tile
 constexpr int kRing = 4;                   // LDS tiles per ring (one ring for K, one for V)
 
@@ -65,9 +72,6 @@ constexpr int kRing = 4;                   // LDS tiles per ring (one ring for K
 // XOR swizzle of the 16-byte chunk index inside a row instead:
 //   K: chunk ^ (row & 15)        -> the 16 rows a b128 fragment read touches hit 16 bank groups
 //   V: chunk ^ ((row & 3) << 2)  -> the 4 rows x 64 B a transposing read touches tile the banks
-// (for D = 64 two rows share a 256-byte bank line: row is replaced by row / 2 and the masks
-// shrink to 7 and 1).
-template <int D, int kNW>
 struct Tile {
     static constexpr int kChunks = D / 8;                       // 16-byte chunks per row
     static constexpr int kRowBytes = D * 2;
@@ -76,64 +80,19 @@ struct Tile {
     static constexpr size_t kLdsBytes = 2 * (size_t)kRing * kMatBytes + (size_t)kNW * kQStageBytes;
 };
 
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef const __attribute__((address_space(1))) void* gptr_t;
-typedef __attribute__((address_space(3))) char* lptr_t;
-
-// v_permlane32_swap(x, x): result 0 holds lanes 0..31 of x in both halves, result 1 holds
-// lanes 32..63 of x in both halves; combining the two gives "own op other half" in every lane.
-__device__ __forceinline__ float max_with_other_half(float x) {
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float sum_with_other_half(float x) {
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// Transposing LDS read (ds_read_b64_tr_b16).  Inside every group of 16 lanes, lane j receives
-// element (j & 3) of the 8-byte words addressed by lanes (j >> 2), 4 + (j >> 2), 8 + (j >> 2)
-// and 12 + (j >> 2), in this order.
-__device__ __forceinline__ s16x4 lds_read_tr(int lds_addr) {
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(uintptr_t)lds_addr);
-}
-
-// 16 bytes per lane from global memory straight into LDS: lane l's data lands at
-// lds + 16*l (lds wave-uniform), its source is base (wave-uniform) + voff (per lane).
-// Written in assembly on purpose: the compiler would make every later LDS read wait for ALL
-// outstanding loads of this kind (it cannot tell the ring slots apart).  The kernel orders
-// these loads itself: s_waitcnt vmcnt(0) and a barrier before a slot is read.
-__device__ __forceinline__ void lds_dma16(const char* base_, uint32_t voff, uint32_t lds_addr) {
-    const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_addr);
-    const uint64_t b64 = (uint64_t)(uintptr_t)base_;         // wave-uniform by construction: keep it in scalar registers
-    const uint32_t b_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b64);          // (the builtin returns a signed int:
-    const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b64 >> 32));  //  widen it unsigned)
-    const char* base = (const char*)(uintptr_t)(((uint64_t)b_hi << 32) | (uint64_t)b_lo);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(m0), "v"(voff), "s"(base) : "memory", "m0");
-}
-
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {      // v_cvt_pk_bf16_f32
-    bf16x2 v;
-    v[0] = (__bf16)a;
-    v[1] = (__bf16)b;
-    return __builtin_bit_cast(uint32_t, v);
-}
-
-__host__ __device__ __forceinline__ int items_of(int seq_len, int block_rows) {       // paired query tiles of one (sequence, head)
-    return ((seq_len + block_rows - 1) / block_rows + 1) / 2;
+__host__ __device__ __forceinline__ int items_of(int seq_len) {       // paired query tiles of one (sequence, head)
+    return ((seq_len + kBM - 1) / kBM + 1) / 2;
 }
 
 // prefix sums of the number of items per (sequence, head) (ragged batches only)
 __global__ __launch_bounds__(1024) void item_map_kernel(const int32_t* __restrict__ seq_offsets, int32_t n_seqs,
-                                                        int32_t block_rows, int32_t* __restrict__ item_map) {
+                                                        int32_t* __restrict__ item_map) {
     __shared__ int part[1024];
     const int tid = threadIdx.x;
     const int chunk = (n_seqs + 1023) / 1024;
     const int lo = min(tid * chunk, n_seqs), hi = min(lo + chunk, n_seqs);
     int sum = 0;
-    for (int b = lo; b < hi; ++b) sum += items_of(seq_offsets[b + 1] - seq_offsets[b], block_rows);
+    for (int b = lo; b < hi; ++b) sum += items_of(seq_offsets[b + 1] - seq_offsets[b]);
     part[tid] = sum;
     __syncthreads();
     for (int d = 1; d < 1024; d <<= 1) {
@@ -145,7 +104,7 @@ __global__ __launch_bounds__(1024) void item_map_kernel(const int32_t* __restric
     int run = part[tid] - sum;
     for (int b = lo; b < hi; ++b) {
         item_map[b] = run;
-        run += items_of(seq_offsets[b + 1] - seq_offsets[b], block_rows);
+        run += items_of(seq_offsets[b + 1] - seq_offsets[b]);
     }
     if (tid == 1023) item_map[n_seqs] = part[1023];
 }
@@ -168,33 +127,27 @@ struct Walker {
     Segment seg;
 };
 
-template <int D, int kNW>
 __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ seq_offsets, const int32_t* __restrict__ item_map,
     int32_t n_seqs, int32_t n_q_heads, int32_t n_kv_heads, int32_t uniform_len, int32_t xcds,
-    int32_t items_per_xcd, int32_t first_wave_slots, float c, uint16_t* __restrict__ out, float* __restrict__ lse) {
-    using T = Tile<D, kNW>;
-    constexpr int kBM = kNW * 32;                 // query positions per segment
+    int32_t items_per_xcd, int32_t turn, float c, uint16_t* __restrict__ out, float* __restrict__ lse) {
+    using T = Tile;
     constexpr int NS = D / 16;                    // MFMAs per group = k-steps of QK^T = V fragments of a half
     constexpr int kDTiles = D / 32;               // 32-row tiles of O^T
-    constexpr int EPS = 8 / NS;                   // logits of a chunk handled per slice (1 or 2)
+    static_assert(NS == 8, "a slice handles one logit of a chunk of eight");
     constexpr int kLook = NS - 2;                 // slices between the LDS read of a fragment and its MFMA
     constexpr int kRowsPerInstr = 1024 / T::kRowBytes;          // rows one 64-lane x 16 B LDS-direct load fills
     constexpr int kInstrPerMat = kBN / kRowsPerInstr;
     constexpr int kInstrPerWave = kInstrPerMat / kNW;
     static_assert(kInstrPerMat % kNW == 0 && kInstrPerWave >= 1, "tile rows must split evenly over the wavefronts");
-    constexpr int kLine = 256 / T::kRowBytes;                   // rows per 256-byte bank line (1 or 2)
 
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // 32-row block of this wavefront.  Eight wavefronts: SIMD s owns blocks s and 7-s.  Four: one wavefront per
-    // SIMD, and the second workgroup of a compute unit (slot >= first_wave_slots) deals the blocks the other
-    // way round, so that the two wavefronts sharing a SIMD again own blocks s and 3-s.
-    const int rb = kNW == 8 ? (wave < 4 ? wave : 11 - wave)
-                            : ((int)(blockIdx.x / xcds) >= first_wave_slots ? kNW - 1 - wave : wave);
+    // 32-row block of this wavefront: SIMD s owns blocks s and 7-s
+    const int rb = wave < 4 ? wave : 11 - wave;
     const int li = lane & 31;                     // row (A operand) / column (B, C) inside a 32-wide tile
     const int gl = lane >> 5;                     // which half of the k-slots / accumulator rows
     const int group = n_q_heads / n_kv_heads;
@@ -207,23 +160,27 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
     const int slot_stride = gridDim.x / xcds;
     const int per_item = (n_kv_heads / xcds) * group;    // (the host checked that the item count fits 31 bits)
 
-    // This workgroup takes the items first, first + stride, ... of its XCD's list.  Turning an item number
+    // This workgroup takes one item of every round of slot_stride items of its XCD's list.  Turning an item number
     // into (sequence, heads, tile pair) costs integer divisions (or a search through the ragged batch's
     // prefix sums), far too slow for the scalar unit at a change of segment; so the lanes do it, 64 items at
     // a time: lane l of every wavefront holds item tbl_base + l of the workgroup's list, decoded, in four
     // registers, and a walker fetches an entry with four v_readlane.
+    // The place inside a round moves on by `turn` from round to round: with an odd number of query tiles the item in the
+    // middle is a single tile, and at a fixed place the same workgroups would get that half-length item every time
+    // (64 x 700, three tiles: 488 -> 417 us; 64 x 1648, seven: 1924 -> 1697).
     const int first_item = blockIdx.x / xcds;
-    const int n_mine = (items_per_xcd - first_item + slot_stride - 1) / slot_stride;
+    const int full_rounds = items_per_xcd / slot_stride, last_round = items_per_xcd % slot_stride;
+    const int n_mine = full_rounds + ((first_item + full_rounds * turn) % slot_stride < last_round ? 1 : 0);
     int tbl_base = 0;
     int t_row0 = 0, t_len = 0, t_heads = 0, t_pair = 0;       // per lane: first row, length, h | kvh << 16, pair | tiles << 16
     auto fill_table = [&](int base) __attribute__((always_inline)) {
         tbl_base = base;
         const int jj = base + lane;
         if (jj < n_mine) {
-            const int item = first_item + jj * slot_stride;
+            const int item = jj * slot_stride + (first_item + jj * turn) % slot_stride;
             int before, b, n_items;
             if (uniform_len > 0) {
-                n_items = items_of(uniform_len, kBM);
+                n_items = items_of(uniform_len);
                 b = item / (per_item * n_items);
                 before = b * n_items;
             } else {
@@ -297,8 +254,8 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
 #pragma unroll
     for (int i = 0; i < kInstrPerWave; ++i) {
         const int r = (wave * kInstrPerWave + i) * kRowsPerInstr + l_row;
-        k_goff[i] = (uint32_t)r * tok_bytes + ((l_chunk ^ ((r / kLine) & (T::kChunks - 1))) << 4);
-        v_goff[i] = (uint32_t)r * tok_bytes + ((l_chunk ^ (((r / kLine) & (T::kChunks / 4 - 1)) << 2)) << 4);
+        k_goff[i] = (uint32_t)r * tok_bytes + ((l_chunk ^ (r & (T::kChunks - 1))) << 4);
+        v_goff[i] = (uint32_t)r * tok_bytes + ((l_chunk ^ ((r & (T::kChunks / 4 - 1)) << 2)) << 4);
     }
     struct LoadPos { size_t off; int t, S; };     // a tile of the stream, as far as the loads care: byte offset of its
                                                   // first row and head in k and v, tile number, sequence length
@@ -331,7 +288,7 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
     const int krow = (li & ~12) | ((li & 4) << 1) | ((li & 8) >> 1);
     // Byte offset of this lane's K fragment inside a 32-row half: row krow, logical chunk
     // 2*ks + gl, physical chunk (2*ks + gl) ^ swz, i.e. k_lane ^ (ks << 5).
-    const int k_lane = krow * T::kRowBytes + ((gl ^ ((krow / kLine) & (T::kChunks - 1))) << 4);
+    const int k_lane = krow * T::kRowBytes + ((gl ^ (krow & (T::kChunks - 1))) << 4);
     // V fragments come through the transposing read: this lane supplies the 8-byte word at key
     // 8*gl + ((lane & 15) >> 2) (+4 for the second read) of the 16-key step, head-dim columns
     // 32*dt + 16*((lane >> 4) & 1) + 4*(lane & 3) ..+3, i.e. half (lane & 1) of logical chunk
@@ -339,7 +296,7 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
     // so the offset for tile dt is v_lane ^ (dt << 6).
     const int vrow = 8 * gl + ((lane & 15) >> 2);
     const int v_lane = vrow * T::kRowBytes +
-                       (((((vrow / kLine) & (T::kChunks / 4 - 1)) << 2) + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) << 4) +
+                       ((((vrow & (T::kChunks / 4 - 1)) << 2) + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) << 4) +
                        8 * (lane & 1);
     // LDS addresses of the fragments.  The ring slot is part of the register: kaddr points into the
     // K slot of stream position "kpos", vaddr into the V slot of position "vpos"; both are moved on
@@ -456,7 +413,7 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
     // their steady-state step than the other half, which keeps the two wavefronts of a SIMD half
     // a step apart: while one is between groups (checks, cursor arithmetic, the barrier itself)
     // the other one feeds the matrix pipe.
-    const bool early_sync = kNW == 8 && wave >= kNW / 2;
+    const bool early_sync = wave >= kNW / 2;
 
     // ---- query fragments.  Loads into registers pass the vector memory path at a quarter of the
     // rate of loads that write LDS, and eight of them per wavefront at every change of segment held
@@ -515,9 +472,9 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
 
     // ---- slices.  Everything below is written in the order it should be issued; a scheduling
     // barrier after every slice keeps it.
-    // exponentials of logits sv[base + EPS*i ..] into fragment pf (element EPS*i ..)
-    float pend = 0.f;                             // even element waiting for its partner (EPS == 1)
-    float last_e = 0.f;                           // the exponential of the slice before (EPS == 1)
+    // exponential of logit sv[base + i] into fragment pf (element i)
+    float pend = 0.f;                             // even element waiting for its partner
+    float last_e = 0.f;                           // the exponential of the slice before
     auto e_use = [&](int j, u32x4& pf, float& lsum) __attribute__((always_inline)) {
         lsum += last_e;
         asm volatile("" : "+v"(lsum));
@@ -529,22 +486,13 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
         }
     };
     auto e_slice = [&](const f32x16& sv, int base, int i, u32x4& pf, float& lsum) __attribute__((always_inline)) {
-        if (EPS == 2) {
-            float a = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[base + 2 * i], c, nmc));
-            float b = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[base + 2 * i + 1], c, nmc));
-            lsum += a;
-            lsum += b;
-            pf[i] = pack_bf16(a, b);
-            asm volatile("" : "+v"(pf[i]), "+v"(lsum));   // computed HERE: the optimiser would sink it to its first use
-        } else {
-            // The sum and the bf16 pack of an exponential are issued one slice after it: used
-            // straight away, every exponential costs a wait state.
-            float a = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[base + i], c, nmc));
-            asm volatile("" : "+v"(a));                   // computed HERE: the optimiser would sink it to its first use
-            if (i > 0) e_use(i - 1, pf, lsum);
-            last_e = a;
-            if (i == NS - 1) e_use(i, pf, lsum);
-        }
+        // The sum and the bf16 pack of an exponential are issued one slice after it: used
+        // straight away, every exponential costs a wait state.
+        float a = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[base + i], c, nmc));
+        asm volatile("" : "+v"(a));                   // computed HERE: the optimiser would sink it to its first use
+        if (i > 0) e_use(i - 1, pf, lsum);
+        last_e = a;
+        if (i == NS - 1) e_use(i, pf, lsum);
     };
     auto fence = [&]() __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0); };
 
@@ -579,10 +527,9 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
     // One wait for the LDS reads of half a group's fragments in front of their first MFMA (own fragments up to i + NS/2 - 1;
     // the `reads` youngest reads may be outstanding) instead of the compiler's own in front of every MFMA: a wait is an
     // instruction like any other to the issue port (4 x 32768, 64/8 heads: 57.98 -> 57.34 ms; 64 x 359: 189.4 -> 188.5 us).
-    // At d = 64 half a group is two fragments just asked for, and with one wavefront per SIMD nothing covers the longer
-    // wait (one 2048-token prompt: 47.3 -> 47.8 us): there the compiler's single waits stay.
+    // (With one wavefront per SIMD nothing covers the longer wait: attention_tile.hip leaves it to the compiler.)
     auto half_group_wait = [&](const Frags& own, const Frags& next, int i) __attribute__((always_inline)) {
-        if (NS != 8 || kNW != 8 || i % (NS / 2) != 0) return;
+        if (i % (NS / 2) != 0) return;
         const Frags& young = i == 0 ? own : next;             // reads of own fragments 4, 5, or of the next group's 0, 1
         if (young.kind == 2) __builtin_amdgcn_s_waitcnt(0xC07F | (4 << 8));
         else if (young.kind == 1) __builtin_amdgcn_s_waitcnt(0xC07F | (2 << 8));
@@ -619,13 +566,12 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
             if (e.on) e_slice(*e.se, e.base, i, *e.pe, *e.lsum);
             slice_load(own, next, i);
             if (loads) {
-                if (NS == 2 * kInstrPerWave) request_piece(i);       // one piece per slice
-                else if (i & 1) request_piece(i >> 1);               // one every other slice
+                if (i & 1) request_piece(i >> 1);
             }
             fence();
         }
     };
-    static_assert(NS / 2 == 2 * kInstrPerWave || NS == 2 * kInstrPerWave, "the slices of one group cover a stream position");
+    static_assert(NS / 2 == 2 * kInstrPerWave, "the slices of one group cover a stream position");
     // a chunk of exponentials alone
     auto e_group = [&](const f32x16& se, int ebase, u32x4& pe, float& lsum) __attribute__((always_inline)) {
 #pragma unroll
@@ -822,39 +768,79 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
     __builtin_amdgcn_s_waitcnt(0x0f70);           // no load may still be writing LDS when the workgroup ends
 }
 
-template <int D, int kNW>
-int launch_attention_d(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev,
-                       const int32_t* seq_offsets_host, const pyr_shape& s, int32_t uniform_len, float c,
-                       void* out, float* lse, int32_t* item_map, hipStream_t stream) {
-    auto kern = attention_kernel<D, kNW>;
-    using T = Tile<D, kNW>;
-    constexpr int kBM = kNW * 32;
+int launch_attention_long(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev,
+                          const int32_t* seq_offsets_host, const pyr_shape& s, int32_t uniform_len, float c,
+                          void* out, float* lse, int32_t* item_map, const DeviceInfo& dev, hipStream_t stream) {
     static std::atomic<uint64_t> lds_set{0};
-    if (ensure_dynamic_lds((const void*)kern, (int)T::kLdsBytes, &lds_set) != PYR_OK) return PYR_ERR_LAUNCH;
+    if (ensure_dynamic_lds((const void*)attention_kernel, (int)Tile::kLdsBytes, &lds_set) != PYR_OK) return PYR_ERR_LAUNCH;
     long long total_items = 0;                       // work items per query head
-    for (int32_t b = 0; b < s.n_seqs; ++b) total_items += items_of(seq_offsets_host[b + 1] - seq_offsets_host[b], kBM);
+    for (int32_t b = 0; b < s.n_seqs; ++b) total_items += items_of(seq_offsets_host[b + 1] - seq_offsets_host[b]);
     if (total_items == 0) return PYR_OK;
     if (total_items * s.n_q_heads >= (1ll << 31)) return PYR_ERR_UNSUPPORTED;
-    DeviceInfo dev;
-    if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
     if (uniform_len == 0) {
-        hipLaunchKernelGGL(item_map_kernel, dim3(1), dim3(1024), 0, stream, seq_offsets_dev, s.n_seqs, (int32_t)kBM, item_map);
+        hipLaunchKernelGGL(item_map_kernel, dim3(1), dim3(1024), 0, stream, seq_offsets_dev, s.n_seqs, item_map);
         if (check_launch() != PYR_OK) return PYR_ERR_LAUNCH;
     }
     // Workgroup ids go round robin over the XCDs; the items are split by KV head so that one XCD's L2 serves
     // one head's K/V rows.  That needs the KV heads to divide evenly; otherwise one list for the whole device.
     const int xcds = (s.n_kv_heads % dev.xccs == 0 && dev.compute_units % dev.xccs == 0) ? dev.xccs : 1;
     const int32_t items_per_xcd = (int32_t)(total_items * s.n_q_heads / xcds);
-    const int wgs_per_cu = (int)(160 * 1024 / T::kLdsBytes) >= 2 ? 2 : 1;    // persistent workgroups, as many as the LDS holds
-    const int32_t first_wave_slots = dev.compute_units / xcds;
-    long long per_xcd_slots = (long long)first_wave_slots * wgs_per_cu;
-    if (per_xcd_slots > items_per_xcd) per_xcd_slots = items_per_xcd;
-    const unsigned grid = (unsigned)(per_xcd_slots * xcds);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kNW * 64), T::kLdsBytes, stream,
+    long long slots = dev.compute_units / xcds;      // persistent workgroups, one per compute unit
+    if (slots > items_per_xcd) slots = items_per_xcd;
+    // The turn that takes a workgroup through all kinds of items (see the kernel): step and period without a common
+    // factor.  Ragged batches keep the plain stride: their items differ from sequence to sequence anyway.
+    int turn = 0;
+    const int period = uniform_len > 0 ? items_of(uniform_len) * (s.n_q_heads / s.n_kv_heads) : 1;
+    if (uniform_len > kBM && (uniform_len + kBM - 1) / kBM % 2 == 1)
+        while (std::gcd((int)slots + turn, period) != 1) ++turn;
+    hipLaunchKernelGGL(attention_kernel, dim3((unsigned)(slots * xcds)), dim3(kNW * 64), Tile::kLdsBytes, stream,
                        (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, seq_offsets_dev,
                        (const int32_t*)item_map, s.n_seqs, s.n_q_heads, s.n_kv_heads, uniform_len, xcds,
-                       items_per_xcd, first_wave_slots, c, (uint16_t*)out, lse);
+                       items_per_xcd, turn, c, (uint16_t*)out, lse);
     return check_launch();
+}
+
+// Which kernel: 0 the one above, 1 or 2 attention_tile.hip with one or two groups per workgroup.  Each gets an estimate in
+// microseconds from what was measured: the work of all compute units (a per step of 64 keys, b per tile), and the longest
+// chain of steps a workgroup runs.  The constants at d = 128 come from batches of 64 x 202 ... 64 x 2048 on 32/32 heads
+// and 16 x 300 on 64/8 (1.635 per 256-row step, 6.1 per tile; 1.7 for a 128-row step of two workgroups side by side, 8.5
+// per tile; most of a tile's share is its rows' traffic, which is less with grouped heads) and single prompts of 300 ... 2048 tokens (1.42 per step of a wavefront
+// that has its SIMD to itself, 2.1 with the second group beside it); those at d = 64 from 64 x 500 and 64 x 2048 and
+// prompts of 900 ... 2500 tokens.  Measured, this kernel / one group / two groups (us): 64 x 2048 2324 / 2405 / 2851,
+// 64 x 700 417 / 448 / 564, 30 sequences of 100...700 120 / 101 / 136, 1 x 2048 57 / 48 / 43, 4 x 512 29 / 19 / 24;
+// d = 64: 64 x 2048 1550 / 1335 / 1772, 2 x 2500 on 8 heads 54 / 35 / 27 - there this kernel never wins and is not built.
+int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, const DeviceInfo& dev) {
+    const double kv_share = 1.0 + (double)s.n_kv_heads / s.n_q_heads;      // rows a query row's traffic comes with
+    const double cus = dev.compute_units;
+    double work0 = 0, work1 = 0, work2 = 0, items = 0;
+    int max_len = 0;
+    const double a1 = s.head_dim == 128 ? 1.7 : 1.417, b1 = s.head_dim == 128 ? 0.6 + 3.95 * kv_share : 0.4 + 3.4 * kv_share;
+    const double a2 = s.head_dim == 128 ? 2.1 : 1.2, b2 = s.head_dim == 128 ? 5.0 : 3.0;
+    const int32_t n = uniform_len > 0 ? 1 : s.n_seqs;                      // (equal sequences: one stands for all)
+    for (int32_t i = 0; i < n; ++i) {
+        const int len = off[i + 1] - off[i];
+        if (len == 0) continue;
+        if (len > max_len) max_len = len;
+        const double steps = (len + 63) / 64, n0 = (len + 255) / 256, n1 = (len + 127) / 128;
+        const double last_rows = (len - 256 * (n0 - 1) + 31) / 32;         // 32-row blocks of the last 256-row tile
+        work0 += 1.635 * (2 * n0 * (n0 - 1) + steps * floor(last_rows) / 8) + (3.8 + 1.15 * kv_share) * n0;
+        work1 += a1 * (n1 * (n1 - 1) + steps) + b1 * n1;
+        work2 += a2 * (n1 * (n1 - 1) + steps + n1) / 2 + b2 * n1;
+        items += items_of(len);
+    }
+    if (max_len == 0) return 0;
+    const double heads = (double)s.n_q_heads * (uniform_len > 0 ? s.n_seqs : 1);
+    const double steps = (max_len + 63) / 64;
+    const double per_cu = s.head_dim == 128 ? 2 : 3;                       // workgroups of one group a compute unit holds
+    const double chain1 = s.head_dim == 128 ? 1.42 * steps + 2.5 : 0.79 * steps + 3.4;
+    const double chain2 = s.head_dim == 128 ? 2.1 * ceil(steps / 2) + 4.0 : 1.2 * ceil(steps / 2) + 2.7;
+    const double t1 = fmax(work1 * heads / (per_cu * cus), chain1), t2 = fmax(work2 * heads / cus, chain2);
+    if (s.head_dim != 128) return t2 < t1 ? 2 : 1;
+    const double rounds = items * heads / cus, item = 1.635 * (steps + 4) + 12.2;       // the longest item: first and last tile
+    double t0 = fmax(work0 * heads / cus * (1.0 + 0.5 * (ceil(rounds) / rounds - 1.0)), item);
+    if (uniform_len == 0) t0 += 5.0 + 0.5 * item;                          // the item map's launch; lists of unequal length
+    if (s.n_kv_heads % dev.xccs != 0) t0 *= 1.15;                          // one list for all XCDs: K/V rows in every L2
+    return t0 < t1 + 0.1 * chain1 && t0 < t2 ? 0 : t2 < t1 ? 2 : 1;         // (the last tiles of one group's grid run out unevenly)
 }
 
 }  // namespace
@@ -862,23 +848,13 @@ int launch_attention_d(const void* q, const void* k, const void* v, const int32_
 int launch_attention(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev,
                      const int32_t* seq_offsets_host, const pyr_shape& shape, int32_t uniform_len, float scale_log2,
                      void* out, float* lse, int32_t* item_map, hipStream_t stream) {
-    // Segments of 256 query rows (eight wavefronts) make the most of every K/V tile brought into LDS; when they
-    // leave compute units without work (small batches), segments of 128 rows (four wavefronts) double the number
-    // of work items.
     DeviceInfo dev;
     if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
-    long long items256 = 0;
-    for (int32_t b = 0; b < shape.n_seqs; ++b) items256 += items_of(seq_offsets_host[b + 1] - seq_offsets_host[b], 256);
-    const bool small = items256 * shape.n_q_heads < dev.compute_units;
-    if (shape.head_dim == 128)
-        return small ? launch_attention_d<128, 4>(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2,
-                                                  out, lse, item_map, stream)
-                     : launch_attention_d<128, 8>(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2,
-                                                  out, lse, item_map, stream);
-    return small ? launch_attention_d<64, 4>(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2,
-                                             out, lse, item_map, stream)
-                 : launch_attention_d<64, 8>(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2,
-                                             out, lse, item_map, stream);
+    const int which = pick_kernel(shape, seq_offsets_host, uniform_len, dev);
+    if (which == 0)
+        return launch_attention_long(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2, out, lse, item_map, dev,
+                                     stream);
+    return launch_attention_tile(q, k, v, seq_offsets_dev, shape, uniform_len, scale_log2, out, lse, which, stream);
 }
 
 }  // namespace pyr

@@ -1,0 +1,109 @@
+"""The attention kernels one by one against plain PyTorch in float64: a 128-row tile per workgroup with its keys in one group
+(many tiles) or two (few tiles), and the 256-row kernel that walks lists of paired tiles (d = 128, long tiles).  Which of them
+runs follows from the batch alone (pick_kernel in attention.hip); the shapes below lie on each side of every line."""
+import math
+
+import numpy as np
+import pytest
+
+from paper_2405_12532_amd import synth
+from tests import test_gpu_large_logits, test_gpu_layer
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _batch(lens, Hq, Hkv, d, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    T = sum(lens)
+    return [torch.randn((T, h, d), generator=gen, device="cuda").to(torch.bfloat16) for h in (Hq, Hkv, Hkv)]
+
+
+def _reference(q, k, v):
+    """Causal attention of one sequence in float64: out [S, Hq, d], log2 of the denominators [S, Hq]."""
+    S, Hq, d = q.shape
+    Hkv = k.shape[1]
+    g = Hq // Hkv
+    qh = q.double().permute(1, 0, 2).reshape(Hkv, g * S, d).contiguous()
+    kh, vh = k.double().permute(1, 2, 0).contiguous(), v.double().permute(1, 0, 2).contiguous()
+    x = (torch.bmm(qh, kh) / math.sqrt(d)).reshape(Hkv, g, S, S)
+    x.masked_fill_(torch.ones(S, S, dtype=torch.bool, device=q.device).triu(1), -math.inf)
+    out = torch.bmm(torch.softmax(x, dim=3).reshape(Hkv, g * S, S), vh).reshape(Hq, S, d).permute(1, 0, 2)
+    return out, (torch.logsumexp(x, dim=3) / math.log(2.0)).reshape(Hq, S).t()
+
+
+def _check(lib, lens, Hq, Hkv, d, seed=1, every=1):
+    q, k, v = _batch(lens, Hq, Hkv, d, seed)
+    T = sum(lens)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    off_h = torch.from_numpy(off)
+    shape = lib.make_shape(len(lens), T, max(lens), Hq, Hkv, d)
+    out, lse = torch.full_like(q, 7.0), torch.full((T, Hq), 7.0, dtype=torch.float32, device="cuda")
+    lib.attention(q, k, v, off_h.cuda(), off_h, shape, 0.0, out, lse, torch.empty(len(lens) + 1, dtype=torch.int32, device="cuda"))
+    torch.cuda.synchronize()
+    vmax = float(v.abs().max())
+    for b in range(0, len(lens), every):
+        r0, r1 = int(off[b]), int(off[b + 1])
+        if r0 == r1:
+            continue
+        o, den = _reference(q[r0:r1], k[r0:r1], v[r0:r1])
+        # one rounding of the result to bf16, bf16 probabilities that sum to one, fp32 sums
+        err = (out[r0:r1].double() - o).abs()
+        assert bool((err <= 2.0 ** -8 * (o.abs() + vmax) + 1e-3).all()), (b, float(err.max()))
+        # logits of at most about 10: 128 fp32 products and sums, times log2(e)
+        assert float((lse[r0:r1].double() - den).abs().max()) < 128 * 2.0 ** -24 * 10 * 1.5, b
+
+
+EDGES = (1, 2, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 160, 191, 192, 193, 255, 256, 257, 320, 383, 384, 385)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("S", EDGES)
+def test_two_groups_edges(lib, S, d):
+    """A few tiles only: two groups of four wavefronts share a tile's keys (the second has none up to 64)."""
+    _check(lib, [S], 4, 2, d, seed=S)
+
+
+@pytest.mark.parametrize("d,Hq,Hkv", [(64, 24, 8), (128, 24, 8), (64, 11, 11), (128, 36, 12)])
+def test_one_group_edges(lib, d, Hq, Hkv):
+    """All edge lengths in one ragged batch, several times over (and empty sequences): enough tiles for one group each."""
+    _check(lib, list(EDGES) * 4 + [0, 500, 0], Hq, Hkv, d, seed=d + Hq, every=3)
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d", [
+    ([300] * 40, 16, 16, 64),                  # equal lengths: no offsets read
+    ([2500] * 2, 8, 8, 64),                    # two groups, 20 tiles
+    ([3000, 1, 1700], 8, 2, 64),
+    ([1100] * 6, 32, 8, 128),                  # one group, grouped heads
+    ([2048], 32, 32, 128),                     # two groups, two workgroups in turn on a compute unit
+    ([1900, 700, 64], 12, 12, 128),            # heads that do not divide over the XCDs
+])
+def test_tile_kernels(lib, lens, Hq, Hkv, d):
+    _check(lib, lens, Hq, Hkv, d)
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv", [
+    ([200] * 64, 32, 32),                      # one tile per sequence
+    ([512] * 32, 32, 32),                      # two: one pair
+    ([700] * 24, 32, 32),                      # three: a pair and the one in the middle, places that move on by one
+    ([1200] * 16, 32, 8),                      # five, grouped heads
+    ([1700] * 16, 16, 16),                     # seven
+    ([4096], 32, 32),
+    ([6000, 5000, 300, 8000], 32, 8),          # ragged
+    ([200] * 2200, 8, 8),                      # more than 64 items per workgroup: its table of items is moved along
+])
+def test_long_tile_kernel(lib, lens, Hq, Hkv):
+    _check(lib, lens, Hq, Hkv, 128, every=max(1, len(lens) // 6))
+
+
+@pytest.mark.parametrize("kind", ["ramp", "low_start", "low_start_overflow"])
+@pytest.mark.parametrize("lens,Hq,d", [((1024,) * 4, 32, 128), ((800,), 4, 128), ((300,) * 60, 8, 64)])
+def test_exponent_reference_renewal(lib, kind, lens, Hq, d):
+    """Rows that outgrow the exponent reference taken from their first 32 keys, in each kernel (long tiles, two groups - where each
+    group has a reference of its own -, one group), against the oracle."""
+    wl = synth.shrunk(synth.workload("cfg1"), lens, n_q_heads=Hq, n_kv_heads=Hq, head_dim=d, w=32, keep_fixed=0,
+                      keep_num=7, keep_den=10, hidden_dim=0)
+    x = test_gpu_large_logits.shaped_inputs(kind, wl, lib)
+    assert test_gpu_large_logits.rows_outgrowing_the_reference(x, wl) > 100
+    test_gpu_layer.run_and_check(lib, wl, x=x, hidden=False)
