@@ -476,9 +476,11 @@ struct StripPlan {
 
 // Two limits, in microseconds as measured at d = 128.  The chain: a wavefront takes 0.82 per tile of its stream alone on its
 // SIMD (wait, copy, products, exponentials) and 1.0 beside a second one, and a compute unit runs its workgroups in rounds
-// (a grid that fits exactly does not always start at once: nine tenths are counted on).  The stream: a compute unit's
+// (a single round that fits exactly does not start at once: above nine tenths half a round more is counted).  The stream: a compute unit's
 // share of the memory system delivers a tile of K from HBM in 0.35 and one of Q from L2 in 0.08; a last round that is
-// not full costs half of what it leaves idle.  The cut with the smallest larger one wins.
+// not full costs half of what it leaves idle (one that fits exactly 0.15: 64 x 359, ranges of 3 tiles in 256 workgroups 52 us, of 4
+// in 192 50 us), and the shares of a ragged batch differ (32 sequences of 512...8192 tokens on 40
+// heads, ranges of 12, 10, 9, 8, 7 tiles: 257, 242, 292, 322, 257 us).  The cut with the smallest larger one wins.
 // (Predicted / measured: 64 x 2048, ranges of 256 keys, 189 / 187 us, of 352 keys 218 / 224; 4 x 32768 with 64/8 heads
 // and w = 128, 256 keys, 326 / 378, of 384 keys 454 / 460; 8 x 2048, 64 keys, 28 / 30, of 256 keys 46 / 49.)
 StripPlan plan_strip(const pyr_shape& s, int32_t min_seqlen, int32_t w, int compute_units, int min_range_tiles, int max_groups) {
@@ -486,7 +488,7 @@ StripPlan plan_strip(const pyr_shape& s, int32_t min_seqlen, int32_t w, int comp
     const int64_t n_rb = (L + 31) / 32, pairs = (s.n_q_heads / s.n_kv_heads * n_rb + 1) / 2, tasks = s.n_kv_heads * pairs;
     const int64_t max_tiles = (s.max_seqlen + 31) / 32;
     const double tiles = min_seqlen == s.max_seqlen ? (double)s.n_seqs * max_tiles : s.total_tokens / 32.0 + 0.5 * s.n_seqs;
-    const double spill = min_seqlen == s.max_seqlen ? 0.0 : 0.4;       // (ragged: the XCDs' shares of a round differ)
+    const double uneven = min_seqlen == s.max_seqlen ? 1.0 : 1.17;     // (ragged: the XCDs' shares of the ranges differ)
     StripPlan best{1, 1, 1};
     double best_cost = 1e300;
     for (int nt = kMaxRangeTiles; nt >= 1; --nt) {
@@ -503,10 +505,10 @@ StripPlan plan_strip(const pyr_shape& s, int32_t min_seqlen, int32_t w, int comp
             if (wgs_per_cu > (s.head_dim == 64 ? 12 : 8) / waves) wgs_per_cu = (s.head_dim == 64 ? 12 : 8) / waves;
             for (int g = 1; g <= max_groups && (g == 1 || (int64_t)g * waves < 2 * tasks); g *= 2) {
                 const int64_t tpw = (tasks + (int64_t)g * waves - 1) / ((int64_t)g * waves);
-                const double wgs = ranges * g, rounds = wgs / ((double)compute_units * wgs_per_cu), whole = ceil(rounds + spill);
+                const double wgs = ranges * g, rounds = wgs / ((double)compute_units * wgs_per_cu), whole = ceil(rounds * uneven);
                 const double tile = (wgs * waves > 4.0 * compute_units ? 1.0 : 0.82) * (0.4 + 0.6 * size);
-                const double chain = ceil(rounds / 0.9) * tpw * (nt + 2) * tile;
-                const double idle = 1.0 + 0.5 * (whole / rounds - 1.0);
+                const double chain = (ceil(rounds) + (ceil(rounds / 0.9) > ceil(rounds) ? 0.5 : 0.0)) * tpw * (nt + 2) * tile;
+                const double idle = rounds > 0.9 && rounds <= 1.0 ? 1.15 : 1.0 + 0.5 * (whole / rounds - 1.0);
                 const double cost = (chain + 6.0 > stream * idle ? chain + 6.0 : stream * idle) + 0.25 * (g - 1);
                 if (cost < best_cost * 0.999) {
                     best_cost = cost;

@@ -243,16 +243,29 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
     uint32_t kmin = 0xffffffffu, kmax = 0u;
     if (ranked || groups > 1) {
         constexpr int kAhead = 8;               // scores a lane has in flight
+        constexpr int kRowsAhead = 4;           // rows of partial sums (the latency of a row at a time is what this would wait for)
         const float* __restrict__ from = groups > 1 ? parts + row0 : sc;
         const int n = groups > 1 ? S : C;
         for (int i0 = tid; i0 < n; i0 += kAhead * kT) {
             float x[kAhead];
+            if (groups <= 1) {
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) x[u] = i0 + u * kT < n ? from[i0 + u * kT] : 0.f;
-            for (int g = 1; g < groups; ++g) {
-                const float* __restrict__ more = from + (size_t)g * total_tokens;
+                for (int u = 0; u < kAhead; ++u) x[u] = i0 + u * kT < n ? from[i0 + u * kT] : 0.f;
+            } else {
 #pragma unroll
-                for (int u = 0; u < kAhead; ++u) x[u] += i0 + u * kT < n ? more[i0 + u * kT] : 0.f;
+                for (int u = 0; u < kAhead; ++u) x[u] = 0.f;
+                for (int g0 = 0; g0 < groups; g0 += kRowsAhead) {
+                    float y[kRowsAhead][kAhead];
+#pragma unroll
+                    for (int g = 0; g < kRowsAhead; ++g)
+#pragma unroll
+                        for (int u = 0; u < kAhead; ++u)
+                            y[g][u] = i0 + u * kT < n && g0 + g < groups ? from[(size_t)(g0 + g) * total_tokens + i0 + u * kT] : 0.f;
+#pragma unroll
+                    for (int g = 0; g < kRowsAhead; ++g)
+#pragma unroll
+                        for (int u = 0; u < kAhead; ++u) x[u] += y[g][u];
+                }
             }
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
