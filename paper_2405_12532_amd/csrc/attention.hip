@@ -803,18 +803,19 @@ int launch_attention_long(const void* q, const void* k, const void* v, const int
 // Which kernel: 0 the one above, 1 or 2 attention_tile.hip with one or two groups per workgroup.  Each gets an estimate in
 // microseconds from what was measured: the work of all compute units (a per step of 64 keys, b per tile), and the longest
 // chain of steps a workgroup runs.  The constants at d = 128 come from batches of 64 x 202 ... 64 x 2048 on 32/32 heads
-// and 16 x 300 on 64/8 (1.635 per 256-row step, 6.1 per tile; 1.7 for a 128-row step of two workgroups side by side, 8.5
-// per tile; most of a tile's share is its rows' traffic, which is less with grouped heads) and single prompts of 300 ... 2048 tokens (1.42 per step of a wavefront
+// and 16 x 300 on 64/8 (1.635 per 256-row step, 6.1 per tile; 1.755 for a 128-row step of two workgroups side by side, 7.4
+// per 128 rows, whose traffic that is: less with grouped heads) and single prompts of 300 ... 2048 tokens (1.42 per step of a wavefront
 // that has its SIMD to itself, 2.1 with the second group beside it); those at d = 64 from 64 x 500 and 64 x 2048 and
-// prompts of 900 ... 2500 tokens.  Measured, this kernel / one group / two groups (us): 64 x 2048 2324 / 2405 / 2851,
-// 64 x 700 417 / 448 / 564, 30 sequences of 100...700 120 / 101 / 136, 1 x 2048 57 / 48 / 43, 4 x 512 29 / 19 / 24;
-// d = 64: 64 x 2048 1550 / 1335 / 1772, 2 x 2500 on 8 heads 54 / 35 / 27 - there this kernel never wins and is not built.
+// prompts of 900 ... 2500 tokens.  Measured, this kernel / one group / two groups (us): 64 x 2048 2330 / 2392 / 2889,
+// 64 x 700 416 / 432 / 544, 64 x 359 189 / 173 / 223, 30 sequences of 100...700 122 / 95 / 128, 1 x 2048 57 / 48 / 43,
+// 4 x 512 29 / 20 / 24; d = 64: 64 x 2048 1550 / 1340 / 1770, 2 x 2500 on 8 heads 54 / 34 / 26 -
+// there this kernel never wins and is not built.
 int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, const DeviceInfo& dev) {
     const double kv_share = 1.0 + (double)s.n_kv_heads / s.n_q_heads;      // rows a query row's traffic comes with
     const double cus = dev.compute_units;
     double work0 = 0, work1 = 0, work2 = 0, items = 0;
     int max_len = 0;
-    const double a1 = s.head_dim == 128 ? 1.7 : 1.417, b1 = s.head_dim == 128 ? 0.6 + 3.95 * kv_share : 0.4 + 3.4 * kv_share;
+    const double a1 = s.head_dim == 128 ? 1.755 : 1.437, b1 = s.head_dim == 128 ? 0.38 + 3.49 * kv_share : 3.95 + 1.4 * kv_share;
     const double a2 = s.head_dim == 128 ? 2.1 : 1.2, b2 = s.head_dim == 128 ? 5.0 : 3.0;
     const int32_t n = uniform_len > 0 ? 1 : s.n_seqs;                      // (equal sequences: one stands for all)
     for (int32_t i = 0; i < n; ++i) {
@@ -824,7 +825,7 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
         const double steps = (len + 63) / 64, n0 = (len + 255) / 256, n1 = (len + 127) / 128;
         const double last_rows = (len - 256 * (n0 - 1) + 31) / 32;         // 32-row blocks of the last 256-row tile
         work0 += 1.635 * (2 * n0 * (n0 - 1) + steps * floor(last_rows) / 8) + (3.8 + 1.15 * kv_share) * n0;
-        work1 += a1 * (n1 * (n1 - 1) + steps) + b1 * n1;
+        work1 += a1 * (n1 * (n1 - 1) + steps) + b1 * len / 128;
         work2 += a2 * (n1 * (n1 - 1) + steps + n1) / 2 + b2 * n1;
         items += items_of(len);
     }
@@ -838,9 +839,9 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
     if (s.head_dim != 128) return t2 < t1 ? 2 : 1;
     const double rounds = items * heads / cus, item = 1.635 * (steps + 4) + 12.2;       // the longest item: first and last tile
     double t0 = fmax(work0 * heads / cus * (1.0 + 0.5 * (ceil(rounds) / rounds - 1.0)), item);
-    if (uniform_len == 0) t0 += 5.0 + 0.5 * item;                          // the item map's launch; lists of unequal length
+    t0 += uniform_len > 0 ? 3.0 : 5.0 + item;                              // the lists' start; the item map's launch and lists of unequal length
     if (s.n_kv_heads % dev.xccs != 0) t0 *= 1.15;                          // one list for all XCDs: K/V rows in every L2
-    return t0 < t1 + 0.1 * chain1 && t0 < t2 ? 0 : t2 < t1 ? 2 : 1;         // (the last tiles of one group's grid run out unevenly)
+    return t0 < t1 + 0.05 * chain1 && t0 < t2 ? 0 : t2 < t1 ? 2 : 1;         // (the last tiles of one group's grid run out unevenly)
 }
 
 }  // namespace

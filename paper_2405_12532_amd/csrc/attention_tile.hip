@@ -510,15 +510,23 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
     a.c = scale_log2;
     a.out = (uint16_t*)out;
     a.lse = lse;
-    // A chunk: the units one XCD works on at a time, enough for every workgroup it can hold twice over.  All units where they
-    // are at most a sixth of those workgroups: the longest tiles of all of them then start first and nothing long starts late
-    // (3 x 5000 tokens, 24 heads, nine units per XCD: 533 us in chunks of four, 459 in one); with more of them the tiles that
-    // run together would no longer share their K/V rows (8 x 2048, 32 units: 348 us in one chunk, 304 in chunks of eight).
+    // A chunk: the units one XCD works on at a time, long tiles first.  Half the workgroups an XCD holds, in units that come in
+    // fours (rows a power of two apart) or, in a ragged batch, in whole sequences' worth of heads, which are equally long: the
+    // tiles that run together then share their K/V rows in L2 (us, two rounds of workgroups to a chunk / now: 64 x 359
+    // 190 / 173, 64 x 269 154 / 136, 64 x 512 282 / 258; d = 64: 64 x 500 153 / 147).  All units where they are few and the
+    // grid is at most eight rounds: what counts there is that nothing long starts late (3 x 5000 tokens, 24 heads,
+    // nine units per XCD: 533 in chunks of four, 459 in one).
     const int tiles = (s.max_seqlen + kRows - 1) / kRows, head_group = s.n_q_heads / s.n_kv_heads;
     const int slots = dev.compute_units / dev.xccs * (groups == 2 ? 1 : s.head_dim == 128 ? 2 : 3);
     const int units_per_xcd = (a.n_units + a.xcds - 1) / a.xcds;
-    int chunk = (2 * slots + tiles * head_group - 1) / (tiles * head_group);
-    if (units_per_xcd <= slots / 6) chunk = units_per_xcd;
+    const int64_t unit_tiles = (int64_t)tiles * head_group;
+    const int target = (int)((slots + unit_tiles) / (2 * unit_tiles));                   // (rounded)
+    int chunk = target < 6 ? 4 : (target + 2) / 4 * 4;
+    if (uniform_len == 0) {
+        const int per_seq = s.n_kv_heads % a.xcds == 0 ? s.n_kv_heads / a.xcds : 1;
+        chunk = per_seq * (target < 2 * per_seq ? 1 : (target + per_seq / 2) / per_seq);
+    }
+    if (units_per_xcd <= slots / 6 && units_per_xcd * unit_tiles <= 8 * (int64_t)slots) chunk = units_per_xcd;
     if (chunk > units_per_xcd) chunk = units_per_xcd;
     constexpr int kMaxGrid = 65535;              // of y and z
     if (chunk < (units_per_xcd + kMaxGrid - 1) / kMaxGrid) chunk = (units_per_xcd + kMaxGrid - 1) / kMaxGrid;
