@@ -164,7 +164,9 @@ int pyr_attention(const void* q, const void* k, const void* v,
     rc = check_offsets(seq_offsets_host, shape->n_seqs, shape->total_tokens, shape->max_seqlen, &info);
     if (rc != PYR_OK) return rc;
     if (info.uniform_len == 0 && shape->total_tokens > 0 && tile_map == nullptr) return PYR_ERR_WORKSPACE;
-    return pyr::launch_attention(q, k, v, seq_offsets_dev, seq_offsets_host, *shape, info.uniform_len,
+    pyr_shape s = *shape;
+    s.max_seqlen = info.max_len;                 // (the caller's may be any upper bound: a grid made for it would hold tiles that are not there)
+    return pyr::launch_attention(q, k, v, seq_offsets_dev, seq_offsets_host, s, info.uniform_len,
                                  scale_log2(softmax_scale, shape->head_dim), out, lse, tile_map, (hipStream_t)stream);
 }
 

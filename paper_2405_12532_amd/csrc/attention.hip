@@ -54,6 +54,7 @@
 // exchange and no rescale of the output.
 #include <math.h>
 
+#include <algorithm>
 #include <numeric>
 
 #include "attention_device.h"
@@ -801,20 +802,30 @@ int launch_attention_long(const void* q, const void* k, const void* v, const int
 }
 
 // Which kernel: 0 the one above, 1 or 2 attention_tile.hip with one or two groups per workgroup.  Each gets an estimate in
-// microseconds from what was measured: the work of all compute units (a per step of 64 keys, b per tile), and the longest
-// chain of steps a workgroup runs.  The constants at d = 128 come from batches of 64 x 202 ... 64 x 2048 on 32/32 heads
-// and 16 x 300 on 64/8 (1.635 per 256-row step, 6.1 per tile; 1.755 for a 128-row step of two workgroups side by side, 7.4
-// per 128 rows, whose traffic that is: less with grouped heads) and single prompts of 300 ... 2048 tokens (1.42 per step of a wavefront
-// that has its SIMD to itself, 2.1 with the second group beside it); those at d = 64 from 64 x 500 and 64 x 2048 and
-// prompts of 900 ... 2500 tokens.  Measured, this kernel / one group / two groups (us): 64 x 2048 2330 / 2392 / 2889,
-// 64 x 700 416 / 432 / 544, 64 x 359 189 / 173 / 223, 30 sequences of 100...700 122 / 95 / 128, 1 x 2048 57 / 48 / 43,
-// 4 x 512 29 / 20 / 24; d = 64: 64 x 2048 1550 / 1340 / 1770, 2 x 2500 on 8 heads 54 / 34 / 26 -
-// there this kernel never wins and is not built.
+// microseconds from what was measured: the work of all compute units (a per step of 64 keys, b per tile), the longest
+// chain of steps a workgroup runs and, for the kernel above on a ragged batch, the longest of its lists.  The constants at
+// d = 128 come from batches of 64 x 202 ... 64 x 2048 on 32/32 heads and 16 x 300 on 64/8 (1.635 per 256-row step, 6.1 per
+// tile; 1.755 for a 128-row step of two workgroups side by side, 7.4 per 128 rows, whose traffic that is: less with grouped
+// heads) and single prompts of 300 ... 2048 tokens (1.42 per step of a wavefront that has its SIMD to itself, 2.1 with the
+// second group beside it); those at d = 64 from 64 x 500 and 64 x 2048 and prompts of 900 ... 2500 tokens.
+// Measured, this kernel / one group / two groups (us): 64 x 2048 2330 / 2392 / 2889, 64 x 700 416 / 432 / 544,
+// 64 x 359 189 / 173 / 223, 1 x 2048 57 / 48 / 43, 4 x 512 29 / 20 / 24; ragged: 30 sequences of 100...700 122 / 97 / 131,
+// 32 of 512...8192 on 40 heads 6530 / 6630 / 7470, 32768 and 255 x 64 7240 / 8280 / 8960, 8192 and 500 x 100 850 / 840 / 1050;
+// heads that do not divide over the XCDs: 1 x 8192 on 32/4 heads 471 / 513 / 566, on 20/20 415 / 349 / 365.
+// d = 64: 64 x 2048 1550 / 1340 / 1770, 2 x 2500 on 8 heads 54 / 34 / 26 - there this kernel never wins and is not built.
 int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, const DeviceInfo& dev) {
     const double kv_share = 1.0 + (double)s.n_kv_heads / s.n_q_heads;      // rows a query row's traffic comes with
     const double cus = dev.compute_units;
     double work0 = 0, work1 = 0, work2 = 0, items = 0;
     int max_len = 0;
+    // the lists of the kernel above, if they differ: what each has, as differences from one to the next
+    constexpr int kMaxSlots = 1024;
+    const int xcds = s.n_kv_heads % dev.xccs == 0 && dev.compute_units % dev.xccs == 0 ? dev.xccs : 1;
+    const int slots = dev.compute_units / xcds < kMaxSlots ? dev.compute_units / xcds : kMaxSlots;
+    double more[kMaxSlots + 1];
+    if (uniform_len == 0) std::fill(more, more + slots + 1, 0.0);
+    double all_lists = 0;
+    int turn = 0;
     const double a1 = s.head_dim == 128 ? 1.755 : 1.437, b1 = s.head_dim == 128 ? 0.38 + 3.49 * kv_share : 3.95 + 1.4 * kv_share;
     const double a2 = s.head_dim == 128 ? 2.1 : 1.2, b2 = s.head_dim == 128 ? 5.0 : 3.0;
     const int32_t n = uniform_len > 0 ? 1 : s.n_seqs;                      // (equal sequences: one stands for all)
@@ -824,8 +835,19 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
         if (len > max_len) max_len = len;
         const double steps = (len + 63) / 64, n0 = (len + 255) / 256, n1 = (len + 127) / 128;
         const double last_rows = (len - 256 * (n0 - 1) + 31) / 32;         // 32-row blocks of the last 256-row tile
-        work0 += 1.635 * (2 * n0 * (n0 - 1) + steps * floor(last_rows) / 8) + (3.8 + 1.15 * kv_share) * n0;
-        work1 += a1 * (n1 * (n1 - 1) + steps) + b1 * len / 128;
+        const double seq0 = 1.635 * (2 * n0 * (n0 - 1) + steps * floor(last_rows) / 8) + (3.8 + 1.15 * kv_share) * n0;
+        work0 += seq0;
+        if (uniform_len == 0) {                                            // its items go to the lists in turn
+            const int64_t n = (int64_t)items_of(len) * s.n_q_heads / xcds;
+            const double item = seq0 / items_of(len);
+            const int rem = (int)(n % slots), end = turn + rem;
+            all_lists += item * (n / slots);
+            more[turn] += item;
+            more[end < slots ? end : slots] -= item;
+            if (end >= slots) { more[0] += item; more[end - slots] -= item; }
+            turn = end % slots;
+        }
+        work1 += (len > 8192 ? 1.06 : 1.0) * a1 * (n1 * (n1 - 1) + steps) + b1 * len / 128;       // (K/V of one head then exceed an L2)
         work2 += a2 * (n1 * (n1 - 1) + steps + n1) / 2 + b2 * n1;
         items += items_of(len);
     }
@@ -835,12 +857,21 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
     const double per_cu = s.head_dim == 128 ? 2 : 3;                       // workgroups of one group a compute unit holds
     const double chain1 = s.head_dim == 128 ? 1.42 * steps + 2.5 : 0.79 * steps + 3.4;
     const double chain2 = s.head_dim == 128 ? 2.1 * ceil(steps / 2) + 4.0 : 1.2 * ceil(steps / 2) + 2.7;
-    const double t1 = fmax(work1 * heads / (per_cu * cus), chain1), t2 = fmax(work2 * heads / cus, chain2);
+    const double ragged = uniform_len > 0 ? 1.0 : 1.05;                    // (measured: tiles of unequal length share fewer K/V rows)
+    const double t1 = fmax(ragged * work1 * heads / (per_cu * cus), chain1), t2 = fmax(ragged * work2 * heads / cus, chain2);
     if (s.head_dim != 128) return t2 < t1 ? 2 : 1;
     const double rounds = items * heads / cus, item = 1.635 * (steps + 4) + 12.2;       // the longest item: first and last tile
     double t0 = fmax(work0 * heads / cus * (1.0 + 0.5 * (ceil(rounds) / rounds - 1.0)), item);
-    t0 += uniform_len > 0 ? 3.0 : 5.0 + item;                              // the lists' start; the item map's launch and lists of unequal length
-    if (s.n_kv_heads % dev.xccs != 0) t0 *= 1.15;                          // one list for all XCDs: K/V rows in every L2
+    if (uniform_len == 0) {                                                // the longest list, and the item map's launch
+        double run = 0, most = 0;
+        for (int i = 0; i < slots; ++i) {
+            run += more[i];
+            most = fmax(most, run);
+        }
+        t0 = fmax(all_lists + most, item) + 2.0;
+    }
+    t0 += 3.0;
+    if (s.n_kv_heads % dev.xccs != 0) t0 *= 0.85 + 0.15 * kv_share;        // one list for all XCDs: K/V rows in every L2
     return t0 < t1 + 0.05 * chain1 && t0 < t2 ? 0 : t2 < t1 ? 2 : 1;         // (the last tiles of one group's grid run out unevenly)
 }
 
@@ -855,7 +886,8 @@ int launch_attention(const void* q, const void* k, const void* v, const int32_t*
     if (which == 0)
         return launch_attention_long(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2, out, lse, item_map, dev,
                                      stream);
-    return launch_attention_tile(q, k, v, seq_offsets_dev, shape, uniform_len, scale_log2, out, lse, which, stream);
+    return launch_attention_tile(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2, out, lse, item_map, which,
+                                 stream);
 }
 
 }  // namespace pyr

@@ -36,6 +36,8 @@ struct TileArgs {
     const uint16_t* k;
     const uint16_t* v;
     const int32_t* seq_offsets;
+    const int32_t* tile_map;                      // the list of a ragged batch's tiles (prefix sums of tiles per sequence), or nullptr
+    int32_t n_seqs;
     int32_t n_units, n_q_heads, n_kv_heads;       // unit: one KV head of one sequence
     int32_t units_per_chunk, xcds, uniform_len, first_tile;
     float c;
@@ -46,6 +48,8 @@ struct TileArgs {
 // Grid: x = ((unit of the chunk's share of one XCD) * group + query head of the group) * xcds + xcd; y = query tile, the last
 // one first; z = chunk.  Workgroup ids go round robin over the XCDs, so a unit's K and V are fetched into one L2 only;
 // inside a chunk the long tiles of all its units start first.
+// With a list (very unequal sequences, see the launch): x = (place * group + query head of the group) * xcds + xcd, where the
+// places are the KV heads of a sequence that one XCD serves; y = position in the list of all sequences' tiles.
 template <int D, int kGroups>
 __global__ __launch_bounds__(kGroups * 256, 2) void attention_tile_kernel(TileArgs a) {
     using T = TileLds<D, kGroups>;
@@ -71,9 +75,31 @@ __global__ __launch_bounds__(kGroups * 256, 2) void attention_tile_kernel(TileAr
     // ---- which tile
     const int head_group = a.n_q_heads / a.n_kv_heads;
     const int xcd = (int)blockIdx.x % a.xcds, slot = (int)blockIdx.x / a.xcds;
-    const int unit = ((int)blockIdx.z * a.units_per_chunk + slot / head_group) * a.xcds + xcd;
-    if (unit >= a.n_units) return;                // (uniform over the workgroup, like the next one)
-    const int b = unit / a.n_kv_heads, kvh = unit % a.n_kv_heads, h = kvh * head_group + slot % head_group;
+    int b, kvh, q_tile;
+    if (a.tile_map != nullptr) {
+        // The sequence: the last b with tile_map[b] <= position, found 64 candidates at a time (a binary search would be a chain of
+        // a dozen loads in front of each tile).  [b, b + span) holds it; candidate lane l stands at b + l * step.
+        const int pos = a.first_tile + (int)blockIdx.y;
+        b = 0;
+        for (int span = a.n_seqs; span > 1;) {
+            const int step = (span + 63) / 64;
+            const int cand = b + lane * step;
+            const bool below = lane * step < span && a.tile_map[cand] <= pos;
+            const int hits = __builtin_popcountll(__builtin_amdgcn_ballot_w64(below));
+            b += (hits - 1) * step;               // (candidate 0 always is one)
+            span = min(step, span - (hits - 1) * step);
+        }
+        q_tile = a.tile_map[b + 1] - 1 - pos;
+        kvh = (xcd + a.xcds - (int)((int64_t)b * a.n_kv_heads % a.xcds)) % a.xcds + slot / head_group * a.xcds;      // the XCDs take turns at the odd heads
+        if (kvh >= a.n_kv_heads) return;          // (uniform over the workgroup, like the others)
+    } else {
+        const int unit = ((int)blockIdx.z * a.units_per_chunk + slot / head_group) * a.xcds + xcd;
+        if (unit >= a.n_units) return;
+        b = unit / a.n_kv_heads;
+        kvh = unit % a.n_kv_heads;
+        q_tile = a.first_tile + (int)gridDim.y - 1 - (int)blockIdx.y;
+    }
+    const int h = kvh * head_group + slot % head_group;
     int row0, S;
     if (a.uniform_len > 0) {
         row0 = b * a.uniform_len;
@@ -82,7 +108,7 @@ __global__ __launch_bounds__(kGroups * 256, 2) void attention_tile_kernel(TileAr
         row0 = a.seq_offsets[b];
         S = a.seq_offsets[b + 1] - row0;
     }
-    const int q_base = (a.first_tile + (int)gridDim.y - 1 - (int)blockIdx.y) * kRows;
+    const int q_base = q_tile * kRows;
     if (q_base >= S) return;
     const int n_tiles = (min(S, q_base + kRows) + kBN - 1) / kBN;
     const int n_grp = (n_tiles - grp + kGroups - 1) / kGroups;       // key tiles of this group: grp, grp + kGroups, ...
@@ -480,6 +506,31 @@ __global__ __launch_bounds__(kGroups * 256, 2) void attention_tile_kernel(TileAr
     }
 }
 
+// prefix sums of the number of query tiles per sequence
+__global__ __launch_bounds__(1024) void tile_map_kernel(const int32_t* __restrict__ seq_offsets, int32_t n_seqs,
+                                                        int32_t* __restrict__ tile_map) {
+    __shared__ int part[1024];
+    const int tid = threadIdx.x;
+    const int chunk = (n_seqs + 1023) / 1024;
+    const int lo = min(tid * chunk, n_seqs), hi = min(lo + chunk, n_seqs);
+    int sum = 0;
+    for (int b = lo; b < hi; ++b) sum += (seq_offsets[b + 1] - seq_offsets[b] + kRows - 1) / kRows;
+    part[tid] = sum;
+    __syncthreads();
+    for (int d = 1; d < 1024; d <<= 1) {
+        const int add = tid >= d ? part[tid - d] : 0;
+        __syncthreads();
+        part[tid] += add;
+        __syncthreads();
+    }
+    int run = part[tid] - sum;
+    for (int b = lo; b < hi; ++b) {
+        tile_map[b] = run;
+        run += (seq_offsets[b + 1] - seq_offsets[b] + kRows - 1) / kRows;
+    }
+    if (tid == 1023) tile_map[n_seqs] = part[1023];
+}
+
 template <int D, int kGroups>
 int launch_tile(const TileArgs& a, dim3 grid, hipStream_t stream) {
     using T = TileLds<D, kGroups>;
@@ -489,10 +540,36 @@ int launch_tile(const TileArgs& a, dim3 grid, hipStream_t stream) {
     return check_launch();
 }
 
+// The work of the XCD that has most of it, relative to an equal share, if unit u goes to XCD u % xcds.  Where that is far from one
+// (few KV heads and few sequences, or one sequence far longer than the others) units are not bound to XCDs: each L2 then
+// fetches the K/V rows itself. Measured, bound / not (us): 32768 and 255 x 64 tokens on 16/2 heads 15600 / 3930,
+// d = 64: the same on 12/12 heads 2230 / 1680.
+double xcd_share(const pyr_shape& s, const int32_t* off, int32_t uniform_len, int xcds) {
+    const int odd = s.n_kv_heads % xcds;
+    if (odd == 0) return 1.0;
+    if (uniform_len > 0) {
+        const int64_t units = (int64_t)s.n_seqs * s.n_kv_heads;
+        return (double)((units + xcds - 1) / xcds * xcds) / units;
+    }
+    constexpr int kMaxXcds = 64;
+    if (xcds > kMaxXcds) return xcds;
+    double extra[kMaxXcds] = {}, even = 0, all = 0;
+    for (int32_t b = 0, at = 0; b < s.n_seqs; ++b, at = (at + odd) % xcds) {
+        const double len = off[b + 1] - off[b], work = len * (len + 512);      // (a tile costs what four steps do, besides its own)
+        even += work * (s.n_kv_heads / xcds);
+        all += work * s.n_kv_heads;
+        for (int i = 0; i < odd; ++i) extra[(at + i) % xcds] += work;
+    }
+    double most = 0;
+    for (int i = 0; i < xcds; ++i) most = extra[i] > most ? extra[i] : most;
+    return all > 0 ? (even + most) * xcds / all : 1.0;
+}
+
 }  // namespace
 
-int launch_attention_tile(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev, const pyr_shape& s,
-                          int32_t uniform_len, float scale_log2, void* out, float* lse, int groups, hipStream_t stream) {
+int launch_attention_tile(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
+                          const pyr_shape& s, int32_t uniform_len, float scale_log2, void* out, float* lse, int32_t* tile_map,
+                          int groups, hipStream_t stream) {
     if (s.n_seqs == 0 || s.max_seqlen == 0) return PYR_OK;
     DeviceInfo dev;
     if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
@@ -502,10 +579,11 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
     a.v = (const uint16_t*)v;
     a.seq_offsets = seq_offsets_dev;
     if ((int64_t)s.n_seqs * s.n_kv_heads >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
+    a.n_seqs = s.n_seqs;
     a.n_units = s.n_seqs * s.n_kv_heads;
     a.n_q_heads = s.n_q_heads;
     a.n_kv_heads = s.n_kv_heads;
-    a.xcds = dev.xccs;
+    a.xcds = xcd_share(s, seq_offsets_host, uniform_len, dev.xccs) <= 1.15 ? dev.xccs : 1;
     a.uniform_len = uniform_len;
     a.c = scale_log2;
     a.out = (uint16_t*)out;
@@ -517,8 +595,34 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
     // grid is at most eight rounds: what counts there is that nothing long starts late (3 x 5000 tokens, 24 heads,
     // nine units per XCD: 533 in chunks of four, 459 in one).
     const int tiles = (s.max_seqlen + kRows - 1) / kRows, head_group = s.n_q_heads / s.n_kv_heads;
-    const int slots = dev.compute_units / dev.xccs * (groups == 2 ? 1 : s.head_dim == 128 ? 2 : 3);
+    const int slots = dev.compute_units / a.xcds * (groups == 2 ? 1 : s.head_dim == 128 ? 2 : 3);
     const int units_per_xcd = (a.n_units + a.xcds - 1) / a.xcds;
+    constexpr int kMaxGrid = 65535;              // of y and z
+    const auto launch = [&](dim3 grid) {
+        if (s.head_dim == 128) return groups == 2 ? launch_tile<128, 2>(a, grid, stream) : launch_tile<128, 1>(a, grid, stream);
+        return groups == 2 ? launch_tile<64, 2>(a, grid, stream) : launch_tile<64, 1>(a, grid, stream);
+    };
+    // A list of the tiles that exist, sequence after sequence with the last tile first (the order a chunk of one sequence has),
+    // where the grid below would mostly hold workgroups that find no rows.  One of those costs about 0.8 ns; finding its place
+    // in the list costs a tile about 1.2 us, 2.3 ns of the whole device, and the list is a launch of its own, 4.5 us.
+    // Measured, grid / list (us): 32768 and 255 x 64 tokens 10310 / 8280, 4096 and 2000 x 16 2400 / 721, d = 64: 8192 and
+    // 500 x 100 on 12 heads 530 / 180; but 32 sequences of 512...4096 on 32/8 heads 1946 / 2000.
+    if (uniform_len == 0) {
+        int64_t listed = 0;
+        for (int32_t b = 0; b < s.n_seqs; ++b) listed += (seq_offsets_host[b + 1] - seq_offsets_host[b] + kRows - 1) / kRows;
+        if (((int64_t)s.n_seqs * tiles - 4 * listed) * s.n_q_heads > 6000) {
+            hipLaunchKernelGGL(tile_map_kernel, dim3(1), dim3(1024), 0, stream, seq_offsets_dev, s.n_seqs, tile_map);
+            int rc = check_launch();
+            a.tile_map = tile_map;
+            const int64_t x = (int64_t)(s.n_kv_heads + a.xcds - 1) / a.xcds * head_group * a.xcds;
+            if (x * 256 * groups >= (int64_t)1 << 32) return PYR_ERR_UNSUPPORTED;
+            for (int64_t first = 0; rc == PYR_OK && first < listed; first += kMaxGrid) {
+                a.first_tile = (int32_t)first;
+                rc = launch(dim3((unsigned)x, (unsigned)(listed - first < kMaxGrid ? listed - first : kMaxGrid)));
+            }
+            return rc;
+        }
+    }
     const int64_t unit_tiles = (int64_t)tiles * head_group;
     const int target = (int)((slots + unit_tiles) / (2 * unit_tiles));                   // (rounded)
     int chunk = target < 6 ? 4 : (target + 2) / 4 * 4;
@@ -528,7 +632,6 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
     }
     if (units_per_xcd <= slots / 6 && units_per_xcd * unit_tiles <= 8 * (int64_t)slots) chunk = units_per_xcd;
     if (chunk > units_per_xcd) chunk = units_per_xcd;
-    constexpr int kMaxGrid = 65535;              // of y and z
     if (chunk < (units_per_xcd + kMaxGrid - 1) / kMaxGrid) chunk = (units_per_xcd + kMaxGrid - 1) / kMaxGrid;
     const int chunks = (units_per_xcd + chunk - 1) / chunk;
     chunk = (units_per_xcd + chunks - 1) / chunks;               // (equal chunks)
@@ -537,8 +640,7 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
         const int n = left < kMaxGrid ? left : kMaxGrid;
         a.first_tile = left - n;
         const dim3 grid((unsigned)(a.xcds * chunk * head_group), (unsigned)n, (unsigned)chunks);
-        const int rc = s.head_dim == 128 ? (groups == 2 ? launch_tile<128, 2>(a, grid, stream) : launch_tile<128, 1>(a, grid, stream))
-                                         : (groups == 2 ? launch_tile<64, 2>(a, grid, stream) : launch_tile<64, 1>(a, grid, stream));
+        const int rc = launch(grid);
         if (rc != PYR_OK) return rc;
     }
     return PYR_OK;

@@ -38,8 +38,9 @@ int launch_attention(const void* q, const void* k, const void* v, const int32_t*
                      void* out, float* lse, int32_t* item_map, hipStream_t stream);
 
 // One 128-row query tile per workgroup, by one group of four wavefronts or by two that share its keys (attention_tile.hip).
-int launch_attention_tile(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev, const pyr_shape& shape,
-                          int32_t uniform_len, float scale_log2, void* out, float* lse, int groups, hipStream_t stream);
+int launch_attention_tile(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
+                          const pyr_shape& shape, int32_t uniform_len, float scale_log2, void* out, float* lse, int32_t* tile_map,
+                          int groups, hipStream_t stream);
 
 // row_weights: device [w] or nullptr (uniform); min_seqlen: the shortest sequence (0 if not known)
 int launch_score(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev,

@@ -107,3 +107,16 @@ def test_exponent_reference_renewal(lib, kind, lens, Hq, d):
     x = test_gpu_large_logits.shaped_inputs(kind, wl, lib)
     assert test_gpu_large_logits.rows_outgrowing_the_reference(x, wl) > 100
     test_gpu_layer.run_and_check(lib, wl, x=x, hidden=False)
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d", [
+    ([3000] + [17, 0, 130] * 100, 8, 8, 64),   # 301 sequences: two rounds of the search, empty ones among them
+    ([40] * 63 + [0, 6000], 12, 12, 64),       # 65, heads that take turns over the XCDs
+    ([1] * 4200 + [700] + [0] * 70 + [129], 36, 12, 64),      # three rounds, empty sequences in a row
+    ([9000] + [100] * 63, 6, 2, 64),           # 64: one round; fewer heads than XCDs
+    ([4000] + [64] * 260, 16, 8, 128),
+    ([8000, 8000] + [33] * 500, 4, 1, 128),
+])
+def test_list_of_tiles(lib, lens, Hq, Hkv, d):
+    """One long sequence among many short ones: the tile kernel's grid would be mostly empty, and it works on a list."""
+    _check(lib, lens, Hq, Hkv, d, every=1 if len(lens) < 100 else 97)
