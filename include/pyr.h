@@ -310,7 +310,7 @@ PYR_API int pyr_diag_mfma_only(int32_t iters, float* sink_dev, void* stream, dou
 
 /*
  * Diagnostic for the benchmark report, not part of the method: a launch that only reads `bytes` of device
- * memory with the LDS-direct loads the score pass uses for K (16 KB tiles, one in flight per wavefront, six
+ * memory with LDS-direct loads, as the score pass reads K (16 KB tiles here, one in flight per wavefront, six
  * wavefronts per compute unit) and discards them, so that the read rate this very GPU sustains can be printed
  * beside the published HBM peak.
  *   data_dev           dev, `bytes` readable bytes, 16-byte aligned

@@ -14,6 +14,8 @@
 // ring is as short as that pipeline allows: two K tiles and three V tiles.  Synchronisation t sits in front of the last
 // group of step t: every wavefront has read K(t+1) and finished with V(t-1) then, so K(t+3) and V(t+2) are requested
 // into their slots, and K(t+2) and V(t+1), requested one step earlier, must have landed.
+// Measured, lists of 256- or 128-row tiles as in attention.hip / this kernel (us): 1 x 2048, 32 heads 55 / 43, 64 x 359
+// 190 / 173; d = 64: 64 x 2048 1550 / 1340, seven sequences of 100...3000 tokens on 32/8 heads 131 / 93.
 #include "attention_device.h"
 
 namespace pyr {

@@ -33,7 +33,7 @@ __global__ __launch_bounds__(512, 2) void mfma_only_kernel(float* __restrict__ s
     if (r == 12345.678f) sink[0] = r;                 // never true: keeps the loop alive without memory traffic
 }
 
-// Nothing but LDS-direct loads, as the score pass issues them for K: two wavefronts per workgroup, three workgroups
+// Nothing but LDS-direct loads in the layout the score pass reads K in: two wavefronts per workgroup, three workgroups
 // per compute unit (50 KB of LDS each), one 16 KB tile in flight per wavefront, requested again as soon as it has
 // landed.  k_layout == 0: a wavefront reads consecutive 16 KB pieces; != 0: a tile is 64 rows of 256 bytes, 8 KB apart
 // (one head of 64 tokens of a [T, 32, 128] bf16 K), the two wavefronts walk the 32 heads of the workgroup's 64 tokens.
