@@ -6,7 +6,7 @@
 //
 // Four wavefronts of 32 query rows each are a GROUP with a K/V stream of its own.  kGroups == 1: a workgroup is one group
 // (80 KB of LDS at d = 128: two per compute unit).  kGroups == 2: two groups share the 128 rows and take the
-// key tiles alternately, each with its own exponent reference, denominator and output, which are merged through LDS
+// key tiles alternately, each with its own denominator, output and renewals of the exponent reference, which are merged through LDS
 // at the end: a grid too small to put two wavefronts on every SIMD gets them that way, and its longest chain is halved.
 //
 // Everything inside a wavefront - MFMA mapping, transposed logits, the interleaving of products and exponentials,
@@ -367,19 +367,33 @@ __global__ __launch_bounds__(kGroups * 256, 2) void attention_tile_kernel(TileAr
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // in registers before the next synchronisation frees the area
 
-    // ---- first logits: QK0(0), reference from its true maxima, QK1(0) | E0a(0), E0b(0)
+    // ---- first logits: QK0(0), reference, QK1(0) | E0a(0), E0b(0)
     if (n_my > 0) {
         prime(fk0);
         qk_group(s0, no_e, fk0, fk1);
         mask_half(s0, 0, 0);
-        m_run = max_of(s0);                       // the half's first key is visible to every row: finite
+        m_run = max_of(s0);                       // (group 0: the sequence's first key is visible to every row)
+    }
+    // The reference is the row's maximum over its first 32 keys, for both groups: a reference of its own would have the second
+    // group depend on keys 64...95, which may all be masked by the caller (logits of -inf), and round its probabilities apart from the
+    // other kernels'.  Group 0 leaves it where the wavefront's queries were.  (One more barrier: 42.0 -> 42.3 us at 1 x 2048 on 32 heads,
+    // 6.4 -> 6.6 at 1 x 256, d = 64, 8 heads.)
+    if (kGroups == 2 && n_tiles > 1) {
+        float __attribute__((address_space(3)))* ref =
+            (float __attribute__((address_space(3)))*)(uintptr_t)(q_stage - grp * T::kGroupBytes + 4 * lane);
+        if (grp == 0 && n_my > 0) *ref = m_run;
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (grp == 1 && n_my > 0) m_run = *ref;
+    }
+    if (n_my > 0) {
         nmc = -m_run * a.c;
         ls0 = 0.f;
         fence();
         const Chunk e0a = {true, &s0, 0, &p0[0], &ls0};
         qk_group(s1, e0a, fk1, no_f);
         e_group(s0, 8, p0[1], ls0);
-        l_run += ls0;
+        if (grp == 0) l_run += ls0;
+        else settle_half(s0, p0, ls0);            // (not these keys' own maximum)
         mask_half(s1, 0, 1);
         fence();
     }

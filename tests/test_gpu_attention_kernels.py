@@ -33,10 +33,15 @@ def _reference(q, k, v):
     return out, (torch.logsumexp(x, dim=3) / math.log(2.0)).reshape(Hq, S).t()
 
 
-def _check(lib, lens, Hq, Hkv, d, seed=1, every=1):
+def _check(lib, lens, Hq, Hkv, d, seed=1, every=1, masked=()):
+    """masked: positions of every sequence whose keys nobody may see, a logit of -inf by way of one head dimension."""
     q, k, v = _batch(lens, Hq, Hkv, d, seed)
     T = sum(lens)
     off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    if len(masked):
+        q[:, :, 0], k[:, :, 0] = 1.0, 0.0
+        for r0, r1 in zip(off[:-1], off[1:]):
+            k[[int(r0) + j for j in masked if r0 + j < r1], :, 0] = -math.inf
     off_h = torch.from_numpy(off)
     shape = lib.make_shape(len(lens), T, max(lens), Hq, Hkv, d)
     out, lse = torch.full_like(q, 7.0), torch.full((T, Hq), 7.0, dtype=torch.float32, device="cuda")
@@ -120,3 +125,18 @@ def test_exponent_reference_renewal(lib, kind, lens, Hq, d):
 def test_list_of_tiles(lib, lens, Hq, Hkv, d):
     """One long sequence among many short ones: the tile kernel's grid would be mostly empty, and it works on a list."""
     _check(lib, lens, Hq, Hkv, d, every=1 if len(lens) < 100 else 97)
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d", [
+    ([300], 4, 2, 64),                         # two groups: all the second one has seen of a row may be masked keys
+    ([800], 4, 4, 128),
+    ([2048], 32, 32, 128),
+    ([300] * 60, 8, 8, 64),                    # one group
+    ([1100] * 6, 32, 8, 128),
+    ([2048] * 32, 32, 32, 128),                # lists of tiles
+])
+def test_masked_keys(lib, lens, Hq, Hkv, d):
+    """Infinitely negative logits weigh nothing wherever they lie beyond a row's first 32 keys: a group's whole first tile, a half
+    of a tile, every other key."""
+    masked = [*range(40, 200), *range(256, 288), *range(301, 700, 2)]
+    _check(lib, lens, Hq, Hkv, d, masked=masked, every=max(1, len(lens) // 4))
