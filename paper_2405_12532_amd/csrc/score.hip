@@ -36,6 +36,7 @@
 // Small batches.  When ranges times wavefronts leave the chip idle, the tasks of a range are also split over
 // gridDim.y workgroups that write partial sums, one row of `sums` each; the selection kernel, which reads
 // every score anyway, adds the rows up in order.
+#include <float.h>
 #include <math.h>
 
 #include "pyr_internal.h"
@@ -117,7 +118,8 @@ __device__ __forceinline__ float tile_sum(const f32x16& s, float c, const float 
 }
 
 // Statistics pass (rows: keys, column: window row): the row's running maximum and sum of exponentials.  Without kPlain
-// keys past the row, and rows past the sequence, are masked (key0: position of the lane's key 0).
+// keys past the row, and rows past the sequence, are masked (key0: position of the lane's key 0).  m_run starts at the lowest
+// finite value, so that a row whose keys so far all have logits of -inf has the sum zero and not the NaN of -inf - -inf.
 template <bool kPlain>
 __device__ __forceinline__ void tile_stats(f32x16& s, float c, int key0, int qpos, int S, float& m_run, float& l_run) {
     float mx = -INFINITY;
@@ -127,7 +129,6 @@ __device__ __forceinline__ void tile_stats(f32x16& s, float c, int key0, int qpo
         if (!kPlain) s[r] = key0 + 8 * (r >> 2) + (r & 3) <= qpos && qpos < S ? s[r] : -INFINITY;
         mx = fmaxf(mx, s[r]);
     }
-    if (!(mx > -INFINITY)) return;
     const float m_new = fmaxf(m_run, mx);
     float l4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -137,7 +138,7 @@ __device__ __forceinline__ void tile_stats(f32x16& s, float c, int key0, int qpo
 }
 
 // kStats writes part[((range * B + b) * Hq + h) * w + slot] = (max, sum of 2^(x - max)) over the
-// range's visible keys, x = c * q.k, and touches neither lse nor sums.
+// range's visible keys, x = c * q.k, for every row that sees the range, and touches neither lse nor sums.
 template <int D, int kMode>
 __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(StripArgs a) {
     constexpr bool kWeighted = kMode == kScoresWeighted;
@@ -341,7 +342,7 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
                 behind = request(ahead, slot);
                 slot ^= 1;
             }
-            float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};       // kStats: this lane's window rows
+            float m_run[2] = {-FLT_MAX, -FLT_MAX}, l_run[2] = {0.f, 0.f};         // kStats: this lane's window rows
             for (int t = 0; t < n_tiles; ++t) {
                 bf16x8 kf[kSteps];
                 wait_front(behind);
@@ -393,9 +394,8 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
                     const float mo = __shfl_xor(m_run[j], 32, 64), so = __shfl_xor(l_run[j], 32, 64);
                     const float m_all = fmaxf(m_run[j], mo);
                     const int rb = j ? rb1 : rb0;
-                    if (gl == 0 && m_all > -INFINITY && 32 * rb + li < L) {
-                        const float total = (m_run[j] > -INFINITY ? l_run[j] * __builtin_amdgcn_exp2f(m_run[j] - m_all) : 0.f) +
-                                            (mo > -INFINITY ? so * __builtin_amdgcn_exp2f(mo - m_all) : 0.f);
+                    if (gl == 0 && 32 * rb + li < L && key_base <= q_lo[j] + li) {      // every range that the fold reads for this row
+                        const float total = l_run[j] * __builtin_amdgcn_exp2f(m_run[j] - m_all) + so * __builtin_amdgcn_exp2f(mo - m_all);
                         const int h = kvh * group + (2 * now.pair + j) / n_rb, at = (a.w - L) + 32 * rb + li;
                         a.part[(((size_t)range * a.n_seqs + b) * a.n_q_heads + h) * a.w + at] = make_float2(m_all, total);   // 32 rows: 256 consecutive bytes
                     }

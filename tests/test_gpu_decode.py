@@ -126,3 +126,31 @@ def test_decode_update_with_empty_sequences(lib):
     wl = synth.shrunk(synth.workload("cfg2"), (0, 130, 0, 9, 0), n_q_heads=4, n_kv_heads=2, head_dim=128, w=32,
                       hidden_dim=0)
     run_and_check(lib, wl, with_pos=True)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("garbage", [0x00, 0x7F, 0xFF])                # of the workspace: zeros, 3.4e38, NaN
+def test_decode_update_masked_ranges(lib, d, garbage):
+    """Cache rows nobody may see (a logit of -inf by way of one head dimension), more of them in a row than a range of the
+    statistics pass holds: their statistics are written like any other range's, whatever lay in the workspace."""
+    wl = synth.shrunk(synth.workload("cfg2"), (1300, 70), n_q_heads=4, n_kv_heads=2, head_dim=d, w=32, hidden_dim=0)
+    x = parity.inputs(wl, lib, want_hidden=False)
+    off, keep = x["seq_offsets"], x["keep_len"]
+    x["q"][:, :, 0], x["k"][:, :, 0] = 0x3F80, 0                       # 1.0, 0.0
+    x["k"][:800, :, 0] = 0xFF80                                        # -inf
+    q_win = window_queries(x["q"], off, wl.w)
+    q, k, v = (lib.to_device_bf16(a) for a in (q_win, x["k"], x["v"]))
+    off_h, keep_h = (torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)) for a in (off, keep))
+    off_d, keep_d = off_h.cuda(), keep_h.cuda()
+    shape = lib.make_shape(2, k.shape[0], 1300, 4, 2, d)
+    n_kept, ws_bytes = int(keep_h.sum()), lib.decode_workspace_bytes(shape, wl.w)
+    ws = torch.full((ws_bytes,), garbage, dtype=torch.uint8, device="cuda")
+    scores = torch.empty(k.shape[0], dtype=torch.float32, device="cuda")
+    kept, out_off = torch.empty(n_kept, dtype=torch.int32, device="cuda"), torch.empty(3, dtype=torch.int32, device="cuda")
+    lib.decode_update(q, k, v, off_d, off_h, shape, wl.w, 0.0, keep_d, keep_h, None, None, scores, kept, out_off, None, None, None,
+                      ws, ws_bytes)
+    torch.cuda.synchronize()
+    ref = orc.decode_update(F64(q_win.reshape(-1)).reshape(q_win.shape), F64(x["k"]), F64(x["v"]), off, wl.w, keep)
+    assert ref["scores"][:800].max() == 0.0
+    parity.check_scores(scores.cpu().numpy(), ref)
+    parity.check_index_sets(kept.cpu().numpy(), ref, off, keep, wl.w)
