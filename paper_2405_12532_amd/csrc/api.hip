@@ -184,7 +184,7 @@ int pyr_score_weighted(const void* q, const void* k, const float* lse,
     if (rc != PYR_OK) return rc;
     pyr_shape s = *shape;
     s.max_seqlen = info.max_len;
-    return pyr::launch_score(q, k, lse, seq_offsets_dev, s, info.min_len, w, scale_log2(softmax_scale, shape->head_dim),
+    return pyr::launch_score(q, k, lse, seq_offsets_dev, seq_offsets_host, s, info.min_len, w, scale_log2(softmax_scale, shape->head_dim),
                              row_weights_dev, scores, (hipStream_t)stream);
 }
 
@@ -316,7 +316,7 @@ int pyr_prefill_layer_fused(const void* q, const void* k, const void* v,
     rc = pyr::launch_attention(q, k, v, seq_offsets_dev, seq_offsets_host, s, info.uniform_len, c, out, lse, tile_map, st);
     if (rc != PYR_OK) return rc;
     int groups = 1;
-    rc = pyr::launch_score_groups(q, k, lse, seq_offsets_dev, s, info.min_len, w, c, row_weights_dev, scores, parts, &groups, st);
+    rc = pyr::launch_score_groups(q, k, lse, seq_offsets_dev, seq_offsets_host, s, info.min_len, w, c, row_weights_dev, scores, parts, &groups, st);
     if (rc != PYR_OK) return rc;
     rc = pyr::launch_select(parts, groups, s.total_tokens, scores, seq_offsets_dev, keep_len_dev, s.n_seqs, info.max_len, w, kept_idx,
                             out_offsets_dev, st);
@@ -400,7 +400,7 @@ int pyr_decode_update(const void* q_win, const void* k, const void* v,
     pyr_shape s = *shape;
     s.max_seqlen = info.max_len;
     int groups = 1;
-    rc = pyr::launch_window_score(q_win, k, seq_offsets_dev, s, info.min_len, w, scale_log2(softmax_scale, shape->head_dim),
+    rc = pyr::launch_window_score(q_win, k, seq_offsets_dev, seq_offsets_host, s, info.min_len, w, scale_log2(softmax_scale, shape->head_dim),
                                   row_weights_dev, lse_win, part, scores, &groups, st);
     if (rc != PYR_OK) return rc;
     rc = pyr::launch_select((const float*)part, groups, s.total_tokens, scores, seq_offsets_dev, keep_len_dev, s.n_seqs, info.max_len,

@@ -43,7 +43,7 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
                           int groups, hipStream_t stream);
 
 // row_weights: device [w] or nullptr (uniform); min_seqlen: the shortest sequence (0 if not known)
-int launch_score(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev,
+int launch_score(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
                  const pyr_shape& shape, int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights,
                  float* scores, hipStream_t stream);
 
@@ -54,15 +54,15 @@ int launch_score(const void* q, const void* k, const float* lse, const int32_t* 
 constexpr int kMaxScoreGroups = 16;
 size_t score_parts_bytes(const pyr_shape& shape);
 int launch_score_groups(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev,
-                        const pyr_shape& shape, int32_t min_seqlen, int32_t w, float scale_log2,
+                        const int32_t* seq_offsets_host, const pyr_shape& shape, int32_t min_seqlen, int32_t w, float scale_log2,
                         const float* row_weights, float* scores, float* parts, int* groups, hipStream_t stream);
 
 // Generation phase: the same scores from the window's own query buffer q_win [B, w, Hq, d]
 // (right-aligned), three launches: row statistics per range of keys -> part, folded into lse_win
 // [B, w, Hq], then the score pass.  part holds window_score_part_bytes() bytes; *groups as above, the partial sums in part.
 size_t window_score_part_bytes(const pyr_shape& shape, int32_t w);
-int launch_window_score(const void* q_win, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& shape,
-                        int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights, float* lse_win, void* part,
+int launch_window_score(const void* q_win, const void* k, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
+                        const pyr_shape& shape, int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights, float* lse_win, void* part,
                         float* scores, int* groups, hipStream_t stream);
 
 int launch_gather_positions(const int32_t* pos, const int32_t* kept_idx, int64_t n_kept, int32_t* pos_out,

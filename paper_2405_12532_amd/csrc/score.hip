@@ -51,6 +51,21 @@ constexpr int kSlots = 2;            // tiles of a wavefront's ring
 
 enum Mode { kScores = 0, kScoresWeighted = 1, kStats = 2 };
 
+// Which range a workgroup takes.  Consecutive workgroup ids go round robin over the XCDs and, inside one, over its four shader
+// engines, whether a workgroup finds work there or not.  A grid with places for ranges that do not exist therefore fills
+// some engines' compute units twice while others stand idle (24 sequences of 235...2226 tokens on 40 heads, w = 256, ranges of
+// 6 tiles: 175 workgroups, 354 us; 7 tiles, 152 workgroups, 232 us).
+enum Order {
+    kSeqPerXcd = 0,      // equal lengths, a multiple of the XCD count: all ranges of a sequence on one XCD
+    kEqual = 1,          // as many ranges in every sequence: range after range, sequence after sequence
+    kPacked = 2,         // ragged: the same, and the workgroup counts the ranges in front of it
+    kGrid = 3,           // ragged: ranges_per_seq places for each sequence
+};
+// Counting costs a workgroup 0.3 us per 64 sequences.  Measured, packed / grid (us): 17 sequences of 3292...7710 tokens, 24
+// heads, w = 512 404 / 691, 48 of 30...400 26 / 37, 128 of 60...1500 171 / 214; but 64 of 16...120 5.6 / 5.3, 256 12.6 / 10.8,
+// 800 of 30...400 231 / 231.
+constexpr int kMaxPackedSeqs = 256, kMinPackedLen = 256;
+
 typedef __attribute__((address_space(3))) char* lptr_t;
 typedef __attribute__((address_space(3))) float* lfloat_t;
 
@@ -61,7 +76,7 @@ struct StripArgs {
     const int32_t* seq_offsets;
     int32_t n_seqs, n_q_heads, n_kv_heads, w;
     int32_t range_tiles, ranges_per_seq;      // tiles of a range; ranges of the longest sequence
-    int32_t chunk_ranges, xcds, head_step;    // order of the ranges over the XCDs, of the heads over the ranges
+    int32_t order, xcds, head_step;           // order of the ranges over the workgroups, of the heads over the ranges
     int32_t q_window;                         // 0: q and lse by packed row; else by (sequence, window slot)
     float c;
     const float* row_weights;
@@ -154,17 +169,45 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
     const int lane = threadIdx.x & 63, waves = (int)(blockDim.x >> 6);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int li = lane & 31, gl = lane >> 5;
-    // Workgroup -> (sequence, range).  Consecutive workgroup ids go to consecutive XCDs; a chunk of
-    // chunk_ranges ranges of one sequence stays on one XCD, so that the window's Q rows, which every
-    // range of the sequence re-reads, are found in that XCD's L2.
-    const int wg_slot = (int)blockIdx.x / a.xcds;
-    const int chunk = (wg_slot / a.chunk_ranges) * a.xcds + (int)blockIdx.x % a.xcds;
-    const int chunks_per_seq = (a.ranges_per_seq + a.chunk_ranges - 1) / a.chunk_ranges;
-    const int b = chunk / chunks_per_seq;
-    const int range = (chunk % chunks_per_seq) * a.chunk_ranges + wg_slot % a.chunk_ranges;
-    if (b >= a.n_seqs || range >= a.ranges_per_seq) return;      // (uniform over the workgroup, like the next one)
-    const int row0 = a.seq_offsets[b];
-    const int S = a.seq_offsets[b + 1] - row0;
+    // ---- which sequence, which range (uniform over the workgroup)
+    int b, range, row0, S;
+    if (a.order == kPacked) {
+        // lane l counts the ranges of sequence first + l; a sum over the wavefront says which of them holds this workgroup's
+        const int range_keys = 32 * a.range_tiles;
+        int left = (int)blockIdx.x;
+        for (int first = 0;; first += 64) {
+            if (first >= a.n_seqs) return;
+            const bool is_seq = first + lane < a.n_seqs;
+            const int from = is_seq ? a.seq_offsets[first + lane] : 0, len = is_seq ? a.seq_offsets[first + lane + 1] - from : 0;
+            const int mine = (len + range_keys - 1) / range_keys;
+            int incl = mine;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int up = __shfl_up(incl, d);
+                if (lane >= d) incl += up;
+            }
+            const uint64_t past = __ballot(incl > left);
+            if (past != 0) {
+                const int at = __ffsll((unsigned long long)past) - 1;
+                b = first + at;
+                range = left - (__builtin_amdgcn_readlane(incl, at) - __builtin_amdgcn_readlane(mine, at));
+                row0 = __builtin_amdgcn_readlane(from, at);
+                S = __builtin_amdgcn_readlane(len, at);
+                break;
+            }
+            left -= __builtin_amdgcn_readlane(incl, 63);
+        }
+    } else {
+        const int id = (int)blockIdx.x, slot = a.order == kSeqPerXcd ? id / a.xcds : id;
+        const int turn = slot / a.ranges_per_seq;
+        b = a.order == kSeqPerXcd ? turn * a.xcds + id % a.xcds : turn;
+        if (b >= a.n_seqs) return;
+        range = slot % a.ranges_per_seq;
+        // (the sequences start at different ranges: the last one, which may be short, does not fall to the same engine every time)
+        if (a.order != kGrid) range = (range + turn) % a.ranges_per_seq;
+        row0 = a.seq_offsets[b];
+        S = a.seq_offsets[b + 1] - row0;
+    }
     const int key_base = range * a.range_tiles * 32;
     if (key_base >= S) return;
     const int n_tiles = min(a.range_tiles, (S - key_base + 31) / 32);
@@ -469,6 +512,39 @@ __global__ __launch_bounds__(kFoldRows * kFoldLanes) void fold_stats_kernel(cons
     lse_win[((size_t)b * w + slot) * n_q_heads + h] = n_ranges > 0 ? m_run + __builtin_amdgcn_logf(s_run) : 0.f;
 }
 
+// How many ranges a batch has if a range has that many tiles (for the plan: counted in fp32).
+struct BatchCut {
+    int64_t ranges[kMaxRangeTiles + 1];
+};
+
+int64_t count_ranges(const int32_t* seq_offsets_host, int32_t n_seqs, int32_t range_keys) {
+    int64_t n = 0;
+    for (int32_t b = 0; b < n_seqs; ++b) n += (seq_offsets_host[b + 1] - seq_offsets_host[b] + range_keys - 1) / range_keys;
+    return n;
+}
+
+BatchCut cut_batch(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t min_seqlen) {
+    BatchCut cut{};
+    if (min_seqlen == s.max_seqlen) {
+        for (int nt = 1; nt <= kMaxRangeTiles; ++nt) cut.ranges[nt] = (int64_t)s.n_seqs * (((s.max_seqlen + 31) / 32 + nt - 1) / nt);
+        return cut;
+    }
+    // 256 sequences at a time, without divisions: the loops over them run on the host's vector unit
+    constexpr int kBlock = 256;
+    float tiles[kBlock];
+    for (int32_t b0 = 0; b0 < s.n_seqs; b0 += kBlock) {
+        const int n = s.n_seqs - b0 < kBlock ? s.n_seqs - b0 : kBlock;
+        for (int i = 0; i < n; ++i) tiles[i] = (float)((seq_offsets_host[b0 + i + 1] - seq_offsets_host[b0 + i] + 31) / 32);
+        for (int nt = 1; nt <= kMaxRangeTiles; ++nt) {
+            const float inv = 1.0f / nt, up = (nt - 0.5f) * inv;
+            int32_t sum = 0;
+            for (int i = 0; i < n; ++i) sum += (int32_t)(tiles[i] * inv + up);
+            cut.ranges[nt] += sum;
+        }
+    }
+    return cut;
+}
+
 // How a walk over K is cut up.
 struct StripPlan {
     int range_tiles, waves, groups;
@@ -483,7 +559,8 @@ struct StripPlan {
 // heads, ranges of 12, 10, 9, 8, 7 tiles: 257, 242, 292, 322, 257 us).  The cut with the smallest larger one wins.
 // (Predicted / measured: 64 x 2048, ranges of 256 keys, 189 / 187 us, of 352 keys 218 / 224; 4 x 32768 with 64/8 heads
 // and w = 128, 256 keys, 326 / 378, of 384 keys 454 / 460; 8 x 2048, 64 keys, 28 / 30, of 256 keys 46 / 49.)
-StripPlan plan_strip(const pyr_shape& s, int32_t min_seqlen, int32_t w, int compute_units, int min_range_tiles, int max_groups) {
+StripPlan plan_strip(const pyr_shape& s, int32_t min_seqlen, const BatchCut& cut, int32_t w, int compute_units, int min_range_tiles,
+                     int max_groups) {
     const int L = w < s.max_seqlen ? w : s.max_seqlen;
     const int64_t n_rb = (L + 31) / 32, pairs = (s.n_q_heads / s.n_kv_heads * n_rb + 1) / 2, tasks = s.n_kv_heads * pairs;
     const int64_t max_tiles = (s.max_seqlen + 31) / 32;
@@ -495,7 +572,7 @@ StripPlan plan_strip(const pyr_shape& s, int32_t min_seqlen, int32_t w, int comp
         if (nt < min_range_tiles && nt < max_tiles) continue;
         const int64_t ranges_per_seq = (max_tiles + nt - 1) / nt;
         if (nt > min_range_tiles && ranges_per_seq == (max_tiles + nt - 2) / (nt - 1)) continue;   // the same number of ranges, more evenly
-        const double ranges = min_seqlen == s.max_seqlen ? (double)s.n_seqs * ranges_per_seq : tiles / nt + 0.5 * s.n_seqs;
+        const double ranges = (double)cut.ranges[nt];
         const double size = s.head_dim / 128.0, stream = tasks * (tiles * 0.35 + ranges * 2 * 0.08) * size / compute_units;
         for (int waves = kMaxWaves; waves >= 1; waves /= 2) {
             if (waves > tasks && waves > 1) continue;
@@ -530,8 +607,8 @@ int launch_strip_d(const StripArgs& a, dim3 grid, int waves, hipStream_t stream)
 }
 
 template <int kMode>
-int launch_strip(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev, const pyr_shape& s,
-                 int32_t min_seqlen, int32_t w, int32_t q_window, float scale_log2, const float* row_weights, float* sums,
+int launch_strip(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
+                 const pyr_shape& s, int32_t min_seqlen, int32_t w, int32_t q_window, float scale_log2, const float* row_weights, float* sums,
                  float2* part, const StripPlan& plan, const DeviceInfo& dev, hipStream_t stream) {
     StripArgs a{};
     a.q = (const uint16_t*)q;
@@ -545,14 +622,17 @@ int launch_strip(const void* q, const void* k, const float* lse, const int32_t* 
     a.range_tiles = plan.range_tiles;
     a.ranges_per_seq = ((s.max_seqlen + 31) / 32 + plan.range_tiles - 1) / plan.range_tiles;
     // A whole sequence per XCD where that spreads the work evenly by construction (equal lengths, a multiple of the XCD
-    // count: 64 x 2048 216 -> 196 us); otherwise the plain order, range after range over the XCDs: with ragged lengths the
-    // sequences of one XCD can be much longer than another's.  An odd number of ranges per sequence (the last one may be
-    // empty) keeps range r of all sequences from meeting on one XCD (32 sequences of 512...8192 tokens, ranges of 256
-    // keys: 326 us with 32 ranges per sequence).
+    // count: 64 x 2048 216 -> 196 us), so that the window's Q rows, which every range of the sequence re-reads, are found in that
+    // XCD's L2; with ragged lengths the sequences of one XCD can be much longer than another's.  Where the places of a grid are
+    // kept, an odd number per sequence keeps range r of all sequences from meeting on one XCD.
     a.xcds = dev.xccs;
-    const bool seq_per_xcd = min_seqlen == s.max_seqlen && s.n_seqs % dev.xccs == 0;
-    if (!seq_per_xcd && s.n_seqs > 1) a.ranges_per_seq |= 1;
-    a.chunk_ranges = seq_per_xcd ? a.ranges_per_seq : 1;
+    const int64_t ranges = min_seqlen == s.max_seqlen ? (int64_t)s.n_seqs * a.ranges_per_seq
+                                                      : count_ranges(seq_offsets_host, s.n_seqs, 32 * plan.range_tiles);
+    a.order = min_seqlen == s.max_seqlen && s.n_seqs % dev.xccs == 0              ? kSeqPerXcd
+              : ranges == (int64_t)s.n_seqs * a.ranges_per_seq                    ? kEqual
+              : s.n_seqs <= kMaxPackedSeqs && s.max_seqlen > kMinPackedLen ? kPacked
+                                                                           : kGrid;
+    if (a.order == kGrid) a.ranges_per_seq |= 1;
     // (rows a power of two apart: 64 x 2048 in ranges of 256 keys 210 us without, 188 with steps of 8, 196 with 7, 8 x 2048
     //  in ranges of 64 keys 31.8, 36.7 and 29.8; rows of 10 KB: no difference)
     const size_t k_row_bytes = (size_t)s.n_kv_heads * s.head_dim * 2;
@@ -563,36 +643,36 @@ int launch_strip(const void* q, const void* k, const float* lse, const int32_t* 
     a.sums = sums;
     a.total_tokens = s.total_tokens;
     a.part = part;
-    const int64_t chunks = (int64_t)s.n_seqs * ((a.ranges_per_seq + a.chunk_ranges - 1) / a.chunk_ranges);
-    const int64_t n = (chunks + a.xcds - 1) / a.xcds * a.xcds * a.chunk_ranges;
+    const int64_t n = a.order == kPacked ? ranges : (int64_t)s.n_seqs * a.ranges_per_seq;
     if (n >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)n, (unsigned)plan.groups, 1);
     return s.head_dim == 128 ? launch_strip_d<128, kMode>(a, grid, plan.waves, stream)
                              : launch_strip_d<64, kMode>(a, grid, plan.waves, stream);
 }
 
-int launch_scores(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev, const pyr_shape& s,
-                  int32_t min_seqlen, int32_t w, int32_t q_window, float scale_log2, const float* row_weights, float* scores,
-                  float* parts, int max_groups, int* groups, hipStream_t stream) {
+int launch_scores(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
+                  const pyr_shape& s, int32_t min_seqlen, const BatchCut& cut, int32_t w, int32_t q_window, float scale_log2,
+                  const float* row_weights, float* scores, float* parts, int max_groups, int* groups, hipStream_t stream) {
     DeviceInfo dev;
     if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
-    const StripPlan plan = plan_strip(s, min_seqlen, w, dev.compute_units, 1, max_groups);
+    const StripPlan plan = plan_strip(s, min_seqlen, cut, w, dev.compute_units, 1, max_groups);
     *groups = plan.groups;
     float* sums = plan.groups > 1 ? parts : scores;
-    return row_weights ? launch_strip<kScoresWeighted>(q, k, lse, seq_offsets_dev, s, min_seqlen, w, q_window, scale_log2, row_weights,
-                                                       sums, nullptr, plan, dev, stream)
-                       : launch_strip<kScores>(q, k, lse, seq_offsets_dev, s, min_seqlen, w, q_window, scale_log2, nullptr, sums,
-                                               nullptr, plan, dev, stream);
+    return row_weights ? launch_strip<kScoresWeighted>(q, k, lse, seq_offsets_dev, seq_offsets_host, s, min_seqlen, w, q_window,
+                                                       scale_log2, row_weights, sums, nullptr, plan, dev, stream)
+                       : launch_strip<kScores>(q, k, lse, seq_offsets_dev, seq_offsets_host, s, min_seqlen, w, q_window, scale_log2,
+                                               nullptr, sums, nullptr, plan, dev, stream);
 }
 
 }  // namespace
 
-int launch_score(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev,
+int launch_score(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
                  const pyr_shape& s, int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights,
                  float* scores, hipStream_t stream) {
     if (s.n_seqs == 0 || s.max_seqlen == 0) return PYR_OK;
     int groups = 1;
-    return launch_scores(q, k, lse, seq_offsets_dev, s, min_seqlen, w, 0, scale_log2, row_weights, scores, nullptr, 1, &groups, stream);
+    return launch_scores(q, k, lse, seq_offsets_dev, seq_offsets_host, s, min_seqlen, cut_batch(s, seq_offsets_host, min_seqlen), w, 0,
+                         scale_log2, row_weights, scores, nullptr, 1, &groups, stream);
 }
 
 // (Only batches of fewer than 1024 blocks of 64 keys are ever split: beyond that the ranges alone fill the chip.)
@@ -602,12 +682,12 @@ size_t score_parts_bytes(const pyr_shape& s) {
 }
 
 int launch_score_groups(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev,
-                        const pyr_shape& s, int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights,
+                        const int32_t* seq_offsets_host, const pyr_shape& s, int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights,
                         float* scores, float* parts, int* groups, hipStream_t stream) {
     *groups = 1;
     if (s.n_seqs == 0 || s.max_seqlen == 0) return PYR_OK;
-    return launch_scores(q, k, lse, seq_offsets_dev, s, min_seqlen, w, 0, scale_log2, row_weights, scores, parts,
-                         parts != nullptr ? kMaxScoreGroups : 1, groups, stream);
+    return launch_scores(q, k, lse, seq_offsets_dev, seq_offsets_host, s, min_seqlen, cut_batch(s, seq_offsets_host, min_seqlen), w, 0,
+                         scale_log2, row_weights, scores, parts, parts != nullptr ? kMaxScoreGroups : 1, groups, stream);
 }
 
 size_t window_score_part_bytes(const pyr_shape& s, int32_t w) {
@@ -615,16 +695,17 @@ size_t window_score_part_bytes(const pyr_shape& s, int32_t w) {
     return ranges * (size_t)s.n_seqs * (size_t)w * (size_t)s.n_q_heads * sizeof(float2);
 }
 
-int launch_window_score(const void* q_win, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& s,
-                        int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights, float* lse_win, void* part, float* scores,
+int launch_window_score(const void* q_win, const void* k, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
+                        const pyr_shape& s, int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights, float* lse_win, void* part, float* scores,
                         int* groups, hipStream_t stream) {
     *groups = 1;
     if (s.n_seqs == 0 || s.max_seqlen == 0) return PYR_OK;
     DeviceInfo dev;
     if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
-    const StripPlan stats = plan_strip(s, min_seqlen, w, dev.compute_units, 2, kMaxScoreGroups);
-    int rc = launch_strip<kStats>(q_win, k, nullptr, seq_offsets_dev, s, min_seqlen, w, 1, scale_log2, nullptr, nullptr, (float2*)part,
-                                  stats, dev, stream);
+    const BatchCut cut = cut_batch(s, seq_offsets_host, min_seqlen);
+    const StripPlan stats = plan_strip(s, min_seqlen, cut, w, dev.compute_units, 2, kMaxScoreGroups);
+    int rc = launch_strip<kStats>(q_win, k, nullptr, seq_offsets_dev, seq_offsets_host, s, min_seqlen, w, 1, scale_log2, nullptr, nullptr,
+                                  (float2*)part, stats, dev, stream);
     if (rc != PYR_OK) return rc;
     const int64_t n = (int64_t)s.n_seqs * w * s.n_q_heads;
     if ((n + kFoldRows - 1) / kFoldRows >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
@@ -634,8 +715,8 @@ int launch_window_score(const void* q_win, const void* k, const int32_t* seq_off
     // the statistics are dead once folded: their space takes the partial sums, as many as fit
     int most = 1;
     while (most < kMaxScoreGroups && 2 * (size_t)most * s.total_tokens * sizeof(float) <= window_score_part_bytes(s, w)) most *= 2;
-    return launch_scores(q_win, k, lse_win, seq_offsets_dev, s, min_seqlen, w, 1, scale_log2, row_weights, scores, (float*)part, most,
-                         groups, stream);
+    return launch_scores(q_win, k, lse_win, seq_offsets_dev, seq_offsets_host, s, min_seqlen, cut, w, 1, scale_log2, row_weights, scores,
+                         (float*)part, most, groups, stream);
 }
 
 }  // namespace pyr

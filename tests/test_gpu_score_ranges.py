@@ -73,3 +73,26 @@ def test_loose_max_seqlen(lib):
         assert bool((ws[ws_bytes:] == 0x5A).all())
         results.append(scores.cpu().numpy())
     np.testing.assert_allclose(results[0], results[1], rtol=2e-6, atol=1e-12)
+
+
+def _spread(n, lo, hi, seed):
+    return tuple(int(x) for x in np.random.default_rng(seed).integers(lo, hi + 1, size=n))
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w", [
+    ((900,) * 7, 4, 4, 64, 32),                                 # as many ranges in every sequence, not a multiple of the XCDs
+    ((380, 370, 384, 361), 4, 2, 128, 16),                      # ... of lengths that differ
+    ((0, 700, 0, 0, 33, 1), 4, 2, 128, 32),                     # counted by the workgroup: empty sequences in front and between
+    (_spread(64, 1, 400, 1), 2, 2, 64, 16),                     # one round of the count
+    (_spread(65, 1, 400, 2) + (0,), 2, 1, 128, 16),             # two
+    (_spread(255, 0, 300, 3) + (600,), 2, 2, 64, 16),           # four, the last sequence the longest
+    (_spread(257, 0, 300, 4), 2, 2, 64, 16),                    # places for every sequence
+    (_spread(40, 1, 250, 5), 2, 2, 128, 16),                    # ... short sequences
+])
+def test_order_of_the_ranges(lib, lens, Hq, Hkv, d, w):
+    """Every range is taken by exactly one workgroup, whichever way the grid is laid out: scores of the prefill step, and of the
+    cache update, whose statistics walk is laid out the same way."""
+    wl = _wl(lens, Hq, Hkv, d, w)
+    for run in (test_gpu_layer.run_and_check, test_gpu_decode.run_and_check):
+        res, ref, _ = run(lib, wl)
+        np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
