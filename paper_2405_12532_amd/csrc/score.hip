@@ -203,8 +203,6 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
         b = a.order == kSeqPerXcd ? turn * a.xcds + id % a.xcds : turn;
         if (b >= a.n_seqs) return;
         range = slot % a.ranges_per_seq;
-        // (the sequences start at different ranges: the last one, which may be short, does not fall to the same engine every time)
-        if (a.order != kGrid) range = (range + turn) % a.ranges_per_seq;
         row0 = a.seq_offsets[b];
         S = a.seq_offsets[b + 1] - row0;
     }
