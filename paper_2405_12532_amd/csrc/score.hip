@@ -220,9 +220,9 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
     const int64_t n_tasks = (int64_t)a.n_kv_heads * pairs;
     const int t_begin = (int)(n_tasks * blockIdx.y / gridDim.y), t_end = (int)(n_tasks * (blockIdx.y + 1) / gridDim.y);
     const int n_my = max(0, (t_end - t_begin - wave + waves - 1) / waves);
-    // Where the launcher asks for it (head_step != 0), every range starts its walk at another head: workgroups
-    // that run side by side then read different columns of their token rows, which spreads them over the memory
-    // channels when the rows are a power of two apart.
+    // Where the launcher asks for it (head_step != 0), neighbouring ranges start their walks head_step heads apart (a step of 8: at
+    // two different heads of 16, four of 32; an odd step: at all of them): workgroups that run side by side then read different
+    // columns of their token rows, which spreads them over the memory channels when the rows are a power of two apart.
     const int head_rot = (range * a.head_step) % a.n_kv_heads;
 
     // sum of the weights in use (fixed order: every lane strides over them, then a butterfly).
@@ -595,6 +595,20 @@ StripPlan plan_strip(const pyr_shape& s, int32_t min_seqlen, const BatchCut& cut
     return best;
 }
 
+// By how many heads the walks of neighbouring ranges are apart, where K rows are a power of two apart.  Measured (us), steps of
+// 0 / 2 / 7 / 8, d = 128 unless said: 64 x 2048 on 8 heads, d = 64, 30.6 / 28.5 / 28.5 / 30.8 (8 is a multiple of them), 16 heads
+// 114 / 105 / 99 / 97, 32 heads 211 / 218 / 194 / 188, 64 heads 381 / 384 / 406 / 404; 4 x 32768 on 16 heads 112 / 103 / 97 / 93, 32
+// heads 210 / 185 / 182 / 184, 64 heads 377 / 356 / 368 / 419; in short ranges, 8 x 2048 on 32 heads 28.5 / 27.6 / 27.2 / 35.6, 16 x 1000 on
+// 64 heads 50.6 / 53.2 / 55.9 / 56.4.  Rows of 10 KB: no difference; 8 heads with four or more query heads each, where the window's
+// Q rows that neighbouring ranges share count for more: 64 x 2048 on 32/8 heads 103 / 104 / 105 / 103, on 64/8 178 / 180 / 179 / 178.
+int pick_head_step(const pyr_shape& s, int range_tiles) {
+    const size_t k_row_bytes = (size_t)s.n_kv_heads * s.head_dim * 2;
+    if ((k_row_bytes & (k_row_bytes - 1)) != 0) return 0;
+    if (s.n_kv_heads <= 8) return s.n_q_heads > 2 * s.n_kv_heads ? 0 : 7;
+    if (s.n_kv_heads > 32) return 2;
+    return range_tiles >= 8 ? 8 : 7;
+}
+
 template <int D, int kMode>
 int launch_strip_d(const StripArgs& a, dim3 grid, int waves, hipStream_t stream) {
     static std::atomic<uint64_t> lds_set{0};
@@ -631,10 +645,7 @@ int launch_strip(const void* q, const void* k, const float* lse, const int32_t* 
               : s.n_seqs <= kMaxPackedSeqs && s.max_seqlen > kMinPackedLen ? kPacked
                                                                            : kGrid;
     if (a.order == kGrid) a.ranges_per_seq |= 1;
-    // (rows a power of two apart: 64 x 2048 in ranges of 256 keys 210 us without, 188 with steps of 8, 196 with 7, 8 x 2048
-    //  in ranges of 64 keys 31.8, 36.7 and 29.8; rows of 10 KB: no difference)
-    const size_t k_row_bytes = (size_t)s.n_kv_heads * s.head_dim * 2;
-    a.head_step = (k_row_bytes & (k_row_bytes - 1)) != 0 ? 0 : plan.range_tiles >= 8 ? 8 : 7;
+    a.head_step = pick_head_step(s, plan.range_tiles);
     a.q_window = q_window;
     a.c = scale_log2;
     a.row_weights = row_weights;
