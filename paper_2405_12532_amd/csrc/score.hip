@@ -466,8 +466,8 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
 // window slot, head) fold (max, sum) over the ranges the row can see, in a fixed order:
 //   lse = M + log2(sum_r sum_r * 2^(m_r - M)),  M = max_r m_r.
 // Bound: the latency of the loads, so eight lanes share a row (lane u takes ranges u, u + 8, ..., four of them in flight)
-// and their eight results are folded through LDS.
-constexpr int kFoldRows = 32, kFoldLanes = 8;
+// and their eight results are folded through LDS; where a row has four ranges at most, one lane has them all in flight.
+constexpr int kFoldThreads = 256;
 
 __device__ __forceinline__ void fold_one(float& m_run, float& s_run, float m, float s) {
     const float m_new = fmaxf(m_run, m);
@@ -477,9 +477,11 @@ __device__ __forceinline__ void fold_one(float& m_run, float& s_run, float m, fl
     }
 }
 
-__global__ __launch_bounds__(kFoldRows * kFoldLanes) void fold_stats_kernel(const float2* __restrict__ part,
+template <int kFoldLanes>
+__global__ __launch_bounds__(kFoldThreads) void fold_stats_kernel(const float2* __restrict__ part,
                                                          const int32_t* __restrict__ seq_offsets, int32_t n_seqs,
                                                          int32_t n_q_heads, int32_t w, int32_t range_keys, float* __restrict__ lse_win) {
+    constexpr int kFoldRows = kFoldThreads / kFoldLanes;
     __shared__ float2 folded[kFoldLanes][kFoldRows + 1];
     const int row = threadIdx.x % kFoldRows, u = threadIdx.x / kFoldRows;
     const int64_t idx = (int64_t)blockIdx.x * kFoldRows + row;          // (b, h, slot), slot fastest, as in part
@@ -503,11 +505,24 @@ __global__ __launch_bounds__(kFoldRows * kFoldLanes) void fold_stats_kernel(cons
         for (int v = 0; v < kAhead; ++v)
             if (r0 + kFoldLanes * v < n_ranges) fold_one(m_run, s_run, p[v].x, p[v].y);
     }
-    folded[u][row] = make_float2(m_run, s_run);
-    __syncthreads();
+    if (kFoldLanes > 1) {
+        folded[u][row] = make_float2(m_run, s_run);
+        __syncthreads();
+    }
     if (u != 0 || idx >= n_rows) return;
     for (int v = 1; v < kFoldLanes; ++v) fold_one(m_run, s_run, folded[v][row].x, folded[v][row].y);
     lse_win[((size_t)b * w + slot) * n_q_heads + h] = n_ranges > 0 ? m_run + __builtin_amdgcn_logf(s_run) : 0.f;
+}
+
+template <int kFoldLanes>
+int launch_fold(const float2* part, const int32_t* seq_offsets_dev, const pyr_shape& s, int32_t w, int32_t range_keys, float* lse_win,
+                hipStream_t stream) {
+    constexpr int64_t kRows = kFoldThreads / kFoldLanes;
+    const int64_t blocks = ((int64_t)s.n_seqs * w * s.n_q_heads + kRows - 1) / kRows;
+    if (blocks >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((fold_stats_kernel<kFoldLanes>), dim3((unsigned)blocks), dim3(kFoldThreads), 0, stream, part, seq_offsets_dev,
+                       s.n_seqs, s.n_q_heads, w, range_keys, lse_win);
+    return check_launch();
 }
 
 // How many ranges a batch has if a range has that many tiles (for the plan: counted in fp32).
@@ -716,11 +731,11 @@ int launch_window_score(const void* q_win, const void* k, const int32_t* seq_off
     int rc = launch_strip<kStats>(q_win, k, nullptr, seq_offsets_dev, seq_offsets_host, s, min_seqlen, w, 1, scale_log2, nullptr, nullptr,
                                   (float2*)part, stats, dev, stream);
     if (rc != PYR_OK) return rc;
-    const int64_t n = (int64_t)s.n_seqs * w * s.n_q_heads;
-    if ((n + kFoldRows - 1) / kFoldRows >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(fold_stats_kernel, dim3((unsigned)((n + kFoldRows - 1) / kFoldRows)), dim3(kFoldRows * kFoldLanes), 0, stream, (const float2*)part,
-                       seq_offsets_dev, s.n_seqs, s.n_q_heads, w, (int32_t)(32 * stats.range_tiles), lse_win);
-    if (check_launch() != PYR_OK) return PYR_ERR_LAUNCH;
+    const int range_keys = 32 * stats.range_tiles;
+    rc = (s.max_seqlen + range_keys - 1) / range_keys <= 4
+             ? launch_fold<1>((const float2*)part, seq_offsets_dev, s, w, range_keys, lse_win, stream)
+             : launch_fold<8>((const float2*)part, seq_offsets_dev, s, w, range_keys, lse_win, stream);
+    if (rc != PYR_OK) return rc;
     // the statistics are dead once folded: their space takes the partial sums, as many as fit
     int most = 1;
     while (most < kMaxScoreGroups && 2 * (size_t)most * s.total_tokens * sizeof(float) <= window_score_part_bytes(s, w)) most *= 2;
