@@ -62,9 +62,9 @@ enum Order {
     kGrid = 3,           // ragged: ranges_per_seq places for each sequence
 };
 // Counting costs a workgroup 0.3 us per 64 sequences.  Measured, packed / grid (us): 17 sequences of 3292...7710 tokens, 24
-// heads, w = 512 404 / 691, 48 of 30...400 26 / 37, 128 of 60...1500 171 / 214; but 64 of 16...120 5.6 / 5.3, 256 12.6 / 10.8,
-// 800 of 30...400 231 / 231.
-constexpr int kMaxPackedSeqs = 256, kMinPackedLen = 256;
+// heads, w = 512 404 / 691, 97 of 45...71, 24 heads, 12.0 / 18.6, 48 of 30...400 26 / 37, 128 of 60...1500 171 / 214; but 192 of 16...120,
+// 8 heads, d = 64, 7.5 / 7.3, 256 12.5 / 10.7, 800 of 30...400 231 / 231.
+constexpr int kMaxPackedSeqs = 256, kMaxPackedShortSeqs = 128, kShortLen = 256;
 
 typedef __attribute__((address_space(3))) char* lptr_t;
 typedef __attribute__((address_space(3))) float* lfloat_t;
@@ -76,7 +76,7 @@ struct StripArgs {
     const int32_t* seq_offsets;
     int32_t n_seqs, n_q_heads, n_kv_heads, w;
     int32_t range_tiles, ranges_per_seq;      // tiles of a range; ranges of the longest sequence
-    int32_t order, xcds, head_step;           // order of the ranges over the workgroups, of the heads over the ranges
+    int32_t order, xcds, turn, head_step;     // order of the ranges over the workgroups, of the heads over the ranges
     int32_t q_window;                         // 0: q and lse by packed row; else by (sequence, window slot)
     float c;
     const float* row_weights;
@@ -199,10 +199,10 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
         }
     } else {
         const int id = (int)blockIdx.x, slot = a.order == kSeqPerXcd ? id / a.xcds : id;
-        const int turn = slot / a.ranges_per_seq;
-        b = a.order == kSeqPerXcd ? turn * a.xcds + id % a.xcds : turn;
+        const int at = slot / a.ranges_per_seq;
+        b = a.order == kSeqPerXcd ? at * a.xcds + id % a.xcds : at;
         if (b >= a.n_seqs) return;
-        range = slot % a.ranges_per_seq;
+        range = (slot + a.turn * at) % a.ranges_per_seq;       // (the same ranges of the sequence, from its at-th on)
         row0 = a.seq_offsets[b];
         S = a.seq_offsets[b + 1] - row0;
     }
@@ -657,9 +657,13 @@ int launch_strip(const void* q, const void* k, const float* lse, const int32_t* 
                                                       : count_ranges(seq_offsets_host, s.n_seqs, 32 * plan.range_tiles);
     a.order = min_seqlen == s.max_seqlen && s.n_seqs % dev.xccs == 0              ? kSeqPerXcd
               : ranges == (int64_t)s.n_seqs * a.ranges_per_seq                    ? kEqual
-              : s.n_seqs <= kMaxPackedSeqs && s.max_seqlen > kMinPackedLen ? kPacked
+              : s.n_seqs <= (s.max_seqlen > kShortLen ? kMaxPackedSeqs : kMaxPackedShortSeqs) ? kPacked
                                                                            : kGrid;
     if (a.order == kGrid) a.ranges_per_seq |= 1;
+    // Where the window is a good part of the sequence, fewer of its rows see the later ranges; each sequence then starts at another
+    // range, or the long ones would meet on the same engines (31 x 2048, w = 1024, on 32/8 heads 1038 us without, 809 with it; but
+    // 30 x 1100, w = 128, on 32 heads 86.6 without, 91.1 with it).
+    a.turn = (a.order == kSeqPerXcd || a.order == kEqual) && 2 * (int64_t)w >= s.max_seqlen ? 1 : 0;
     a.head_step = pick_head_step(s, plan.range_tiles);
     a.q_window = q_window;
     a.c = scale_log2;

@@ -87,7 +87,9 @@ def _spread(n, lo, hi, seed):
     (_spread(65, 1, 400, 2) + (0,), 2, 1, 128, 16),             # two
     (_spread(255, 0, 300, 3) + (600,), 2, 2, 64, 16),           # four, the last sequence the longest
     (_spread(257, 0, 300, 4), 2, 2, 64, 16),                    # places for every sequence
-    (_spread(40, 1, 250, 5), 2, 2, 128, 16),                    # ... short sequences
+    (_spread(129, 1, 250, 5), 2, 2, 128, 16),                   # ... more than 128 short ones
+    ((700,) * 7, 2, 2, 64, 400),                                # half a sequence in the window: each starts at another range
+    ((520,) * 16, 2, 1, 128, 300),                              # ... on one XCD each
 ])
 def test_order_of_the_ranges(lib, lens, Hq, Hkv, d, w):
     """Every range is taken by exactly one workgroup, whichever way the grid is laid out: scores of the prefill step, and of the
@@ -96,3 +98,11 @@ def test_order_of_the_ranges(lib, lens, Hq, Hkv, d, w):
     for run in (test_gpu_layer.run_and_check, test_gpu_decode.run_and_check):
         res, ref, _ = run(lib, wl)
         np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
+
+
+@pytest.mark.parametrize("S", [1, 64, 256, 257, 512, 513, 2100])
+def test_fold_of_the_statistics(lib, S):
+    """Ranges of 64 keys, the smallest the statistics walk takes and what it takes for one short cache: one lane folds a row of up
+    to four of them, eight lanes share it from five on, and each has several from nine on."""
+    res, ref, _ = test_gpu_decode.run_and_check(lib, _wl((S,), 4, 2, 128, 40))
+    np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
