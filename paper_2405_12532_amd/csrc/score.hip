@@ -65,6 +65,7 @@ enum Order {
 // heads, w = 512 404 / 691, 97 of 45...71, 24 heads, 12.0 / 18.6, 48 of 30...400 26 / 37, 128 of 60...1500 171 / 214; but 192 of 16...120,
 // 8 heads, d = 64, 7.5 / 7.3, 256 12.5 / 10.7, 800 of 30...400 231 / 231.
 constexpr int kMaxPackedSeqs = 256, kMaxPackedShortSeqs = 128, kShortLen = 256;
+constexpr int kEnginesPerXcd = 4;
 
 typedef __attribute__((address_space(3))) char* lptr_t;
 typedef __attribute__((address_space(3))) float* lfloat_t;
@@ -525,10 +526,18 @@ int launch_fold(const float2* part, const int32_t* seq_offsets_dev, const pyr_sh
     return check_launch();
 }
 
-// How many ranges a batch has if a range has that many tiles (for the plan: counted in fp32).
+// What the plan needs to know of a batch: tiles in all, and how many ranges there are if a range has that many tiles (counted in fp32).
 struct BatchCut {
+    bool equal;
+    double tiles;
     int64_t ranges[kMaxRangeTiles + 1];
 };
+
+Order pick_order(const pyr_shape& s, bool equal, int64_t ranges, int64_t ranges_per_seq, int xcds) {
+    if (equal && s.n_seqs % xcds == 0) return kSeqPerXcd;
+    if (ranges == s.n_seqs * ranges_per_seq) return kEqual;
+    return s.n_seqs <= (s.max_seqlen > kShortLen ? kMaxPackedSeqs : kMaxPackedShortSeqs) ? kPacked : kGrid;
+}
 
 int64_t count_ranges(const int32_t* seq_offsets_host, int32_t n_seqs, int32_t range_keys) {
     int64_t n = 0;
@@ -538,7 +547,9 @@ int64_t count_ranges(const int32_t* seq_offsets_host, int32_t n_seqs, int32_t ra
 
 BatchCut cut_batch(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t min_seqlen) {
     BatchCut cut{};
-    if (min_seqlen == s.max_seqlen) {
+    cut.equal = min_seqlen == s.max_seqlen;
+    if (cut.equal) {
+        cut.tiles = (double)s.n_seqs * ((s.max_seqlen + 31) / 32);
         for (int nt = 1; nt <= kMaxRangeTiles; ++nt) cut.ranges[nt] = (int64_t)s.n_seqs * (((s.max_seqlen + 31) / 32 + nt - 1) / nt);
         return cut;
     }
@@ -547,7 +558,9 @@ BatchCut cut_batch(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t 
     float tiles[kBlock];
     for (int32_t b0 = 0; b0 < s.n_seqs; b0 += kBlock) {
         const int n = s.n_seqs - b0 < kBlock ? s.n_seqs - b0 : kBlock;
-        for (int i = 0; i < n; ++i) tiles[i] = (float)((seq_offsets_host[b0 + i + 1] - seq_offsets_host[b0 + i] + 31) / 32);
+        float sum_tiles = 0.f;
+        for (int i = 0; i < n; ++i) sum_tiles += tiles[i] = (float)((seq_offsets_host[b0 + i + 1] - seq_offsets_host[b0 + i] + 31) / 32);
+        cut.tiles += sum_tiles;
         for (int nt = 1; nt <= kMaxRangeTiles; ++nt) {
             const float inv = 1.0f / nt, up = (nt - 0.5f) * inv;
             int32_t sum = 0;
@@ -563,44 +576,60 @@ struct StripPlan {
     int range_tiles, waves, groups;
 };
 
-// Two limits, in microseconds as measured at d = 128.  The chain: a wavefront takes 0.82 per tile of its stream alone on its
-// SIMD (wait, copy, products, exponentials) and 1.0 beside a second one, and a compute unit runs its workgroups in rounds
-// (a single round that fits exactly does not start at once: above nine tenths half a round more is counted).  The stream: a compute unit's
-// share of the memory system delivers a tile of K from HBM in 0.35 and one of Q from L2 in 0.08; a last round that is
-// not full costs half of what it leaves idle (one that fits exactly 0.15: 64 x 359, ranges of 3 tiles in 256 workgroups 52 us, of 4
-// in 192 50 us), and the shares of a ragged batch differ (32 sequences of 512...8192 tokens on 40
-// heads, ranges of 12, 10, 9, 8, 7 tiles: 257, 242, 292, 322, 257 us).  The cut with the smallest larger one wins.
-// (Predicted / measured: 64 x 2048, ranges of 256 keys, 189 / 187 us, of 352 keys 218 / 224; 4 x 32768 with 64/8 heads
-// and w = 128, 256 keys, 326 / 378, of 384 keys 454 / 460; 8 x 2048, 64 keys, 28 / 30, of 256 keys 46 / 49.)
-StripPlan plan_strip(const pyr_shape& s, int32_t min_seqlen, const BatchCut& cut, int32_t w, int compute_units, int min_range_tiles,
-                     int max_groups) {
+// The cut with the lowest cost, in microseconds, of two limits joined smoothly (the fourth root of the sum of fourth powers):
+// - The chain.  An engine's compute units take its workgroups in rounds.  A round takes 1.9 until its first tiles are there, then a
+//   wavefront goes through its tasks, each the range's tiles and the task's row blocks, one step after the other.  A step takes
+//   `alone` where latency sets the time, and `shared` times the wavefronts of its SIMD where they wait for each other.
+// - The stream.  A compute unit's share of the memory system delivers a tile of K in 0.35 from HBM, in 0.136 from L2 to every
+//   further task of its KV head, and a tile of Q in 0.063 (d = 128; half of it at d = 64); a last round that leaves compute units
+//   without a workgroup costs a tenth of what it leaves idle.
+// Places for tiles that are not there (ranges that do not divide the sequences) add a tenth of their share.
+// A row of partial sums costs the selection, one workgroup per sequence, 0.1 and 0.05 per 1000 tokens.
+// The constants are fitted to 710 calls (d = 64 and 128, eleven head shapes, w = 16...512, one 16-token sequence to 200 x 655 and
+// 3 x 40000 tokens, equal and ragged lengths, 173 of them powers of two), each timed with all cuts: nine in ten predictions near a
+// call's best lie within 14 %, and the cut chosen takes 0.9 % longer than the best one in the mean, at most 6 % in 95 of 100
+// calls (lengths of powers of two 0.3 %); the generation phase, with split tasks, 0.8 % (scores) and 1.3 % (statistics) of
+// the whole call.  Fewer than four wavefronts per workgroup never were the best choice where there are tasks for four, nor fewer
+// than eight where a KV head has 48 tasks or more, which then share its tiles (161 x 814, w >= 814, on 48/8 heads: eight 1880 us, four 2170).
+StripPlan plan_strip(const pyr_shape& s, const BatchCut& cut, int32_t w, const DeviceInfo& dev, int min_range_tiles, int max_groups,
+                     bool partial_sums) {
     const int L = w < s.max_seqlen ? w : s.max_seqlen;
-    const int64_t n_rb = (L + 31) / 32, pairs = (s.n_q_heads / s.n_kv_heads * n_rb + 1) / 2, tasks = s.n_kv_heads * pairs;
+    const int64_t blocks = (int64_t)(s.n_q_heads / s.n_kv_heads) * ((L + 31) / 32), pairs = (blocks + 1) / 2, tasks = s.n_kv_heads * pairs;
     const int64_t max_tiles = (s.max_seqlen + 31) / 32;
-    const double tiles = min_seqlen == s.max_seqlen ? (double)s.n_seqs * max_tiles : s.total_tokens / 32.0 + 0.5 * s.n_seqs;
-    const double uneven = min_seqlen == s.max_seqlen ? 1.0 : 1.17;     // (ragged: the XCDs' shares of the ranges differ)
+    const bool d64 = s.head_dim == 64;
+    const double task_blocks = (double)blocks / pairs, size = s.head_dim / 128.0;
+    const double alone = d64 ? 0.42 + 0.085 * task_blocks : 0.54 + 0.11 * task_blocks;
+    const double shared = d64 ? 0.21 + 0.082 * task_blocks : 0.48;
+    const int engines = kEnginesPerXcd * dev.xccs, engine_cus = dev.compute_units > engines ? dev.compute_units / engines : 1;
+    const double per_row = partial_sums ? 0.1 + 5e-5 * s.max_seqlen : 0.0;
     StripPlan best{1, 1, 1};
     double best_cost = 1e300;
     for (int nt = kMaxRangeTiles; nt >= 1; --nt) {
         if (nt < min_range_tiles && nt < max_tiles) continue;
-        const int64_t ranges_per_seq = (max_tiles + nt - 1) / nt;
+        const int64_t ranges_per_seq = (max_tiles + nt - 1) / nt, places = s.n_seqs * ranges_per_seq;
         if (nt > min_range_tiles && ranges_per_seq == (max_tiles + nt - 2) / (nt - 1)) continue;   // the same number of ranges, more evenly
-        const double ranges = (double)cut.ranges[nt];
-        const double size = s.head_dim / 128.0, stream = tasks * (tiles * 0.35 + ranges * 2 * 0.08) * size / compute_units;
+        // (empty places of a grid: half of them count, as what they cost in balance)
+        const double ranges = pick_order(s, cut.equal, cut.ranges[nt], ranges_per_seq, dev.xccs) == kGrid
+                                  ? 0.5 * (cut.ranges[nt] + places) : (double)cut.ranges[nt];
+        const double stream = (cut.tiles * (0.35 * s.n_kv_heads + 0.136 * (tasks - s.n_kv_heads)) + 0.063 * task_blocks * ranges * tasks) *
+                              size / dev.compute_units;
+        const double padding = 1.0 + 0.1 * (cut.ranges[nt] * (double)nt / cut.tiles - 1.0);
         for (int waves = kMaxWaves; waves >= 1; waves /= 2) {
-            if (waves > tasks && waves > 1) continue;
+            if ((waves > tasks && waves > 1) || (waves < 4 && 2 * waves <= tasks) || (waves < kMaxWaves && pairs >= 48)) continue;
             // workgroups a compute unit holds: 8 wavefronts at d = 128 and 12 at d = 64 by registers, 160 KB of LDS
-            const int bytes = s.head_dim == 64 ? wave_lds_bytes<64>(nt) : wave_lds_bytes<128>(nt);
-            int wgs_per_cu = 160 * 1024 / (waves * bytes);
-            if (wgs_per_cu > (s.head_dim == 64 ? 12 : 8) / waves) wgs_per_cu = (s.head_dim == 64 ? 12 : 8) / waves;
+            const int bytes = d64 ? wave_lds_bytes<64>(nt) : wave_lds_bytes<128>(nt);
+            const int by_lds = 160 * 1024 / (waves * bytes), by_registers = (d64 ? 12 : 8) / waves;
+            const int wgs_per_cu = by_lds < by_registers ? by_lds : by_registers;
             for (int g = 1; g <= max_groups && (g == 1 || (int64_t)g * waves < 2 * tasks); g *= 2) {
-                const int64_t tpw = (tasks + (int64_t)g * waves - 1) / ((int64_t)g * waves);
-                const double wgs = ranges * g, rounds = wgs / ((double)compute_units * wgs_per_cu), whole = ceil(rounds * uneven);
-                const double tile = (wgs * waves > 4.0 * compute_units ? 1.0 : 0.82) * (0.4 + 0.6 * size);
-                const double chain = (ceil(rounds) + (ceil(rounds / 0.9) > ceil(rounds) ? 0.5 : 0.0)) * tpw * (nt + 2) * tile;
-                const double idle = rounds > 0.9 && rounds <= 1.0 ? 1.15 : 1.0 + 0.5 * (whole / rounds - 1.0);
-                const double cost = (chain + 6.0 > stream * idle ? chain + 6.0 : stream * idle) + 0.25 * (g - 1);
-                if (cost < best_cost * 0.999) {
+                const double wave_tasks = (double)((tasks + (int64_t)g * waves - 1) / ((int64_t)g * waves)), steps = wave_tasks * (nt + task_blocks);
+                const int64_t queue = ((int64_t)(ranges * g) + engines - 1) / engines, round = (int64_t)engine_cus * wgs_per_cu;
+                const int64_t per_cu = (queue + engine_cus - 1) / engine_cus, rest = queue % round;
+                const double full = shared * wgs_per_cu * waves / 4, last = shared * (double)((rest + engine_cus - 1) / engine_cus * waves) / 4;
+                const double chain = (double)(queue / round) * (1.9 + steps * (full > alone ? full : alone)) +
+                                     (rest == 0 ? 0.0 : 1.9 + steps * (last > alone ? last : alone));
+                const double flow = stream * (1.0 + 0.1 * ((double)per_cu * engine_cus / queue - 1.0));
+                const double cost = sqrt(sqrt(chain * chain * chain * chain + flow * flow * flow * flow)) * padding + per_row * (g - 1);
+                if (cost < best_cost) {
                     best_cost = cost;
                     best = StripPlan{nt, waves, g};
                 }
@@ -655,10 +684,7 @@ int launch_strip(const void* q, const void* k, const float* lse, const int32_t* 
     a.xcds = dev.xccs;
     const int64_t ranges = min_seqlen == s.max_seqlen ? (int64_t)s.n_seqs * a.ranges_per_seq
                                                       : count_ranges(seq_offsets_host, s.n_seqs, 32 * plan.range_tiles);
-    a.order = min_seqlen == s.max_seqlen && s.n_seqs % dev.xccs == 0              ? kSeqPerXcd
-              : ranges == (int64_t)s.n_seqs * a.ranges_per_seq                    ? kEqual
-              : s.n_seqs <= (s.max_seqlen > kShortLen ? kMaxPackedSeqs : kMaxPackedShortSeqs) ? kPacked
-                                                                           : kGrid;
+    a.order = pick_order(s, min_seqlen == s.max_seqlen, ranges, a.ranges_per_seq, dev.xccs);
     if (a.order == kGrid) a.ranges_per_seq |= 1;
     // Where the window is a good part of the sequence, fewer of its rows see the later ranges; each sequence then starts at another
     // range, or the long ones would meet on the same engines (31 x 2048, w = 1024, on 32/8 heads 1038 us without, 809 with it; but
@@ -683,7 +709,7 @@ int launch_scores(const void* q, const void* k, const float* lse, const int32_t*
                   const float* row_weights, float* scores, float* parts, int max_groups, int* groups, hipStream_t stream) {
     DeviceInfo dev;
     if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
-    const StripPlan plan = plan_strip(s, min_seqlen, cut, w, dev.compute_units, 1, max_groups);
+    const StripPlan plan = plan_strip(s, cut, w, dev, 1, max_groups, true);
     *groups = plan.groups;
     float* sums = plan.groups > 1 ? parts : scores;
     return row_weights ? launch_strip<kScoresWeighted>(q, k, lse, seq_offsets_dev, seq_offsets_host, s, min_seqlen, w, q_window,
@@ -703,7 +729,8 @@ int launch_score(const void* q, const void* k, const float* lse, const int32_t* 
                          scale_log2, row_weights, scores, nullptr, 1, &groups, stream);
 }
 
-// (Only batches of fewer than 1024 blocks of 64 keys are ever split: beyond that the ranges alone fill the chip.)
+// (A prefill step only has room for partial sums where the batch has fewer than 1024 blocks of 64 keys: beyond that its ranges fill
+// the chip.  The generation phase takes the room of the statistics, and may split larger batches where windows are wide.)
 size_t score_parts_bytes(const pyr_shape& s) {
     const size_t blocks = (size_t)s.n_seqs * (((size_t)s.max_seqlen + 63) / 64);
     return blocks < 1024 ? (size_t)kMaxScoreGroups * s.total_tokens * sizeof(float) : 0;
@@ -731,7 +758,7 @@ int launch_window_score(const void* q_win, const void* k, const int32_t* seq_off
     DeviceInfo dev;
     if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
     const BatchCut cut = cut_batch(s, seq_offsets_host, min_seqlen);
-    const StripPlan stats = plan_strip(s, min_seqlen, cut, w, dev.compute_units, 2, kMaxScoreGroups);
+    const StripPlan stats = plan_strip(s, cut, w, dev, 2, kMaxScoreGroups, false);
     int rc = launch_strip<kStats>(q_win, k, nullptr, seq_offsets_dev, seq_offsets_host, s, min_seqlen, w, 1, scale_log2, nullptr, nullptr,
                                   (float2*)part, stats, dev, stream);
     if (rc != PYR_OK) return rc;
