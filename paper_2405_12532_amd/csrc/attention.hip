@@ -55,7 +55,6 @@
 #include <math.h>
 
 #include <algorithm>
-#include <numeric>
 
 #include "attention_device.h"
 
@@ -167,7 +166,7 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
     // a time: lane l of every wavefront holds item tbl_base + l of the workgroup's list, decoded, in four
     // registers, and a walker fetches an entry with four v_readlane.
     // The place inside a round moves on by `turn` from round to round: with an odd number of query tiles the item in the
-    // middle is a single tile, and at a fixed place the same workgroups would get that half-length item every time
+    // middle is a single tile, and at a fixed place the same workgroups can get that half-length item every time
     // (64 x 700, three tiles: 488 -> 417 us; 64 x 1648, seven: 1924 -> 1697).
     const int first_item = blockIdx.x / xcds;
     const int full_rounds = items_per_xcd / slot_stride, last_round = items_per_xcd % slot_stride;
@@ -769,6 +768,41 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
     __builtin_amdgcn_s_waitcnt(0x0f70);           // no load may still be writing LDS when the workgroup ends
 }
 
+// By how much a workgroup's place moves from round to round (see the kernel), for equal sequences of an odd number of tiles: the
+// smallest move, up to three, under which the fullest workgroup has least to do, counted in tiles over the first 64 rounds.
+// A move that the balance does not need costs (4 x 3233 on 64/8 heads 642 us without, 666 with one of one place; 10 x 6400 on
+// 16/2 1507 and 1577).
+// Ragged batches keep the plain stride: their items differ from sequence to sequence anyway.
+int pick_turn(int32_t uniform_len, int group, int slots, int32_t items_per_xcd) {
+    const int tiles = (uniform_len + kBM - 1) / kBM;
+    if (uniform_len == 0 || tiles == 1 || tiles % 2 == 0) return 0;
+    constexpr int kMaxTurn = 3, kMaxRounds = 64, kMaxSlots = 1024;
+    if (slots > kMaxSlots) return 0;
+    const int n_items = items_of(uniform_len), period = n_items * group, middle = (n_items - 1) * group;      // places of the single tiles in a period
+    int best = 0, least = 0x7fffffff;
+    for (int turn = 0; turn <= kMaxTurn; ++turn) {
+        int load[kMaxSlots] = {}, most = 0;
+        int first = 0, place0 = 0;                    // item at place 0 of the round, modulo the period; workgroup there
+        for (int32_t round = 0; round < kMaxRounds && (int64_t)round * slots < items_per_xcd; ++round) {
+            const int64_t left = items_per_xcd - (int64_t)round * slots;
+            const int here = left < slots ? (int)left : slots;
+            for (int place = 0, kind = first, wg = place0; place < here; ++place) {
+                load[wg] += kind >= middle ? 1 : 2;
+                if (load[wg] > most) most = load[wg];
+                if (++kind == period) kind = 0;
+                if (++wg == slots) wg = 0;
+            }
+            first = (first + slots) % period;
+            place0 = ((place0 - turn) % slots + slots) % slots;      // (the workgroup with first_item + round * turn = 0)
+        }
+        if (most < least) {
+            least = most;
+            best = turn;
+        }
+    }
+    return best;
+}
+
 int launch_attention_long(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev,
                           const int32_t* seq_offsets_host, const pyr_shape& s, int32_t uniform_len, float c,
                           void* out, float* lse, int32_t* item_map, const DeviceInfo& dev, hipStream_t stream) {
@@ -788,12 +822,7 @@ int launch_attention_long(const void* q, const void* k, const void* v, const int
     const int32_t items_per_xcd = (int32_t)(total_items * s.n_q_heads / xcds);
     long long slots = dev.compute_units / xcds;      // persistent workgroups, one per compute unit
     if (slots > items_per_xcd) slots = items_per_xcd;
-    // The turn that takes a workgroup through all kinds of items (see the kernel): step and period without a common
-    // factor.  Ragged batches keep the plain stride: their items differ from sequence to sequence anyway.
-    int turn = 0;
-    const int period = uniform_len > 0 ? items_of(uniform_len) * (s.n_q_heads / s.n_kv_heads) : 1;
-    if (uniform_len > kBM && (uniform_len + kBM - 1) / kBM % 2 == 1)
-        while (std::gcd((int)slots + turn, period) != 1) ++turn;
+    const int turn = pick_turn(uniform_len, s.n_q_heads / s.n_kv_heads, (int)slots, items_per_xcd);
     hipLaunchKernelGGL(attention_kernel, dim3((unsigned)(slots * xcds)), dim3(kNW * 64), Tile::kLdsBytes, stream,
                        (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, seq_offsets_dev,
                        (const int32_t*)item_map, s.n_seqs, s.n_q_heads, s.n_kv_heads, uniform_len, xcds,
