@@ -322,6 +322,24 @@ PYR_API int pyr_diag_mfma_only(int32_t iters, float* sink_dev, void* stream, dou
  */
 PYR_API int pyr_diag_read_stream(const void* data_dev, size_t bytes, int32_t k_layout, int32_t* sink_dev, void* stream);
 
+/*
+ * Diagnostic, not part of the method: which kernels and which cut of the work the entry points above take for a batch,
+ * so that a test can assert that it reaches the path it is written for.  Host only; launches nothing.
+ *   compute_units, xcds  of the device to answer for; both 0: the current device
+ *   route_out            host, written:
+ */
+typedef struct pyr_route {
+    int32_t attention;          /* 0: lists of 256-row tiles; 1, 2: one 128-row tile per workgroup, keys in one or two groups */
+    int32_t attention_items;    /* attention == 0: most items (pairs of tiles) in one workgroup's list, else 0 */
+    int32_t attention_listed;   /* attention != 0: 1 if the grid is a list of the tiles that exist, else 0 */
+    int32_t score_tiles, score_waves, score_groups;     /* prefill score pass: 32-key tiles of a range, wavefronts, split */
+    int32_t score_order;        /* 0: a sequence per XCD, 1: equally many ranges, 2: counted, 3: places for the longest sequence */
+    int32_t stats_tiles, stats_waves, stats_groups;     /* the same of the generation phase's statistics ... */
+    int32_t window_tiles, window_waves, window_groups;  /* ... and of its score pass */
+} pyr_route;
+PYR_API int pyr_diag_route(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t w, int32_t compute_units,
+                           int32_t xcds, pyr_route* route_out);
+
 #ifdef __cplusplus
 }
 #endif

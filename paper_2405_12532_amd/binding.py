@@ -20,6 +20,12 @@ class PyrShape(ctypes.Structure):
                 ("n_q_heads", ctypes.c_int32), ("n_kv_heads", ctypes.c_int32), ("head_dim", ctypes.c_int32)]
 
 
+class PyrRoute(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in (
+        "attention", "attention_items", "attention_listed", "score_tiles", "score_waves", "score_groups", "score_order",
+        "stats_tiles", "stats_waves", "stats_groups", "window_tiles", "window_waves", "window_groups")]
+
+
 class PyrError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = status
@@ -54,6 +60,7 @@ _SIGNATURES = {
                                          _VP, _VP, _VP, _VP, _VP, _VP, _VP, _SZ, _VP]),
     "pyr_diag_mfma_only": (ctypes.c_int, [_I32, _VP, _VP, ctypes.POINTER(ctypes.c_double)]),
     "pyr_diag_read_stream": (ctypes.c_int, [_VP, _SZ, _I32, _VP, _VP]),
+    "pyr_diag_route": (ctypes.c_int, [ctypes.POINTER(PyrShape), _VP, _I32, _I32, _I32, ctypes.POINTER(PyrRoute)]),
 }
 EXPORTS = tuple(_SIGNATURES)
 
@@ -234,6 +241,14 @@ def diag_read_stream(data, nbytes, k_layout, sink, stream=None) -> None:
     """Launch the read-only diagnostic over the first nbytes of data (LDS-direct loads, discarded)."""
     _check(load().pyr_diag_read_stream(_ptr(data), int(nbytes), int(bool(k_layout)), _ptr(sink), _stream(stream)),
            "pyr_diag_read_stream")
+
+
+def diag_route(shape: PyrShape, seq_offsets_host, w: int, compute_units: int = 0, xcds: int = 0) -> PyrRoute:
+    """Which kernels and which cut of the work this batch gets (host only); without a device's sizes, the current one's."""
+    out = PyrRoute()
+    _check(load().pyr_diag_route(ctypes.byref(shape), _ptr(seq_offsets_host), int(w), int(compute_units), int(xcds), ctypes.byref(out)),
+           "pyr_diag_route")
+    return out
 
 
 def decode_workspace_bytes(shape: PyrShape, w: int) -> int:

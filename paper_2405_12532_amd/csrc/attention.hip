@@ -768,6 +768,12 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
     __builtin_amdgcn_s_waitcnt(0x0f70);           // no load may still be writing LDS when the workgroup ends
 }
 
+// Lists of items: workgroup ids go round robin over the XCDs; the items are split by KV head so that one XCD's L2 serves
+// one head's K/V rows.  That needs the KV heads to divide evenly; otherwise one list for the whole device.
+int list_count(const pyr_shape& s, const DeviceInfo& dev) {
+    return s.n_kv_heads % dev.xccs == 0 && dev.compute_units % dev.xccs == 0 ? dev.xccs : 1;
+}
+
 // By how much a workgroup's place moves from round to round (see the kernel), for equal sequences of an odd number of tiles: the
 // smallest move, up to three, under which the fullest workgroup has least to do, counted in tiles over the first 64 rounds.
 // A move that the balance does not need costs (4 x 3233 on 64/8 heads 642 us without, 666 with one of one place; 10 x 6400 on
@@ -816,9 +822,7 @@ int launch_attention_long(const void* q, const void* k, const void* v, const int
         hipLaunchKernelGGL(item_map_kernel, dim3(1), dim3(1024), 0, stream, seq_offsets_dev, s.n_seqs, item_map);
         if (check_launch() != PYR_OK) return PYR_ERR_LAUNCH;
     }
-    // Workgroup ids go round robin over the XCDs; the items are split by KV head so that one XCD's L2 serves
-    // one head's K/V rows.  That needs the KV heads to divide evenly; otherwise one list for the whole device.
-    const int xcds = (s.n_kv_heads % dev.xccs == 0 && dev.compute_units % dev.xccs == 0) ? dev.xccs : 1;
+    const int xcds = list_count(s, dev);
     const int32_t items_per_xcd = (int32_t)(total_items * s.n_q_heads / xcds);
     long long slots = dev.compute_units / xcds;      // persistent workgroups, one per compute unit
     if (slots > items_per_xcd) slots = items_per_xcd;
@@ -849,7 +853,7 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
     int max_len = 0;
     // the lists of the kernel above, if they differ: what each has, as differences from one to the next
     constexpr int kMaxSlots = 1024;
-    const int xcds = s.n_kv_heads % dev.xccs == 0 && dev.compute_units % dev.xccs == 0 ? dev.xccs : 1;
+    const int xcds = list_count(s, dev);
     const int slots = dev.compute_units / xcds < kMaxSlots ? dev.compute_units / xcds : kMaxSlots;
     double more[kMaxSlots + 1];
     if (uniform_len == 0) std::fill(more, more + slots + 1, 0.0);
@@ -905,6 +909,19 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
 }
 
 }  // namespace
+
+void attention_route(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t uniform_len, const DeviceInfo& dev, pyr_route* out) {
+    out->attention = pick_kernel(s, seq_offsets_host, uniform_len, dev);
+    if (out->attention != 0) {
+        out->attention_listed = attention_tile_listed(s, seq_offsets_host, uniform_len) ? 1 : 0;
+        return;
+    }
+    const int xcds = list_count(s, dev);
+    long long items = 0;
+    for (int32_t b = 0; b < s.n_seqs; ++b) items += items_of(seq_offsets_host[b + 1] - seq_offsets_host[b]);
+    const long long slots = dev.compute_units / xcds;
+    out->attention_items = (int32_t)((items * s.n_q_heads / xcds + slots - 1) / slots);
+}
 
 int launch_attention(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev,
                      const int32_t* seq_offsets_host, const pyr_shape& shape, int32_t uniform_len, float scale_log2,

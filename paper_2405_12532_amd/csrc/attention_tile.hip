@@ -581,7 +581,23 @@ double xcd_share(const pyr_shape& s, const int32_t* off, int32_t uniform_len, in
     return all > 0 ? (even + most) * xcds / all : 1.0;
 }
 
+int64_t count_tiles(const pyr_shape& s, const int32_t* seq_offsets_host) {
+    int64_t tiles = 0;
+    for (int32_t b = 0; b < s.n_seqs; ++b) tiles += (seq_offsets_host[b + 1] - seq_offsets_host[b] + kRows - 1) / kRows;
+    return tiles;
+}
+
 }  // namespace
+
+// A list of the tiles that exist, where the grid would mostly hold workgroups that find no rows.  One of those costs about 0.8 ns;
+// finding its place in the list costs a tile about 1.2 us, 2.3 ns of the whole device, and the list is a launch of its own, 4.5 us.
+// Measured, grid / list (us): 32768 and 255 x 64 tokens 10310 / 8280, 4096 and 2000 x 16 2400 / 721, d = 64: 8192 and
+// 500 x 100 on 12 heads 530 / 180; but 32 sequences of 512...4096 on 32/8 heads 1946 / 2000.
+bool attention_tile_listed(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t uniform_len) {
+    if (uniform_len > 0) return false;
+    const int tiles = (s.max_seqlen + kRows - 1) / kRows;
+    return ((int64_t)s.n_seqs * tiles - 4 * count_tiles(s, seq_offsets_host)) * s.n_q_heads > 6000;
+}
 
 int launch_attention_tile(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
                           const pyr_shape& s, int32_t uniform_len, float scale_log2, void* out, float* lse, int32_t* tile_map,
@@ -618,26 +634,19 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
         if (s.head_dim == 128) return groups == 2 ? launch_tile<128, 2>(a, grid, stream) : launch_tile<128, 1>(a, grid, stream);
         return groups == 2 ? launch_tile<64, 2>(a, grid, stream) : launch_tile<64, 1>(a, grid, stream);
     };
-    // A list of the tiles that exist, sequence after sequence with the last tile first (the order a chunk of one sequence has),
-    // where the grid below would mostly hold workgroups that find no rows.  One of those costs about 0.8 ns; finding its place
-    // in the list costs a tile about 1.2 us, 2.3 ns of the whole device, and the list is a launch of its own, 4.5 us.
-    // Measured, grid / list (us): 32768 and 255 x 64 tokens 10310 / 8280, 4096 and 2000 x 16 2400 / 721, d = 64: 8192 and
-    // 500 x 100 on 12 heads 530 / 180; but 32 sequences of 512...4096 on 32/8 heads 1946 / 2000.
-    if (uniform_len == 0) {
-        int64_t listed = 0;
-        for (int32_t b = 0; b < s.n_seqs; ++b) listed += (seq_offsets_host[b + 1] - seq_offsets_host[b] + kRows - 1) / kRows;
-        if (((int64_t)s.n_seqs * tiles - 4 * listed) * s.n_q_heads > 6000) {
-            hipLaunchKernelGGL(tile_map_kernel, dim3(1), dim3(1024), 0, stream, seq_offsets_dev, s.n_seqs, tile_map);
-            int rc = check_launch();
-            a.tile_map = tile_map;
-            const int64_t x = (int64_t)(s.n_kv_heads + a.xcds - 1) / a.xcds * head_group * a.xcds;
-            if (x * 256 * groups >= (int64_t)1 << 32) return PYR_ERR_UNSUPPORTED;
-            for (int64_t first = 0; rc == PYR_OK && first < listed; first += kMaxGrid) {
-                a.first_tile = (int32_t)first;
-                rc = launch(dim3((unsigned)x, (unsigned)(listed - first < kMaxGrid ? listed - first : kMaxGrid)));
-            }
-            return rc;
+    // (sequence after sequence with the last tile first, the order a chunk of one sequence has)
+    if (attention_tile_listed(s, seq_offsets_host, uniform_len)) {
+        const int64_t listed = count_tiles(s, seq_offsets_host);
+        hipLaunchKernelGGL(tile_map_kernel, dim3(1), dim3(1024), 0, stream, seq_offsets_dev, s.n_seqs, tile_map);
+        int rc = check_launch();
+        a.tile_map = tile_map;
+        const int64_t x = (int64_t)(s.n_kv_heads + a.xcds - 1) / a.xcds * head_group * a.xcds;
+        if (x * 256 * groups >= (int64_t)1 << 32) return PYR_ERR_UNSUPPORTED;
+        for (int64_t first = 0; rc == PYR_OK && first < listed; first += kMaxGrid) {
+            a.first_tile = (int32_t)first;
+            rc = launch(dim3((unsigned)x, (unsigned)(listed - first < kMaxGrid ? listed - first : kMaxGrid)));
         }
+        return rc;
     }
     const int64_t unit_tiles = (int64_t)tiles * head_group;
     const int target = (int)((slots + unit_tiles) / (2 * unit_tiles));                   // (rounded)

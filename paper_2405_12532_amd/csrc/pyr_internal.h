@@ -19,6 +19,11 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+// Compute units and XCDs of the current device (cached per device); PYR_ERR_LAUNCH if the runtime
+// cannot tell - the launchers do not guess.
+struct DeviceInfo { int device, compute_units, xccs; };
+int device_info(DeviceInfo* out);
+
 // Every launcher returns PYR_OK or PYR_ERR_LAUNCH; arguments are already validated.
 int launch_gather(const void* src0, void* dst0, const void* src1, void* dst1, size_t row_bytes,
                   const int32_t* kept_idx, int64_t n_kept, hipStream_t stream);
@@ -41,6 +46,12 @@ int launch_attention(const void* q, const void* k, const void* v, const int32_t*
 int launch_attention_tile(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
                           const pyr_shape& shape, int32_t uniform_len, float scale_log2, void* out, float* lse, int32_t* tile_map,
                           int groups, hipStream_t stream);
+
+// What the launchers above and below would do with a batch (pyr_diag_route).
+void attention_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len, const DeviceInfo& dev, pyr_route* out);
+bool attention_tile_listed(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len);
+void score_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, bool parts, const DeviceInfo& dev,
+                 pyr_route* out);
 
 // row_weights: device [w] or nullptr (uniform); min_seqlen: the shortest sequence (0 if not known)
 int launch_score(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
@@ -67,11 +78,6 @@ int launch_window_score(const void* q_win, const void* k, const int32_t* seq_off
 
 int launch_gather_positions(const int32_t* pos, const int32_t* kept_idx, int64_t n_kept, int32_t* pos_out,
                             hipStream_t stream);
-
-// Compute units and XCDs of the current device (cached per device); PYR_ERR_LAUNCH if the runtime
-// cannot tell - the launchers do not guess.
-struct DeviceInfo { int device, compute_units, xccs; };
-int device_info(DeviceInfo* out);
 
 // Raise a kernel's dynamic LDS limit to `bytes`, once per device (done_mask: one bit per device id).
 int ensure_dynamic_lds(const void* kernel, int bytes, std::atomic<uint64_t>* done_mask);

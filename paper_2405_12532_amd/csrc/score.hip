@@ -745,6 +745,32 @@ int launch_score_groups(const void* q, const void* k, const float* lse, const in
                          scale_log2, row_weights, scores, parts, parts != nullptr ? kMaxScoreGroups : 1, groups, stream);
 }
 
+// Partial sums of the generation phase's score pass: the statistics are dead once folded, their space takes as many as fit.
+static int window_score_groups(const pyr_shape& s, int32_t w) {
+    int most = 1;
+    while (most < kMaxScoreGroups && 2 * (size_t)most * s.total_tokens * sizeof(float) <= window_score_part_bytes(s, w)) most *= 2;
+    return most;
+}
+
+void score_route(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, bool parts, const DeviceInfo& dev,
+                 pyr_route* out) {
+    const BatchCut cut = cut_batch(s, seq_offsets_host, min_seqlen);
+    const StripPlan score = plan_strip(s, cut, w, dev, 1, parts ? kMaxScoreGroups : 1, true);
+    const StripPlan stats = plan_strip(s, cut, w, dev, 2, kMaxScoreGroups, false);
+    const StripPlan window = plan_strip(s, cut, w, dev, 1, window_score_groups(s, w), true);
+    out->score_tiles = score.range_tiles;
+    out->score_waves = score.waves;
+    out->score_groups = score.groups;
+    out->score_order = pick_order(s, cut.equal, count_ranges(seq_offsets_host, s.n_seqs, 32 * score.range_tiles),
+                                  ((s.max_seqlen + 31) / 32 + score.range_tiles - 1) / score.range_tiles, dev.xccs);
+    out->stats_tiles = stats.range_tiles;
+    out->stats_waves = stats.waves;
+    out->stats_groups = stats.groups;
+    out->window_tiles = window.range_tiles;
+    out->window_waves = window.waves;
+    out->window_groups = window.groups;
+}
+
 size_t window_score_part_bytes(const pyr_shape& s, int32_t w) {
     const size_t ranges = ((size_t)s.max_seqlen + 63) / 64;           // (statistics ranges are at least 64 keys)
     return ranges * (size_t)s.n_seqs * (size_t)w * (size_t)s.n_q_heads * sizeof(float2);
@@ -767,11 +793,8 @@ int launch_window_score(const void* q_win, const void* k, const int32_t* seq_off
              ? launch_fold<1>((const float2*)part, seq_offsets_dev, s, w, range_keys, lse_win, stream)
              : launch_fold<8>((const float2*)part, seq_offsets_dev, s, w, range_keys, lse_win, stream);
     if (rc != PYR_OK) return rc;
-    // the statistics are dead once folded: their space takes the partial sums, as many as fit
-    int most = 1;
-    while (most < kMaxScoreGroups && 2 * (size_t)most * s.total_tokens * sizeof(float) <= window_score_part_bytes(s, w)) most *= 2;
     return launch_scores(q_win, k, lse_win, seq_offsets_dev, seq_offsets_host, s, min_seqlen, cut, w, 1, scale_log2, row_weights, scores,
-                         (float*)part, most, groups, stream);
+                         (float*)part, window_score_groups(s, w), groups, stream);
 }
 
 }  // namespace pyr

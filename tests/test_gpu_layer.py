@@ -73,8 +73,8 @@ def test_small_shapes_complete(lib, lens, Hq, Hkv, d, w):
 
 
 def test_many_short_sequences(lib):
-    """2200 sequences of 3..70 tokens: every persistent workgroup walks far more than 64 work items, so the
-    table of decoded items the attention kernel keeps in registers (64 entries) is refilled several times."""
+    """2200 sequences of 3..70 tokens: one tile each for the attention kernel, more of them than the score walk's workgroups
+    count (each sequence has its places in the grid), one workgroup each for the selection."""
     rng = np.random.default_rng(11)
     lens = tuple(int(v) for v in rng.integers(3, 71, size=2200))
     wl = synth.shrunk(synth.workload("cfg2"), lens, n_q_heads=8, n_kv_heads=8, head_dim=64, w=8, hidden_dim=0)

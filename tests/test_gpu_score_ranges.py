@@ -8,6 +8,7 @@ import pytest
 
 from paper_2405_12532_amd import synth
 from tests import parity, test_gpu_decode, test_gpu_layer
+from tests.routes import COUNTED, EQUAL, PLACES, SEQ_PER_XCD, route
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -79,28 +80,35 @@ def _spread(n, lo, hi, seed):
     return tuple(int(x) for x in np.random.default_rng(seed).integers(lo, hi + 1, size=n))
 
 
-@pytest.mark.parametrize("lens,Hq,Hkv,d,w", [
-    ((900,) * 7, 4, 4, 64, 32),                                 # as many ranges in every sequence, not a multiple of the XCDs
-    ((380, 370, 384, 361), 4, 2, 128, 16),                      # ... of lengths that differ
-    ((0, 700, 0, 0, 33, 1), 4, 2, 128, 32),                     # counted by the workgroup: empty sequences in front and between
-    (_spread(64, 1, 400, 1), 2, 2, 64, 16),                     # one round of the count
-    (_spread(65, 1, 400, 2) + (0,), 2, 1, 128, 16),             # two
-    (_spread(255, 0, 300, 3) + (600,), 2, 2, 64, 16),           # four, the last sequence the longest
-    (_spread(257, 0, 300, 4), 2, 2, 64, 16),                    # places for every sequence
-    (_spread(129, 1, 250, 5), 2, 2, 128, 16),                   # ... more than 128 short ones
-    ((700,) * 7, 2, 2, 64, 400),                                # half a sequence in the window: each starts at another range
-    ((520,) * 16, 2, 1, 128, 300),                              # ... on one XCD each
-])
-def test_order_of_the_ranges(lib, lens, Hq, Hkv, d, w):
+ORDERS = [
+    ((900,) * 7, 4, 4, 64, 32, EQUAL),                          # as many ranges in every sequence, not a multiple of the XCDs
+    ((380, 370, 384, 361), 4, 2, 128, 16, EQUAL),               # ... of lengths that differ
+    ((0, 700, 0, 0, 33, 1), 4, 2, 128, 32, COUNTED),            # counted by the workgroup: empty sequences in front and between
+    (_spread(64, 1, 400, 1), 2, 2, 64, 16, COUNTED),            # one round of the count
+    (_spread(65, 1, 400, 2) + (0,), 2, 1, 128, 16, COUNTED),    # two
+    (_spread(255, 0, 300, 3) + (600,), 2, 2, 64, 16, COUNTED),  # four, the last sequence the longest
+    (_spread(257, 0, 300, 4), 2, 2, 64, 16, PLACES),            # places for every sequence
+    (_spread(129, 1, 250, 5), 2, 2, 128, 16, PLACES),           # ... more than 128 short ones
+    ((700,) * 7, 2, 2, 64, 400, EQUAL),                         # half a sequence in the window: each starts at another range
+    ((520,) * 16, 2, 1, 128, 300, SEQ_PER_XCD),                 # ... on one XCD each
+]
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w,order", ORDERS)
+def test_order_of_the_ranges(lib, lens, Hq, Hkv, d, w, order):
     """Every range is taken by exactly one workgroup, whichever way the grid is laid out: scores of the prefill step, and of the
     cache update, whose statistics walk is laid out the same way."""
+    assert route(lib, lens, Hq, Hkv, d, w).score_order == order
     wl = _wl(lens, Hq, Hkv, d, w)
     for run in (test_gpu_layer.run_and_check, test_gpu_decode.run_and_check):
         res, ref, _ = run(lib, wl)
         np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
 
 
-@pytest.mark.parametrize("S", [1, 64, 256, 257, 512, 513, 2100])
+FOLDS = (1, 64, 256, 257, 512, 513, 2100)
+
+
+@pytest.mark.parametrize("S", FOLDS)
 def test_fold_of_the_statistics(lib, S):
     """Ranges of 64 keys, the smallest the statistics walk takes and what it takes for one short cache: one lane folds a row of up
     to four of them, eight lanes share it from five on, and each has several from nine on."""

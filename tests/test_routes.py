@@ -1,0 +1,51 @@
+"""The batches of the GPU tests get the kernels those tests are for on an MI355X (host only: pyr_diag_route)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+from paper_2405_12532_amd import binding
+from tests import test_gpu_attention_kernels as att, test_gpu_score_ranges as ranges
+from tests.routes import COUNTED, EQUAL, LISTS, MI355X, ONE_GROUP, PLACES, SEQ_PER_XCD, TWO_GROUPS, route
+
+
+def _kernel(lens, Hq, Hkv, d):
+    return route(binding, lens, Hq, Hkv, d, **MI355X)
+
+
+def test_attention_kernels():
+    for lens, d in att.TWO_GROUP_EDGES:
+        assert _kernel(lens, 4, 2, d).attention == TWO_GROUPS, (lens, d)
+    for batch in att.ONE_GROUP_EDGES:
+        assert _kernel(*batch).attention == ONE_GROUP, batch
+    for *batch, kernel in att.TILE_BATCHES + att.MASKED_BATCHES:
+        assert _kernel(*batch).attention == kernel, batch
+    for lens, Hq, Hkv in att.LONG_BATCHES:
+        r = _kernel(lens, Hq, Hkv, 128)
+        assert r.attention == LISTS and (r.attention_items > att.TABLE) == (len(lens) > 600), (len(lens), r.attention_items)
+    for lens, Hq, d, kernel in att.RENEWAL_BATCHES:
+        assert _kernel(lens, Hq, Hq, d).attention == kernel, (lens, Hq, d)
+    for batch in att.LISTED_BATCHES:
+        assert _kernel(*batch).attention_listed == 1, batch[1:]
+
+
+def test_score_walks():
+    for lens, Hq, Hkv, d, w, order in ranges.ORDERS:
+        assert route(binding, lens, Hq, Hkv, d, w, **MI355X).score_order == order, (len(lens), d, w)
+    folds = [-(-S // (32 * route(binding, (S,), 4, 2, 128, 40, **MI355X).stats_tiles)) for S in ranges.FOLDS]
+    assert folds == [1, 1, 4, 5, 8, 9, 33], folds
+
+
+def test_route_arguments():
+    off = torch.tensor([0, 100], dtype=torch.int32)
+    shape = binding.make_shape(1, 100, 100, 4, 2, 64)
+    assert binding.diag_route(shape, off, 16, 256, 8).score_groups >= 1
+    for args in ((shape, off, 0, 256, 8), (shape, off, 16, 256, 0), (shape, off, 16, -1, 8)):
+        with pytest.raises(binding.PyrError):
+            binding.diag_route(*args)
+    lib = binding.load()
+    assert lib.pyr_diag_route(ctypes.byref(shape), off.data_ptr(), 16, 256, 8, None) == -1
+    assert lib.pyr_diag_route(ctypes.byref(shape), None, 16, 256, 8, ctypes.byref(binding.PyrRoute())) == -1
+    empty = binding.make_shape(0, 0, 0, 4, 2, 64)
+    assert binding.diag_route(empty, torch.zeros(1, dtype=torch.int32), 16, 256, 8).score_tiles == 0
