@@ -50,10 +50,15 @@ def test_decode_long_cache(lib):
     np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
 
 
+LOOSE = ((64,) * 64, 32, 64, 16)
+
+
 def test_loose_max_seqlen(lib):
-    """A caller whose max_seqlen is far above the longest sequence gets no more workspace than it asked for: the score pass may not
-    split itself into partial sums there.  The guard behind the workspace stays as it was."""
-    lens, H, d, w = (64,) * 64, 8, 64, 16
+    """A caller whose max_seqlen is far above the longest sequence gets no more workspace than it asked for: the score pass, which does
+    split this batch into partial sums where there is room for them, may not do so there.  The guard behind the workspace stays
+    as it was."""
+    lens, H, d, w = LOOSE
+    assert route(lib, lens, H, H, d, w).score_groups > 1
     wl = _wl(lens, H, H, d, w)
     x = parity.inputs(wl, lib, want_hidden=False)
     q, k, v = (lib.to_device_bf16(x[n]) for n in ("q", "k", "v"))
@@ -72,6 +77,8 @@ def test_loose_max_seqlen(lib):
         lib.prefill_layer(q, k, v, off_d, off_h, shape, w, 0.0, keep_d, keep_h, out, scores, kept, out_off, None, None, ws, ws_bytes)
         torch.cuda.synchronize()
         assert bool((ws[ws_bytes:] == 0x5A).all())
+        parts = ws_bytes - 4 * 16 * T                      # (where the partial sums begin, if there is room for them)
+        assert claimed == T or bool((ws[parts:ws_bytes] != 0x5A).any())
         results.append(scores.cpu().numpy())
     np.testing.assert_allclose(results[0], results[1], rtol=2e-6, atol=1e-12)
 

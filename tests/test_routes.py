@@ -35,6 +35,8 @@ def test_score_walks():
         assert route(binding, lens, Hq, Hkv, d, w, **MI355X).score_order == order, (len(lens), d, w)
     folds = [-(-S // (32 * route(binding, (S,), 4, 2, 128, 40, **MI355X).stats_tiles)) for S in ranges.FOLDS]
     assert folds == [1, 1, 4, 5, 8, 9, 33], folds
+    lens, H, d, w = ranges.LOOSE
+    assert route(binding, lens, H, H, d, w, **MI355X).score_groups > 1
 
 
 def test_route_arguments():
