@@ -779,17 +779,22 @@ int list_count(const pyr_shape& s, const DeviceInfo& dev) {
 // A move that the balance does not need costs (4 x 3233 on 64/8 heads 642 us without, 666 with one of one place; 10 x 6400 on
 // 16/2 1507 and 1577).
 // Ragged batches keep the plain stride: their items differ from sequence to sequence anyway.
-int pick_turn(int32_t uniform_len, int group, int slots, int32_t items_per_xcd) {
-    const int tiles = (uniform_len + kBM - 1) / kBM;
-    if (uniform_len == 0 || tiles == 1 || tiles % 2 == 0) return 0;
+struct Turn {
+    int turn;
+    double most;      // tiles of the fullest workgroup
+};
+
+Turn pick_turn(int32_t uniform_len, int group, int slots, int64_t items_per_xcd) {
     constexpr int kMaxTurn = 3, kMaxRounds = 64, kMaxSlots = 1024;
-    if (slots > kMaxSlots) return 0;
+    const int tiles = (uniform_len + kBM - 1) / kBM;
+    const int64_t rounds = (items_per_xcd + slots - 1) / slots;
+    if (tiles == 1 || tiles % 2 == 0 || slots > kMaxSlots) return Turn{0, (double)rounds * (tiles == 1 ? 1 : 2)};
     const int n_items = items_of(uniform_len), period = n_items * group, middle = (n_items - 1) * group;      // places of the single tiles in a period
     int best = 0, least = 0x7fffffff;
     for (int turn = 0; turn <= kMaxTurn; ++turn) {
         int load[kMaxSlots] = {}, most = 0;
         int first = 0, place0 = 0;                    // item at place 0 of the round, modulo the period; workgroup there
-        for (int32_t round = 0; round < kMaxRounds && (int64_t)round * slots < items_per_xcd; ++round) {
+        for (int round = 0; round < kMaxRounds && round < rounds; ++round) {
             const int64_t left = items_per_xcd - (int64_t)round * slots;
             const int here = left < slots ? (int)left : slots;
             for (int place = 0, kind = first, wg = place0; place < here; ++place) {
@@ -806,12 +811,12 @@ int pick_turn(int32_t uniform_len, int group, int slots, int32_t items_per_xcd) 
             best = turn;
         }
     }
-    return best;
+    return Turn{best, rounds > kMaxRounds ? (double)least * rounds / kMaxRounds : (double)least};
 }
 
 int launch_attention_long(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev,
                           const int32_t* seq_offsets_host, const pyr_shape& s, int32_t uniform_len, float c,
-                          void* out, float* lse, int32_t* item_map, const DeviceInfo& dev, hipStream_t stream) {
+                          void* out, float* lse, int32_t* item_map, int turn, const DeviceInfo& dev, hipStream_t stream) {
     static std::atomic<uint64_t> lds_set{0};
     if (ensure_dynamic_lds((const void*)attention_kernel, (int)Tile::kLdsBytes, &lds_set) != PYR_OK) return PYR_ERR_LAUNCH;
     long long total_items = 0;                       // work items per query head
@@ -826,7 +831,6 @@ int launch_attention_long(const void* q, const void* k, const void* v, const int
     const int32_t items_per_xcd = (int32_t)(total_items * s.n_q_heads / xcds);
     long long slots = dev.compute_units / xcds;      // persistent workgroups, one per compute unit
     if (slots > items_per_xcd) slots = items_per_xcd;
-    const int turn = pick_turn(uniform_len, s.n_q_heads / s.n_kv_heads, (int)slots, items_per_xcd);
     hipLaunchKernelGGL(attention_kernel, dim3((unsigned)(slots * xcds)), dim3(kNW * 64), Tile::kLdsBytes, stream,
                        (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, seq_offsets_dev,
                        (const int32_t*)item_map, s.n_seqs, s.n_q_heads, s.n_kv_heads, uniform_len, xcds,
@@ -835,21 +839,27 @@ int launch_attention_long(const void* q, const void* k, const void* v, const int
 }
 
 // Which kernel: 0 the one above, 1 or 2 attention_tile.hip with one or two groups per workgroup.  Each gets an estimate in
-// microseconds from what was measured: the work of all compute units (a per step of 64 keys, b per tile), the longest
-// chain of steps a workgroup runs and, for the kernel above on a ragged batch, the longest of its lists.  The constants at
-// d = 128 come from batches of 64 x 202 ... 64 x 2048 on 32/32 heads and 16 x 300 on 64/8 (1.635 per 256-row step, 6.1 per
-// tile; 1.755 for a 128-row step of two workgroups side by side, 7.4 per 128 rows, whose traffic that is: less with grouped
-// heads) and single prompts of 300 ... 2048 tokens (1.42 per step of a wavefront that has its SIMD to itself, 2.1 with the
-// second group beside it); those at d = 64 from 64 x 500 and 64 x 2048 and prompts of 900 ... 2500 tokens.
-// Measured, this kernel / one group / two groups (us): 64 x 2048 2330 / 2392 / 2889, 64 x 700 416 / 432 / 544,
-// 64 x 359 189 / 173 / 223, 1 x 2048 57 / 48 / 43, 4 x 512 29 / 20 / 24; ragged: 30 sequences of 100...700 122 / 97 / 131,
-// 32 of 512...8192 on 40 heads 6530 / 6630 / 7470, 32768 and 255 x 64 7240 / 8280 / 8960, 8192 and 500 x 100 850 / 840 / 1050;
-// heads that do not divide over the XCDs: 1 x 8192 on 32/4 heads 471 / 513 / 566, on 20/20 415 / 349 / 365.
-// d = 64: 64 x 2048 1550 / 1340 / 1770, 2 x 2500 on 8 heads 54 / 34 / 26 - there this kernel never wins and is not built.
-int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, const DeviceInfo& dev) {
+// microseconds: the work of all compute units (a per step of 64 keys, b per tile and per 128 rows, whose traffic is less with grouped
+// heads; a last tile of few rows leaves its other wavefronts' share of the matrix pipes to the workgroups beside it), the longest
+// chain of steps a workgroup runs and, for the kernel above, what the fullest of its lists holds.  The constants at d = 128
+// are fitted to the three kernels' times, taken in turn, on 2028 batches (15 head shapes, one sequence of 60 tokens to
+// 4 x 12000 and 200 x 655, equal and ragged lengths): the kernel chosen takes 0.4 % longer than the best one in the mean, at most
+// 2.7 % in 95 of 100 batches (worst for many sequences of 650 ... 720 or 870 ... 890 tokens, up to 15 %: 97 x 651 565 with lists, 644
+// as chosen, 148 x 885 on 40 heads 1718 with one group, 1979; 350 sequences of 1300 ... 1500 on 8 heads 1794 with lists, 1885).  Single
+// chains: 1.42 per step of a wavefront that has its SIMD to itself, 2.1 with the second group beside it; the constants at d = 64
+// come from 64 x 500 and 64 x 2048 and prompts of 900 ... 2500 tokens.
+// Measured, this kernel / one group / two groups (us): 64 x 2048 2330 / 2392 / 2889, 64 x 700 409 / 441 / 544,
+// 64 x 359 189 / 173 / 223, 16 x 1008 on 64/8 heads 335 / 362 / 460, 25 x 5242 on 16/2 2716 / 2948 / 3213, 18 x 815 on 32/8
+// 177 / 153 / 196, 1 x 2048 57 / 48 / 42, 4 x 512 29 / 20 / 24; ragged: 30 sequences of 100...700 122 / 97 / 131, 32 of 512...8192 on 40
+// heads 6530 / 6630 / 7470, 32768 and 255 x 64 7240 / 8280 / 8960, 8192 and 500 x 100 850 / 840 / 1050; heads that do not divide over the
+// XCDs: 1 x 8192 on 32/4 heads 471 / 513 / 566, on 20/20 415 / 349 / 365.  d = 64: 64 x 2048 1550 / 1340 / 1770, 2 x 2500 on 8 heads
+// 54 / 34 / 26 - there this kernel never wins and is not built.
+// turn_out: of the kernel above, where it is chosen.
+int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, const DeviceInfo& dev, int* turn_out) {
+    *turn_out = 0;
     const double kv_share = 1.0 + (double)s.n_kv_heads / s.n_q_heads;      // rows a query row's traffic comes with
     const double cus = dev.compute_units;
-    double work0 = 0, work1 = 0, work2 = 0, items = 0;
+    double work0 = 0, work1 = 0, work2 = 0;
     int max_len = 0;
     // the lists of the kernel above, if they differ: what each has, as differences from one to the next
     constexpr int kMaxSlots = 1024;
@@ -859,7 +869,8 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
     if (uniform_len == 0) std::fill(more, more + slots + 1, 0.0);
     double all_lists = 0;
     int turn = 0;
-    const double a1 = s.head_dim == 128 ? 1.755 : 1.437, b1 = s.head_dim == 128 ? 0.38 + 3.49 * kv_share : 3.95 + 1.4 * kv_share;
+    const double a1 = s.head_dim == 128 ? 1.69 : 1.437, b1 = s.head_dim == 128 ? 0.43 + 3.43 * kv_share : 3.95 + 1.4 * kv_share;
+    const double tile1 = s.head_dim == 128 ? 0.3 : 0.0, last1 = s.head_dim == 128 ? 0.43 : 1.0;       // last1: of a last tile's steps, whatever its rows
     const double a2 = s.head_dim == 128 ? 2.1 : 1.2, b2 = s.head_dim == 128 ? 5.0 : 3.0;
     const int32_t n = uniform_len > 0 ? 1 : s.n_seqs;                      // (equal sequences: one stands for all)
     for (int32_t i = 0; i < n; ++i) {
@@ -868,7 +879,7 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
         if (len > max_len) max_len = len;
         const double steps = (len + 63) / 64, n0 = (len + 255) / 256, n1 = (len + 127) / 128;
         const double last_rows = (len - 256 * (n0 - 1) + 31) / 32;         // 32-row blocks of the last 256-row tile
-        const double seq0 = 1.635 * (2 * n0 * (n0 - 1) + steps * floor(last_rows) / 8) + (3.8 + 1.15 * kv_share) * n0;
+        const double seq0 = 1.37 * (2 * n0 * (n0 - 1) + steps * floor(last_rows) / 8) + (3.86 + 1.79 * kv_share) * n0;
         work0 += seq0;
         if (uniform_len == 0) {                                            // its items go to the lists in turn
             const int64_t n = (int64_t)items_of(len) * s.n_q_heads / xcds;
@@ -880,9 +891,10 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
             if (end >= slots) { more[0] += item; more[end - slots] -= item; }
             turn = end % slots;
         }
-        work1 += (len > 8192 ? 1.06 : 1.0) * a1 * (n1 * (n1 - 1) + steps) + b1 * len / 128;       // (K/V of one head then exceed an L2)
+        const double part = (len - 128 * ((len + 127) / 128 - 1) + 31) / 32 / 4.0;                // wavefronts at work in the last 128-row tile
+        work1 += (len > 8192 ? 1.06 : 1.0) * a1 * (n1 * (n1 - 1) + steps * (last1 + (1.0 - last1) * part)) +      // (K/V of one head then exceed an L2)
+                 b1 * len / 128 + tile1 * n1;
         work2 += a2 * (n1 * (n1 - 1) + steps + n1) / 2 + b2 * n1;
-        items += items_of(len);
     }
     if (max_len == 0) return 0;
     const double heads = (double)s.n_q_heads * (uniform_len > 0 ? s.n_seqs : 1);
@@ -890,12 +902,18 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
     const double per_cu = s.head_dim == 128 ? 2 : 3;                       // workgroups of one group a compute unit holds
     const double chain1 = s.head_dim == 128 ? 1.42 * steps + 2.5 : 0.79 * steps + 3.4;
     const double chain2 = s.head_dim == 128 ? 2.1 * ceil(steps / 2) + 4.0 : 1.2 * ceil(steps / 2) + 2.7;
-    const double ragged = uniform_len > 0 ? 1.0 : 1.05;                    // (measured: tiles of unequal length share fewer K/V rows)
-    const double t1 = fmax(ragged * work1 * heads / (per_cu * cus), chain1), t2 = fmax(ragged * work2 * heads / cus, chain2);
+    // (tiles of unequal length share fewer K/V rows, but fill each other's gaps)
+    const double ragged1 = uniform_len > 0 ? 1.0 : s.head_dim == 128 ? 0.925 : 1.05, ragged2 = uniform_len > 0 ? 1.0 : 1.05;
+    const double t1 = fmax(ragged1 * work1 * heads / (per_cu * cus), chain1), t2 = fmax(ragged2 * work2 * heads / cus, chain2);
     if (s.head_dim != 128) return t2 < t1 ? 2 : 1;
-    const double rounds = items * heads / cus, item = 1.635 * (steps + 4) + 12.2;       // the longest item: first and last tile
-    double t0 = fmax(work0 * heads / cus * (1.0 + 0.5 * (ceil(rounds) / rounds - 1.0)), item);
-    if (uniform_len == 0) {                                                // the longest list, and the item map's launch
+    const double item = 1.37 * (steps + 4) + 12.2;                         // the longest item: first and last tile
+    double t0;
+    if (uniform_len > 0) {
+        const int64_t list = (int64_t)s.n_seqs * items_of(max_len) * s.n_q_heads / xcds;
+        const Turn turns = pick_turn(uniform_len, s.n_q_heads / s.n_kv_heads, list < slots ? (int)list : slots, list);
+        *turn_out = turns.turn;
+        t0 = fmax(work0 / ((max_len + kBM - 1) / kBM) * turns.most, item);
+    } else {                                                               // the longest list, and the item map's launch
         double run = 0, most = 0;
         for (int i = 0; i < slots; ++i) {
             run += more[i];
@@ -904,14 +922,15 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
         t0 = fmax(all_lists + most, item) + 2.0;
     }
     t0 += 3.0;
-    if (s.n_kv_heads % dev.xccs != 0) t0 *= 0.85 + 0.15 * kv_share;        // one list for all XCDs: K/V rows in every L2
-    return t0 < t1 + 0.05 * chain1 && t0 < t2 ? 0 : t2 < t1 ? 2 : 1;         // (the last tiles of one group's grid run out unevenly)
+    if (s.n_kv_heads % dev.xccs != 0) t0 *= 0.865 + 0.09 * kv_share;       // one list for all XCDs
+    return t0 < t1 + 0.054 * chain1 && t0 < t2 ? 0 : t2 < t1 ? 2 : 1;        // (the last tiles of one group's grid run out unevenly)
 }
 
 }  // namespace
 
 void attention_route(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t uniform_len, const DeviceInfo& dev, pyr_route* out) {
-    out->attention = pick_kernel(s, seq_offsets_host, uniform_len, dev);
+    int turn = 0;
+    out->attention = pick_kernel(s, seq_offsets_host, uniform_len, dev, &turn);
     if (out->attention != 0) {
         out->attention_listed = attention_tile_listed(s, seq_offsets_host, uniform_len) ? 1 : 0;
         return;
@@ -928,10 +947,11 @@ int launch_attention(const void* q, const void* k, const void* v, const int32_t*
                      void* out, float* lse, int32_t* item_map, hipStream_t stream) {
     DeviceInfo dev;
     if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
-    const int which = pick_kernel(shape, seq_offsets_host, uniform_len, dev);
+    int turn = 0;
+    const int which = pick_kernel(shape, seq_offsets_host, uniform_len, dev, &turn);
     if (which == 0)
-        return launch_attention_long(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2, out, lse, item_map, dev,
-                                     stream);
+        return launch_attention_long(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2, out, lse, item_map, turn,
+                                     dev, stream);
     return launch_attention_tile(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2, out, lse, item_map, which,
                                  stream);
 }

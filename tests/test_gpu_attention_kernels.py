@@ -111,7 +111,7 @@ LONG_BATCHES = [
     ([4096], 32, 32),
     ([6000, 5000, 300, 8000, 200, 0, 1], 32, 8),    # ragged, sequences of one tile and of none
     ([1500] * 700, 8, 8),                      # more than 64 items per workgroup: its table of items is moved along
-    ([1300, 1500] * 350, 8, 8),                # ... of a ragged batch
+    ([1792, 1536] * 350, 8, 8),                # ... of a ragged batch
 ]
 TABLE = 64                                     # items a workgroup's table holds
 
@@ -123,7 +123,7 @@ def test_long_tile_kernel(lib, lens, Hq, Hkv):
     _check(lib, lens, Hq, Hkv, 128, every=max(1, len(lens) // 30))
 
 
-RENEWAL_BATCHES = [((1024,) * 16, 16, 128, LISTS), ((800,), 4, 128, TWO_GROUPS), ((300,) * 60, 8, 64, ONE_GROUP), ((1024,) * 4, 32, 128, ONE_GROUP)]
+RENEWAL_BATCHES = [((1024,) * 16, 16, 128, LISTS), ((800,), 4, 128, TWO_GROUPS), ((300,) * 60, 8, 64, ONE_GROUP), ((1024,) * 3, 32, 128, ONE_GROUP)]
 
 
 @pytest.mark.parametrize("kind", ["ramp", "low_start", "low_start_overflow"])
