@@ -334,8 +334,8 @@ typedef struct pyr_route {
     int32_t attention_listed;   /* attention != 0: 1 if the grid is a list of the tiles that exist, else 0 */
     int32_t score_tiles, score_waves, score_groups;     /* prefill score pass: 32-key tiles of a range, wavefronts, split */
     int32_t score_order;        /* 0: a sequence per XCD, 1: equally many ranges, 2: counted, 3: places for the longest sequence */
-    int32_t stats_tiles, stats_waves, stats_groups;     /* the same of the generation phase's statistics ... */
-    int32_t window_tiles, window_waves, window_groups;  /* ... and of its score pass */
+    int32_t stats_tiles, stats_waves, stats_groups;     /* the same of the generation phase's statistics (waves == 0: one pass does both) ... */
+    int32_t window_tiles, window_waves, window_groups;  /* ... and of its score pass (or of the one pass: tiles per wavefront) */
 } pyr_route;
 PYR_API int pyr_diag_route(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t w, int32_t compute_units,
                            int32_t xcds, pyr_route* route_out);

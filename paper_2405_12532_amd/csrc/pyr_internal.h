@@ -76,6 +76,18 @@ int launch_window_score(const void* q_win, const void* k, const int32_t* seq_off
                         const pyr_shape& shape, int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights, float* lse_win, void* part,
                         float* scores, int* groups, hipStream_t stream);
 
+// The same in one launch, where every sequence is short enough for a workgroup to keep its logits (window.hip): workgroups of `waves`
+// wavefronts, a sequence's tasks spread over `groups` of them, each with a row of partial sums.  waves == 0: not for this batch.
+// tiles: 32-key tiles of the batch.  launch_window writes sums [groups, total_tokens] (the scores themselves if groups == 1).
+struct WindowPlan {
+    int waves, groups;
+    double cost;                  // microseconds, selection included
+};
+WindowPlan plan_window(const pyr_shape& shape, double tiles, int32_t w, int max_groups, const DeviceInfo& dev);
+int launch_window(const void* q, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& shape, bool equal, int32_t w,
+                  int32_t q_window, float scale_log2, const float* row_weights, float* sums, const WindowPlan& plan, const DeviceInfo& dev,
+                  hipStream_t stream);
+
 int launch_gather_positions(const int32_t* pos, const int32_t* kept_idx, int64_t n_kept, int32_t* pos_out,
                             hipStream_t stream);
 

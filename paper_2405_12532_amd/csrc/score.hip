@@ -39,7 +39,7 @@
 #include <float.h>
 #include <math.h>
 
-#include "pyr_internal.h"
+#include "score_device.h"
 
 namespace pyr {
 namespace {
@@ -67,9 +67,6 @@ enum Order {
 constexpr int kMaxPackedSeqs = 256, kMaxPackedShortSeqs = 128, kShortLen = 256;
 constexpr int kEnginesPerXcd = 4;
 
-typedef __attribute__((address_space(3))) char* lptr_t;
-typedef __attribute__((address_space(3))) float* lfloat_t;
-
 struct StripArgs {
     const uint16_t* q;
     const uint16_t* k;
@@ -85,27 +82,6 @@ struct StripArgs {
     int32_t total_tokens;
     float2* part;                             // kStats: [range, sequence, query head, window slot]
 };
-
-// 64 lanes x 16 bytes (or x 4 bytes) from base + voff[lane] to LDS at lds_addr + 16 (4) * lane.
-// Assembly because the wavefront orders these loads itself with s_waitcnt vmcnt(N); they
-// retire in the order issued.
-__device__ __forceinline__ void lds_dma(const char* base_, uint32_t voff, uint32_t lds_addr, bool dword) {
-    const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_addr);
-    const uint64_t b64 = (uint64_t)(uintptr_t)base_;         // wave-uniform by construction: keep it in scalar registers
-    const uint32_t b_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b64);          // (the builtin returns a signed int:
-    const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b64 >> 32));  //  widen it unsigned)
-    const char* base = (const char*)(uintptr_t)(((uint64_t)b_hi << 32) | (uint64_t)b_lo);
-    if (dword)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(m0), "v"(voff), "s"(base) : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0), "v"(voff), "s"(base) : "memory", "m0");
-}
-
-template <int N>
-__device__ __forceinline__ void wait_loads() {      // until at most N of this wavefront's loads are outstanding
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 template <int D>
 constexpr int wave_lds_bytes(int range_tiles) { return kSlots * 32 * D * 2 + 2 * kRowArea + 256 * range_tiles; }
@@ -574,6 +550,7 @@ BatchCut cut_batch(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t 
 // How a walk over K is cut up.
 struct StripPlan {
     int range_tiles, waves, groups;
+    double cost;                 // microseconds
 };
 
 // The cut with the lowest cost, in microseconds, of two limits joined smoothly (the fourth root of the sum of fourth powers):
@@ -602,8 +579,7 @@ StripPlan plan_strip(const pyr_shape& s, const BatchCut& cut, int32_t w, const D
     const double shared = d64 ? 0.21 + 0.082 * task_blocks : 0.48;
     const int engines = kEnginesPerXcd * dev.xccs, engine_cus = dev.compute_units > engines ? dev.compute_units / engines : 1;
     const double per_row = partial_sums ? 0.1 + 5e-5 * s.max_seqlen : 0.0;
-    StripPlan best{1, 1, 1};
-    double best_cost = 1e300;
+    StripPlan best{1, 1, 1, 1e300};
     for (int nt = kMaxRangeTiles; nt >= 1; --nt) {
         if (nt < min_range_tiles && nt < max_tiles) continue;
         const int64_t ranges_per_seq = (max_tiles + nt - 1) / nt, places = s.n_seqs * ranges_per_seq;
@@ -629,10 +605,7 @@ StripPlan plan_strip(const pyr_shape& s, const BatchCut& cut, int32_t w, const D
                                      (rest == 0 ? 0.0 : 1.9 + steps * (last > alone ? last : alone));
                 const double flow = stream * (1.0 + 0.1 * ((double)per_cu * engine_cus / queue - 1.0));
                 const double cost = sqrt(sqrt(chain * chain * chain * chain + flow * flow * flow * flow)) * padding + per_row * (g - 1);
-                if (cost < best_cost) {
-                    best_cost = cost;
-                    best = StripPlan{nt, waves, g};
-                }
+                if (cost < best.cost) best = StripPlan{nt, waves, g, cost};
             }
         }
     }
@@ -705,12 +678,8 @@ int launch_strip(const void* q, const void* k, const float* lse, const int32_t* 
 }
 
 int launch_scores(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
-                  const pyr_shape& s, int32_t min_seqlen, const BatchCut& cut, int32_t w, int32_t q_window, float scale_log2,
-                  const float* row_weights, float* scores, float* parts, int max_groups, int* groups, hipStream_t stream) {
-    DeviceInfo dev;
-    if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
-    const StripPlan plan = plan_strip(s, cut, w, dev, 1, max_groups, true);
-    *groups = plan.groups;
+                  const pyr_shape& s, int32_t min_seqlen, int32_t w, int32_t q_window, float scale_log2, const float* row_weights, float* scores,
+                  float* parts, const StripPlan& plan, const DeviceInfo& dev, hipStream_t stream) {
     float* sums = plan.groups > 1 ? parts : scores;
     return row_weights ? launch_strip<kScoresWeighted>(q, k, lse, seq_offsets_dev, seq_offsets_host, s, min_seqlen, w, q_window,
                                                        scale_log2, row_weights, sums, nullptr, plan, dev, stream)
@@ -724,9 +693,11 @@ int launch_score(const void* q, const void* k, const float* lse, const int32_t* 
                  const pyr_shape& s, int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights,
                  float* scores, hipStream_t stream) {
     if (s.n_seqs == 0 || s.max_seqlen == 0) return PYR_OK;
-    int groups = 1;
-    return launch_scores(q, k, lse, seq_offsets_dev, seq_offsets_host, s, min_seqlen, cut_batch(s, seq_offsets_host, min_seqlen), w, 0,
-                         scale_log2, row_weights, scores, nullptr, 1, &groups, stream);
+    DeviceInfo dev;
+    if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
+    const StripPlan plan = plan_strip(s, cut_batch(s, seq_offsets_host, min_seqlen), w, dev, 1, 1, true);
+    return launch_scores(q, k, lse, seq_offsets_dev, seq_offsets_host, s, min_seqlen, w, 0, scale_log2, row_weights, scores, nullptr, plan, dev,
+                         stream);
 }
 
 // (A prefill step only has room for partial sums where the batch has fewer than 1024 blocks of 64 keys: beyond that its ranges fill
@@ -741,34 +712,57 @@ int launch_score_groups(const void* q, const void* k, const float* lse, const in
                         float* scores, float* parts, int* groups, hipStream_t stream) {
     *groups = 1;
     if (s.n_seqs == 0 || s.max_seqlen == 0) return PYR_OK;
-    return launch_scores(q, k, lse, seq_offsets_dev, seq_offsets_host, s, min_seqlen, cut_batch(s, seq_offsets_host, min_seqlen), w, 0,
-                         scale_log2, row_weights, scores, parts, parts != nullptr ? kMaxScoreGroups : 1, groups, stream);
+    DeviceInfo dev;
+    if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
+    const StripPlan plan = plan_strip(s, cut_batch(s, seq_offsets_host, min_seqlen), w, dev, 1, parts != nullptr ? kMaxScoreGroups : 1, true);
+    *groups = plan.groups;
+    return launch_scores(q, k, lse, seq_offsets_dev, seq_offsets_host, s, min_seqlen, w, 0, scale_log2, row_weights, scores, parts, plan, dev,
+                         stream);
 }
 
-// Partial sums of the generation phase's score pass: the statistics are dead once folded, their space takes as many as fit.
-static int window_score_groups(const pyr_shape& s, int32_t w) {
-    int most = 1;
-    while (most < kMaxScoreGroups && 2 * (size_t)most * s.total_tokens * sizeof(float) <= window_score_part_bytes(s, w)) most *= 2;
-    return most;
+// How the generation phase gets its scores: by one walk over K (window.hip), or by two with the denominators folded between them.
+struct UpdatePlan {
+    bool one_walk;
+    WindowPlan window;
+    StripPlan stats, scores;
+};
+
+// Partial sums of the scores go where the statistics lie, which are dead once folded: as many rows as fit.
+// One walk reads K once and is one launch where two walks are three, but it has the window's rows in blocks of 32 and its loads go by once
+// per block: it wins where row blocks per KV head are few or sequences short.  Measured, two walks / one walk with the selection (us): 88 x
+// 692, 64 heads, w = 64 410 / 253, 22 of 286...914, 32 heads, w = 32 61 / 34, 5 x 199, 16/2 heads, d = 64 19.5 / 12.8; but 23 of
+// 1243...1911, 32/8 heads, w = 64 89 / 104, 33 x 807, 24 heads, w = 256 173 / 207, 1 x 1782, 64 heads, w = 128 35 / 47.  Both costs
+// are predicted (the two walks' with the fold and the selection, to 10 %) and one walk is taken where it is a tenth lower: over 270 calls
+// that takes 18 % off in the mean, where the better one of both would take 19 %, and leaves three slower, by 5, 8 and 17 %.
+UpdatePlan plan_update(const pyr_shape& s, const BatchCut& cut, int32_t w, const DeviceInfo& dev) {
+    UpdatePlan p{};
+    const size_t room = window_score_part_bytes(s, w), row = (size_t)s.total_tokens * sizeof(float);
+    int split = 1;
+    while (split < kMaxScoreGroups && 2 * (size_t)split * row <= room) split *= 2;
+    p.stats = plan_strip(s, cut, w, dev, 2, kMaxScoreGroups, false);
+    p.scores = plan_strip(s, cut, w, dev, 1, split, true);
+    p.window = plan_window(s, cut.tiles, w, room / row < 1 ? 1 : room / row > 256 ? 256 : (int)(room / row), dev);
+    const double folded = (double)s.n_seqs * w * s.n_q_heads * ((s.max_seqlen + 63) / 64);
+    p.one_walk = p.window.waves > 0 && p.window.cost < 0.9 * (11.5 + 1.16 * p.stats.cost + 0.86 * p.scores.cost + 7.6e-6 * folded);
+    return p;
 }
 
 void score_route(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, bool parts, const DeviceInfo& dev,
                  pyr_route* out) {
     const BatchCut cut = cut_batch(s, seq_offsets_host, min_seqlen);
     const StripPlan score = plan_strip(s, cut, w, dev, 1, parts ? kMaxScoreGroups : 1, true);
-    const StripPlan stats = plan_strip(s, cut, w, dev, 2, kMaxScoreGroups, false);
-    const StripPlan window = plan_strip(s, cut, w, dev, 1, window_score_groups(s, w), true);
+    const UpdatePlan update = plan_update(s, cut, w, dev);
     out->score_tiles = score.range_tiles;
     out->score_waves = score.waves;
     out->score_groups = score.groups;
     out->score_order = pick_order(s, cut.equal, count_ranges(seq_offsets_host, s.n_seqs, 32 * score.range_tiles),
                                   ((s.max_seqlen + 31) / 32 + score.range_tiles - 1) / score.range_tiles, dev.xccs);
-    out->stats_tiles = stats.range_tiles;
-    out->stats_waves = stats.waves;
-    out->stats_groups = stats.groups;
-    out->window_tiles = window.range_tiles;
-    out->window_waves = window.waves;
-    out->window_groups = window.groups;
+    out->stats_tiles = update.stats.range_tiles;
+    out->stats_waves = update.one_walk ? 0 : update.stats.waves;
+    out->stats_groups = update.stats.groups;
+    out->window_tiles = update.one_walk ? ((s.max_seqlen + 31) / 32 + update.window.waves - 1) / update.window.waves : update.scores.range_tiles;
+    out->window_waves = update.one_walk ? update.window.waves : update.scores.waves;
+    out->window_groups = update.one_walk ? update.window.groups : update.scores.groups;
 }
 
 size_t window_score_part_bytes(const pyr_shape& s, int32_t w) {
@@ -784,17 +778,21 @@ int launch_window_score(const void* q_win, const void* k, const int32_t* seq_off
     DeviceInfo dev;
     if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
     const BatchCut cut = cut_batch(s, seq_offsets_host, min_seqlen);
-    const StripPlan stats = plan_strip(s, cut, w, dev, 2, kMaxScoreGroups, false);
+    const UpdatePlan plan = plan_update(s, cut, w, dev);
+    *groups = plan.one_walk ? plan.window.groups : plan.scores.groups;
+    if (plan.one_walk)
+        return launch_window(q_win, k, seq_offsets_dev, s, cut.equal, w, 1, scale_log2, row_weights, *groups > 1 ? (float*)part : scores,
+                             plan.window, dev, stream);
     int rc = launch_strip<kStats>(q_win, k, nullptr, seq_offsets_dev, seq_offsets_host, s, min_seqlen, w, 1, scale_log2, nullptr, nullptr,
-                                  (float2*)part, stats, dev, stream);
+                                  (float2*)part, plan.stats, dev, stream);
     if (rc != PYR_OK) return rc;
-    const int range_keys = 32 * stats.range_tiles;
+    const int range_keys = 32 * plan.stats.range_tiles;
     rc = (s.max_seqlen + range_keys - 1) / range_keys <= 4
              ? launch_fold<1>((const float2*)part, seq_offsets_dev, s, w, range_keys, lse_win, stream)
              : launch_fold<8>((const float2*)part, seq_offsets_dev, s, w, range_keys, lse_win, stream);
     if (rc != PYR_OK) return rc;
-    return launch_scores(q_win, k, lse_win, seq_offsets_dev, seq_offsets_host, s, min_seqlen, cut, w, 1, scale_log2, row_weights, scores,
-                         (float*)part, window_score_groups(s, w), groups, stream);
+    return launch_scores(q_win, k, lse_win, seq_offsets_dev, seq_offsets_host, s, min_seqlen, w, 1, scale_log2, row_weights, scores, (float*)part,
+                         plan.scores, dev, stream);
 }
 
 }  // namespace pyr

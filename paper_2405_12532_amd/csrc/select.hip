@@ -43,7 +43,7 @@ int launch_select(const float* parts, int groups, int32_t total_tokens, float* s
     // Few keys: the barriers' latency counts, and eight wavefronts reach them sooner than sixteen (us per launch, 512 / 1024
     // lanes: 256 tokens 4.9 / 5.8, 2048 tokens 6.3 / 7.5); many: the passes over the keys do (8192 tokens 11.6 / 10.4,
     // 32768 tokens 34.7 / 25.0).
-    return max_seqlen <= 4096 ? launch_select_t<512>(parts, groups, total_tokens, scores, seq_offsets_dev, keep_len_dev, n_seqs,
+    return max_seqlen <= 4096 && (int64_t)groups * max_seqlen <= 32768 ? launch_select_t<512>(parts, groups, total_tokens, scores, seq_offsets_dev, keep_len_dev, n_seqs,
                                                      max_seqlen, w, kept_idx, out_offsets_dev, stream)
                               : launch_select_t<1024>(parts, groups, total_tokens, scores, seq_offsets_dev, keep_len_dev, n_seqs,
                                                       max_seqlen, w, kept_idx, out_offsets_dev, stream);

@@ -24,6 +24,8 @@ constexpr int kDigitBits = 11;
 constexpr int kBins = 1 << kDigitBits;
 constexpr int kCandidates = 256;
 
+template <int N> struct Int { static constexpr int value = N; };
+
 // LDS the selection needs besides the staged keys
 struct SelectShared {
     uint32_t hist[kBins];
@@ -242,43 +244,49 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
     const bool ranked = need > 0 && need < C;   // else there is nothing to decide
     uint32_t kmin = 0xffffffffu, kmax = 0u;
     if (ranked || groups > 1) {
-        constexpr int kAhead = 8;               // scores a lane has in flight
-        constexpr int kRowsAhead = 4;           // rows of partial sums (the latency of a row at a time is what this would wait for)
+        // kAhead scores a lane has in flight, kRows rows of partial sums of each (the latency of a row at a time is what this would wait for)
         const float* __restrict__ from = groups > 1 ? parts + row0 : sc;
         const int n = groups > 1 ? S : C;
-        for (int i0 = tid; i0 < n; i0 += kAhead * kT) {
-            float x[kAhead];
-            if (groups <= 1) {
+        auto stage = [&](auto ahead, auto rows) {
+            constexpr int kAhead = decltype(ahead)::value, kRows = decltype(rows)::value;
+            for (int i0 = tid; i0 < n; i0 += kAhead * kT) {
+                float x[kAhead];
+                if (kRows == 1) {
 #pragma unroll
-                for (int u = 0; u < kAhead; ++u) x[u] = i0 + u * kT < n ? from[i0 + u * kT] : 0.f;
-            } else {
+                    for (int u = 0; u < kAhead; ++u) x[u] = i0 + u * kT < n ? from[i0 + u * kT] : 0.f;
+                } else {
 #pragma unroll
-                for (int u = 0; u < kAhead; ++u) x[u] = 0.f;
-                for (int g0 = 0; g0 < groups; g0 += kRowsAhead) {
-                    float y[kRowsAhead][kAhead];
+                    for (int u = 0; u < kAhead; ++u) x[u] = 0.f;
+                    for (int g0 = 0; g0 < groups; g0 += kRows) {
+                        float y[kRows][kAhead];
 #pragma unroll
-                    for (int g = 0; g < kRowsAhead; ++g)
+                        for (int g = 0; g < kRows; ++g)
 #pragma unroll
-                        for (int u = 0; u < kAhead; ++u)
-                            y[g][u] = i0 + u * kT < n && g0 + g < groups ? from[(size_t)(g0 + g) * total_tokens + i0 + u * kT] : 0.f;
+                            for (int u = 0; u < kAhead; ++u)
+                                y[g][u] = i0 + u * kT < n && g0 + g < groups ? from[(size_t)(g0 + g) * total_tokens + i0 + u * kT] : 0.f;
 #pragma unroll
-                    for (int g = 0; g < kRowsAhead; ++g)
+                        for (int g = 0; g < kRows; ++g)
 #pragma unroll
-                        for (int u = 0; u < kAhead; ++u) x[u] += y[g][u];
+                            for (int u = 0; u < kAhead; ++u) x[u] += y[g][u];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const int i = i0 + u * kT;
+                    if (i >= n) break;
+                    if (groups > 1) sc[i] = x[u];
+                    if (i >= C) break;
+                    const uint32_t key = ordered_key(x[u]);
+                    if (staged) lds_keys[i] = key;
+                    kmin = min(kmin, key);
+                    kmax = max(kmax, key);
                 }
             }
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const int i = i0 + u * kT;
-                if (i >= n) break;
-                if (groups > 1) sc[i] = x[u];
-                if (i >= C) break;
-                const uint32_t key = ordered_key(x[u]);
-                if (staged) lds_keys[i] = key;
-                kmin = min(kmin, key);
-                kmax = max(kmax, key);
-            }
-        }
+        };
+        if (groups <= 1) stage(Int<8>{}, Int<1>{});
+        else if (n > 4 * kT) stage(Int<8>{}, Int<4>{});
+        else if (n > 2 * kT) stage(Int<4>{}, Int<8>{});
+        else stage(Int<2>{}, Int<16>{});
         for (int i = tid; i < kBins; i += kT) sh->hist[i] = 0;
     }
 #pragma unroll

@@ -1,0 +1,127 @@
+// Launch of the one-walk scores (window_device.h): its cut, and the rule that says when it is taken.
+#include <type_traits>
+
+#include "window_device.h"
+
+namespace pyr {
+namespace {
+
+template <int D, int kTiles, bool kWeighted>
+__global__ __launch_bounds__(64 * kWindowWaves, 2) void window_kernel(WindowArgs a) {
+    extern __shared__ __align__(1024) char smem[];
+    int b, g;
+    const int id = (int)blockIdx.x;
+    if (a.xcds > 0) {
+        const int slot = id / a.xcds;
+        b = slot / a.groups * a.xcds + id % a.xcds;
+        g = slot % a.groups;
+    } else {
+        b = id / a.groups;
+        g = id % a.groups;
+    }
+    window_scores<D, kTiles, kWeighted>(a, b, g, smem);
+}
+
+int window_bytes(bool d64, int tiles, int waves) {
+    const auto of = [&](auto t) { return d64 ? window_lds_bytes<64, decltype(t)::value>(waves) : window_lds_bytes<128, decltype(t)::value>(waves); };
+    return tiles <= 2 ? of(std::integral_constant<int, 2>{}) : tiles <= 4 ? of(std::integral_constant<int, 4>{}) : of(std::integral_constant<int, 8>{});
+}
+
+template <int D, int kTiles, bool kWeighted>
+int launch_window_t(const WindowArgs& a, unsigned grid, int waves, hipStream_t stream) {
+    static std::atomic<uint64_t> lds_set{0};
+    if (ensure_dynamic_lds((const void*)window_kernel<D, kTiles, kWeighted>, window_lds_bytes<D, kTiles>(kWindowWaves), &lds_set) != PYR_OK) return PYR_ERR_LAUNCH;
+    const int lds = window_lds_bytes<D, kTiles>(waves);
+    hipLaunchKernelGGL((window_kernel<D, kTiles, kWeighted>), dim3(grid), dim3(64 * waves), lds, stream, a);
+    return check_launch();
+}
+
+template <int D, int kTiles>
+int launch_window_w(const WindowArgs& a, unsigned grid, int waves, hipStream_t stream) {
+    return a.row_weights ? launch_window_t<D, kTiles, true>(a, grid, waves, stream) : launch_window_t<D, kTiles, false>(a, grid, waves, stream);
+}
+
+template <int D>
+int launch_window_d(const WindowArgs& a, int32_t max_seqlen, unsigned grid, int waves, hipStream_t stream) {
+    const int tiles = (max_seqlen + 32 * waves - 1) / (32 * waves);
+    return tiles <= 2 ? launch_window_w<D, 2>(a, grid, waves, stream)
+         : tiles <= 4 ? launch_window_w<D, 4>(a, grid, waves, stream) : launch_window_w<D, 8>(a, grid, waves, stream);
+}
+
+}  // namespace
+
+// The cut with the lowest cost, in microseconds (selection included), joined as in plan_strip from
+// - the chain: 3.1 until the first tiles are there, then a workgroup's tasks one after the other; a task takes a wavefront 1.02 per tile
+//   (query rows count as one) where its latencies set the time, and 0.2 + 0.55 per tile times the wavefronts of its SIMD where they
+//   wait for each other, 0.79 of that at d = 64;
+// - the stream: a tile of K takes a compute unit's share of the memory system 0.236 from HBM and 0.218 from L2 to every task.
+// A row of partial sums costs the selection 0.035 and 0.1 per 1000 tokens.
+// Fitted to 270 calls (eleven head shapes, w = 16...256, one sequence to 160, 33...2048 tokens, equal and ragged), each timed with
+// up to 50 cuts: predictions near a call's best have a standard deviation of 11 %, the cut chosen takes 2.9 % longer than the best one in
+// the mean.  One wavefront is left to sequences of one tile: more of them hide each other's latency less well than predicted.
+WindowPlan plan_window(const pyr_shape& s, double tiles, int32_t w, int max_groups, const DeviceInfo& dev) {
+    WindowPlan best{0, 0, 1e300};
+    if (s.max_seqlen > kWindowMaxKeys) return best;
+    const bool d64 = s.head_dim == 64;
+    const int L = w < s.max_seqlen ? w : s.max_seqlen, max_tiles = (s.max_seqlen + 31) / 32;
+    const int64_t tasks = (int64_t)s.n_q_heads * ((L + 31) / 32);
+    const int fewest = (max_tiles + kWindowMaxTiles - 1) / kWindowMaxTiles, most = max_tiles < kWindowWaves ? max_tiles : kWindowWaves;
+    const double size = s.head_dim / 128.0, k = d64 ? 0.79 : 1.0;
+    const double flow = tiles * (0.236 * s.n_kv_heads + 0.218 * tasks) * size / dev.compute_units;
+    const double per_row = 0.035 + 1e-4 * s.max_seqlen;
+    const int limit = (int)(tasks < max_groups ? tasks : max_groups);
+    for (int waves = fewest > 1 || most == 1 ? fewest : 2; waves <= most; ++waves) {
+        const int wave_tiles = (max_tiles + waves - 1) / waves;
+        // (workgroups a compute unit holds: 8 wavefronts by registers, 12 of up to two tiles; 160 KB of LDS)
+        const int by_registers = (wave_tiles <= 2 ? 12 : 8) / waves;
+        const int bytes = window_bytes(d64, wave_tiles, waves);
+        const int by_lds = 160 * 1024 / bytes, per_cu = by_lds < by_registers ? by_lds : by_registers;
+        const double mean_tiles = tiles == (double)s.n_seqs * max_tiles ? wave_tiles : tiles / s.n_seqs / waves + 0.5 * (1.0 - 1.0 / waves);
+        for (int g = 1, last = 0; !last; g = 2 * g) {
+            if (g >= limit || g >= 256) {
+                last = 1;
+                g = limit < 256 ? limit : 256;
+            }
+            const double task_rounds = (double)((tasks + g - 1) / g), wgs = (double)s.n_seqs * g, slots = (double)dev.compute_units * per_cu;
+            const double there = ceil(wgs / dev.compute_units), on_simd = (there < per_cu ? there : per_cu) * waves / 4;
+            const double own = on_simd > 1.0 ? on_simd : 1.0;
+            const auto task = [&](double t) {
+                const double alone = 1.02 * k * (t + 1), shared = (0.2 + 0.55 * k * (t + 1)) * own;
+                return alone > shared ? alone : shared;
+            };
+            const double longest = task_rounds * task(wave_tiles);
+            double chain = 3.1 + longest;
+            if (wgs > slots) {
+                const double mean = task_rounds * task(mean_tiles), all = wgs * mean / slots;
+                chain = 3.1 + (all > longest ? all : longest) + (wgs < 8 * slots ? 0.5 : 0.25) * mean;
+            }
+            const double cost = 6.0 + sqrt(sqrt(chain * chain * chain * chain + flow * flow * flow * flow)) + per_row * (g - 1);
+            if (cost < best.cost) best = WindowPlan{waves, g, cost};
+        }
+    }
+    return best;
+}
+
+int launch_window(const void* q, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& s, bool equal, int32_t w, int32_t q_window,
+                  float scale_log2, const float* row_weights, float* sums, const WindowPlan& plan, const DeviceInfo& dev, hipStream_t stream) {
+    WindowArgs a{};
+    a.q = (const uint16_t*)q;
+    a.k = (const uint16_t*)k;
+    a.seq_offsets = seq_offsets_dev;
+    a.n_seqs = s.n_seqs;
+    a.n_q_heads = s.n_q_heads;
+    a.n_kv_heads = s.n_kv_heads;
+    a.w = w;
+    a.groups = plan.groups;
+    a.xcds = equal && s.n_seqs % dev.xccs == 0 ? dev.xccs : 0;
+    a.q_window = q_window;
+    a.c = scale_log2;
+    a.row_weights = row_weights;
+    a.sums = sums;
+    a.total_tokens = s.total_tokens;
+    const int64_t n = (int64_t)s.n_seqs * plan.groups;
+    if (n >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
+    return s.head_dim == 128 ? launch_window_d<128>(a, s.max_seqlen, (unsigned)n, plan.waves, stream) : launch_window_d<64>(a, s.max_seqlen, (unsigned)n, plan.waves, stream);
+}
+
+}  // namespace pyr

@@ -1,0 +1,83 @@
+"""The generation phase's one walk over K (csrc/window_device.h): logits of a window's row block kept in registers, eight 32-key tiles per
+wavefront at most.  At the edges of tiles, of wavefronts and of the longest sequence it takes, against the float64 oracle with the
+tolerance of the two walks (tests/test_gpu_score_ranges.py); every batch asserts that it goes there.  The two walks it stands in for at these
+lengths are reached by batches that assert that instead."""
+import numpy as np
+import pytest
+
+from paper_2405_12532_amd import synth
+from tests import parity, test_gpu_decode
+from tests.routes import route
+from tests.test_gpu_large_logits import F64, shaped_inputs
+from tests.test_gpu_decode import window_queries
+from oracle import pyr_oracle as orc
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+SCORE_RTOL = 1.3e-4                                             # (derived in tests/test_gpu_score_ranges.py)
+
+
+def _wl(lens, Hq, Hkv, d, w):
+    return synth.shrunk(synth.workload("cfg2"), lens, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, w=w, hidden_dim=0)
+
+
+ONE_WALK = [
+    ((1, 2, 31, 32), 4, 4, 128, 16),                            # one tile, one wavefront
+    ((33, 64, 65, 255), 4, 4, 64, 32),                          # a second tile of one row; no key left for some wavefronts
+    ((256, 257, 0, 1), 6, 3, 128, 33),                          # row block of one row; empty sequence; groups without a task
+    ((511, 512, 513), 4, 2, 64, 40),                            # two tiles per wavefront and one more
+    ((1023, 1025), 8, 8, 128, 32),                              # four and five: the next register layout
+    ((2047, 2048, 2020, 2017, 1999, 2047), 16, 16, 64, 32),     # the longest sequences
+    ((2048,) * 8, 16, 16, 128, 16),
+    ((300,) * 16, 8, 8, 128, 64),                               # a sequence's workgroups on one XCD
+    ((200,) * 90, 16, 16, 64, 32),                              # several rounds of workgroups, several tasks each
+]
+TWO_WALKS = [
+    ((2049,), 4, 4, 64, 16),                                    # a key too many
+    ((120,) * 60, 32, 1, 128, 128),                             # many row blocks per KV head: one lane folds a row's one range
+    ((250,) * 20, 32, 1, 128, 256),
+    ((1200, 700), 8, 8, 64, 40),                                # few heads
+]
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w", ONE_WALK)
+@pytest.mark.parametrize("weighted", [False, True])
+def test_one_walk(lib, lens, Hq, Hkv, d, w, weighted):
+    assert route(lib, lens, Hq, Hkv, d, w).stats_waves == 0
+    rw = np.linspace(0.0, 1.0, w, dtype=np.float32) if weighted else None            # (the first weight is zero)
+    if weighted and min(S for S in lens if S) == 1:
+        rw = rw + np.float32(0.25)
+    res, ref, _ = test_gpu_decode.run_and_check(lib, _wl(lens, Hq, Hkv, d, w), row_weights=rw)
+    np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w", TWO_WALKS)
+def test_two_walks(lib, lens, Hq, Hkv, d, w):
+    assert route(lib, lens, Hq, Hkv, d, w).stats_waves > 0
+    res, ref, _ = test_gpu_decode.run_and_check(lib, _wl(lens, Hq, Hkv, d, w))
+    np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
+
+
+@pytest.mark.parametrize("kind", ["ramp", "low_start_overflow"])
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w", [((900, 300), 8, 4, 128, 32), ((1100, 130), 16, 16, 64, 32)])
+def test_moved_references(lib, kind, lens, Hq, Hkv, d, w):
+    """Rows that outgrow a wavefront's reference, its first key's logit, by more than 2^40 in later tiles."""
+    r = route(lib, lens, Hq, Hkv, d, w)
+    assert r.stats_waves == 0
+    wl = _wl(lens, Hq, Hkv, d, w)
+    x = shaped_inputs(kind, wl, lib, seed=2)
+    q, k, S = F64(x["q"]), F64(x["k"]), lens[0]
+    moved = 0
+    for h in range(Hq):
+        lg = q[S - w:S, h] @ k[:S, h // (Hq // Hkv)].T / np.sqrt(d)
+        for wave in range(r.window_waves):
+            keys = np.arange(32 * wave, S - w)
+            keys = keys[(keys // 32 - wave) % r.window_waves == 0]
+            moved += int(np.sum(lg[:, keys[32:]].max(axis=1, initial=-np.inf) - lg[:, keys[0]] > 41 * np.log(2.0)))
+    assert moved > 30, moved
+    off, keep = x["seq_offsets"], x["keep_len"]
+    q_win = window_queries(x["q"], off, wl.w)
+    res = lib.decode_update_from_numpy(q_win, x["k"], x["v"], off, keep, wl.w)
+    ref = orc.decode_update(F64(q_win.reshape(-1)).reshape(q_win.shape), F64(x["k"]), F64(x["v"]), off, wl.w, keep)
+    parity.check_scores(res["scores"], ref)
+    parity.check_index_sets(res["kept_idx"], ref, off, keep, wl.w)

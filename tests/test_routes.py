@@ -51,3 +51,11 @@ def test_route_arguments():
     assert lib.pyr_diag_route(ctypes.byref(shape), None, 16, 256, 8, ctypes.byref(binding.PyrRoute())) == -1
     empty = binding.make_shape(0, 0, 0, 4, 2, 64)
     assert binding.diag_route(empty, torch.zeros(1, dtype=torch.int32), 16, 256, 8).score_tiles == 0
+
+
+def test_generation_walks():
+    from tests import test_gpu_window_scores as window
+    for batch in window.ONE_WALK:
+        assert route(binding, *batch, **MI355X).stats_waves == 0, batch
+    for batch in window.TWO_WALKS:
+        assert route(binding, *batch, **MI355X).stats_waves > 0, batch
