@@ -1,41 +1,48 @@
 // Device code of the segmented top-k (Algorithm 1, TopP(A_e, p) with the retention ratio turned
 // into a count, followed by the recent window that is always kept), written for a workgroup of
-// any multiple of 64 lanes; the selection kernel (select.hip) runs it, one workgroup per sequence.
+// 512 or 1024 lanes; the selection kernel (select.hip) runs it, one workgroup per sequence.
 //
 // The paper names the sort inside TopP as the one extra cost of the method that matters
-// (Appendix A.1).  Nothing is sorted here: the workgroup finds the value of the need-th largest
-// context score with a most-significant-digit-first radix select on the fp32 bit patterns, then
-// emits the survivors with wavefront ballots and prefix counts, which yields ascending positions
-// for free.  Ties at the threshold go to the lower positions.
+// (Appendix A.1).  Nothing is sorted here: the workgroup finds the need-th largest context score and the position of the
+// last key of that value that is admitted (ties go to the lower positions), by a histogram over the keys' distance from the
+// smallest one, then emits the survivors with wavefront ballots and prefix counts, which yields ascending positions
+// for free.
 //
-// Bound: latency (a few KB per sequence, one workgroup): barriers and passes over the keys.  The radix
-// select therefore skips the leading bits that all keys share (minimum and maximum are known from
-// staging them), takes digits of 11 bits, and stops as soon as the digit's bin holds at most
-// kCandidates keys, which are then ranked against each other directly: at the score distributions of
-// the method that is one pass instead of the four that fixed 8-bit digits take (us per launch, before / now: one
-// sequence of 256 tokens 6.4 / 4.9, of 2048 9.5 / 6.3, of 8192 27 / 10.4, four of 32768 64 / 25).
+// Bound: latency (a few KB per sequence, one workgroup): loads that depend on each other, barriers, and atomics on one
+// histogram bin, which LDS serves one after the other.  So
+// - a wavefront owns consecutive positions from beginning to end and a lane keeps its keys in registers where there are kRegKeys of them at
+//   most; else they are staged in LDS, and where that is too small re-read from memory in every pass;
+// - the bins divide the span between the smallest and the largest key, not the bits in which keys differ: scores spread over
+//   ten octaves fill all bins (with leading bits 120 of 2048: five lanes of a wavefront on one bin, and bins too full to stop at);
+// - a bin of at most kCandidates keys ends the search: they are ranked against each other by value and position.
+// One pass over the bins at the score distributions of the method.
+// us per launch, leading bits in digits of 11 from LDS / now (a launch that does nothing takes 4 of these): one sequence of
+// 256 tokens 5.1 / 4.2, of 2048 6.5 / 4.6, of 8192 11.4 / 8.2, four of 32768 28.6 / 23.1, two of 60000 73 / 69.
+// (32 instead of 8 scores a lane has in flight while they are loaded: 16384 tokens 13.9 -> 14.9, no gain beyond.)
 #pragma once
 
 #include "pyr_internal.h"
 
 namespace pyr {
 
-constexpr int kDigitBits = 11;
-constexpr int kBins = 1 << kDigitBits;
+constexpr int kRegKeys = 8;                 // keys of a lane in registers, at most
 constexpr int kCandidates = 256;
+
+// where a lane finds its keys after they have been loaded
+enum KeySource { kInRegisters, kInLds, kInMemory };
 
 template <int N> struct Int { static constexpr int value = N; };
 
 // LDS the selection needs besides the staged keys
+template <int kT>
 struct SelectShared {
-    uint32_t hist[kBins];
-    uint32_t cand[kCandidates];
-    int wave_cnt[2 * 16];
-    int red[16];
-    uint32_t wave_min[16], wave_max[16];
-    int n_cand;
-    int bcast[3];
-    uint32_t tau;
+    uint2 hist[kT];                          // 2 * kT bins
+    uint64_t cand[kCandidates];
+    int count[16];                           // per wavefront
+    int found[3];                            // bin, place of the threshold in it, keys in it
+    uint32_t wave_min[16], wave_max[16], part[16];
+    uint32_t n_cand;
+    uint64_t threshold;
 };
 
 // Monotone map float -> uint32 (larger float, larger key); -0 is folded onto +0 so that
@@ -46,187 +53,147 @@ __device__ __forceinline__ uint32_t ordered_key(float x) {
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
+// The order of the selection: by key, then the lower position first.
+__device__ __forceinline__ uint64_t ranked(uint32_t key, int i) { return (uint64_t)key << 32 | (uint32_t)~i; }
+
 __device__ __forceinline__ uint64_t lanemask_lt() {
     const int lane = threadIdx.x & 63;
     return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
-template <bool kStaged>
-__device__ __forceinline__ uint32_t get_key(const uint32_t* lds_keys, const float* __restrict__ g, int i) {
-    if (kStaged) return lds_keys[i];
-    return ordered_key(g[i]);
+template <int kCtrl, int kRowMask = 0xf>
+__device__ __forceinline__ uint32_t lanes(uint32_t old, uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)x, kCtrl, kRowMask, 0xf, false);
 }
 
-// The body after the keys are reachable through get_key<kStaged> and their minimum and maximum are known
-// (sh->hist zeroed, both behind a barrier); kT lanes (a multiple of 64, at most 1024).
-template <bool kStaged, int kT>
-__device__ void select_body(const uint32_t* lds_keys, const float* __restrict__ sc, int C, int need, uint32_t kmin, uint32_t kmax,
-                            int32_t row0, int32_t* __restrict__ out, SelectShared* sh) {
-    constexpr int kW = kT / 64;
-    constexpr int kPer = kBins / kT;            // bins a lane scans
-    constexpr int kAhead = 4;                   // keys a lane fetches before it uses the first
+// op over the 64 lanes of a wavefront, in every lane: mirrors of 16 and 8 lanes, reversed quads, swapped pairs, then
+// rows of 16 and halves.
+template <class Op>
+__device__ __forceinline__ uint32_t over_lanes(uint32_t x, Op op) {
+    x = op(x, lanes<0x140>(x, x));
+    x = op(x, lanes<0x141>(x, x));
+    x = op(x, lanes<0x1b>(x, x));
+    x = op(x, lanes<0xb1>(x, x));
+    auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = op(r[0], r[1]);
+    auto s = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return op(s[0], s[1]);
+}
+
+// The sum of x over this lane and the lanes before it: shifts inside rows of 16, then the rows' totals handed on.
+__device__ __forceinline__ uint32_t sum_up_to_lane(uint32_t x) {
+    x += lanes<0x111>(0u, x);
+    x += lanes<0x112>(0u, x);
+    x += lanes<0x114>(0u, x);
+    x += lanes<0x118>(0u, x);
+    x += lanes<0x142, 0xa>(0u, x);
+    x += lanes<0x143, 0xc>(0u, x);
+    return x;
+}
+
+// The sum of what the wavefronts before this one counted.
+template <int kW>
+__device__ __forceinline__ int sum_before(const int* count, int wave) {
+    int n = 0;
+#pragma unroll
+    for (int u = 0; u < kW; ++u) n += u < wave ? count[u] : 0;
+    return n;
+}
+
+// The smallest kept ranked() of the keys that `each` visits: the need-th largest, 0 < need <= number of keys.  Their
+// minimum and maximum are known, sh->hist is zero and sh->n_cand too, all behind a barrier; ends behind one.
+template <int kT, class Each>
+__device__ uint64_t find_threshold(const Each& each, int need, uint32_t kmin, uint32_t kmax, SelectShared<kT>* sh) {
+    constexpr int kW = kT / 64, kBinBits = kT == 512 ? 10 : 11;
+    static_assert(2 * kT == 1 << kBinBits, "two bins a lane");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-
-    // ---- radix select: threshold key tau and the number of ties still to admit
-    uint32_t tau = kmin;
-    int ties = need;                            // (all keys equal: the first `need` of them)
-    if (kmin != kmax) {
-        int bits_left = 32 - __clz((int)(kmin ^ kmax));        // the keys differ in their low bits_left bits only
-        int remaining = need;
-        uint64_t prefix = (uint64_t)kmin >> bits_left;
-        while (true) {
-            const int nbits = min(kDigitBits, bits_left), shift = bits_left - nbits;
-            for (int i0 = tid - lane; i0 < C; i0 += kAhead * kT) {      // (whole wavefronts: the ballots below)
-                uint32_t keys[kAhead];
-#pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    const int i = i0 + u * kT + lane;
-                    keys[u] = i < C ? get_key<kStaged>(lds_keys, sc, i) : 0u;
-                }
-#pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    const bool match = i0 + u * kT + lane < C && ((uint64_t)keys[u] >> bits_left) == prefix;
-                    const uint32_t digit = (keys[u] >> shift) & ((1u << nbits) - 1);
-                    // equal digits throughout a wavefront (many equal scores) are counted by one lane
-                    const uint64_t active = __ballot(match);
-                    if (active == 0) continue;
-                    const int leader = __ffsll((unsigned long long)active) - 1;
-                    const uint32_t dl = __builtin_amdgcn_readlane(digit, leader);
-                    if (__ballot(match && digit == dl) == active) {
-                        if (lane == leader) atomicAdd(&sh->hist[dl], (uint32_t)__popcll(active));
-                    } else if (match) {
-                        atomicAdd(&sh->hist[digit], 1u);
-                    }
+    uint32_t* const hist = (uint32_t*)sh->hist;
+    if (kmin == kmax) return ranked(kmin, need - 1);
+    int remaining = need, bits = 32 - __clz((int)(kmax - kmin));      // the keys in question are base + less than 2^bits
+    uint32_t base = kmin;
+    bool whole = true;                                                // ... which are all of them
+    while (true) {
+        const int shift = bits > kBinBits ? bits - kBinBits : 0;
+        each([&](uint32_t key, int, bool valid) {
+            const uint32_t from = key - base;
+            if (valid && (whole || from >> bits == 0)) {
+                // equal bins throughout a wavefront (many equal scores) are counted by one lane
+                const uint32_t bin = from >> shift, first = (uint32_t)__builtin_amdgcn_readfirstlane((int)bin);
+                const uint64_t here = __ballot(true);
+                if (__ballot(bin == first) == here) {
+                    if (lane == __ffsll((unsigned long long)here) - 1) atomicAdd(&hist[first], (uint32_t)__popcll(here));
+                } else {
+                    atomicAdd(&hist[bin], 1u);
                 }
             }
+        });
+        __syncthreads();
+        // lane t owns the bins 2 * (kT - 1 - t) + 1 and + 0, in this (descending) order
+        const uint2 h = sh->hist[kT - 1 - tid];
+        const int mine = (int)(h.x + h.y), incl = (int)sum_up_to_lane(h.x + h.y);
+        if (lane == 63) sh->count[wave] = incl;
+        __syncthreads();
+        const int before = incl - mine + sum_before<kW>(sh->count, wave);
+        if (before < remaining && remaining <= before + mine) {
+            const bool upper = remaining <= before + (int)h.y;
+            sh->found[0] = 2 * (kT - 1 - tid) + upper;
+            sh->found[1] = remaining - before - (upper ? 0 : (int)h.y);
+            sh->found[2] = (int)(upper ? h.y : h.x);
+        }
+        __syncthreads();
+        const uint32_t bin = (uint32_t)sh->found[0];
+        const int in_bin = sh->found[2];
+        remaining = sh->found[1];
+        base += bin << shift;
+        bits = shift;
+        whole = false;
+        if (in_bin <= kCandidates) {
+            each([&](uint32_t key, int i, bool valid) {
+                if (valid && (key - base) >> bits == 0) sh->cand[atomicAdd(&sh->n_cand, 1u)] = ranked(key, i);
+            });
             __syncthreads();
-            // lane t owns bins kBins-1 - kPer*t downwards (descending order of value)
-            const int top = kBins - 1 - kPer * tid;
-            uint32_t h[kPer];
-            int mine = 0;
-#pragma unroll
-            for (int u = 0; u < kPer; ++u) {
-                h[u] = sh->hist[top - u];
-                mine += (int)h[u];
-            }
-            int incl = mine;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int up = __shfl_up(incl, d);
-                if (lane >= d) incl += up;
-            }
-            if (lane == 63) sh->red[wave] = incl;
-            if (tid == 0) sh->n_cand = 0;
-            __syncthreads();
-            int run = incl - mine;
-            for (int u = 0; u < wave; ++u) run += sh->red[u];
-            if (run < remaining && remaining <= run + mine) {
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    if (run < remaining && remaining <= run + (int)h[u]) {
-                        sh->bcast[0] = top - u;
-                        sh->bcast[1] = remaining - run;
-                        sh->bcast[2] = (int)h[u];
-                    }
-                    run += (int)h[u];
-                }
-            }
-            __syncthreads();
-            prefix = (prefix << nbits) | (uint32_t)sh->bcast[0];
-            remaining = sh->bcast[1];
-            const int in_bin = sh->bcast[2];
-            bits_left = shift;
-            if (bits_left == 0) {                              // every bit decided: the bin's keys are equal
-                tau = (uint32_t)prefix;
-                ties = remaining;
-                break;
-            }
-            if (in_bin <= kCandidates) {
+            if (tid < in_bin) {
+                const uint64_t my = sh->cand[tid];
+                int larger = 0;
 #pragma unroll 4
-                for (int i = tid; i < C; i += kT) {
-                    const uint32_t key = get_key<kStaged>(lds_keys, sc, i);
-                    if (((uint64_t)key >> bits_left) == prefix) sh->cand[atomicAdd(&sh->n_cand, 1)] = key;
-                }
-                __syncthreads();
-                if (tid < in_bin) {
-                    const uint32_t my = sh->cand[tid];
-                    int gt = 0, eq = 0;
-                    for (int u = 0; u < in_bin; ++u) {
-                        const uint32_t o = sh->cand[u];
-                        gt += o > my;
-                        eq += o == my;
-                    }
-                    if (gt < remaining && remaining <= gt + eq) {      // (equal candidates all write the same)
-                        sh->tau = my;
-                        sh->bcast[0] = remaining - gt;
-                    }
-                }
-                __syncthreads();
-                tau = sh->tau;
-                ties = sh->bcast[0];
-                break;
+                for (int u = 0; u < in_bin; ++u) larger += sh->cand[u] > my;
+                if (larger == remaining - 1) sh->threshold = my;
             }
-            for (int i = tid; i < kBins; i += kT) sh->hist[i] = 0;
             __syncthreads();
+            return sh->threshold;
         }
-    }
-    // ties >= 1 keys equal to tau are admitted, lowest positions first
-
-    // ---- ordered emission: wavefront `wave` owns positions [wave*seg, (wave+1)*seg)
-    const int seg = (C + kW * 64 - 1) / (kW * 64) * 64;
-    const int lo = wave * seg;
-    const int hi = min(C, lo + seg);
-    int n_gt = 0, n_eq = 0;
-#pragma unroll 4
-    for (int i = lo + lane; i < hi; i += 64) {
-        const uint32_t key = get_key<kStaged>(lds_keys, sc, i);
-        n_gt += key > tau;
-        n_eq += key == tau;
-    }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        n_gt += __shfl_xor(n_gt, d);
-        n_eq += __shfl_xor(n_eq, d);
-    }
-    if (lane == 0) { sh->wave_cnt[2 * wave] = n_gt; sh->wave_cnt[2 * wave + 1] = n_eq; }
-    __syncthreads();
-    int gt_before = 0, eq_before = 0;
-    for (int u = 0; u < wave; ++u) { gt_before += sh->wave_cnt[2 * u]; eq_before += sh->wave_cnt[2 * u + 1]; }
-    int kept_cnt = gt_before + min(eq_before, ties);
-    const uint64_t lt = lanemask_lt();
-    for (int i0 = lo; i0 < hi; i0 += 64 * kAhead) {
-        uint32_t keys[kAhead];
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            const int i = i0 + 64 * u + lane;
-            keys[u] = i < hi ? get_key<kStaged>(lds_keys, sc, i) : 0u;
+        if (bits == 0) {                      // the bin's keys are equal: the remaining-th of them in order
+            int n = 0;
+            each([&](uint32_t key, int, bool valid) { n += __popcll(__ballot(valid && key == base)); });
+            if (lane == 0) sh->count[wave] = n;
+            __syncthreads();
+            int at = remaining - sum_before<kW>(sh->count, wave);
+            if (0 < at && at <= n) {
+                each([&](uint32_t key, int i, bool valid) {
+                    const bool equal = valid && key == base;
+                    const uint64_t mask = __ballot(equal);
+                    if (equal && __popcll(mask & lanemask_lt()) == at - 1) sh->threshold = ranked(key, i);
+                    at -= __popcll(mask);
+                });
+            }
+            __syncthreads();
+            return sh->threshold;
         }
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            const int i = i0 + 64 * u + lane;
-            const bool gt = i < hi && keys[u] > tau;
-            const bool eq = i < hi && keys[u] == tau;
-            const uint64_t eq_mask = __ballot(eq);
-            const int eq_rank = eq_before + __popcll(eq_mask & lt);
-            const bool keep = gt || (eq && eq_rank < ties);
-            const uint64_t keep_mask = __ballot(keep);
-            if (keep) out[kept_cnt + __popcll(keep_mask & lt)] = row0 + i;
-            kept_cnt += __popcll(keep_mask);
-            eq_before += __popcll(eq_mask);
-        }
+        sh->hist[tid] = make_uint2(0u, 0u);
+        __syncthreads();
     }
 }
 
 // The selection of sequence b by the calling workgroup (all kT lanes take part; uniform control
 // flow).  groups > 1: the scores are first added up from parts[groups][total_tokens], in order, and written.
-// lds_keys: room for lds_cap keys; scores of longer contexts are re-read from memory in
-// every pass.  Also writes out_offsets[b + 1] (and out_offsets[0] for b == 0).
-template <int kT>
+// kInRegisters: sequences of kRegKeys * kT tokens at most; kInLds: lds_keys has room for a sequence.
+// Also writes out_offsets[b + 1] (and out_offsets[0] for b == 0).
+template <int kT, KeySource kSource>
 __device__ void select_sequence(int b, const float* __restrict__ parts, int groups, int32_t total_tokens, float* scores,
-                                const int32_t* __restrict__ seq_offsets, const int32_t* __restrict__ keep_len, int32_t w, uint32_t* lds_keys, int32_t lds_cap,
-                                SelectShared* sh, int32_t* __restrict__ kept_idx, int32_t* __restrict__ out_offsets) {
-    constexpr int kW = kT / 64;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                const int32_t* __restrict__ seq_offsets, const int32_t* __restrict__ keep_len, int32_t w, uint32_t* lds_keys,
+                                SelectShared<kT>* sh, int32_t* __restrict__ kept_idx, int32_t* __restrict__ out_offsets) {
+    constexpr int kW = kT / 64, kRegs = kSource == kInRegisters ? kRegKeys : 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t row0 = seq_offsets[b];
     const int S = seq_offsets[b + 1] - row0;
     const int L = min(w, S);
@@ -236,24 +203,25 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
     float* sc = scores + row0;
 
     // packed position of this sequence's output: sum of the keep counts before it
-    int part = 0;
-    for (int u = tid; u < b; u += kT) part += keep_len[u];
+    uint32_t part = 0;
+    for (int u = tid; u < b; u += kT) part += (uint32_t)keep_len[u];
 
-    // keys to LDS (if they fit), their minimum and maximum
-    const bool staged = C <= lds_cap;
-    const bool ranked = need > 0 && need < C;   // else there is nothing to decide
-    uint32_t kmin = 0xffffffffu, kmax = 0u;
-    if (ranked || groups > 1) {
+    // wavefront `wave` owns the positions [lo, lo + seg) of the n that are loaded
+    const int n = groups > 1 ? S : C;
+    const int seg = (n + kT - 1) / kT * 64, lo = wave * seg;
+    const bool decide = need > 0 && need < C;
+    uint32_t keys[kRegs], kmin = 0xffffffffu, kmax = 0u;
+    if (decide || groups > 1) {
         // kAhead scores a lane has in flight, kRows rows of partial sums of each (the latency of a row at a time is what this would wait for)
         const float* __restrict__ from = groups > 1 ? parts + row0 : sc;
-        const int n = groups > 1 ? S : C;
+        const int end = min(n, lo + seg);
         auto stage = [&](auto ahead, auto rows) {
             constexpr int kAhead = decltype(ahead)::value, kRows = decltype(rows)::value;
-            for (int i0 = tid; i0 < n; i0 += kAhead * kT) {
+            for (int i0 = lo + lane; i0 < end; i0 += 64 * kAhead) {
                 float x[kAhead];
                 if (kRows == 1) {
 #pragma unroll
-                    for (int u = 0; u < kAhead; ++u) x[u] = i0 + u * kT < n ? from[i0 + u * kT] : 0.f;
+                    for (int u = 0; u < kAhead; ++u) x[u] = i0 + 64 * u < end ? from[i0 + 64 * u] : 0.f;
                 } else {
 #pragma unroll
                     for (int u = 0; u < kAhead; ++u) x[u] = 0.f;
@@ -263,7 +231,7 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
                         for (int g = 0; g < kRows; ++g)
 #pragma unroll
                             for (int u = 0; u < kAhead; ++u)
-                                y[g][u] = i0 + u * kT < n && g0 + g < groups ? from[(size_t)(g0 + g) * total_tokens + i0 + u * kT] : 0.f;
+                                y[g][u] = i0 + 64 * u < end && g0 + g < groups ? from[(size_t)(g0 + g) * total_tokens + i0 + 64 * u] : 0.f;
 #pragma unroll
                         for (int g = 0; g < kRows; ++g)
 #pragma unroll
@@ -272,39 +240,38 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
                 }
 #pragma unroll
                 for (int u = 0; u < kAhead; ++u) {
-                    const int i = i0 + u * kT;
-                    if (i >= n) break;
-                    if (groups > 1) sc[i] = x[u];
-                    if (i >= C) break;
+                    const int i = i0 + 64 * u;
                     const uint32_t key = ordered_key(x[u]);
-                    if (staged) lds_keys[i] = key;
+                    if (kSource == kInRegisters) keys[u] = key;
+                    if (i >= end) continue;
+                    if (groups > 1) sc[i] = x[u];
+                    if (i >= C) continue;
+                    if (kSource == kInLds) lds_keys[i] = key;
                     kmin = min(kmin, key);
                     kmax = max(kmax, key);
                 }
             }
         };
         if (groups <= 1) stage(Int<8>{}, Int<1>{});
-        else if (n > 4 * kT) stage(Int<8>{}, Int<4>{});
-        else if (n > 2 * kT) stage(Int<4>{}, Int<8>{});
+        else if (seg > 256) stage(Int<8>{}, Int<4>{});
+        else if (seg > 128) stage(Int<4>{}, Int<8>{});
         else stage(Int<2>{}, Int<16>{});
-        for (int i = tid; i < kBins; i += kT) sh->hist[i] = 0;
+        sh->hist[tid] = make_uint2(0u, 0u);
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        part += __shfl_xor(part, d);
-        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, d));
-        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, d));
-    }
+    kmin = over_lanes(kmin, [](uint32_t x, uint32_t y) { return min(x, y); });
+    kmax = over_lanes(kmax, [](uint32_t x, uint32_t y) { return max(x, y); });
+    part = over_lanes(part, [](uint32_t x, uint32_t y) { return x + y; });
     if (lane == 0) {
-        sh->red[wave] = part;
+        sh->part[wave] = part;
         sh->wave_min[wave] = kmin;
         sh->wave_max[wave] = kmax;
+        if (wave == 0) sh->n_cand = 0;
     }
     __syncthreads();                            // (also: the scores written above are visible to the workgroup)
     int out_base = 0;
 #pragma unroll
     for (int u = 0; u < kW; ++u) {
-        out_base += sh->red[u];
+        out_base += (int)sh->part[u];
         kmin = min(kmin, sh->wave_min[u]);
         kmax = max(kmax, sh->wave_max[u]);
     }
@@ -321,9 +288,40 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
         for (int i = tid; i < C; i += kT) out[i] = row0 + i;
         return;
     }
-    __syncthreads();                            // (red is used again below)
-    if (staged) select_body<true, kT>(lds_keys, sc, C, need, kmin, kmax, row0, out, sh);
-    else select_body<false, kT>(lds_keys, sc, C, need, kmin, kmax, row0, out, sh);
+
+    // use(key, position, whether there is one) for the wavefront's keys in ascending order, all lanes together
+    auto each = [&](auto use) {
+        if constexpr (kSource == kInRegisters) {
+#pragma unroll
+            for (int u = 0; u < kRegs; ++u) {
+                if (64 * u >= seg) break;
+                use(keys[u], lo + 64 * u + lane, lo + 64 * u + lane < C);
+            }
+        } else {
+            constexpr int kAhead = 8;
+            const int hi = min(C, lo + seg);
+            for (int i0 = lo + lane; i0 - lane < hi; i0 += 64 * kAhead) {
+                uint32_t x[kAhead];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) x[u] = i0 + 64 * u >= hi ? 0u : kSource == kInLds ? lds_keys[i0 + 64 * u] : ordered_key(sc[i0 + 64 * u]);
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) use(x[u], i0 + 64 * u, i0 + 64 * u < hi);
+            }
+        }
+    };
+    const uint64_t threshold = find_threshold<kT>(each, need, kmin, kmax, sh);
+    int kept = 0;
+    each([&](uint32_t key, int i, bool valid) { kept += __popcll(__ballot(valid && ranked(key, i) >= threshold)); });
+    if (lane == 0) sh->count[wave] = kept;
+    __syncthreads();
+    int to = sum_before<kW>(sh->count, wave);
+    const uint64_t lt = lanemask_lt();
+    each([&](uint32_t key, int i, bool valid) {
+        const bool keep = valid && ranked(key, i) >= threshold;
+        const uint64_t mask = __ballot(keep);
+        if (keep) out[to + __popcll(mask & lt)] = row0 + i;
+        to += __popcll(mask);
+    });
 }
 
 }  // namespace pyr

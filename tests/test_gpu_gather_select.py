@@ -159,3 +159,23 @@ def test_gather_positions_bit_exact(lib, n_src, n_kept):
     got = out.cpu().numpy()
     assert np.array_equal(got[:n_kept], pos[idx])
     assert np.all(got[n_kept:] == 0x5A5A5A5A), "nothing is written past n_kept"
+
+
+@pytest.mark.parametrize("dist", ["spread", "tied", "outlier", "signed"])
+@pytest.mark.parametrize("longest", [63, 512, 4096, 4097, 8192, 8193, 36864, 36865])
+def test_select_key_sources_and_search(lib, longest, dist):
+    """Sizes at the ends of the ranges a lane keeps its keys in registers, LDS or memory for, with scores that end the search in its first
+    bin, in a bin of more equal keys than are ranked, and after further passes."""
+    lens = [longest, max(longest - 61, 1), longest // 2 + 1, 3]
+    rng = np.random.default_rng(longest)
+    scores = np.exp(rng.normal(size=sum(lens))).astype(np.float32)
+    if dist == "tied":                                      # six values: hundreds of keys equal the threshold
+        scores = (np.minimum(scores, 5.0).astype(np.int32) * 0.125).astype(np.float32)
+    elif dist == "outlier":                                 # all but two keys share the top bin's neighbourhood
+        scores = (1.0 + 1e-4 * rng.random(sum(lens))).astype(np.float32)
+        scores[0], scores[lens[0]] = 1e-38, 3e38
+    elif dist == "signed":
+        scores = (scores * rng.choice([-1.0, 1.0, 0.0], size=len(scores))).astype(np.float32)
+        scores[1], scores[lens[0] + 1] = np.inf, -np.inf
+    for share in (0.02, 0.5, 0.98):
+        _select_case(lib, lens, 2, [max(min(2, S), int(share * S)) for S in lens], scores)
