@@ -250,7 +250,8 @@ PYR_API int pyr_prefill_layer_ex(const void* q, const void* k, const void* v,
  * The whole layer step in as few launches as it takes (Appendix A.1 and the Limitations section: at small
  * batch the cost of selecting the PvC eats the gain - there every launch counts): attention; the score pass,
  * which, when the batch is too small to fill the chip otherwise, splits the heads over several workgroups that
- * write partial sums; the selection, which adds those in a fixed order; ONE gather for K, V, the hidden rows and the position ids.
+ * write partial sums; the selection, which adds those in a fixed order; ONE gather for K, V, the hidden rows and the position ids
+ * (in the selection's launch where there are only few rows).
  * pyr_prefill_layer and pyr_prefill_layer_ex are this call without the hidden rows.
  *   hidden             dev, rows of hidden_row_bytes bytes (a multiple of 16) indexed by packed row; hidden_out
  *                      dev [sum k_b rows], written; both NULL skips them
@@ -284,8 +285,9 @@ PYR_API int pyr_prefill_layer_fused(const void* q, const void* k, const void* v,
  *   kept_idx, out_offsets_dev, k_out, v_out: as in pyr_prefill_layer (out of place: k_out
  *                      must not overlap k)
  *   workspace          dev, >= pyr_decode_workspace_bytes(), 256-byte aligned
- * Five launches on the stream: softmax statistics of the window rows per range of keys, their
- * fold into row denominators, the score pass, the selection, one gather for K, V and position ids.  The attention
+ * Up to five launches on the stream: softmax statistics of the window rows per range of keys, their
+ * fold into row denominators, the score pass, the selection, one gather for K, V and position ids (or fewer: short
+ * sequences take one walk for the first three, few rows are gathered in the selection's launch).  The attention
  * output of the new token itself is not computed here.
  */
 PYR_API int pyr_decode_workspace_bytes(const pyr_shape* shape, int32_t w, size_t* bytes_out);

@@ -55,16 +55,19 @@ int check_offsets(const int32_t* off, int32_t n_seqs, int32_t total, int32_t max
     return PYR_OK;
 }
 
-int check_keep_len(const int32_t* keep, const int32_t* off, int32_t n_seqs, int32_t w, int64_t* total_kept) {
+int check_keep_len(const int32_t* keep, const int32_t* off, int32_t n_seqs, int32_t w, int64_t* total_kept, int32_t* max_kept) {
     if (keep == nullptr) return PYR_ERR_NULL;
     int64_t sum = 0;
+    int32_t most = 0;
     for (int32_t b = 0; b < n_seqs; ++b) {
         const int32_t len = off[b + 1] - off[b];
         const int32_t lo = w < len ? w : len;
         if (keep[b] < lo || keep[b] > len) return PYR_ERR_KEEP_LEN;
         sum += keep[b];
+        if (keep[b] > most) most = keep[b];
     }
     if (total_kept != nullptr) *total_kept = sum;
+    if (max_kept != nullptr) *max_kept = most;
     return PYR_OK;
 }
 
@@ -208,7 +211,7 @@ int pyr_select(const float* scores,
     BatchInfo info;
     int rc = check_offsets(seq_offsets_host, n_seqs, seq_offsets_host[n_seqs < 0 ? 0 : n_seqs], -1, &info);
     if (rc != PYR_OK) return rc;
-    rc = check_keep_len(keep_len_host, seq_offsets_host, n_seqs, w, nullptr);
+    rc = check_keep_len(keep_len_host, seq_offsets_host, n_seqs, w, nullptr, nullptr);
     if (rc != PYR_OK) return rc;
     return pyr::launch_select(nullptr, 1, 0, const_cast<float*>(scores), seq_offsets_dev, keep_len_dev, n_seqs, info.max_len, w,
                               kept_idx, out_offsets_dev, (hipStream_t)stream);
@@ -292,7 +295,8 @@ int pyr_prefill_layer_fused(const void* q, const void* k, const void* v,
     rc = check_offsets(seq_offsets_host, shape->n_seqs, shape->total_tokens, shape->max_seqlen, &info);
     if (rc != PYR_OK) return rc;
     int64_t total_kept = 0;
-    rc = check_keep_len(keep_len_host, seq_offsets_host, shape->n_seqs, w, &total_kept);
+    int32_t max_kept = 0;
+    rc = check_keep_len(keep_len_host, seq_offsets_host, shape->n_seqs, w, &total_kept, &max_kept);
     if (rc != PYR_OK) return rc;
     size_t need = 0;
     rc = pyr_workspace_bytes(shape, w, &need);
@@ -312,29 +316,23 @@ int pyr_prefill_layer_fused(const void* q, const void* k, const void* v,
     s.max_seqlen = info.max_len;
 
     // four launches (five for a ragged batch: the tile map): attention; the score pass; the selection, which also adds
-    // the partial sums of a score pass that was split; one gather for everything
+    // the partial sums of a score pass that was split; one gather for everything (a small batch's in the selection's launch)
     rc = pyr::launch_attention(q, k, v, seq_offsets_dev, seq_offsets_host, s, info.uniform_len, c, out, lse, tile_map, st);
     if (rc != PYR_OK) return rc;
     int groups = 1;
     rc = pyr::launch_score_groups(q, k, lse, seq_offsets_dev, seq_offsets_host, s, info.min_len, w, c, row_weights_dev, scores, parts, &groups, st);
     if (rc != PYR_OK) return rc;
-    rc = pyr::launch_select(parts, groups, s.total_tokens, scores, seq_offsets_dev, keep_len_dev, s.n_seqs, info.max_len, w, kept_idx,
-                            out_offsets_dev, st);
-    if (rc != PYR_OK) return rc;
-    if (total_kept > 0) {
-        const void* srcs[3];
-        void* dsts[3];
-        size_t rows[3];
-        int n = 0;
-        if (k_out != nullptr) {
-            const size_t kv_row = (size_t)shape->n_kv_heads * shape->head_dim * 2;
-            srcs[n] = k; dsts[n] = k_out; rows[n++] = kv_row;
-            srcs[n] = v; dsts[n] = v_out; rows[n++] = kv_row;
-        }
-        if (hidden != nullptr) { srcs[n] = hidden; dsts[n] = hidden_out; rows[n++] = hidden_row_bytes; }
-        rc = pyr::launch_gather_multi(n, srcs, dsts, rows, pos, pos_out, kept_idx, total_kept, st);
+    pyr::GatherSources g{};
+    if (k_out != nullptr) {
+        const size_t kv_row = (size_t)shape->n_kv_heads * shape->head_dim * 2;
+        g.add(k, k_out, kv_row);
+        g.add(v, v_out, kv_row);
     }
-    return rc;
+    if (hidden != nullptr) g.add(hidden, hidden_out, hidden_row_bytes);
+    g.pos = pos;
+    g.pos_out = pos_out;
+    return pyr::launch_select_gather(parts, groups, s.total_tokens, scores, seq_offsets_dev, keep_len_dev, s.n_seqs, info.max_len, max_kept,
+                                     total_kept, w, kept_idx, out_offsets_dev, g, st);
 }
 
 int pyr_prefill_layer_static(const void* q, const void* k, const void* v,
@@ -407,7 +405,8 @@ int pyr_decode_update(const void* q_win, const void* k, const void* v,
     rc = check_offsets(seq_offsets_host, shape->n_seqs, shape->total_tokens, shape->max_seqlen, &info);
     if (rc != PYR_OK) return rc;
     int64_t total_kept = 0;
-    rc = check_keep_len(keep_len_host, seq_offsets_host, shape->n_seqs, w, &total_kept);
+    int32_t max_kept = 0;
+    rc = check_keep_len(keep_len_host, seq_offsets_host, shape->n_seqs, w, &total_kept, &max_kept);
     if (rc != PYR_OK) return rc;
     size_t need = 0;
     rc = pyr_decode_workspace_bytes(shape, w, &need);
@@ -423,17 +422,16 @@ int pyr_decode_update(const void* q_win, const void* k, const void* v,
     rc = pyr::launch_window_score(q_win, k, seq_offsets_dev, seq_offsets_host, s, info.min_len, w, scale_log2(softmax_scale, shape->head_dim),
                                   row_weights_dev, lse_win, part, scores, &groups, st);
     if (rc != PYR_OK) return rc;
-    rc = pyr::launch_select((const float*)part, groups, s.total_tokens, scores, seq_offsets_dev, keep_len_dev, s.n_seqs, info.max_len,
-                            w, kept_idx, out_offsets_dev, st);
-    if (rc != PYR_OK) return rc;
-    if (total_kept > 0) {                             // K, V and the position ids in one launch
+    pyr::GatherSources g{};
+    if (k_out != nullptr) {
         const size_t row_bytes = (size_t)shape->n_kv_heads * shape->head_dim * 2;
-        const void* srcs[2] = {k, v};
-        void* dsts[2] = {k_out, v_out};
-        const size_t rows[2] = {row_bytes, row_bytes};
-        rc = pyr::launch_gather_multi(k_out != nullptr ? 2 : 0, srcs, dsts, rows, pos, pos_out, kept_idx, total_kept, st);
+        g.add(k, k_out, row_bytes);
+        g.add(v, v_out, row_bytes);
     }
-    return rc;
+    g.pos = pos;
+    g.pos_out = pos_out;
+    return pyr::launch_select_gather((const float*)part, groups, s.total_tokens, scores, seq_offsets_dev, keep_len_dev, s.n_seqs, info.max_len,
+                                     max_kept, total_kept, w, kept_idx, out_offsets_dev, g, st);
 }
 
 }  // extern "C"

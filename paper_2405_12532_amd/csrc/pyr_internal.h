@@ -28,15 +28,32 @@ int device_info(DeviceInfo* out);
 int launch_gather(const void* src0, void* dst0, const void* src1, void* dst1, size_t row_bytes,
                   const int32_t* kept_idx, int64_t n_kept, hipStream_t stream);
 
-// up to three row sources (row_bytes[i] a multiple of 16) and, if pos != nullptr, the position ids, in one launch
-int launch_gather_multi(int n, const void* const* srcs, void* const* dsts, const size_t* row_bytes, const int32_t* pos,
-                        int32_t* pos_out, const int32_t* kept_idx, int64_t n_kept, hipStream_t stream);
+// up to three row sources (chunks of 16 bytes) and, if pos != nullptr, the position ids, in one launch
+struct GatherSources {
+    const u32x4* src[3];
+    u32x4* dst[3];
+    int32_t chunks[3];            // 16-byte chunks per row
+    int32_t n;
+    const int32_t* pos;
+    int32_t* pos_out;
+    void add(const void* from, void* to, size_t row_bytes) {
+        src[n] = (const u32x4*)from;
+        dst[n] = (u32x4*)to;
+        chunks[n++] = (int32_t)(row_bytes / 16);
+    }
+};
+int launch_gather_multi(const GatherSources& sources, const int32_t* kept_idx, int64_t n_kept, hipStream_t stream);
 
 // groups > 1: parts holds `groups` rows of total_tokens partial scores, whose sums the kernel writes to `scores` and ranks;
 // else `scores` is only read.
 int launch_select(const float* parts, int groups, int32_t total_tokens, float* scores, const int32_t* seq_offsets_dev,
                   const int32_t* keep_len_dev, int32_t n_seqs, int32_t max_seqlen, int32_t w, int32_t* kept_idx,
                   int32_t* out_offsets_dev, hipStream_t stream);
+
+// The selection and the gather of what it keeps, in one launch where the batch is small enough for that to be faster.
+int launch_select_gather(const float* parts, int groups, int32_t total_tokens, float* scores, const int32_t* seq_offsets_dev,
+                         const int32_t* keep_len_dev, int32_t n_seqs, int32_t max_seqlen, int32_t max_kept, int64_t n_kept, int32_t w,
+                         int32_t* kept_idx, int32_t* out_offsets_dev, const GatherSources& sources, hipStream_t stream);
 
 int launch_attention(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev,
                      const int32_t* seq_offsets_host, const pyr_shape& shape, int32_t uniform_len, float scale_log2,

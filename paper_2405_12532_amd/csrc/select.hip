@@ -1,10 +1,45 @@
 // Launch of the segmented top-k (Algorithm 1, TopP(A_e, p); see select_device.h): one workgroup per sequence.
+#include "gather_device.h"
 #include "select_device.h"
 
 namespace pyr {
 namespace {
 
+constexpr int kFusedLanes = 512;
 constexpr int kLdsKeys = 36864;            // 144 KiB of the 160 KiB LDS of a gfx950 compute unit
+
+// kept_idx and out_offsets of sequence b
+struct ToMemory {
+    int32_t *kept_idx, *out_offsets;
+    int b;
+    __device__ void begin(int base, int rows) {
+        kept_idx += base;
+        if (threadIdx.x != 0) return;
+        out_offsets[b + 1] = base + rows;
+        if (b == 0) out_offsets[0] = 0;
+    }
+    __device__ void operator()(int rank, int32_t row) { kept_idx[rank] = row; }
+};
+
+// The same, by the workgroups of a sequence together: this one keeps the ranks [lo, hi) in LDS and writes them.
+struct ToPart {
+    ToMemory memory;
+    int32_t* rows;                     // LDS
+    int part, parts, room, base, lo, hi;
+    __device__ void begin(int first, int n) {
+        const int size = (n + parts - 1) / parts;
+        base = first;
+        lo = min(n, part * size);
+        hi = min(n, lo + min(size, room));
+        if (part == 0) memory.begin(first, n);
+        else memory.kept_idx += first;
+    }
+    __device__ void operator()(int rank, int32_t row) {
+        if (rank < lo || rank >= hi) return;
+        rows[rank - lo] = row;
+        memory(rank, row);
+    }
+};
 
 template <int kT, KeySource kSource>
 __global__ __launch_bounds__(kT) void select_topk_kernel(
@@ -13,7 +48,33 @@ __global__ __launch_bounds__(kT) void select_topk_kernel(
     int32_t* __restrict__ kept_idx, int32_t* __restrict__ out_offsets) {
     extern __shared__ uint32_t lds_keys[];
     __shared__ SelectShared<kT> sh;
-    select_sequence<kT, kSource>(blockIdx.x, parts, groups, total_tokens, scores, seq_offsets, keep_len, w, lds_keys, &sh, kept_idx, out_offsets);
+    ToMemory sink{kept_idx, out_offsets, (int)blockIdx.x};
+    select_sequence<kT, kSource>(blockIdx.x, parts, groups, total_tokens, scores, true, seq_offsets, keep_len, w, lds_keys, &sh, sink);
+}
+
+// The selection and the gather of a small batch in one launch: `split` workgroups per sequence, each of which finds the threshold for
+// itself and copies its part of the kept rows (`room` at most).  Bound: latency, and a launch less of it.
+__global__ __launch_bounds__(kFusedLanes, 8) void select_gather_kernel(
+    const float* __restrict__ parts, int32_t groups, int32_t total_tokens, float* scores,
+    const int32_t* __restrict__ seq_offsets, const int32_t* __restrict__ keep_len, int32_t w,
+    int32_t* __restrict__ kept_idx, int32_t* __restrict__ out_offsets, GatherSources g, int32_t split, int32_t room) {
+    extern __shared__ int32_t rows[];
+    __shared__ SelectShared<kFusedLanes> sh;
+    const int b = (int)blockIdx.x / split, part = (int)blockIdx.x - b * split;
+    ToPart sink{{kept_idx, out_offsets, b}, rows, part, split, room, 0, 0, 0};
+    select_sequence<kFusedLanes, kInRegisters>(b, parts, groups, total_tokens, scores, part == 0, seq_offsets, keep_len, w, nullptr, &sh, sink);
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), n = sink.hi - sink.lo;
+    const int64_t first = (int64_t)sink.base + sink.lo;
+    for (int i = wave; i < n * g.n; i += kFusedLanes / 64) {
+        const int y = i / n, j = i - y * n;
+        const u32x4* src = y == 0 ? g.src[0] : y == 1 ? g.src[1] : g.src[2];
+        u32x4* dst = y == 0 ? g.dst[0] : y == 1 ? g.dst[1] : g.dst[2];
+        const int32_t chunks = y == 0 ? g.chunks[0] : y == 1 ? g.chunks[1] : g.chunks[2];
+        copy_row(src + (int64_t)__builtin_amdgcn_readfirstlane(rows[j]) * chunks, dst + (first + j) * chunks, chunks, lane);
+    }
+    if (g.pos != nullptr)
+        for (int j = threadIdx.x; j < n; j += kFusedLanes) g.pos_out[first + j] = g.pos[rows[j]];
 }
 
 template <int kT, KeySource kSource>
@@ -45,6 +106,30 @@ int launch_select(const float* parts, int groups, int32_t total_tokens, float* s
                       : max_seqlen <= 1024 * kRegKeys ? launch_select_t<1024, kInRegisters>
                       : max_seqlen <= kLdsKeys ? launch_select_t<1024, kInLds> : launch_select_t<1024, kInMemory>;
     return launch(parts, groups, total_tokens, scores, seq_offsets_dev, keep_len_dev, n_seqs, max_seqlen, w, kept_idx, out_offsets_dev, stream);
+}
+
+int launch_select_gather(const float* parts, int groups, int32_t total_tokens, float* scores, const int32_t* seq_offsets_dev,
+                         const int32_t* keep_len_dev, int32_t n_seqs, int32_t max_seqlen, int32_t max_kept, int64_t n_kept, int32_t w,
+                         int32_t* kept_idx, int32_t* out_offsets_dev, const GatherSources& g, hipStream_t stream) {
+    // One launch where the rows to copy are so few that the selection's own workgroups are enough for them; counted as if every
+    // sequence kept as many as the one that keeps most, because all get the same number of workgroups.  Whole calls, two launches / one
+    // (us): a 64-token layer on 32 heads (1.0 MB) 18.3 / 16.0, 256 tokens on 8 heads, d = 64 (0.3 MB) 18.5 / 17.2, updates of 16 x 70
+    // rows (2.6 MB) 16.5 / 14.8, of 1 x 176 (3.1 MB) 15.2 / 15.7, of 6 x 368 (5.4 MB) 14.9 / 16.1, of 16 x 512 (120 MB) 69.6 / 68.9...74.8;
+    // 256 workgroups instead of 192 differ by 1 % either way, 64 cost up to 10 % at the upper end.
+    constexpr int64_t kFewBytes = 3000000;
+    constexpr int kFusedGroups = 192;
+    int64_t row_chunks = 0;
+    for (int i = 0; i < g.n; ++i) row_chunks += g.chunks[i];
+    if (n_seqs > 0 && max_kept > 0 && row_chunks > 0 && max_seqlen <= kFusedLanes * kRegKeys && row_chunks <= kFewBytes / 16 &&
+        row_chunks * max_kept <= kFewBytes / 16 && row_chunks * max_kept * n_seqs <= kFewBytes / 16) {
+        const int split = (kFusedGroups + n_seqs - 1) / n_seqs, room = (max_kept + split - 1) / split;
+        hipLaunchKernelGGL(select_gather_kernel, dim3((unsigned)(split * n_seqs)), dim3(kFusedLanes), (size_t)room * sizeof(int32_t), stream, parts,
+                           (int32_t)groups, total_tokens, scores, seq_offsets_dev, keep_len_dev, w, kept_idx, out_offsets_dev, g, (int32_t)split,
+                           (int32_t)room);
+        return check_launch();
+    }
+    const int rc = launch_select(parts, groups, total_tokens, scores, seq_offsets_dev, keep_len_dev, n_seqs, max_seqlen, w, kept_idx, out_offsets_dev, stream);
+    return rc != PYR_OK ? rc : launch_gather_multi(g, kept_idx, n_kept, stream);
 }
 
 }  // namespace pyr

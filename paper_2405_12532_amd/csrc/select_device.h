@@ -185,13 +185,13 @@ __device__ uint64_t find_threshold(const Each& each, int need, uint32_t kmin, ui
 }
 
 // The selection of sequence b by the calling workgroup (all kT lanes take part; uniform control
-// flow).  groups > 1: the scores are first added up from parts[groups][total_tokens], in order, and written.
+// flow).  groups > 1: the scores are first added up from parts[groups][total_tokens], in order, and written by the workgroup that is to.
 // kInRegisters: sequences of kRegKeys * kT tokens at most; kInLds: lds_keys has room for a sequence.
-// Also writes out_offsets[b + 1] (and out_offsets[0] for b == 0).
-template <int kT, KeySource kSource>
-__device__ void select_sequence(int b, const float* __restrict__ parts, int groups, int32_t total_tokens, float* scores,
+// sink.begin(first place, number of rows) is called once, sink(rank, row) for every kept row.
+template <int kT, KeySource kSource, class Sink>
+__device__ void select_sequence(int b, const float* __restrict__ parts, int groups, int32_t total_tokens, float* scores, bool write_scores,
                                 const int32_t* __restrict__ seq_offsets, const int32_t* __restrict__ keep_len, int32_t w, uint32_t* lds_keys,
-                                SelectShared<kT>* sh, int32_t* __restrict__ kept_idx, int32_t* __restrict__ out_offsets) {
+                                SelectShared<kT>* sh, Sink& sink) {
     constexpr int kW = kT / 64, kRegs = kSource == kInRegisters ? kRegKeys : 1;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t row0 = seq_offsets[b];
@@ -244,7 +244,7 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
                     const uint32_t key = ordered_key(x[u]);
                     if (kSource == kInRegisters) keys[u] = key;
                     if (i >= end) continue;
-                    if (groups > 1) sc[i] = x[u];
+                    if (groups > 1 && write_scores) sc[i] = x[u];
                     if (i >= C) continue;
                     if (kSource == kInLds) lds_keys[i] = key;
                     kmin = min(kmin, key);
@@ -275,17 +275,13 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
         kmin = min(kmin, sh->wave_min[u]);
         kmax = max(kmax, sh->wave_max[u]);
     }
-    if (tid == 0) {
-        out_offsets[b + 1] = out_base + k;
-        if (b == 0) out_offsets[0] = 0;
-    }
-    int32_t* __restrict__ out = kept_idx + out_base;
+    sink.begin(out_base, k);
 
     // the recent window is always kept (A_e ranks the columns before it only)
-    for (int i = tid; i < L; i += kT) out[need + i] = row0 + C + i;
+    for (int i = tid; i < L; i += kT) sink(need + i, row0 + C + i);
     if (need == 0) return;
     if (need == C) {                            // nothing to evict: identity
-        for (int i = tid; i < C; i += kT) out[i] = row0 + i;
+        for (int i = tid; i < C; i += kT) sink(i, row0 + i);
         return;
     }
 
@@ -319,7 +315,7 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
     each([&](uint32_t key, int i, bool valid) {
         const bool keep = valid && ranked(key, i) >= threshold;
         const uint64_t mask = __ballot(keep);
-        if (keep) out[to + __popcll(mask & lt)] = row0 + i;
+        if (keep) sink(to + __popcll(mask & lt), row0 + i);
         to += __popcll(mask);
     });
 }
