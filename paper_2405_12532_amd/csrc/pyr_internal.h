@@ -105,6 +105,10 @@ int launch_window(const void* q, const void* k, const int32_t* seq_offsets_dev, 
                   int32_t q_window, float scale_log2, const float* row_weights, float* sums, const WindowPlan& plan, const DeviceInfo& dev,
                   hipStream_t stream);
 
+// scores[t] = the sum of `groups` rows of partial sums; whether that is worth a launch in front of the selection.
+inline bool sums_pay(int groups, int32_t max_seqlen) { return groups >= 48 || (groups >= 24 && groups * (int64_t)max_seqlen >= 36864); }
+int launch_sum_parts(const float* parts, int groups, int32_t total_tokens, float* scores, hipStream_t stream);
+
 int launch_gather_positions(const int32_t* pos, const int32_t* kept_idx, int64_t n_kept, int32_t* pos_out,
                             hipStream_t stream);
 

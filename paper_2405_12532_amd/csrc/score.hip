@@ -729,11 +729,12 @@ struct UpdatePlan {
 
 // Partial sums of the scores go where the statistics lie, which are dead once folded: as many rows as fit.
 // One walk reads K once and is one launch where two walks are three, but it has the window's rows in blocks of 32 and its loads go by once
-// per block: it wins where row blocks per KV head are few or sequences short.  Measured, two walks / one walk with the selection (us): 88 x
-// 692, 64 heads, w = 64 410 / 253, 22 of 286...914, 32 heads, w = 32 61 / 34, 5 x 199, 16/2 heads, d = 64 19.5 / 12.8; but 23 of
-// 1243...1911, 32/8 heads, w = 64 89 / 104, 33 x 807, 24 heads, w = 256 173 / 207, 1 x 1782, 64 heads, w = 128 35 / 47.  Both costs
-// are predicted (the two walks' with the fold and the selection, to 10 %) and one walk is taken where it is a tenth lower: over 270 calls
-// that takes 18 % off in the mean, where the better one of both would take 19 %, and leaves three slower, by 5, 8 and 17 %.
+// per block: it wins where row blocks per KV head are few or sequences short.  Whole updates, two walks / one walk (us): 1 x 1024 rows on
+// 32 heads, w = 64 28.2 / 23.1, 4 x 1537 71.8 / 61, 5 x 1330 on 8 heads, d = 64, w = 128 27.1 / 22.2, 48 of 689 at most on 24 heads, w = 32
+// 135.6 / 100; but 18 x 826 on 64/8 heads, w = 16 55.8 / 74.5, 57 of 1066 at most on 32/8 heads, d = 64, w = 48 87 / 111.  Both costs
+// are predicted (the two walks' with the fold and the selection, to 10 %) and one walk is taken where it is 11.5 % lower: over 160 updates
+// of random shapes two walks take 23 % longer than the best cut of either form in the mean, the choice 1 % longer; where it takes
+// one walk against the faster two, it loses 3 % at most; at 0.9 5 % (59 of 1825 at most), at 1.0 33 %.
 UpdatePlan plan_update(const pyr_shape& s, const BatchCut& cut, int32_t w, const DeviceInfo& dev) {
     UpdatePlan p{};
     const size_t room = window_score_part_bytes(s, w), row = (size_t)s.total_tokens * sizeof(float);
@@ -743,7 +744,7 @@ UpdatePlan plan_update(const pyr_shape& s, const BatchCut& cut, int32_t w, const
     p.scores = plan_strip(s, cut, w, dev, 1, split, true);
     p.window = plan_window(s, cut.tiles, w, room / row < 1 ? 1 : room / row > 256 ? 256 : (int)(room / row), dev);
     const double folded = (double)s.n_seqs * w * s.n_q_heads * ((s.max_seqlen + 63) / 64);
-    p.one_walk = p.window.waves > 0 && p.window.cost < 0.9 * (11.5 + 1.16 * p.stats.cost + 0.86 * p.scores.cost + 7.6e-6 * folded);
+    p.one_walk = p.window.waves > 0 && p.window.cost < 0.885 * (11.5 + 1.16 * p.stats.cost + 0.86 * p.scores.cost + 7.6e-6 * folded);
     return p;
 }
 

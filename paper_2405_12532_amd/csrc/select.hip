@@ -111,6 +111,14 @@ int launch_select(const float* parts, int groups, int32_t total_tokens, float* s
 int launch_select_gather(const float* parts, int groups, int32_t total_tokens, float* scores, const int32_t* seq_offsets_dev,
                          const int32_t* keep_len_dev, int32_t n_seqs, int32_t max_seqlen, int32_t max_kept, int64_t n_kept, int32_t w,
                          int32_t* kept_idx, int32_t* out_offsets_dev, const GatherSources& g, hipStream_t stream) {
+    // Rows of partial sums that would take the selection's one workgroup longer than a launch that adds them with the whole chip (1.7 us):
+    // updates with / without that launch, at 32 heads, w = 64: 64 rows of 200 tokens 20.6 / 21.8, of 1024 23.1 / 26.4, of 1537 28.3 / 31.5,
+    // 32 rows of 700 29.8 / 29.3, of 1024 33.8 / 33.3, of 1537 36.5 / 37.3, 16 rows of 2048 70.3 / 69.4.
+    if (groups > 1 && sums_pay(groups, max_seqlen)) {
+        const int rc = launch_sum_parts(parts, groups, total_tokens, scores, stream);
+        if (rc != PYR_OK) return rc;
+        groups = 1;
+    }
     // One launch where the rows to copy are so few that the selection's own workgroups are enough for them; counted as if every
     // sequence kept as many as the one that keeps most, because all get the same number of workgroups.  Whole calls, two launches / one
     // (us): a 64-token layer on 32 heads (1.0 MB) 18.3 / 16.0, 256 tokens on 8 heads, d = 64 (0.3 MB) 18.5 / 17.2, updates of 16 x 70

@@ -6,6 +6,32 @@
 namespace pyr {
 namespace {
 
+// scores[t] = the sum of parts[0 .. groups)[t]: 64 tokens a workgroup, whose wavefronts take every kSumWaves-th row and meet in LDS.
+// Bound: the latency of one trip to memory up to 64 rows, 1.7 us with its launch; the selection's one workgroup, which has room for 16 rows
+// of 1024 tokens on their way at a time, took 5 us for 64 rows of 1537.
+constexpr int kSumWaves = 8;
+__global__ __launch_bounds__(64 * kSumWaves) void sum_parts_kernel(const float* __restrict__ parts, int32_t groups, int32_t total_tokens,
+                                                                   float* __restrict__ scores) {
+    __shared__ float sums[kSumWaves][64];
+    constexpr int kAhead = 8;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t t = (int64_t)blockIdx.x * 64 + lane;
+    float x = 0.f;
+    for (int g0 = wave; g0 < groups; g0 += kSumWaves * kAhead) {
+        float y[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) y[u] = t < total_tokens && g0 + u * kSumWaves < groups ? parts[(size_t)(g0 + u * kSumWaves) * total_tokens + t] : 0.f;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) x += y[u];
+    }
+    sums[wave][lane] = x;
+    __syncthreads();
+    if (wave != 0 || t >= total_tokens) return;
+#pragma unroll
+    for (int u = 1; u < kSumWaves; ++u) x += sums[u][lane];
+    scores[t] = x;
+}
+
 template <int D, int kTiles, bool kWeighted>
 __global__ __launch_bounds__(64 * kWindowWaves, 2) void window_kernel(WindowArgs a) {
     extern __shared__ __align__(1024) char smem[];
@@ -55,10 +81,11 @@ int launch_window_d(const WindowArgs& a, int32_t max_seqlen, unsigned grid, int 
 //   (query rows count as one) where its latencies set the time, and 0.2 + 0.55 per tile times the wavefronts of its SIMD where they
 //   wait for each other, 0.79 of that at d = 64;
 // - the stream: a tile of K takes a compute unit's share of the memory system 0.236 from HBM and 0.218 from L2 to every task.
-// A row of partial sums costs the selection 0.035 and 0.1 per 1000 tokens.
+// A row of partial sums costs the selection 0.03; where they are added in a launch of their own, that costs 1.7 and 3 per million.
 // Fitted to 270 calls (eleven head shapes, w = 16...256, one sequence to 160, 33...2048 tokens, equal and ragged), each timed with
 // up to 50 cuts: predictions near a call's best have a standard deviation of 11 %, the cut chosen takes 2.9 % longer than the best one in
-// the mean.  One wavefront is left to sequences of one tile: more of them hide each other's latency less well than predicted.
+// the mean (before that launch).  Seven wavefronts are left out where there is work for eight, which were 1 to 5 % faster at every such
+// choice (2 x 889 on 12 heads, d = 64 16.2 / 15.4 us a call).  One wavefront is left to sequences of one tile: more of them hide each other's latency less well than predicted.
 WindowPlan plan_window(const pyr_shape& s, double tiles, int32_t w, int max_groups, const DeviceInfo& dev) {
     WindowPlan best{0, 0, 1e300};
     if (s.max_seqlen > kWindowMaxKeys) return best;
@@ -68,14 +95,15 @@ WindowPlan plan_window(const pyr_shape& s, double tiles, int32_t w, int max_grou
     const int fewest = (max_tiles + kWindowMaxTiles - 1) / kWindowMaxTiles, most = max_tiles < kWindowWaves ? max_tiles : kWindowWaves;
     const double size = s.head_dim / 128.0, k = d64 ? 0.79 : 1.0;
     const double flow = tiles * (0.236 * s.n_kv_heads + 0.218 * tasks) * size / dev.compute_units;
-    const double per_row = 0.035 + 1e-4 * s.max_seqlen;
     const int limit = (int)(tasks < max_groups ? tasks : max_groups);
     for (int waves = fewest > 1 || most == 1 ? fewest : 2; waves <= most; ++waves) {
+        if (waves == 7 && most == 8) continue;
         const int wave_tiles = (max_tiles + waves - 1) / waves;
         // (workgroups a compute unit holds: 8 wavefronts by registers, 12 of up to two tiles; 160 KB of LDS)
         const int by_registers = (wave_tiles <= 2 ? 12 : 8) / waves;
         const int bytes = window_bytes(d64, wave_tiles, waves);
         const int by_lds = 160 * 1024 / bytes, per_cu = by_lds < by_registers ? by_lds : by_registers;
+        const double per_wave = (double)max_tiles / waves;
         const double mean_tiles = tiles == (double)s.n_seqs * max_tiles ? wave_tiles : tiles / s.n_seqs / waves + 0.5 * (1.0 - 1.0 / waves);
         for (int g = 1, last = 0; !last; g = 2 * g) {
             if (g >= limit || g >= 256) {
@@ -86,7 +114,7 @@ WindowPlan plan_window(const pyr_shape& s, double tiles, int32_t w, int max_grou
             const double there = ceil(wgs / dev.compute_units), on_simd = (there < per_cu ? there : per_cu) * waves / 4;
             const double own = on_simd > 1.0 ? on_simd : 1.0;
             const auto task = [&](double t) {
-                const double alone = 1.02 * k * (t + 1), shared = (0.2 + 0.55 * k * (t + 1)) * own;
+                const double alone = 1.02 * k * (t + 1), shared = (0.2 + 0.55 * k * (t < per_wave ? t + 1 : per_wave + 1)) * own;
                 return alone > shared ? alone : shared;
             };
             const double longest = task_rounds * task(wave_tiles);
@@ -95,8 +123,8 @@ WindowPlan plan_window(const pyr_shape& s, double tiles, int32_t w, int max_grou
                 const double mean = task_rounds * task(mean_tiles), all = wgs * mean / slots;
                 chain = 3.1 + (all > longest ? all : longest) + (wgs < 8 * slots ? 0.5 : 0.25) * mean;
             }
-            const double cost = 6.0 + sqrt(sqrt(chain * chain * chain * chain + flow * flow * flow * flow)) + per_row * (g - 1);
-            if (cost < best.cost) best = WindowPlan{waves, g, cost};
+            const double cost = 6.0 + sqrt(sqrt(chain * chain * chain * chain + flow * flow * flow * flow)) + (sums_pay(g, s.max_seqlen) ? 1.7 + 3e-6 * g * s.total_tokens : 0.03 * (g - 1));
+            if (cost <= best.cost) best = WindowPlan{waves, g, cost};
         }
     }
     return best;
@@ -122,6 +150,12 @@ int launch_window(const void* q, const void* k, const int32_t* seq_offsets_dev, 
     const int64_t n = (int64_t)s.n_seqs * plan.groups;
     if (n >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
     return s.head_dim == 128 ? launch_window_d<128>(a, s.max_seqlen, (unsigned)n, plan.waves, stream) : launch_window_d<64>(a, s.max_seqlen, (unsigned)n, plan.waves, stream);
+}
+
+int launch_sum_parts(const float* parts, int groups, int32_t total_tokens, float* scores, hipStream_t stream) {
+    hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)((total_tokens + (int64_t)63) / 64)), dim3(64 * kSumWaves), 0, stream, parts, (int32_t)groups,
+                       total_tokens, scores);
+    return check_launch();
 }
 
 }  // namespace pyr

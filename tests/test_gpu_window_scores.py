@@ -30,12 +30,15 @@ ONE_WALK = [
     ((2047, 2048, 2020, 2017, 1999, 2047), 16, 16, 64, 32),     # the longest sequences
     ((2048,) * 8, 16, 16, 128, 16),
     ((300,) * 16, 8, 8, 128, 64),                               # a sequence's workgroups on one XCD
+    ((1030,), 32, 32, 64, 64),                                  # 64 rows of partial sums, added by a launch of their own
+    ((70, 0, 513, 3), 24, 24, 64, 64),                          # ... 48, their number not a multiple of 64 tokens
+    ((1537, 1100), 9, 9, 64, 128),                              # ... fewer, but of many tokens
     ((200,) * 90, 16, 16, 64, 32),                              # several rounds of workgroups, several tasks each
 ]
 TWO_WALKS = [
     ((2049,), 4, 4, 64, 16),                                    # a key too many
     ((120,) * 60, 32, 1, 128, 128),                             # many row blocks per KV head: one lane folds a row's one range
-    ((250,) * 20, 32, 1, 128, 256),
+    ((250,) * 30, 32, 1, 128, 256),
     ((1200, 700), 8, 8, 64, 40),                                # few heads
 ]
 
