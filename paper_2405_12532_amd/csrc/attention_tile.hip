@@ -625,7 +625,10 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
     // tiles that run together then share their K/V rows in L2 (us, two rounds of workgroups to a chunk / now: 64 x 359
     // 190 / 173, 64 x 269 154 / 136, 64 x 512 282 / 258; d = 64: 64 x 500 153 / 147).  All units where they are few and the
     // grid is at most eight rounds: what counts there is that nothing long starts late (3 x 5000 tokens, 24 heads,
-    // nine units per XCD: 533 in chunks of four, 459 in one).
+    // nine units per XCD: 533 in chunks of four, 459 in one).  At d = 64 unequal
+    // sequences, whose chunks end unevenly, go in one up to twice as many units (17 x 609...3417 tokens on 8 heads 94 / 70, 14 x
+    // 677...3181 on 12 heads 139 / 114, 17 x 148...911 26.8 / 21.7; 30 batches drawn there 0.81 to 1.01 of the time; but 24 equal ones of 1500
+    // on 12 heads 109 / 119, 59 of 487...799 71.5 / 81.5; at d = 128, twenty batches 0.88 to 1.07).
     const int tiles = (s.max_seqlen + kRows - 1) / kRows, head_group = s.n_q_heads / s.n_kv_heads;
     const int slots = dev.compute_units / a.xcds * (groups == 2 ? 1 : s.head_dim == 128 ? 2 : 3);
     const int units_per_xcd = (a.n_units + a.xcds - 1) / a.xcds;
@@ -655,7 +658,10 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
         const int per_seq = s.n_kv_heads % a.xcds == 0 ? s.n_kv_heads / a.xcds : 1;
         chunk = per_seq * (target < 2 * per_seq ? 1 : (target + per_seq / 2) / per_seq);
     }
-    if (units_per_xcd <= slots / 6 && units_per_xcd * unit_tiles <= 8 * (int64_t)slots) chunk = units_per_xcd;
+    const int64_t places = units_per_xcd * unit_tiles;
+    const bool few = units_per_xcd <= slots / 6 && places <= 8 * (int64_t)slots;
+    const bool few_unequal = uniform_len == 0 && s.head_dim == 64 && units_per_xcd <= 2 * slots / 5 && places <= 8 * (int64_t)slots;
+    if (few || few_unequal) chunk = units_per_xcd;
     if (chunk > units_per_xcd) chunk = units_per_xcd;
     if (chunk < (units_per_xcd + kMaxGrid - 1) / kMaxGrid) chunk = (units_per_xcd + kMaxGrid - 1) / kMaxGrid;
     const int chunks = (units_per_xcd + chunk - 1) / chunk;
