@@ -16,9 +16,12 @@
 //   ten octaves fill all bins (with leading bits 120 of 2048: five lanes of a wavefront on one bin, and bins too full to stop at);
 // - a bin of at most kCandidates keys ends the search: they are ranked against each other by value and position.
 // One pass over the bins at the score distributions of the method.
+// - beyond the registers' reach, whole blocks of a wavefront's positions go without the checks of the last one (half the instructions, which
+//   is what 16 keys a lane and more wait for: 16384 tokens 13.9 -> 10.8, 60000 69 -> 39).
 // us per launch, leading bits in digits of 11 from LDS / now (a launch that does nothing takes 4 of these): one sequence of
-// 256 tokens 5.1 / 4.2, of 2048 6.5 / 4.6, of 8192 11.4 / 8.2, four of 32768 28.6 / 23.1, two of 60000 73 / 69.
-// (32 instead of 8 scores a lane has in flight while they are loaded: 16384 tokens 13.9 -> 14.9, no gain beyond.)
+// 256 tokens 5.1 / 4.2, of 2048 6.5 / 4.7, of 8192 11.4 / 8.2, four of 32768 28.6 / 17.0, two of 60000 73 / 39.
+// Tried and taken back: 32 instead of 8 scores a lane has in flight while they are loaded (16384 tokens 13.9 -> 14.9); the whole blocks for
+// keys in registers too, where the second copy of the code costs more than it saves (4096 tokens 6.4 -> 6.9, 8192 8.2 -> 9.0).
 #pragma once
 
 #include "pyr_internal.h"
@@ -217,11 +220,13 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
         const int end = min(n, lo + seg);
         auto stage = [&](auto ahead, auto rows) {
             constexpr int kAhead = decltype(ahead)::value, kRows = decltype(rows)::value;
-            for (int i0 = lo + lane; i0 < end; i0 += 64 * kAhead) {
+            auto block = [&](int at, auto whole) {      // kAhead * 64 positions; whole: all of them candidates
+                constexpr bool kWhole = decltype(whole)::value != 0;
+                const int i0 = at + lane;
                 float x[kAhead];
                 if (kRows == 1) {
 #pragma unroll
-                    for (int u = 0; u < kAhead; ++u) x[u] = i0 + 64 * u < end ? from[i0 + 64 * u] : 0.f;
+                    for (int u = 0; u < kAhead; ++u) x[u] = kWhole || i0 + 64 * u < end ? from[i0 + 64 * u] : 0.f;
                 } else {
 #pragma unroll
                     for (int u = 0; u < kAhead; ++u) x[u] = 0.f;
@@ -231,7 +236,7 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
                         for (int g = 0; g < kRows; ++g)
 #pragma unroll
                             for (int u = 0; u < kAhead; ++u)
-                                y[g][u] = i0 + 64 * u < end && g0 + g < groups ? from[(size_t)(g0 + g) * total_tokens + i0 + 64 * u] : 0.f;
+                                y[g][u] = (kWhole || i0 + 64 * u < end) && g0 + g < groups ? from[(size_t)(g0 + g) * total_tokens + i0 + 64 * u] : 0.f;
 #pragma unroll
                         for (int g = 0; g < kRows; ++g)
 #pragma unroll
@@ -243,14 +248,18 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
                     const int i = i0 + 64 * u;
                     const uint32_t key = ordered_key(x[u]);
                     if (kSource == kInRegisters) keys[u] = key;
-                    if (i >= end) continue;
+                    if (!kWhole && i >= end) continue;
                     if (groups > 1 && write_scores) sc[i] = x[u];
-                    if (i >= C) continue;
+                    if (!kWhole && i >= C) continue;
                     if (kSource == kInLds) lds_keys[i] = key;
                     kmin = min(kmin, key);
                     kmax = max(kmax, key);
                 }
-            }
+            };
+            int at = lo;
+            if (kSource != kInRegisters)
+                for (; at + 64 * kAhead <= min(end, C); at += 64 * kAhead) block(at, Int<1>{});
+            for (; at < end; at += 64 * kAhead) block(at, Int<0>{});
         };
         if (groups <= 1) stage(Int<8>{}, Int<1>{});
         else if (seg > 256) stage(Int<8>{}, Int<4>{});
@@ -285,6 +294,7 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
         return;
     }
 
+    auto key_at = [&](int i) { return kSource == kInLds ? lds_keys[i] : ordered_key(sc[i]); };
     // use(key, position, whether there is one) for the wavefront's keys in ascending order, all lanes together
     auto each = [&](auto use) {
         if constexpr (kSource == kInRegisters) {
@@ -294,14 +304,20 @@ __device__ void select_sequence(int b, const float* __restrict__ parts, int grou
                 use(keys[u], lo + 64 * u + lane, lo + 64 * u + lane < C);
             }
         } else {
-            constexpr int kAhead = 8;
+            constexpr int kAhead = kSource == kInLds ? 4 : 8;
             const int hi = min(C, lo + seg);
-            for (int i0 = lo + lane; i0 - lane < hi; i0 += 64 * kAhead) {
+            int at = lo;
+            for (; at + 64 * kAhead <= hi; at += 64 * kAhead) {      // (nothing to check: half the instructions)
                 uint32_t x[kAhead];
 #pragma unroll
-                for (int u = 0; u < kAhead; ++u) x[u] = i0 + 64 * u >= hi ? 0u : kSource == kInLds ? lds_keys[i0 + 64 * u] : ordered_key(sc[i0 + 64 * u]);
+                for (int u = 0; u < kAhead; ++u) x[u] = key_at(at + lane + 64 * u);
 #pragma unroll
-                for (int u = 0; u < kAhead; ++u) use(x[u], i0 + 64 * u, i0 + 64 * u < hi);
+                for (int u = 0; u < kAhead; ++u) use(x[u], at + lane + 64 * u, true);
+            }
+#pragma unroll 1
+            for (; at < hi; at += 64) {
+                const int i = at + lane;
+                use(i < hi ? key_at(i) : 0u, i, i < hi);
             }
         }
     };
