@@ -31,7 +31,7 @@
 // ([B, w, Hq, d], right-aligned) and no attention pass has left row denominators behind, so a
 // first pass (kStats; S^T = K Q^T there, a lane follows one window row over its keys) writes, per range, every
 // window row's maximum and sum of exponentials, a small kernel folds them into denominators, and the score pass
-// runs as above.
+// runs as above.  (Sequences of 2048 keys at most may get theirs by one walk instead: window_device.h, plan_update below.)
 //
 // Small batches.  When ranges times wavefronts leave the chip idle, the tasks of a range are also split over
 // gridDim.y workgroups that write partial sums, one row of `sums` each; the selection kernel, which reads

@@ -53,8 +53,9 @@ __global__ __launch_bounds__(kT) void select_topk_kernel(
 }
 
 // The selection and the gather of a small batch in one launch: `split` workgroups per sequence, each of which finds the threshold for
-// itself and copies its part of the kept rows (`room` at most).  Bound: latency, and a launch less of it.
-__global__ __launch_bounds__(kFusedLanes, 8) void select_gather_kernel(
+// itself and copies its part of the kept rows (`room` at most).  Bound: latency, and a launch less of it.  (Held
+// to 64 registers, as if a compute unit had more than one of these workgroups, it spills: 1 to 3 % on the whole call.)
+__global__ __launch_bounds__(kFusedLanes) void select_gather_kernel(
     const float* __restrict__ parts, int32_t groups, int32_t total_tokens, float* scores,
     const int32_t* __restrict__ seq_offsets, const int32_t* __restrict__ keep_len, int32_t w,
     int32_t* __restrict__ kept_idx, int32_t* __restrict__ out_offsets, GatherSources g, int32_t split, int32_t room) {
@@ -121,7 +122,7 @@ int launch_select_gather(const float* parts, int groups, int32_t total_tokens, f
     }
     // One launch where the rows to copy are so few that the selection's own workgroups are enough for them; counted as if every
     // sequence kept as many as the one that keeps most, because all get the same number of workgroups.  Whole calls, two launches / one
-    // (us): a 64-token layer on 32 heads (1.0 MB) 18.3 / 16.0, 256 tokens on 8 heads, d = 64 (0.3 MB) 18.5 / 17.2, updates of 16 x 70
+    // (us): a 64-token layer on 32 heads (1.0 MB) 18.3 / 16.0, 256 tokens on 8 heads, d = 64 (0.3 MB) 18.5 / 16.6, updates of 16 x 70
     // rows (2.6 MB) 16.5 / 14.8, of 1 x 176 (3.1 MB) 15.2 / 15.7, of 6 x 368 (5.4 MB) 14.9 / 16.1, of 16 x 512 (120 MB) 69.6 / 68.9...74.8;
     // 256 workgroups instead of 192 differ by 1 % either way, 64 cost up to 10 % at the upper end.
     constexpr int64_t kFewBytes = 3000000;
