@@ -342,6 +342,17 @@ typedef struct pyr_route {
 PYR_API int pyr_diag_route(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t w, int32_t compute_units,
                            int32_t xcds, pyr_route* route_out);
 
+/*
+ * Diagnostic, not part of the method: what pyr_diag_route leaves out, for the same purpose.  Host only; launches nothing.
+ *   compute_units, xcds  as in pyr_diag_route;  launches_out  host, written
+ */
+typedef struct pyr_launches {
+    int32_t attention_chunk;    /* one 128-row tile per workgroup, not listed: KV heads of a sequence that an XCD works on at a time ... */
+    int32_t attention_units;    /* ... of so many that it has; else both 0 */
+} pyr_launches;
+PYR_API int pyr_diag_launches(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t compute_units, int32_t xcds,
+                              pyr_launches* launches_out);
+
 #ifdef __cplusplus
 }
 #endif

@@ -26,6 +26,10 @@ class PyrRoute(ctypes.Structure):
         "stats_tiles", "stats_waves", "stats_groups", "window_tiles", "window_waves", "window_groups")]
 
 
+class PyrLaunches(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("attention_chunk", "attention_units")]
+
+
 class PyrError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = status
@@ -61,6 +65,7 @@ _SIGNATURES = {
     "pyr_diag_mfma_only": (ctypes.c_int, [_I32, _VP, _VP, ctypes.POINTER(ctypes.c_double)]),
     "pyr_diag_read_stream": (ctypes.c_int, [_VP, _SZ, _I32, _VP, _VP]),
     "pyr_diag_route": (ctypes.c_int, [ctypes.POINTER(PyrShape), _VP, _I32, _I32, _I32, ctypes.POINTER(PyrRoute)]),
+    "pyr_diag_launches": (ctypes.c_int, [ctypes.POINTER(PyrShape), _VP, _I32, _I32, ctypes.POINTER(PyrLaunches)]),
 }
 EXPORTS = tuple(_SIGNATURES)
 
@@ -248,6 +253,14 @@ def diag_route(shape: PyrShape, seq_offsets_host, w: int, compute_units: int = 0
     out = PyrRoute()
     _check(load().pyr_diag_route(ctypes.byref(shape), _ptr(seq_offsets_host), int(w), int(compute_units), int(xcds), ctypes.byref(out)),
            "pyr_diag_route")
+    return out
+
+
+def diag_launches(shape: PyrShape, seq_offsets_host, compute_units: int = 0, xcds: int = 0) -> PyrLaunches:
+    """What diag_route leaves out (host only)."""
+    out = PyrLaunches()
+    _check(load().pyr_diag_launches(ctypes.byref(shape), _ptr(seq_offsets_host), int(compute_units), int(xcds), ctypes.byref(out)),
+           "pyr_diag_launches")
     return out
 
 

@@ -374,6 +374,26 @@ int pyr_diag_route(const pyr_shape* shape, const int32_t* seq_offsets_host, int3
     return PYR_OK;
 }
 
+int pyr_diag_launches(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t compute_units, int32_t xcds, pyr_launches* launches_out) {
+    if (launches_out == nullptr) return PYR_ERR_NULL;
+    int rc = check_shape(shape);
+    if (rc != PYR_OK) return rc;
+    if (compute_units < 0 || xcds < 0 || (compute_units == 0) != (xcds == 0)) return PYR_ERR_SHAPE;
+    BatchInfo info;
+    rc = check_offsets(seq_offsets_host, shape->n_seqs, shape->total_tokens, shape->max_seqlen, &info);
+    if (rc != PYR_OK) return rc;
+    pyr::DeviceInfo dev{0, compute_units, xcds};
+    if (compute_units == 0 && pyr::device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
+    *launches_out = pyr_launches{};
+    if (info.max_len == 0) return PYR_OK;
+    pyr_shape s = *shape;
+    s.max_seqlen = info.max_len;
+    pyr_route route{};
+    pyr::attention_route(s, seq_offsets_host, info.uniform_len, dev, &route);
+    if (route.attention != 0) pyr::attention_tile_route(s, seq_offsets_host, info.uniform_len, route.attention, dev, launches_out);
+    return PYR_OK;
+}
+
 int pyr_decode_workspace_bytes(const pyr_shape* shape, int32_t w, size_t* bytes_out) {
     if (bytes_out == nullptr) return PYR_ERR_NULL;
     const int rc = check_shape(shape);

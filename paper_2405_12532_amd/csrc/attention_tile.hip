@@ -587,6 +587,51 @@ int64_t count_tiles(const pyr_shape& s, const int32_t* seq_offsets_host) {
     return tiles;
 }
 
+constexpr int kMaxGrid = 65535;              // of y and z
+
+int bound_xcds(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t uniform_len, const DeviceInfo& dev) {
+    return xcd_share(s, seq_offsets_host, uniform_len, dev.xccs) <= 1.15 ? dev.xccs : 1;
+}
+
+// A chunk: the units one XCD works on at a time, long tiles first.  Half the workgroups an XCD holds, in units that come in
+// fours (rows a power of two apart) or, in a ragged batch, in whole sequences' worth of heads, which are equally long: the
+// tiles that run together then share their K/V rows in L2 (us, two rounds of workgroups to a chunk / now: 64 x 359
+// 190 / 173, 64 x 269 154 / 136, 64 x 512 282 / 258; d = 64: 64 x 500 153 / 147).  All units where they are few and the
+// grid is at most eight rounds: what counts there is that nothing long starts late (3 x 5000 tokens, 24 heads,
+// nine units per XCD: 533 in chunks of four, 459 in one).  At d = 64 ragged batches, whose
+// chunks end unevenly, go in one up to 2/5 of the slots (38 units an XCD, 16 for equal sequences), and where the longest sequence has at most
+// 9/8 of the mean's tiles up to 3/10 (28).  Over 300 batches of 6 to 38 units (eleven head shapes, 130 to 6000 tokens at most, the shortest 0.1
+// to 1 of that), chunks / one (us): 17 x 609...3417 on 8 heads 127 / 101, 19 x 144...720 on 12 22.7 / 16.6, 12 x 1486...1500 on 12 67 / 55.
+// Nearly equal with more than 28 units: 24 x 326...330 on 12 15.0 / 15.7, 33 x 264...330 on 8 13.2 / 14.0, 34 x 267...276 on 8 12.7 / 13.8, of
+// 60 such batches 0.90 to 1.08.  All others take 0.73 to 1.06 of the time in one, 0.92 in the middle (the worst, 32 x 221...542 on 2 heads 9.9 / 10.4).
+// At d = 128, twenty batches took 0.88 to 1.07.
+struct Chunks {
+    int units, count, per_xcd;          // units of a chunk, chunks, units of an XCD
+};
+
+Chunks cut_chunks(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t uniform_len, int groups, int xcds, const DeviceInfo& dev) {
+    const int64_t unit_tiles = (int64_t)((s.max_seqlen + kRows - 1) / kRows) * (s.n_q_heads / s.n_kv_heads);
+    const int slots = dev.compute_units / xcds * (groups == 2 ? 1 : s.head_dim == 128 ? 2 : 3);
+    const int units_per_xcd = (int)(((int64_t)s.n_seqs * s.n_kv_heads + xcds - 1) / xcds);
+    const int target = (int)((slots + unit_tiles) / (2 * unit_tiles));                   // (rounded)
+    int chunk = target < 6 ? 4 : (target + 2) / 4 * 4;
+    int few = slots / 6;
+    if (uniform_len == 0) {
+        const int per_seq = s.n_kv_heads % xcds == 0 ? s.n_kv_heads / xcds : 1;
+        chunk = per_seq * (target < 2 * per_seq ? 1 : (target + per_seq / 2) / per_seq);
+        if (s.head_dim == 64) {
+            const int most = 2 * slots / 5, nearly_equal = 3 * slots / 10;
+            const int64_t places = (int64_t)s.n_seqs * ((s.max_seqlen + kRows - 1) / kRows);
+            few = units_per_xcd > nearly_equal && units_per_xcd <= most && 8 * places <= 9 * count_tiles(s, seq_offsets_host) ? nearly_equal : most;
+        }
+    }
+    if (units_per_xcd <= few && units_per_xcd * unit_tiles <= 8 * (int64_t)slots) chunk = units_per_xcd;
+    if (chunk > units_per_xcd) chunk = units_per_xcd;
+    if (chunk < (units_per_xcd + kMaxGrid - 1) / kMaxGrid) chunk = (units_per_xcd + kMaxGrid - 1) / kMaxGrid;
+    const int chunks = (units_per_xcd + chunk - 1) / chunk;
+    return Chunks{(units_per_xcd + chunks - 1) / chunks, chunks, units_per_xcd};          // (equal chunks)
+}
+
 }  // namespace
 
 // A list of the tiles that exist, where the grid would mostly hold workgroups that find no rows.  One of those costs about 0.8 ns;
@@ -597,6 +642,13 @@ bool attention_tile_listed(const pyr_shape& s, const int32_t* seq_offsets_host, 
     if (uniform_len > 0) return false;
     const int tiles = (s.max_seqlen + kRows - 1) / kRows;
     return ((int64_t)s.n_seqs * tiles - 4 * count_tiles(s, seq_offsets_host)) * s.n_q_heads > 6000;
+}
+
+void attention_tile_route(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t uniform_len, int groups, const DeviceInfo& dev, pyr_launches* out) {
+    if (attention_tile_listed(s, seq_offsets_host, uniform_len)) return;
+    const Chunks cut = cut_chunks(s, seq_offsets_host, uniform_len, groups, bound_xcds(s, seq_offsets_host, uniform_len, dev), dev);
+    out->attention_chunk = cut.units;
+    out->attention_units = cut.per_xcd;
 }
 
 int launch_attention_tile(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
@@ -615,24 +667,12 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
     a.n_units = s.n_seqs * s.n_kv_heads;
     a.n_q_heads = s.n_q_heads;
     a.n_kv_heads = s.n_kv_heads;
-    a.xcds = xcd_share(s, seq_offsets_host, uniform_len, dev.xccs) <= 1.15 ? dev.xccs : 1;
+    a.xcds = bound_xcds(s, seq_offsets_host, uniform_len, dev);
     a.uniform_len = uniform_len;
     a.c = scale_log2;
     a.out = (uint16_t*)out;
     a.lse = lse;
-    // A chunk: the units one XCD works on at a time, long tiles first.  Half the workgroups an XCD holds, in units that come in
-    // fours (rows a power of two apart) or, in a ragged batch, in whole sequences' worth of heads, which are equally long: the
-    // tiles that run together then share their K/V rows in L2 (us, two rounds of workgroups to a chunk / now: 64 x 359
-    // 190 / 173, 64 x 269 154 / 136, 64 x 512 282 / 258; d = 64: 64 x 500 153 / 147).  All units where they are few and the
-    // grid is at most eight rounds: what counts there is that nothing long starts late (3 x 5000 tokens, 24 heads,
-    // nine units per XCD: 533 in chunks of four, 459 in one).  At d = 64 unequal
-    // sequences, whose chunks end unevenly, go in one up to twice as many units (17 x 609...3417 tokens on 8 heads 94 / 70, 14 x
-    // 677...3181 on 12 heads 139 / 114, 17 x 148...911 26.8 / 21.7; 30 batches drawn there 0.81 to 1.01 of the time; but 24 equal ones of 1500
-    // on 12 heads 109 / 119, 59 of 487...799 71.5 / 81.5; at d = 128, twenty batches 0.88 to 1.07).
     const int tiles = (s.max_seqlen + kRows - 1) / kRows, head_group = s.n_q_heads / s.n_kv_heads;
-    const int slots = dev.compute_units / a.xcds * (groups == 2 ? 1 : s.head_dim == 128 ? 2 : 3);
-    const int units_per_xcd = (a.n_units + a.xcds - 1) / a.xcds;
-    constexpr int kMaxGrid = 65535;              // of y and z
     const auto launch = [&](dim3 grid) {
         if (s.head_dim == 128) return groups == 2 ? launch_tile<128, 2>(a, grid, stream) : launch_tile<128, 1>(a, grid, stream);
         return groups == 2 ? launch_tile<64, 2>(a, grid, stream) : launch_tile<64, 1>(a, grid, stream);
@@ -651,26 +691,12 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
         }
         return rc;
     }
-    const int64_t unit_tiles = (int64_t)tiles * head_group;
-    const int target = (int)((slots + unit_tiles) / (2 * unit_tiles));                   // (rounded)
-    int chunk = target < 6 ? 4 : (target + 2) / 4 * 4;
-    if (uniform_len == 0) {
-        const int per_seq = s.n_kv_heads % a.xcds == 0 ? s.n_kv_heads / a.xcds : 1;
-        chunk = per_seq * (target < 2 * per_seq ? 1 : (target + per_seq / 2) / per_seq);
-    }
-    const int64_t places = units_per_xcd * unit_tiles;
-    const bool few = units_per_xcd <= slots / 6 && places <= 8 * (int64_t)slots;
-    const bool few_unequal = uniform_len == 0 && s.head_dim == 64 && units_per_xcd <= 2 * slots / 5 && places <= 8 * (int64_t)slots;
-    if (few || few_unequal) chunk = units_per_xcd;
-    if (chunk > units_per_xcd) chunk = units_per_xcd;
-    if (chunk < (units_per_xcd + kMaxGrid - 1) / kMaxGrid) chunk = (units_per_xcd + kMaxGrid - 1) / kMaxGrid;
-    const int chunks = (units_per_xcd + chunk - 1) / chunk;
-    chunk = (units_per_xcd + chunks - 1) / chunks;               // (equal chunks)
-    a.units_per_chunk = chunk;
+    const Chunks cut = cut_chunks(s, seq_offsets_host, uniform_len, groups, a.xcds, dev);
+    a.units_per_chunk = cut.units;
     for (int left = tiles; left > 0; left -= kMaxGrid) {         // (one launch below 8 million tokens a sequence)
         const int n = left < kMaxGrid ? left : kMaxGrid;
         a.first_tile = left - n;
-        const dim3 grid((unsigned)(a.xcds * chunk * head_group), (unsigned)n, (unsigned)chunks);
+        const dim3 grid((unsigned)(a.xcds * cut.units * head_group), (unsigned)n, (unsigned)cut.count);
         const int rc = launch(grid);
         if (rc != PYR_OK) return rc;
     }

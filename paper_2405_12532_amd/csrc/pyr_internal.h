@@ -64,8 +64,10 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
                           const pyr_shape& shape, int32_t uniform_len, float scale_log2, void* out, float* lse, int32_t* tile_map,
                           int groups, hipStream_t stream);
 
-// What the launchers above and below would do with a batch (pyr_diag_route).
+// What the launchers above and below would do with a batch (pyr_diag_route, pyr_diag_launches).
 void attention_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len, const DeviceInfo& dev, pyr_route* out);
+void attention_tile_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len, int groups, const DeviceInfo& dev,
+                          pyr_launches* out);
 bool attention_tile_listed(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len);
 void score_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, bool parts, const DeviceInfo& dev,
                  pyr_route* out);

@@ -12,3 +12,9 @@ def route(lib, lens, Hq, Hkv, d, w=32, **device):
     off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32))
     shape = lib.make_shape(len(lens), int(sum(lens)), max(lens, default=0), Hq, Hkv, d)
     return lib.diag_route(shape, off, w, **device)
+
+
+def launches(lib, lens, Hq, Hkv, d, **device):
+    import torch
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32))
+    return lib.diag_launches(lib.make_shape(len(lens), int(sum(lens)), max(lens, default=0), Hq, Hkv, d), off, **device)

@@ -7,7 +7,7 @@ import pytest
 torch = pytest.importorskip("torch")
 from paper_2405_12532_amd import binding
 from tests import test_gpu_attention_kernels as att, test_gpu_score_ranges as ranges
-from tests.routes import COUNTED, EQUAL, LISTS, MI355X, ONE_GROUP, PLACES, SEQ_PER_XCD, TWO_GROUPS, route
+from tests.routes import COUNTED, EQUAL, LISTS, MI355X, ONE_GROUP, PLACES, SEQ_PER_XCD, TWO_GROUPS, launches, route
 
 
 def _kernel(lens, Hq, Hkv, d):
@@ -49,8 +49,33 @@ def test_route_arguments():
     lib = binding.load()
     assert lib.pyr_diag_route(ctypes.byref(shape), off.data_ptr(), 16, 256, 8, None) == -1
     assert lib.pyr_diag_route(ctypes.byref(shape), None, 16, 256, 8, ctypes.byref(binding.PyrRoute())) == -1
+    for args in ((shape, off, 256, 0), (shape, off, -1, 8)):
+        with pytest.raises(binding.PyrError):
+            binding.diag_launches(*args)
+    assert lib.pyr_diag_launches(ctypes.byref(shape), off.data_ptr(), 256, 8, None) == -1
     empty = binding.make_shape(0, 0, 0, 4, 2, 64)
+    assert binding.diag_launches(empty, torch.zeros(1, dtype=torch.int32), 256, 8).attention_units == 0
     assert binding.diag_route(empty, torch.zeros(1, dtype=torch.int32), 16, 256, 8).score_tiles == 0
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,one", [
+    ((1500,) * 24, 12, 12, False),                               # equal
+    ((1500,) * 23 + (1499,), 12, 12, False),                     # nearly: as equal ones go
+    (tuple(range(1477, 1501)), 12, 12, False),
+    ((330,) * 20 + (264,) * 13, 8, 8, False),
+    ((1280,) * 19 + (640,) * 4 + (512,), 12, 12, False),         # the longest has just under 9/8 of the mean's tiles ...
+    ((1280,) * 19 + (640,) * 3 + (512,) * 2, 12, 12, True),      # ... and just over
+    ((1500,) * 18 + (1499,), 12, 12, False),                     # 29 units an XCD, 28, ...
+    ((1500,) * 27 + (1499,), 8, 8, True),
+    (tuple(range(609, 3418, 175)), 8, 8, True),                  # unequal
+    ((900,) * 30 + (300,) * 8, 8, 8, True),                      # 38 units
+    ((900,) * 30 + (300,) * 9, 8, 8, False),                     # 39
+])
+def test_chunks_of_units_at_d64(lens, Hq, Hkv, one):
+    """The units of an XCD go in one chunk by how unequal the sequences are, not by whether one of them differs from the rest."""
+    assert _kernel(lens, Hq, Hkv, 64).attention != LISTS
+    r = launches(binding, lens, Hq, Hkv, 64, **MI355X)
+    assert r.attention_units == -(-len(lens) * Hkv // 8) and (r.attention_chunk == r.attention_units) == one
 
 
 def test_generation_walks():
