@@ -9,6 +9,8 @@
 // behind the loads.  The eight references and sums per row then meet in LDS behind one barrier, and the exponentials, still
 // in registers, are weighted and added up per key:
 //   e = 2^(c*s - m_wave),  score += e * (omega_row * 2^(m_wave - M_row) / Z_row)
+// A probability of 2^-126 and more may be a large exponential times a factor below the normal numbers (a wavefront whose first key is far below the
+// row's other keys), so the factors, and the sums with them, stand 2^64 higher until the end; a reference's move is kept as an exponent.
 // A key belongs to one wavefront, so its sum over the tasks is one LDS word per half-wavefront: no atomics, a fixed order.
 //
 // Bound at large batches: reading K, once from HBM (the row blocks and query heads that share a KV head run side by side on one XCD and
@@ -32,6 +34,7 @@ namespace pyr {
 constexpr int kWindowWaves = 8;                                  // wavefronts of a workgroup
 constexpr int kWindowMaxTiles = 8;                               // 32-key tiles per wavefront, at most
 constexpr float kWindowGrowth = 1099511627776.f;                 // 2^40: how far a row may outgrow its reference
+constexpr int kWindowRaise = 64;                                 // factors and sums are kept times 2^64
 constexpr int kWindowMaxKeys = kWindowWaves * 32 * kWindowMaxTiles;
 
 struct WindowArgs {
@@ -84,6 +87,12 @@ __device__ __forceinline__ float sum_rows(const float (&v)[16], int li) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// v * 2^(x + up), also where 2^x by itself is no normal number.
+__device__ __forceinline__ float times_exp2(float v, float x, int up) {
+    const float bounded = fmaxf(x, -1000.f), whole = rintf(bounded);
+    return __builtin_amdgcn_ldexpf(v * __builtin_amdgcn_exp2f(bounded - whole), (int)whole + up);
+}
+
 // The tasks of workgroup g of sequence b; at most kWindowWaves wavefronts, S <= 32 * kTiles * wavefronts, window_lds_bytes<D, kTiles>(wavefronts) of LDS at smem.
 template <int D, int kTiles, bool kWeighted>
 __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
@@ -112,6 +121,7 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
 
     // (the only ordinary loads; complete before the first LDS-direct load is issued)
     float weight_sum = (float)L;
+    int raised = kWindowRaise;
     if (kWeighted) {
         float part = 0.f;
         for (int j = lane; j < L; j += 64) part += a.row_weights[a.w - L + j];
@@ -119,6 +129,7 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
         for (int m = 32; m >= 1; m >>= 1) part += __shfl_xor(part, m, 64);
         asm volatile("s_waitcnt vmcnt(0)" : "+v"(part) : : "memory");
         weight_sum = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, part)));
+        if (!(weight_sum < 4294967296.f)) raised = max(0, kWindowRaise + 32 - __builtin_amdgcn_frexp_expf(weight_sum));      // (large weights leave less room)
     }
 
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
@@ -224,7 +235,7 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
         // logits of -inf, keeps the sum zero.
         if (gl == 0) *(lfloat_t)(uintptr_t)(factors_at + 4 * li) = -FLT_MAX;
         lanes_meet();
-        uint32_t moved = 0;                           // tiles in front of which references moved, by the factors at moved_at
+        uint32_t moved = 0;                           // tiles in front of which references moved, by the exponents at moved_at
         if (n_my > 0) {
             bf16x8 qf[kSteps];
             wait_front(behind);
@@ -274,12 +285,12 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
                     lanes_meet();
                     rows_of(factors_at + 16 * gl, [&](int r, float y) {
                         const int row = 8 * (r >> 2) + (r & 3);
-                        const float to = fmaxf(y, a.c * max_of_half(x[r])), alpha = __builtin_amdgcn_exp2f(y - to);
-                        l[r] *= alpha;
+                        const float to = fmaxf(y, a.c * max_of_half(x[r])), by = y - to;
+                        l[r] *= __builtin_amdgcn_exp2f(by);
                         e[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], a.c, -to));
                         if (li == 0) {
                             ((lfloat_t)(uintptr_t)(factors_at + 16 * gl))[row] = to;
-                            ((lfloat_t)(uintptr_t)moved_at)[32 * t + row] = alpha;
+                            ((lfloat_t)(uintptr_t)moved_at)[32 * t + row] = by;
                         }
                     });
                     moved |= 1u << t;
@@ -312,7 +323,7 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
         }
 #pragma unroll
         for (int u = 0; u < kWindowWaves; ++u) z += ls[u] * __builtin_amdgcn_exp2f(ms[u] - m_all);
-        float f = __builtin_amdgcn_exp2f(m_own - m_all) / z;
+        float f = times_exp2(1.f, m_own - m_all, raised) / z;
         if (kWeighted) f *= omega;
         if (32 * rb + li >= L) f = 0.f;               // a row past the window adds nothing
         if (gl == 0) *(lfloat_t)(uintptr_t)(factors_at + 4 * li) = f;
@@ -328,11 +339,11 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
                 const lfloat_t at = (lfloat_t)(uintptr_t)(sums_at + 256 * t + 4 * lane);
                 *at = *at + ((p4[0] + p4[1]) + (p4[2] + p4[3]));
             }
-            if (moved >> t & 1) rows_of(moved_at + 128 * t, [&](int r, float x) { fr[r] *= x; });
+            if (moved >> t & 1) rows_of(moved_at + 128 * t, [&](int r, float x) { fr[r] = times_exp2(fr[r], x, 0); });
         }
     }
     // every load issued above has been waited for; the two half-wavefronts' rows
-    const float norm = 1.0f / ((float)a.n_q_heads * weight_sum);
+    const float norm = __builtin_amdgcn_ldexpf(1.0f / ((float)a.n_q_heads * weight_sum), -raised);
     float* dst = a.sums + (size_t)g * a.total_tokens + row0;
     for (int t = 0; t < n_my; ++t) {
         const float mine = *(lfloat_t)(uintptr_t)(sums_at + 256 * t + 4 * lane);

@@ -84,3 +84,46 @@ def test_moved_references(lib, kind, lens, Hq, Hkv, d, w):
     ref = orc.decode_update(F64(q_win.reshape(-1)).reshape(q_win.shape), F64(x["k"]), F64(x["v"]), off, wl.w, keep)
     parity.check_scores(res["scores"], ref)
     parity.check_index_sets(res["kept_idx"], ref, off, keep, wl.w)
+
+
+def _planted(lens, Hq, Hkv, d, w, lib):
+    """Inputs whose logits are the first component of the keys, in nats, for every row and head."""
+    wl = _wl(lens, Hq, Hkv, d, w)
+    x = parity.inputs(wl, lib)
+    x["q"][:], x["k"][:] = 0, 0
+    x["q"][:, :, 0] = synth.f32_to_bf16_bits(np.float32([np.sqrt(d)]))[0]
+    return wl, x
+
+
+def _set_logits(x, rows, log2s):
+    x["k"][rows, :, 0] = synth.f32_to_bf16_bits(np.float32(np.asarray(log2s) * np.log(2.0)))[..., None]
+
+
+def _update(lib, wl, x, row_weights=None):
+    off, keep = x["seq_offsets"], x["keep_len"]
+    q_win = window_queries(x["q"], off, wl.w)
+    res = lib.decode_update_from_numpy(q_win, x["k"], x["v"], off, keep, wl.w, row_weights=row_weights)
+    return res, orc.decode_update(F64(q_win.reshape(-1)).reshape(q_win.shape), F64(x["k"]), F64(x["v"]), off, wl.w, keep, row_weights=row_weights)
+
+
+@pytest.mark.parametrize("weights", [None, 1.0, 2.0 ** 40])
+def test_probabilities_down_to_the_smallest_normal_number(lib, weights):
+    """Keys of probability 2^-101 in wavefronts whose first key lies below 2^-126: as the wavefront's last reference (its factor is then
+    below the normal numbers), and in front of a tile that moves the reference by more than 126.  A logit of 102 (base 2) carries at most 130 roundings of its
+    own, its denominator as many of logits near zero: 130 * 2^-24 * 102 ~ 8e-4."""
+    lens, H, d, w = (1030,), 16, 64, 32
+    r = route(lib, lens, H, H, d, w)
+    assert r.stats_waves == 0 and r.window_waves >= 3 and r.window_tiles >= 2
+    wl, x = _planted(lens, H, H, d, w, lib)
+    tile, wave = np.arange(1030) // 32, (np.arange(1030) // 32) % r.window_waves
+    logits = np.where(wave == 1, -100.0, 0.0)
+    logits[tile == 2] = -100.0
+    logits[32], logits[64] = -130.0, -135.0
+    _set_logits(x, np.arange(1030), logits)
+    rw = None if weights is None else np.linspace(0.0, weights, w, dtype=np.float32)
+    res, ref = _update(lib, wl, x, rw)
+    far = ref["scores"] < 2.0 ** -100
+    assert far.sum() > 100
+    far[[32, 64]] = False
+    np.testing.assert_allclose(res["scores"][far], ref["scores"][far], rtol=8e-4, atol=0)
+    np.testing.assert_allclose(res["scores"][~far], ref["scores"][~far], rtol=SCORE_RTOL, atol=2.0 ** -126)
