@@ -127,3 +127,30 @@ def test_probabilities_down_to_the_smallest_normal_number(lib, weights):
     far[[32, 64]] = False
     np.testing.assert_allclose(res["scores"][far], ref["scores"][far], rtol=8e-4, atol=0)
     np.testing.assert_allclose(res["scores"][~far], ref["scores"][~far], rtol=SCORE_RTOL, atol=2.0 ** -126)
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w", [((300,), 8, 4, 128, 40), ((700, 90), 16, 16, 64, 64)])
+@pytest.mark.parametrize("kind", ["nan", "all_keys_minus_inf"])
+def test_rows_without_a_sum_leave_later_keys_alone(lib, kind, lens, Hq, Hkv, d, w):
+    """A window row that is NaN, or one that sees logits of -inf only, makes the scores of the keys it sees NaN and no others'."""
+    assert route(lib, lens, Hq, Hkv, d, w).stats_waves == 0
+    wl, x = _planted(lens, Hq, Hkv, d, w, lib)
+    rng = np.random.default_rng(5)
+    _set_logits(x, np.arange(sum(lens)), rng.normal(size=sum(lens)))
+    S, bad = lens[0], lens[0] - w // 2 - 3
+    if kind == "nan":
+        x["q"][bad] = 0x7FC1
+    else:                                                        # keys up to `bad`, which every row then finds at -inf
+        x["q"][:, :, 1], x["k"][:bad + 1, :, 1] = 0x3F80, 0xFF80
+    off, keep = x["seq_offsets"], x["keep_len"]
+    res = lib.decode_update_from_numpy(window_queries(x["q"], off, wl.w), x["k"], x["v"], off, keep, wl.w)
+    logits = F64(x["k"][:S, 0, 0]) * F64(x["q"][:1, 0, 0])[0] / np.sqrt(d)
+    if kind != "nan":
+        logits[:bad + 1] = -np.inf
+    ref = np.zeros(S)
+    for i in range(bad + 1, S):                                  # (the rows that later keys depend on)
+        e = np.exp(logits[:i + 1] - logits[bad + 1:i + 1].max())
+        ref[:i + 1] += e / e.sum() / w
+    assert np.isnan(res["scores"][:bad + 1]).all()
+    np.testing.assert_allclose(res["scores"][bad + 1:S], ref[bad + 1:], rtol=SCORE_RTOL, atol=1e-12)
+    assert np.isfinite(res["scores"][S:]).all()
