@@ -336,7 +336,7 @@ typedef struct pyr_route {
     int32_t attention_listed;   /* attention != 0: 1 if the grid is a list of the tiles that exist, else 0 */
     int32_t score_tiles, score_waves, score_groups;     /* prefill score pass: 32-key tiles of a range, wavefronts, split */
     int32_t score_order;        /* 0: a sequence per XCD, 1: equally many ranges, 2: counted, 3: places for the longest sequence */
-    int32_t stats_tiles, stats_waves, stats_groups;     /* the same of the generation phase's statistics (waves == 0: one pass does both) ... */
+    int32_t stats_tiles, stats_waves, stats_groups;     /* the same of the generation phase's statistics (all 0: one pass does both) ... */
     int32_t window_tiles, window_waves, window_groups;  /* ... and of its score pass (or of the one pass: tiles per wavefront) */
 } pyr_route;
 PYR_API int pyr_diag_route(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t w, int32_t compute_units,
@@ -344,13 +344,21 @@ PYR_API int pyr_diag_route(const pyr_shape* shape, const int32_t* seq_offsets_ho
 
 /*
  * Diagnostic, not part of the method: what pyr_diag_route leaves out, for the same purpose.  Host only; launches nothing.
- *   compute_units, xcds  as in pyr_diag_route;  launches_out  host, written
+ *   generation         0: of pyr_prefill_layer_fused, else of pyr_decode_update
+ *   keep_len_host      as in those; NULL: the selection and the gather are left out
+ *   row_bytes          bytes gathered per kept row from all sources together, position ids aside (K and V: 2 * n_kv_heads * head_dim * 2)
+ *   compute_units, xcds  as in pyr_diag_route
+ *   launches_out       host, written
  */
 typedef struct pyr_launches {
     int32_t attention_chunk;    /* one 128-row tile per workgroup, not listed: KV heads of a sequence that an XCD works on at a time ... */
     int32_t attention_units;    /* ... of so many that it has; else both 0 */
+    int32_t stats_order, window_order;  /* generation phase, two walks: score_order of the statistics and of the score pass; else -1 */
+    int32_t sums;               /* 1: rows of partial sums are added by a launch of their own */
+    int32_t select_split;       /* selection and gather in one launch: workgroups per sequence; in two: 0 */
 } pyr_launches;
-PYR_API int pyr_diag_launches(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t compute_units, int32_t xcds,
+PYR_API int pyr_diag_launches(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t w, int32_t generation,
+                              const int32_t* keep_len_host, int64_t row_bytes, int32_t compute_units, int32_t xcds,
                               pyr_launches* launches_out);
 
 #ifdef __cplusplus

@@ -27,7 +27,7 @@ class PyrRoute(ctypes.Structure):
 
 
 class PyrLaunches(ctypes.Structure):
-    _fields_ = [(n, ctypes.c_int32) for n in ("attention_chunk", "attention_units")]
+    _fields_ = [(n, ctypes.c_int32) for n in ("attention_chunk", "attention_units", "stats_order", "window_order", "sums", "select_split")]
 
 
 class PyrError(RuntimeError):
@@ -65,7 +65,7 @@ _SIGNATURES = {
     "pyr_diag_mfma_only": (ctypes.c_int, [_I32, _VP, _VP, ctypes.POINTER(ctypes.c_double)]),
     "pyr_diag_read_stream": (ctypes.c_int, [_VP, _SZ, _I32, _VP, _VP]),
     "pyr_diag_route": (ctypes.c_int, [ctypes.POINTER(PyrShape), _VP, _I32, _I32, _I32, ctypes.POINTER(PyrRoute)]),
-    "pyr_diag_launches": (ctypes.c_int, [ctypes.POINTER(PyrShape), _VP, _I32, _I32, ctypes.POINTER(PyrLaunches)]),
+    "pyr_diag_launches": (ctypes.c_int, [ctypes.POINTER(PyrShape), _VP, _I32, _I32, _VP, _I64, _I32, _I32, ctypes.POINTER(PyrLaunches)]),
 }
 EXPORTS = tuple(_SIGNATURES)
 
@@ -256,11 +256,12 @@ def diag_route(shape: PyrShape, seq_offsets_host, w: int, compute_units: int = 0
     return out
 
 
-def diag_launches(shape: PyrShape, seq_offsets_host, compute_units: int = 0, xcds: int = 0) -> PyrLaunches:
+def diag_launches(shape: PyrShape, seq_offsets_host, w: int, generation: bool, keep_len_host=None, row_bytes: int = 0,
+                  compute_units: int = 0, xcds: int = 0) -> PyrLaunches:
     """What diag_route leaves out (host only)."""
     out = PyrLaunches()
-    _check(load().pyr_diag_launches(ctypes.byref(shape), _ptr(seq_offsets_host), int(compute_units), int(xcds), ctypes.byref(out)),
-           "pyr_diag_launches")
+    _check(load().pyr_diag_launches(ctypes.byref(shape), _ptr(seq_offsets_host), int(w), int(bool(generation)), _ptr(keep_len_host),
+                                    int(row_bytes), int(compute_units), int(xcds), ctypes.byref(out)), "pyr_diag_launches")
     return out
 
 

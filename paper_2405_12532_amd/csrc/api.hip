@@ -374,23 +374,31 @@ int pyr_diag_route(const pyr_shape* shape, const int32_t* seq_offsets_host, int3
     return PYR_OK;
 }
 
-int pyr_diag_launches(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t compute_units, int32_t xcds, pyr_launches* launches_out) {
+int pyr_diag_launches(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t w, int32_t generation, const int32_t* keep_len_host,
+                      int64_t row_bytes, int32_t compute_units, int32_t xcds, pyr_launches* launches_out) {
+    pyr_route route;
+    int rc = pyr_diag_route(shape, seq_offsets_host, w, compute_units, xcds, &route);
+    if (rc != PYR_OK) return rc;
     if (launches_out == nullptr) return PYR_ERR_NULL;
-    int rc = check_shape(shape);
+    if (row_bytes < 0 || row_bytes % 16 != 0) return PYR_ERR_SHAPE;
+    int32_t max_kept = 0;
+    if (keep_len_host != nullptr) rc = check_keep_len(keep_len_host, seq_offsets_host, shape->n_seqs, w, nullptr, &max_kept);
     if (rc != PYR_OK) return rc;
-    if (compute_units < 0 || xcds < 0 || (compute_units == 0) != (xcds == 0)) return PYR_ERR_SHAPE;
+    *launches_out = pyr_launches{0, 0, -1, -1, 0, 0};
     BatchInfo info;
-    rc = check_offsets(seq_offsets_host, shape->n_seqs, shape->total_tokens, shape->max_seqlen, &info);
-    if (rc != PYR_OK) return rc;
+    check_offsets(seq_offsets_host, shape->n_seqs, shape->total_tokens, shape->max_seqlen, &info);
+    if (info.max_len == 0) return PYR_OK;
     pyr::DeviceInfo dev{0, compute_units, xcds};
     if (compute_units == 0 && pyr::device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
-    *launches_out = pyr_launches{};
-    if (info.max_len == 0) return PYR_OK;
     pyr_shape s = *shape;
     s.max_seqlen = info.max_len;
-    pyr_route route{};
-    pyr::attention_route(s, seq_offsets_host, info.uniform_len, dev, &route);
-    if (route.attention != 0) pyr::attention_tile_route(s, seq_offsets_host, info.uniform_len, route.attention, dev, launches_out);
+    int groups = route.score_groups;
+    if (generation != 0) groups = pyr::update_route(s, seq_offsets_host, info.min_len, w, dev, launches_out);
+    else if (route.attention != 0) pyr::attention_tile_route(s, seq_offsets_host, info.uniform_len, route.attention, dev, launches_out);
+    if (keep_len_host == nullptr) return PYR_OK;
+    const pyr::SelectPlan plan = pyr::plan_select(groups, s.n_seqs, s.max_seqlen, max_kept, row_bytes / 16);
+    launches_out->sums = plan.sums ? 1 : 0;
+    launches_out->select_split = plan.split;
     return PYR_OK;
 }
 

@@ -50,7 +50,12 @@ int launch_select(const float* parts, int groups, int32_t total_tokens, float* s
                   const int32_t* keep_len_dev, int32_t n_seqs, int32_t max_seqlen, int32_t w, int32_t* kept_idx,
                   int32_t* out_offsets_dev, hipStream_t stream);
 
-// The selection and the gather of what it keeps, in one launch where the batch is small enough for that to be faster.
+// How the selection and the gather of what it keeps go about it (groups rows of partial sums; row_chunks: 16-byte chunks gathered per kept row).
+struct SelectPlan {
+    bool sums;                    // the rows of partial sums are added by a launch of their own
+    int split;                    // > 0: selection and gather in one launch, so many workgroups per sequence; 0: in two
+};
+SelectPlan plan_select(int groups, int32_t n_seqs, int32_t max_seqlen, int32_t max_kept, int64_t row_chunks);
 int launch_select_gather(const float* parts, int groups, int32_t total_tokens, float* scores, const int32_t* seq_offsets_dev,
                          const int32_t* keep_len_dev, int32_t n_seqs, int32_t max_seqlen, int32_t max_kept, int64_t n_kept, int32_t w,
                          int32_t* kept_idx, int32_t* out_offsets_dev, const GatherSources& sources, hipStream_t stream);
@@ -69,6 +74,8 @@ void attention_route(const pyr_shape& shape, const int32_t* seq_offsets_host, in
 void attention_tile_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len, int groups, const DeviceInfo& dev,
                           pyr_launches* out);
 bool attention_tile_listed(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len);
+// (returns the rows of partial sums)
+int update_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, const DeviceInfo& dev, pyr_launches* out);
 void score_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, bool parts, const DeviceInfo& dev,
                  pyr_route* out);
 
@@ -88,7 +95,7 @@ int launch_score_groups(const void* q, const void* k, const float* lse, const in
                         const float* row_weights, float* scores, float* parts, int* groups, hipStream_t stream);
 
 // Generation phase: the same scores from the window's own query buffer q_win [B, w, Hq, d]
-// (right-aligned), three launches: row statistics per range of keys -> part, folded into lse_win
+// (right-aligned), in one launch (launch_window) or three: row statistics per range of keys -> part, folded into lse_win
 // [B, w, Hq], then the score pass.  part holds window_score_part_bytes() bytes; *groups as above, the partial sums in part.
 size_t window_score_part_bytes(const pyr_shape& shape, int32_t w);
 int launch_window_score(const void* q_win, const void* k, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,

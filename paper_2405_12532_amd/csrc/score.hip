@@ -758,12 +758,27 @@ void score_route(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t mi
     out->score_groups = score.groups;
     out->score_order = pick_order(s, cut.equal, count_ranges(seq_offsets_host, s.n_seqs, 32 * score.range_tiles),
                                   ((s.max_seqlen + 31) / 32 + score.range_tiles - 1) / score.range_tiles, dev.xccs);
-    out->stats_tiles = update.stats.range_tiles;
-    out->stats_waves = update.one_walk ? 0 : update.stats.waves;
-    out->stats_groups = update.stats.groups;
+    if (!update.one_walk) {
+        out->stats_tiles = update.stats.range_tiles;
+        out->stats_waves = update.stats.waves;
+        out->stats_groups = update.stats.groups;
+    }
     out->window_tiles = update.one_walk ? ((s.max_seqlen + 31) / 32 + update.window.waves - 1) / update.window.waves : update.scores.range_tiles;
     out->window_waves = update.one_walk ? update.window.waves : update.scores.waves;
     out->window_groups = update.one_walk ? update.window.groups : update.scores.groups;
+}
+
+int update_route(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, const DeviceInfo& dev, pyr_launches* out) {
+    const BatchCut cut = cut_batch(s, seq_offsets_host, min_seqlen);
+    const UpdatePlan update = plan_update(s, cut, w, dev);
+    if (update.one_walk) return update.window.groups;
+    const auto order = [&](const StripPlan& plan) {
+        return pick_order(s, cut.equal, count_ranges(seq_offsets_host, s.n_seqs, 32 * plan.range_tiles),
+                          ((s.max_seqlen + 31) / 32 + plan.range_tiles - 1) / plan.range_tiles, dev.xccs);
+    };
+    out->stats_order = order(update.stats);
+    out->window_order = order(update.scores);
+    return update.scores.groups;
 }
 
 size_t window_score_part_bytes(const pyr_shape& s, int32_t w) {

@@ -109,32 +109,41 @@ int launch_select(const float* parts, int groups, int32_t total_tokens, float* s
     return launch(parts, groups, total_tokens, scores, seq_offsets_dev, keep_len_dev, n_seqs, max_seqlen, w, kept_idx, out_offsets_dev, stream);
 }
 
+// Rows of partial sums that would take the selection's one workgroup longer than a launch that adds them with the whole chip (1.7 us):
+// updates with / without that launch, at 32 heads, w = 64: 64 rows of 200 tokens 20.6 / 21.8, of 1024 23.1 / 26.4, of 1537 28.3 / 31.5,
+// 32 rows of 700 29.8 / 29.3, of 1024 33.8 / 33.3, of 1537 36.5 / 37.3, 16 rows of 2048 70.3 / 69.4.
+// One launch where the rows to copy are so few that the selection's own workgroups are enough for them; counted as if every
+// sequence kept as many as the one that keeps most, because all get the same number of workgroups.  Whole calls, two launches / one
+// (us): a 64-token layer on 32 heads (1.0 MB) 18.3 / 16.0, 256 tokens on 8 heads, d = 64 (0.3 MB) 18.5 / 16.6, updates of 16 x 70
+// rows (2.6 MB) 16.5 / 14.8, of 1 x 176 (3.1 MB) 15.2 / 15.7, of 6 x 368 (5.4 MB) 14.9 / 16.1, of 16 x 512 (120 MB) 69.6 / 68.9...74.8;
+// 256 workgroups instead of 192 differ by 1 % either way, 64 cost up to 10 % at the upper end.
+SelectPlan plan_select(int groups, int32_t n_seqs, int32_t max_seqlen, int32_t max_kept, int64_t row_chunks) {
+    constexpr int64_t kFewBytes = 3000000;
+    constexpr int kFusedGroups = 192;
+    SelectPlan p{};
+    p.sums = groups > 1 && sums_pay(groups, max_seqlen);
+    if (n_seqs > 0 && max_kept > 0 && row_chunks > 0 && max_seqlen <= kFusedLanes * kRegKeys && row_chunks <= kFewBytes / 16 &&
+        row_chunks * max_kept <= kFewBytes / 16 && row_chunks * max_kept * n_seqs <= kFewBytes / 16)
+        p.split = (kFusedGroups + n_seqs - 1) / n_seqs;
+    return p;
+}
+
 int launch_select_gather(const float* parts, int groups, int32_t total_tokens, float* scores, const int32_t* seq_offsets_dev,
                          const int32_t* keep_len_dev, int32_t n_seqs, int32_t max_seqlen, int32_t max_kept, int64_t n_kept, int32_t w,
                          int32_t* kept_idx, int32_t* out_offsets_dev, const GatherSources& g, hipStream_t stream) {
-    // Rows of partial sums that would take the selection's one workgroup longer than a launch that adds them with the whole chip (1.7 us):
-    // updates with / without that launch, at 32 heads, w = 64: 64 rows of 200 tokens 20.6 / 21.8, of 1024 23.1 / 26.4, of 1537 28.3 / 31.5,
-    // 32 rows of 700 29.8 / 29.3, of 1024 33.8 / 33.3, of 1537 36.5 / 37.3, 16 rows of 2048 70.3 / 69.4.
-    if (groups > 1 && sums_pay(groups, max_seqlen)) {
+    int64_t row_chunks = 0;
+    for (int i = 0; i < g.n; ++i) row_chunks += g.chunks[i];
+    const SelectPlan plan = plan_select(groups, n_seqs, max_seqlen, max_kept, row_chunks);
+    if (plan.sums) {
         const int rc = launch_sum_parts(parts, groups, total_tokens, scores, stream);
         if (rc != PYR_OK) return rc;
         groups = 1;
     }
-    // One launch where the rows to copy are so few that the selection's own workgroups are enough for them; counted as if every
-    // sequence kept as many as the one that keeps most, because all get the same number of workgroups.  Whole calls, two launches / one
-    // (us): a 64-token layer on 32 heads (1.0 MB) 18.3 / 16.0, 256 tokens on 8 heads, d = 64 (0.3 MB) 18.5 / 16.6, updates of 16 x 70
-    // rows (2.6 MB) 16.5 / 14.8, of 1 x 176 (3.1 MB) 15.2 / 15.7, of 6 x 368 (5.4 MB) 14.9 / 16.1, of 16 x 512 (120 MB) 69.6 / 68.9...74.8;
-    // 256 workgroups instead of 192 differ by 1 % either way, 64 cost up to 10 % at the upper end.
-    constexpr int64_t kFewBytes = 3000000;
-    constexpr int kFusedGroups = 192;
-    int64_t row_chunks = 0;
-    for (int i = 0; i < g.n; ++i) row_chunks += g.chunks[i];
-    if (n_seqs > 0 && max_kept > 0 && row_chunks > 0 && max_seqlen <= kFusedLanes * kRegKeys && row_chunks <= kFewBytes / 16 &&
-        row_chunks * max_kept <= kFewBytes / 16 && row_chunks * max_kept * n_seqs <= kFewBytes / 16) {
-        const int split = (kFusedGroups + n_seqs - 1) / n_seqs, room = (max_kept + split - 1) / split;
-        hipLaunchKernelGGL(select_gather_kernel, dim3((unsigned)(split * n_seqs)), dim3(kFusedLanes), (size_t)room * sizeof(int32_t), stream, parts,
-                           (int32_t)groups, total_tokens, scores, seq_offsets_dev, keep_len_dev, w, kept_idx, out_offsets_dev, g, (int32_t)split,
-                           (int32_t)room);
+    if (plan.split > 0) {
+        const int32_t room = (max_kept + plan.split - 1) / plan.split;
+        hipLaunchKernelGGL(select_gather_kernel, dim3((unsigned)(plan.split * n_seqs)), dim3(kFusedLanes), (size_t)room * sizeof(int32_t), stream, parts,
+                           (int32_t)groups, total_tokens, scores, seq_offsets_dev, keep_len_dev, w, kept_idx, out_offsets_dev, g,
+                           (int32_t)plan.split, room);
         return check_launch();
     }
     const int rc = launch_select(parts, groups, total_tokens, scores, seq_offsets_dev, keep_len_dev, n_seqs, max_seqlen, w, kept_idx, out_offsets_dev, stream);

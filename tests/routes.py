@@ -14,7 +14,8 @@ def route(lib, lens, Hq, Hkv, d, w=32, **device):
     return lib.diag_route(shape, off, w, **device)
 
 
-def launches(lib, lens, Hq, Hkv, d, **device):
+def launches(lib, lens, Hq, Hkv, d, w=32, generation=False, keep=None, row_bytes=0, **device):
     import torch
     off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32))
-    return lib.diag_launches(lib.make_shape(len(lens), int(sum(lens)), max(lens, default=0), Hq, Hkv, d), off, **device)
+    keep = None if keep is None else torch.from_numpy(np.asarray(keep, dtype=np.int32))
+    return lib.diag_launches(lib.make_shape(len(lens), int(sum(lens)), max(lens, default=0), Hq, Hkv, d), off, w, generation, keep, row_bytes, **device)

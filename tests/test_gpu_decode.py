@@ -5,6 +5,7 @@ import pytest
 from oracle import pyr_oracle as orc
 from paper_2405_12532_amd import synth
 from tests import parity
+from tests.routes import route
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -130,10 +131,14 @@ def test_decode_update_with_empty_sequences(lib):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("garbage", [0x00, 0x7F, 0xFF])                # of the workspace: zeros, 3.4e38, NaN
-def test_decode_update_masked_ranges(lib, d, garbage):
+@pytest.mark.parametrize("longest", [1300, 2100])                      # one walk, two
+def test_decode_update_masked_ranges(lib, d, garbage, longest):
     """Cache rows nobody may see (a logit of -inf by way of one head dimension), more of them in a row than a range of the
-    statistics pass holds: their statistics are written like any other range's, whatever lay in the workspace."""
-    wl = synth.shrunk(synth.workload("cfg2"), (1300, 70), n_q_heads=4, n_kv_heads=2, head_dim=d, w=32, hidden_dim=0)
+    statistics pass holds: their statistics are written like any other range's, whatever lay in the workspace.  And in the
+    one walk tiles without a logit, a wavefront's first among them."""
+    r = route(lib, (longest, 70), 4, 2, d, 32)
+    assert 32 * r.stats_tiles <= 400 if longest > 2048 else r.stats_waves == 0
+    wl = synth.shrunk(synth.workload("cfg2"), (longest, 70), n_q_heads=4, n_kv_heads=2, head_dim=d, w=32, hidden_dim=0)
     x = parity.inputs(wl, lib, want_hidden=False)
     off, keep = x["seq_offsets"], x["keep_len"]
     x["q"][:, :, 0], x["k"][:, :, 0] = 0x3F80, 0                       # 1.0, 0.0
@@ -142,7 +147,7 @@ def test_decode_update_masked_ranges(lib, d, garbage):
     q, k, v = (lib.to_device_bf16(a) for a in (q_win, x["k"], x["v"]))
     off_h, keep_h = (torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)) for a in (off, keep))
     off_d, keep_d = off_h.cuda(), keep_h.cuda()
-    shape = lib.make_shape(2, k.shape[0], 1300, 4, 2, d)
+    shape = lib.make_shape(2, k.shape[0], longest, 4, 2, d)
     n_kept, ws_bytes = int(keep_h.sum()), lib.decode_workspace_bytes(shape, wl.w)
     ws = torch.full((ws_bytes,), garbage, dtype=torch.uint8, device="cuda")
     scores = torch.empty(k.shape[0], dtype=torch.float32, device="cuda")

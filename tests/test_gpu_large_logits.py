@@ -10,6 +10,7 @@ import pytest
 from oracle import pyr_oracle as orc
 from paper_2405_12532_amd import synth
 from tests import parity
+from tests.routes import route
 from tests.test_gpu_layer import run_and_check
 from tests.test_gpu_decode import window_queries
 
@@ -149,9 +150,11 @@ def test_unit_softmax_scale_full_range_values(lib):
 
 
 @pytest.mark.parametrize("kind", ["ramp", "low_start_overflow"])
-def test_decode_update_large_logits(lib, kind):
-    """The generation-phase update (row statistics per key block, their fold, the score pass) on the same inputs."""
-    wl = synth.shrunk(synth.workload("cfg1"), (700, 130, 33), n_q_heads=8, n_kv_heads=4, head_dim=128, w=32,
+@pytest.mark.parametrize("longest", [700, 2200])
+def test_decode_update_large_logits(lib, kind, longest):
+    """The generation-phase update on the same inputs: in one walk, and by row statistics per range of keys, their fold and the score pass."""
+    assert (route(lib, (longest, 130, 33), 8, 4, 128, 32).stats_waves > 0) == (longest == 2200)
+    wl = synth.shrunk(synth.workload("cfg1"), (longest, 130, 33), n_q_heads=8, n_kv_heads=4, head_dim=128, w=32,
                       keep_fixed=0, keep_num=6, keep_den=10)
     x = shaped_inputs(kind, wl, lib, seed=1)
     off, keep = x["seq_offsets"], x["keep_len"]

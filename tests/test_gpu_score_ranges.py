@@ -8,7 +8,7 @@ import pytest
 
 from paper_2405_12532_amd import synth
 from tests import parity, test_gpu_decode, test_gpu_layer
-from tests.routes import COUNTED, EQUAL, PLACES, SEQ_PER_XCD, route
+from tests.routes import COUNTED, EQUAL, PLACES, SEQ_PER_XCD, launches, route
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -103,8 +103,8 @@ ORDERS = [
 
 @pytest.mark.parametrize("lens,Hq,Hkv,d,w,order", ORDERS)
 def test_order_of_the_ranges(lib, lens, Hq, Hkv, d, w, order):
-    """Every range is taken by exactly one workgroup, whichever way the grid is laid out: scores of the prefill step, and of the
-    cache update, whose statistics walk is laid out the same way."""
+    """Every range is taken by exactly one workgroup, whichever way the grid is laid out: scores of the prefill step; and the cache update of
+    the same batches, which these lengths send through one walk (test_order_of_the_updates_ranges has the two walks)."""
     assert route(lib, lens, Hq, Hkv, d, w).score_order == order
     wl = _wl(lens, Hq, Hkv, d, w)
     for run in (test_gpu_layer.run_and_check, test_gpu_decode.run_and_check):
@@ -112,12 +112,55 @@ def test_order_of_the_ranges(lib, lens, Hq, Hkv, d, w, order):
         np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
 
 
-FOLDS = (1, 64, 256, 257, 512, 513, 2100)
+UPDATE_ORDERS = [                                               # statistics and scores, two walks
+    ((2100,) * 3, 2, 1, 64, 16, EQUAL, EQUAL),
+    ((2100, 2098, 2112), 4, 2, 128, 33, EQUAL, EQUAL),          # lengths that differ, as many ranges
+    ((2100,) * 8, 2, 1, 64, 16, SEQ_PER_XCD, SEQ_PER_XCD),
+    ((0, 2100, 0, 0, 33, 1), 4, 2, 128, 32, COUNTED, COUNTED),  # empty sequences in front and between
+    (_spread(64, 1, 400, 1) + (0, 2100), 2, 2, 64, 16, COUNTED, COUNTED),
+    (_spread(255, 0, 300, 3) + (2100,), 2, 2, 64, 16, COUNTED, COUNTED),
+    (_spread(257, 0, 300, 4) + (2100,), 2, 2, 64, 16, PLACES, PLACES),
+    ((2100,) * 7, 2, 2, 64, 1100, EQUAL, EQUAL),                # half a sequence in the window: each starts at another range
+    ((2060,) * 8, 1, 1, 64, 1030, SEQ_PER_XCD, SEQ_PER_XCD),    # ... on one XCD each
+]
 
 
-@pytest.mark.parametrize("S", FOLDS)
-def test_fold_of_the_statistics(lib, S):
-    """Ranges of 64 keys, the smallest the statistics walk takes and what it takes for one short cache: one lane folds a row of up
-    to four of them, eight lanes share it from five on, and each has several from nine on."""
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w,stats,scores", UPDATE_ORDERS)
+@pytest.mark.parametrize("weighted", [False, True])
+def test_order_of_the_updates_ranges(lib, lens, Hq, Hkv, d, w, stats, scores, weighted):
+    r = launches(lib, lens, Hq, Hkv, d, w, generation=True)
+    assert (r.stats_order, r.window_order) == (stats, scores)
+    rw = np.linspace(0.25, 1.0, w, dtype=np.float32) if weighted else None
+    res, ref, _ = test_gpu_decode.run_and_check(lib, _wl(lens, Hq, Hkv, d, w), row_weights=rw)
+    np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
+
+
+FOLDS = [                                                       # the ranges of the longest sequence, then of the others
+    ((257,) * 24, 32, 1, 128, 100, [1] * 24),                   # one lane folds a row of up to four ranges
+    ((500,) * 28 + (1, 33, 128, 129, 384, 385), 16, 1, 64, 33, [4] * 28 + [1, 1, 1, 2, 3, 4]),
+    ((600,) * 32 + (1, 33, 128, 129, 256, 257), 16, 1, 64, 33, [5] * 32 + [1, 1, 1, 2, 2, 3]),           # eight lanes share it from five on
+    ((513, 512), 2, 2, 128, 16, [9, 8]),                        # ... and one of them has a second one
+    ((2100, 1, 64, 65, 256, 257, 512, 513), 4, 2, 128, 40, [33, 1, 1, 2, 4, 5, 8, 9]),
+    ((40, 2900), 4, 4, 64, 64, [1, 46]),                        # more than the fold keeps in flight; a sequence shorter than the window
+]
+
+
+def fold_ranges(lib, lens, Hq, Hkv, d, w, **device):
+    tiles = route(lib, lens, Hq, Hkv, d, w, **device).stats_tiles
+    return [-(-S // (32 * tiles)) for S in lens] if tiles else None
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w,ranges", FOLDS)
+def test_fold_of_the_statistics(lib, lens, Hq, Hkv, d, w, ranges):
+    """A row's ranges, folded by one lane where there are four at most in the longest sequence, else by eight."""
+    assert fold_ranges(lib, lens, Hq, Hkv, d, w) == ranges
+    res, ref, _ = test_gpu_decode.run_and_check(lib, _wl(lens, Hq, Hkv, d, w))
+    np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
+
+
+@pytest.mark.parametrize("S", [1, 64, 256, 257, 512, 513, 2100])
+def test_update_of_one_cache(lib, S):
+    """One walk up to 2048 rows, two beyond."""
+    assert (route(lib, (S,), 4, 2, 128, 40).stats_waves > 0) == (S > 2048)
     res, ref, _ = test_gpu_decode.run_and_check(lib, _wl((S,), 4, 2, 128, 40))
     np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)

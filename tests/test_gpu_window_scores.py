@@ -40,6 +40,10 @@ TWO_WALKS = [
     ((120,) * 60, 32, 1, 128, 128),                             # many row blocks per KV head: one lane folds a row's one range
     ((250,) * 30, 32, 1, 128, 256),
     ((1200, 700), 8, 8, 64, 40),                                # few heads
+    ((2081, 200, 1, 90), 6, 2, 128, 20),                        # group of 3: pairs of row blocks span query heads, one is left over
+    ((2500, 130), 12, 4, 64, 96),                               # nine row blocks per KV head
+    ((2300,), 5, 5, 64, 100),                                   # fewer tasks than wavefronts; four row blocks, the last of four rows
+    ((2052, 33, 64), 40, 40, 128, 64),                          # rows not a power of two apart; tasks split over workgroups
 ]
 
 
@@ -55,9 +59,13 @@ def test_one_walk(lib, lens, Hq, Hkv, d, w, weighted):
 
 
 @pytest.mark.parametrize("lens,Hq,Hkv,d,w", TWO_WALKS)
-def test_two_walks(lib, lens, Hq, Hkv, d, w):
+@pytest.mark.parametrize("weighted", [False, True])
+def test_two_walks(lib, lens, Hq, Hkv, d, w, weighted):
     assert route(lib, lens, Hq, Hkv, d, w).stats_waves > 0
-    res, ref, _ = test_gpu_decode.run_and_check(lib, _wl(lens, Hq, Hkv, d, w))
+    rw = np.linspace(0.0, 1.0, w, dtype=np.float32) if weighted else None            # (the first weight is zero)
+    if weighted and min(S for S in lens if S) == 1:
+        rw = rw + np.float32(0.25)
+    res, ref, _ = test_gpu_decode.run_and_check(lib, _wl(lens, Hq, Hkv, d, w), row_weights=rw)
     np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
 
 

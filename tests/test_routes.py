@@ -33,8 +33,11 @@ def test_attention_kernels():
 def test_score_walks():
     for lens, Hq, Hkv, d, w, order in ranges.ORDERS:
         assert route(binding, lens, Hq, Hkv, d, w, **MI355X).score_order == order, (len(lens), d, w)
-    folds = [-(-S // (32 * route(binding, (S,), 4, 2, 128, 40, **MI355X).stats_tiles)) for S in ranges.FOLDS]
-    assert folds == [1, 1, 4, 5, 8, 9, 33], folds
+    for *batch, stats, scores in ranges.UPDATE_ORDERS:
+        r = launches(binding, *batch, generation=True, **MI355X)
+        assert (r.stats_order, r.window_order) == (stats, scores), (len(batch[0]), batch[1:], r.stats_order, r.window_order)
+    for *batch, counts in ranges.FOLDS:
+        assert ranges.fold_ranges(binding, *batch, **MI355X) == counts, (batch, ranges.fold_ranges(binding, *batch, **MI355X))
     lens, H, d, w = ranges.LOOSE
     assert route(binding, lens, H, H, d, w, **MI355X).score_groups > 1
 
@@ -49,12 +52,14 @@ def test_route_arguments():
     lib = binding.load()
     assert lib.pyr_diag_route(ctypes.byref(shape), off.data_ptr(), 16, 256, 8, None) == -1
     assert lib.pyr_diag_route(ctypes.byref(shape), None, 16, 256, 8, ctypes.byref(binding.PyrRoute())) == -1
-    for args in ((shape, off, 256, 0), (shape, off, -1, 8)):
+    keep = torch.tensor([101], dtype=torch.int32)
+    for args in ((shape, off, 16, 0, None, 0, 256, 0), (shape, off, 0, 0, None, 0, 256, 8), (shape, off, 16, 1, keep, 256, 256, 8),
+                 (shape, off, 16, 1, None, 8, 256, 8)):
         with pytest.raises(binding.PyrError):
             binding.diag_launches(*args)
-    assert lib.pyr_diag_launches(ctypes.byref(shape), off.data_ptr(), 256, 8, None) == -1
+    assert lib.pyr_diag_launches(ctypes.byref(shape), off.data_ptr(), 16, 0, None, 0, 256, 8, None) == -1
     empty = binding.make_shape(0, 0, 0, 4, 2, 64)
-    assert binding.diag_launches(empty, torch.zeros(1, dtype=torch.int32), 256, 8).attention_units == 0
+    assert binding.diag_launches(empty, torch.zeros(1, dtype=torch.int32), 16, 1, None, 0, 256, 8).attention_units == 0
     assert binding.diag_route(empty, torch.zeros(1, dtype=torch.int32), 16, 256, 8).score_tiles == 0
 
 
@@ -81,6 +86,7 @@ def test_chunks_of_units_at_d64(lens, Hq, Hkv, one):
 def test_generation_walks():
     from tests import test_gpu_window_scores as window
     for batch in window.ONE_WALK:
-        assert route(binding, *batch, **MI355X).stats_waves == 0, batch
+        r = route(binding, *batch, **MI355X)
+        assert r.stats_waves == r.stats_tiles == r.stats_groups == 0, batch
     for batch in window.TWO_WALKS:
         assert route(binding, *batch, **MI355X).stats_waves > 0, batch
