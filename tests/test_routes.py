@@ -90,3 +90,11 @@ def test_generation_walks():
         assert r.stats_waves == r.stats_tiles == r.stats_groups == 0, batch
     for batch in window.TWO_WALKS:
         assert route(binding, *batch, **MI355X).stats_waves > 0, batch
+
+
+def test_selection_and_gather():
+    from tests import test_gpu_select_gather as small
+    for lens, Hkv, d, w, plain, with_hidden in small.LAYERS:
+        assert [small.merged(binding, lens, Hkv, d, w, hidden, **MI355X) for hidden in (0, 72)] == [plain, with_hidden], (lens, Hkv, d)
+    for *batch, rows, sums, one in small.UPDATES:
+        assert small.update_launches(binding, *batch, **MI355X) == (rows, sums, one), batch
