@@ -127,17 +127,17 @@ def _ulps_above(base, steps):
 
 
 @pytest.mark.parametrize("n", [300, 4096, 4097])                     # 512 lanes up to 4096 tokens, 1024 beyond
-@pytest.mark.parametrize("spread", ["few_ulps", "digit_edge", "outlier", "two_digits", "bin_256", "bin_257"])
-def test_select_radix_passes(lib, n, spread):
-    """Score distributions that end the radix select in its different ways: every bit decided in one digit, keys that
-    differ in exactly 11 and 12 bits, one pass and a crowded bin, two and three digits, a bin of 256 keys (ranked
-    directly) and of 257 (another pass)."""
+@pytest.mark.parametrize("spread", ["few_ulps", "few_to_a_bin", "outlier", "clusters", "bin_256", "bin_257"])
+def test_select_search_passes(lib, n, spread):
+    """Score distributions that end the search for the threshold in its different ways (bins divide the span of the keys in 1024 parts with 512
+    lanes, in 2048 with 1024): a bin for every value; bins of one, two and four values; all keys but one in the first bin, so
+    that a second pass, and at 4096 keys a third, divides it; four clusters; a bin of 256 keys (ranked directly) and of 257 (another pass)."""
     rng = np.random.default_rng(n)
     steps = {
         "few_ulps": lambda: rng.integers(0, 40, n),
-        "digit_edge": lambda: rng.integers(0, 1 << int(rng.integers(11, 13)), n),
+        "few_to_a_bin": lambda: rng.integers(0, 1 << int(rng.integers(11, 13)), n),
         "outlier": lambda: np.where(np.arange(n) == n // 2, 0x08000000, rng.integers(0, 3000, n)),
-        "two_digits": lambda: rng.integers(0, 4, n) * 0x00400000 + rng.integers(0, 1 << 20, n),
+        "clusters": lambda: rng.integers(0, 4, n) * 0x00400000 + rng.integers(0, 1 << 20, n),
         "bin_256": lambda: np.where(np.arange(n) < 256, rng.integers(0, 1 << 12, n), 0x00800000 + np.arange(n) * 8192),
         "bin_257": lambda: np.where(np.arange(n) < 257, rng.integers(0, 1 << 12, n), 0x00800000 + np.arange(n) * 8192),
     }[spread]()
