@@ -732,9 +732,10 @@ struct UpdatePlan {
 // per block: it wins where row blocks per KV head are few or sequences short.  Whole updates, two walks / one walk (us): 1 x 1024 rows on
 // 32 heads, w = 64 28.2 / 23.1, 4 x 1537 71.8 / 61, 5 x 1330 on 8 heads, d = 64, w = 128 27.1 / 22.2, 48 of 689 at most on 24 heads, w = 32
 // 135.6 / 100; but 18 x 826 on 64/8 heads, w = 16 55.8 / 74.5, 57 of 1066 at most on 32/8 heads, d = 64, w = 48 87 / 111.  Both costs
-// are predicted (the two walks' with the fold and the selection, to 10 %) and one walk is taken where it is 11.5 % lower: over 160 updates
-// of random shapes two walks take 23 % longer than the best cut of either form in the mean, the choice 1 % longer; where it takes
-// one walk against the faster two, it loses 3 % at most; at 0.9 5 % (59 of 1825 at most), at 1.0 33 %.
+// are predicted (the two walks' with the fold and the selection, to 10 %) and one walk is taken where it is 11.5 % lower.  That share was set on
+// 160 updates of random shapes (at 0.9 the worst loss was 5 % there, at 1.0 33 %); over 300 others the two walks take 27 % longer than the faster
+// form in the mean, one walk throughout 1.1 %, the choice 0.4 %.  It takes one walk against the faster two at a loss of 8 % at most (12 of
+// 135...1243 rows on 32/8 heads, d = 64 34.8 / 37.7) and keeps two against a faster one of 21 % at most (3 x 554...605 on 64/8, w = 256 52.9 / 43.7).
 UpdatePlan plan_update(const pyr_shape& s, const BatchCut& cut, int32_t w, const DeviceInfo& dev) {
     UpdatePlan p{};
     const size_t room = window_score_part_bytes(s, w), row = (size_t)s.total_tokens * sizeof(float);

@@ -1,12 +1,12 @@
 // The scores of short sequences by one walk over K that finds the row denominators itself (Algorithm 1,
 // A_e = weighted_avg(A[-L:, :-L]); see score.hip for the two-walk form and for what is computed).
 //
-// A workgroup of eight wavefronts holds the logits of 32 window rows (one query head) against ALL keys of a sequence in its
-// registers: 16 accumulator registers per 32-key tile, up to kTiles tiles per wavefront, so 8 * 32 * kTiles keys at most
-// (2048 with the 128 registers of kTiles = 8, half of the register file).  Per task (query head, row block) the wavefronts
+// A workgroup of up to eight wavefronts holds the logits of 32 window rows (one query head) against ALL keys of a sequence in its
+// registers: 16 accumulator registers per 32-key tile, up to kTiles tiles per wavefront, so 32 * kTiles keys a wavefront at most
+// (2048 in eight with the 128 registers of kTiles = 8, half of the register file).  Per task (query head, row block) the wavefronts
 // turn their tiles' logits into exponentials tile by tile, against a reference per row that is the row's logit of the wavefront's
 // first key and is only moved (which the tiles before are told at the end) when a row outgrows it by 2^40; so the vector work hides
-// behind the loads.  The eight references and sums per row then meet in LDS behind one barrier, and the exponentials, still
+// behind the loads.  The wavefronts' references and sums per row then meet in LDS behind one barrier, and the exponentials, still
 // in registers, are weighted and added up per key:
 //   e = 2^(c*s - m_wave),  score += e * (omega_row * 2^(m_wave - M_row) / Z_row)
 // A probability of 2^-126 and more may be a large exponential times a factor below the normal numbers (a wavefront whose first key is far below the
@@ -117,7 +117,7 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
     const int n_tasks = a.n_q_heads * n_rb;
     const int n_task_my = g < n_tasks ? (n_tasks - g + a.groups - 1) / a.groups : 0;
     const int n_all = (S + 31) / 32;
-    const int n_my = wave < n_all ? (n_all - wave + waves - 1) / waves : 0;     // tiles wave, wave + 8, ...
+    const int n_my = wave < n_all ? (n_all - wave + waves - 1) / waves : 0;     // tiles wave, wave + waves, ...
 
     // (the only ordinary loads; complete before the first LDS-direct load is issued)
     float weight_sum = (float)L;
