@@ -221,9 +221,6 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
 
     for (int t = 0; t < n_my; ++t) *(lfloat_t)(uintptr_t)(sums_at + 256 * t + 4 * lane) = 0.f;
     const int my_row = 8 * ((li >> 2) & 3) + 4 * gl + (li & 3);      // the row whose sum sum_rows leaves in this lane
-    // A row without a finite sum (NaN, or only logits of -inf) is NaN at the keys it sees, and not by way of 0 * NaN at later ones: the
-    // last key that such a row sees.
-    int nan_upto = -1;
     request(0);
     int behind = request(1);
     int slot = 0;
@@ -330,8 +327,12 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
         if (kWeighted) f *= omega;
         if (32 * rb + li >= L) f = 0.f;               // a row past the window adds nothing
         const uint32_t odd = (uint32_t)__ballot(!(f < INFINITY));
-        f = f < INFINITY ? f : 0.f;
-        nan_upto = odd != 0 ? max(nan_upto, q_lo + 31 - __clz((int)odd)) : nan_upto;
+        if (__builtin_expect(odd != 0, 0)) {          // a row without a finite sum: NaN at the keys it sees, and not by way of 0 * NaN at later ones
+            if (!(f < INFINITY)) f = 0.f;
+#pragma unroll 1
+            for (int t = 0; t < n_my; ++t)
+                if (32 * (wave + waves * t) + li <= q_lo + 31 - __clz((int)odd)) *(lfloat_t)(uintptr_t)(sums_at + 256 * t + 4 * lane) = NAN;
+        }
         if (gl == 0) *(lfloat_t)(uintptr_t)(factors_at + 4 * li) = f;
         lanes_meet();
         float fr[16];
@@ -355,7 +356,7 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
         const float mine = *(lfloat_t)(uintptr_t)(sums_at + 256 * t + 4 * lane);
         const float sum = mine + __shfl_xor(mine, 32, 64);
         const int key = 32 * (wave + waves * t) + li;
-        if (gl == 0 && key < S) dst[key] = key <= nan_upto ? NAN : sum * norm;
+        if (gl == 0 && key < S) dst[key] = sum * norm;
     }
 }
 
