@@ -110,10 +110,10 @@ int launch_select(const float* parts, int groups, int32_t total_tokens, float* s
 }
 
 // Rows of partial sums that would take the selection's one workgroup longer than a launch that adds them with the whole chip (1.7 us).
-// What that launch adds to an update (us; 140 of random shapes, 1 to 12 sequences): 16 rows of up to 800 tokens +1.2...+2.5, of 1000...1600
-// +0.4...+0.8, 24 rows of up to 500 +0.3...+1.1, 32 rows of up to 1020 +0.2...+0.6, of 1100 -0.8, of 1240...1670 -0.3...-1.0 (beyond 32768
-// sums the selection goes to 1024 lanes), 40 rows of 190...710 -0.4...+0.2, 48 of up to 640 -0.2...-0.7, of 730...1240 -1.8, 64 of 100...500
-// -1.1...-1.8, of 540...1700 -1.4...-4.7.
+// What that launch adds to an update (us; 180 of random shapes, 1 to 12 sequences): 16 rows of up to 800 tokens +1.2...+2.5, of 1000...1600
+// +0.4...+0.8, 24 rows of up to 1000 +0.3...+1.1, of 1140...1410 -0.2...-0.4, of 1810...1950 -1.0, 32 rows of up to 1010 0...+0.7, of 1040...1130
+// -0.5...-1.0 (beyond 32768 sums the selection goes to 1024 lanes; the line at 36864 leaves these), of 1240...1980 -0.3...-1.8, 40 rows of
+// 190...710 -0.4...+0.2, 48 of up to 640 -0.2...-0.7, of 730...1240 -1.8, 64 of 100...500 -1.1...-1.8, of 540...1700 -1.4...-4.7.
 // One launch where the rows to copy are so few that the selection's own workgroups are enough for them; counted as if every
 // sequence kept as many as the one that keeps most, because all get the same number of workgroups.  Whole calls, two launches / one
 // (us): a 64-token layer on 32 heads (1.0 MB) 18.3 / 16.0, 256 tokens on 8 heads, d = 64 (0.3 MB) 18.5 / 16.6, updates of 16 x 70
