@@ -141,7 +141,11 @@ int launch_select_gather(const float* parts, int groups, int32_t total_tokens, f
         if (rc != PYR_OK) return rc;
         groups = 1;
     }
-    if (plan.split > 0) {
+    // (offsets written over the ones that are read, which one sequence can afford where one workgroup does both: not with several)
+    const auto overlap = [](const int32_t* a, int64_t n, const int32_t* b, int64_t m) { return a < b + m && b < a + n; };
+    const bool in_place = overlap(out_offsets_dev, n_seqs + (int64_t)1, seq_offsets_dev, n_seqs + (int64_t)1) ||
+                          overlap(out_offsets_dev, n_seqs + (int64_t)1, keep_len_dev, n_seqs);
+    if (plan.split > 0 && !in_place) {
         const int32_t room = (max_kept + plan.split - 1) / plan.split;
         hipLaunchKernelGGL(select_gather_kernel, dim3((unsigned)(plan.split * n_seqs)), dim3(kFusedLanes), (size_t)room * sizeof(int32_t), stream, parts,
                            (int32_t)groups, total_tokens, scores, seq_offsets_dev, keep_len_dev, w, kept_idx, out_offsets_dev, g,

@@ -79,3 +79,24 @@ def test_updates_add_select_and_gather(lib, lens, Hq, Hkv, d, w, rows, sums, one
     off = x["seq_offsets"]
     kept = [orc.select_pvc(res["scores"][off[b]:off[b + 1]], w, x["keep_len"][b]) + off[b] for b in range(len(lens))]
     assert np.array_equal(res["kept_idx"], np.concatenate(kept))
+
+
+def test_offsets_written_in_place(lib):
+    """One sequence whose offsets are replaced by the kept rows': workgroups that share the selection must not find them already replaced."""
+    lens, Hkv, d, w = (900,), 2, 64, 32
+    x = parity.inputs(workload(lens, 2 * Hkv, Hkv, d, w), lib)
+    want = lib.prefill_layer_from_numpy(x, w)
+    q, k, v = (lib.to_device_bf16(x[n]) for n in ("q", "k", "v"))
+    off_h, keep_h = (torch.from_numpy(np.ascontiguousarray(x[n], dtype=np.int32)) for n in ("seq_offsets", "keep_len"))
+    n_kept, shape = int(keep_h.sum()), lib.make_shape(1, 900, 900, 2 * Hkv, Hkv, d)
+    off_d, keep_d = off_h.cuda(), keep_h.cuda()
+    ws = torch.empty(lib.workspace_bytes(shape, w), dtype=torch.uint8, device="cuda")
+    out, scores = torch.empty_like(q), torch.empty(900, dtype=torch.float32, device="cuda")
+    kept, k_out = torch.empty(n_kept, dtype=torch.int32, device="cuda"), torch.empty(n_kept, Hkv, d, dtype=torch.bfloat16, device="cuda")
+    v_out = torch.empty_like(k_out)
+    for _ in range(20):
+        off_d.copy_(off_h)
+        lib.prefill_layer(q, k, v, off_d, off_h, shape, w, 0.0, keep_d, keep_h, out, scores, kept, off_d, k_out, v_out, ws, ws.numel())
+        assert off_d.tolist() == [0, n_kept]
+        assert np.array_equal(kept.cpu().numpy(), want["kept_idx"])
+        assert np.array_equal(lib.to_host_bits(k_out), want["k_out"]) and np.array_equal(lib.to_host_bits(v_out), want["v_out"])
