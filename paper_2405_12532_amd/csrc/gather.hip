@@ -10,7 +10,7 @@
 // about a tenth faster than the far-apart rows a short grid with a stride loop has in flight
 // (measured on an 8 KB-row copy of 1 GiB: 6.1-6.3 TB/s read + write against 5.5; two wavefronts
 // per workgroup were the best of 1, 2, 4, 8, 16).
-#include "gather_device.h"
+#include "pyr_internal.h"
 
 namespace pyr {
 namespace {
@@ -18,6 +18,24 @@ namespace {
 constexpr int kThreads = 128;
 constexpr int kWavesPerBlock = kThreads / 64;
 constexpr int64_t kMaxBlocks = 0x7fffffff;      // gridDim.x limit; beyond it the kernels' stride loops take over
+
+// One row by the calling wavefront: 16 bytes a lane, up to kUnroll loads per lane issued before the first store.
+__device__ __forceinline__ void copy_row(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int32_t chunks_per_row, int lane) {
+    constexpr int kUnroll = 8;
+    for (int c0 = 0; c0 < chunks_per_row; c0 += 64 * kUnroll) {
+        u32x4 buf[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int c = c0 + u * 64 + lane;
+            if (c < chunks_per_row) buf[u] = __builtin_nontemporal_load(src + c);
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int c = c0 + u * 64 + lane;
+            if (c < chunks_per_row) __builtin_nontemporal_store(buf[u], dst + c);
+        }
+    }
+}
 
 __global__ __launch_bounds__(kThreads) void gather_rows_kernel(
     const u32x4* __restrict__ src0, u32x4* __restrict__ dst0,

@@ -1,5 +1,4 @@
 // Launch of the segmented top-k (Algorithm 1, TopP(A_e, p); see select_device.h): one workgroup per sequence.
-#include "gather_device.h"
 #include "select_device.h"
 
 namespace pyr {
@@ -53,7 +52,10 @@ __global__ __launch_bounds__(kT) void select_topk_kernel(
 }
 
 // The selection and the gather of a small batch in one launch: `split` workgroups per sequence, each of which finds the threshold for
-// itself and copies its part of the kept rows (`room` at most).  Bound: latency, and a launch less of it.  (Held
+// itself and copies its part of the kept rows (`room` at most).  Bound: latency, and a launch less of it.  The copy goes by 16 bytes and not by rows,
+// so that all of a workgroup's (16 KB where the batch is as large as this launch takes) are on their way at once whatever a row's
+// length: whole calls, two launches / one with a wavefront per row / one (us): 203 x 55 tokens on 2/1 heads, d = 64 17.8 / 22.0 / 13.8, 16 x 370
+// 20.2 / 21.8 / 17.8, 1 x 64 on 32 heads, d = 128 17.9 / 16.7 / 15.3.  (Held
 // to 64 registers, as if a compute unit had more than one of these workgroups, it spills: 1 to 3 % on the whole call.)
 __global__ __launch_bounds__(kFusedLanes) void select_gather_kernel(
     const float* __restrict__ parts, int32_t groups, int32_t total_tokens, float* scores,
@@ -65,14 +67,28 @@ __global__ __launch_bounds__(kFusedLanes) void select_gather_kernel(
     ToPart sink{{kept_idx, out_offsets, b}, rows, part, split, room, 0, 0, 0};
     select_sequence<kFusedLanes, kInRegisters>(b, parts, groups, total_tokens, scores, part == 0, seq_offsets, keep_len, w, nullptr, &sh, sink);
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), n = sink.hi - sink.lo;
+    // item i: the 16 bytes at i % all of row i / all, which is its row of every source, one after the other
+    constexpr int kAhead = 4;
+    const int n = sink.hi - sink.lo;
     const int64_t first = (int64_t)sink.base + sink.lo;
-    for (int i = wave; i < n * g.n; i += kFusedLanes / 64) {
-        const int y = i / n, j = i - y * n;
-        const u32x4* src = y == 0 ? g.src[0] : y == 1 ? g.src[1] : g.src[2];
-        u32x4* dst = y == 0 ? g.dst[0] : y == 1 ? g.dst[1] : g.dst[2];
-        const int32_t chunks = y == 0 ? g.chunks[0] : y == 1 ? g.chunks[1] : g.chunks[2];
-        copy_row(src + (int64_t)__builtin_amdgcn_readfirstlane(rows[j]) * chunks, dst + (first + j) * chunks, chunks, lane);
+    const int32_t end0 = g.chunks[0], end1 = end0 + (g.n > 1 ? g.chunks[1] : 0), all = end1 + (g.n > 2 ? g.chunks[2] : 0);
+    for (int i0 = threadIdx.x; i0 < n * all; i0 += kAhead * kFusedLanes) {
+        u32x4 x[kAhead];
+        u32x4* to[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int i = i0 + u * kFusedLanes;
+            if (i >= n * all) break;
+            const int j = i / all, c = i - j * all, y = (c >= end0) + (c >= end1);
+            const int32_t chunks = y == 0 ? g.chunks[0] : y == 1 ? g.chunks[1] : g.chunks[2], at = c - (y == 0 ? 0 : y == 1 ? end0 : end1);
+            const u32x4* src = y == 0 ? g.src[0] : y == 1 ? g.src[1] : g.src[2];
+            u32x4* dst = y == 0 ? g.dst[0] : y == 1 ? g.dst[1] : g.dst[2];
+            x[u] = __builtin_nontemporal_load(src + (int64_t)rows[j] * chunks + at);
+            to[u] = dst + (first + j) * chunks + at;
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (i0 + u * kFusedLanes < n * all) __builtin_nontemporal_store(x[u], to[u]);
     }
     if (g.pos != nullptr)
         for (int j = threadIdx.x; j < n; j += kFusedLanes) g.pos_out[first + j] = g.pos[rows[j]];
@@ -116,9 +132,10 @@ int launch_select(const float* parts, int groups, int32_t total_tokens, float* s
 // 190...710 -0.4...+0.2, 48 of up to 640 -0.2...-0.7, of 730...1240 -1.8, 64 of 100...500 -1.1...-1.8, of 540...1700 -1.4...-4.7.
 // One launch where the rows to copy are so few that the selection's own workgroups are enough for them; counted as if every
 // sequence kept as many as the one that keeps most, because all get the same number of workgroups.  Whole calls, two launches / one
-// (us): a 64-token layer on 32 heads (1.0 MB) 18.3 / 16.0, 256 tokens on 8 heads, d = 64 (0.3 MB) 18.5 / 16.6, updates of 16 x 70
-// rows (2.6 MB) 16.5 / 14.8, of 1 x 176 (3.1 MB) 15.2 / 15.7, of 6 x 368 (5.4 MB) 14.9 / 16.1, of 16 x 512 (120 MB) 69.6 / 68.9...74.8;
-// 256 workgroups instead of 192 differ by 1 % either way, 64 cost up to 10 % at the upper end.
+// (us): a 64-token layer on 32 heads (1.0 MB) 17.9 / 15.3, 256 tokens on 8 heads, d = 64 (0.3 MB) 17.0 / 15.9, 16 x 183 on 8/4 heads, d = 64
+// (2.9 MB) 18.6 / 17.1; of 139 calls below the line one launch takes 0.78 to 0.99 of the time.  The line was drawn where the copy with a wavefront per
+// row lost (updates of 1 x 176 rows, 3.1 MB 15.2 / 15.7, of 6 x 368, 5.4 MB 14.9 / 16.1); 256 workgroups instead of 192 differed by 1 % either
+// way then, 64 cost up to 10 % at the upper end.
 SelectPlan plan_select(int groups, int32_t n_seqs, int32_t max_seqlen, int32_t max_kept, int64_t row_chunks) {
     constexpr int64_t kFewBytes = 3000000;
     constexpr int kFusedGroups = 192;

@@ -52,7 +52,7 @@ def update_launches(lib, lens, Hq, Hkv, d, w, **device):
     return route(lib, lens, Hq, Hkv, d, w, **device).window_groups > 1, bool(r.sums), r.select_split > 0
 
 
-@pytest.mark.parametrize("hidden,pos", [(0, False), (72, True)])
+@pytest.mark.parametrize("hidden,pos", [(0, False), (72, True)])      # 144 bytes: lanes of a wavefront in several rows and sources
 @pytest.mark.parametrize("lens,Hkv,d,w,plain,with_hidden", LAYERS)
 def test_small_batches_select_and_gather(lib, lens, Hkv, d, w, plain, with_hidden, hidden, pos):
     assert merged(lib, lens, Hkv, d, w, hidden) == (with_hidden if hidden else plain)
@@ -70,6 +70,28 @@ def test_small_batches_select_and_gather(lib, lens, Hkv, d, w, plain, with_hidde
         assert np.array_equal(r["hidden_out"], x["hidden"][kept])
     if pos:
         assert np.array_equal(r["pos_out"], ids[kept])
+
+
+@pytest.mark.parametrize("hidden", [8, 72, 4104])                      # rows of one 16-byte piece, of nine, of 513
+@pytest.mark.parametrize("lens", [(300,), (100, 7, 220), (5,) * 100])
+def test_rows_of_any_length_by_themselves(lib, lens, hidden):
+    """Hidden rows without K and V: one source, whose rows are shorter or longer than what a wavefront moves at a time."""
+    wl = workload(lens, 4, 2, 64, 16, hidden)
+    x = parity.inputs(wl, lib)
+    n_kept, T = int(x["keep_len"].sum()), sum(lens)
+    assert (launches(lib, lens, 4, 2, 64, 16, False, x["keep_len"], 2 * hidden).select_split > 0) == (max(x["keep_len"]) * len(lens) * 2 * hidden <= 3000000)
+    q, k, v, h = (lib.to_device_bf16(x[n]) for n in ("q", "k", "v", "hidden"))
+    off_h, keep_h = (torch.from_numpy(np.ascontiguousarray(x[n], dtype=np.int32)) for n in ("seq_offsets", "keep_len"))
+    shape = lib.make_shape(len(lens), T, max(lens), 4, 2, 64)
+    ws = torch.empty(lib.workspace_bytes(shape, 16), dtype=torch.uint8, device="cuda")
+    out, scores = torch.empty_like(q), torch.empty(T, dtype=torch.float32, device="cuda")
+    kept, out_off = torch.empty(n_kept, dtype=torch.int32, device="cuda"), torch.empty(len(lens) + 1, dtype=torch.int32, device="cuda")
+    h_out = torch.full((n_kept + 1, hidden), -7.0, dtype=torch.bfloat16, device="cuda")
+    lib.prefill_layer_fused(q, k, v, off_h.cuda(), off_h, shape, 16, 0.0, keep_h.cuda(), keep_h, None, h, 2 * hidden, None, out, scores, kept, out_off,
+                            None, None, h_out, None, ws, ws.numel())
+    torch.cuda.synchronize()
+    assert np.array_equal(lib.to_host_bits(h_out)[:n_kept], x["hidden"][kept.cpu().numpy()])
+    assert bool((h_out[n_kept] == -7.0).all()), "nothing is written past the kept rows"
 
 
 @pytest.mark.parametrize("lens,Hq,Hkv,d,w,rows,sums,one", UPDATES)
