@@ -14,7 +14,9 @@
 //   most; else they are staged in LDS, and where that is too small re-read from memory in every pass;
 // - the bins divide the span between the smallest and the largest key, not the bits in which keys differ: scores spread over
 //   ten octaves fill all bins (with leading bits 120 of 2048: five lanes of a wavefront on one bin, and bins too full to stop at);
-// - a bin of at most kCandidates keys ends the search: they are ranked against each other by value and position.
+// - a bin of at most kCandidates keys ends the search: they are ranked against each other by value and position.  Of equal keys only
+//   kEqualCandidates: more are counted in order, which costs two passes and not a look of every key at every other (scores of a few values,
+//   250 keys of each, one sequence of 2048 tokens 9.0 ranked, 5.0 counted, 6.2 by digits; 64 of each 6.0 / 4.9 / 6.2, 40 of each 5.5 / 5.7 / 6.2).
 // One pass over the bins at the score distributions of the method.
 // - beyond the registers' reach, whole blocks of a wavefront's positions go without the checks of the last one (half the instructions, which
 //   is what 16 keys a lane and more wait for: 16384 tokens 13.9 -> 10.8, 60000 69 -> 39).
@@ -30,6 +32,7 @@ namespace pyr {
 
 constexpr int kRegKeys = 8;                 // keys of a lane in registers, at most
 constexpr int kCandidates = 256;
+constexpr int kEqualCandidates = 48;
 
 // where a lane finds its keys after they have been loaded
 enum KeySource { kInRegisters, kInLds, kInMemory };
@@ -150,7 +153,7 @@ __device__ uint64_t find_threshold(const Each& each, int need, uint32_t kmin, ui
         base += bin << shift;
         bits = shift;
         whole = false;
-        if (in_bin <= kCandidates) {
+        if (in_bin <= kEqualCandidates || (bits > 0 && in_bin <= kCandidates)) {
             each([&](uint32_t key, int i, bool valid) {
                 if (valid && (key - base) >> bits == 0) sh->cand[atomicAdd(&sh->n_cand, 1u)] = ranked(key, i);
             });

@@ -179,3 +179,14 @@ def test_select_key_sources_and_search(lib, longest, dist):
         scores[1], scores[lens[0] + 1] = np.inf, -np.inf
     for share in (0.02, 0.5, 0.98):
         _select_case(lib, lens, 2, [max(min(2, S), int(share * S)) for S in lens], scores)
+
+
+@pytest.mark.parametrize("longest", [700, 4096, 8192, 9000, 40000])          # keys in registers (512 and 1024 lanes), LDS, memory
+@pytest.mark.parametrize("equal", [47, 48, 49, 256, 257])
+def test_select_equal_keys(lib, longest, equal):
+    """Neighbouring fp32 numbers, each the score of so many tokens: equal keys of the threshold's bin are ranked or counted in order."""
+    rng = np.random.default_rng(longest + equal)
+    lens, w = [longest, longest - 63, equal + 5], 5
+    scores = np.concatenate([_ulps_above(0.25, rng.permutation(np.arange(S) // equal)) for S in lens])
+    for k in (1, equal - 1, equal, equal + 1, longest // 2):
+        _select_case(lib, lens, w, [w + min(k, S - w) for S in lens], scores)
