@@ -90,6 +90,10 @@ def test_generation_walks():
         assert r.stats_waves == r.stats_tiles == r.stats_groups == 0, batch
     for batch in window.TWO_WALKS:
         assert route(binding, *batch, **MI355X).stats_waves > 0, batch
+    # measured, two walks / one (us): 115 / 127, 66 / 71, 145 / 159, and with other numbers of row blocks per KV head 34 / 31, 1073 / 900
+    for *batch, walks in (((793,) * 10, 40, 40, 128, 100, 2), ((300,) * 52, 64, 8, 128, 32, 2), ((1518,) * 69, 32, 8, 64, 32, 2),
+                          ((1537,), 32, 32, 128, 64, 1), ((2048,) * 64, 32, 32, 128, 64, 1)):
+        assert (route(binding, *batch, **MI355X).stats_waves > 0) == (walks == 2), batch
 
 
 def test_selection_and_gather():
