@@ -248,7 +248,8 @@ PYR_API int pyr_prefill_layer_ex(const void* q, const void* k, const void* v,
 
 /*
  * The whole layer step in as few launches as it takes (Appendix A.1 and the Limitations section: at small
- * batch the cost of selecting the PvC eats the gain - there every launch counts): attention; the score pass,
+ * batch the cost of selecting the PvC eats the gain - there every launch counts): attention; the score pass (a small
+ * batch's in the attention's launch, by a walk that finds the denominators itself),
  * which, when the batch is too small to fill the chip otherwise, splits the heads over several workgroups that
  * write partial sums; the selection, which adds those in a fixed order; ONE gather for K, V, the hidden rows and the position ids
  * (in the selection's launch where there are only few rows).
@@ -256,7 +257,7 @@ PYR_API int pyr_prefill_layer_ex(const void* q, const void* k, const void* v,
  *   hidden             dev, rows of hidden_row_bytes bytes (a multiple of 16) indexed by packed row; hidden_out
  *                      dev [sum k_b rows], written; both NULL skips them
  *   everything else as in pyr_prefill_layer_ex; results are those of the separate calls (scores may differ in
- *   the last bit when the heads are split: the partial sums are rounded once more).
+ *   the last bits when the heads are split, as the partial sums are rounded once more, and where a walk finds the denominators itself).
  */
 PYR_API int pyr_prefill_layer_fused(const void* q, const void* k, const void* v,
                       const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
@@ -360,6 +361,14 @@ typedef struct pyr_launches {
 PYR_API int pyr_diag_launches(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t w, int32_t generation,
                               const int32_t* keep_len_host, int64_t row_bytes, int32_t compute_units, int32_t xcds,
                               pyr_launches* launches_out);
+
+/*
+ * Diagnostic, not part of the method: whether pyr_prefill_layer_fused takes a batch's attention and scores in one launch.  Host only; launches nothing.
+ *   compute_units, xcds  as in pyr_diag_route
+ *   groups_out           host, written: rows of partial scores of that launch; 0: attention and scores have a launch each
+ */
+PYR_API int pyr_diag_layer(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t w, int32_t compute_units, int32_t xcds,
+                           int32_t* groups_out);
 
 #ifdef __cplusplus
 }

@@ -66,6 +66,7 @@ _SIGNATURES = {
     "pyr_diag_read_stream": (ctypes.c_int, [_VP, _SZ, _I32, _VP, _VP]),
     "pyr_diag_route": (ctypes.c_int, [ctypes.POINTER(PyrShape), _VP, _I32, _I32, _I32, ctypes.POINTER(PyrRoute)]),
     "pyr_diag_launches": (ctypes.c_int, [ctypes.POINTER(PyrShape), _VP, _I32, _I32, _VP, _I64, _I32, _I32, ctypes.POINTER(PyrLaunches)]),
+    "pyr_diag_layer": (ctypes.c_int, [ctypes.POINTER(PyrShape), _VP, _I32, _I32, _I32, ctypes.POINTER(_I32)]),
 }
 EXPORTS = tuple(_SIGNATURES)
 
@@ -263,6 +264,13 @@ def diag_launches(shape: PyrShape, seq_offsets_host, w: int, generation: bool, k
     _check(load().pyr_diag_launches(ctypes.byref(shape), _ptr(seq_offsets_host), int(w), int(bool(generation)), _ptr(keep_len_host),
                                     int(row_bytes), int(compute_units), int(xcds), ctypes.byref(out)), "pyr_diag_launches")
     return out
+
+
+def diag_layer(shape: PyrShape, seq_offsets_host, w: int, compute_units: int = 0, xcds: int = 0) -> int:
+    """Rows of partial scores where a layer's attention and scores go in one launch, 0 where they go in two (host only)."""
+    out = _I32(0)
+    _check(load().pyr_diag_layer(ctypes.byref(shape), _ptr(seq_offsets_host), int(w), int(compute_units), int(xcds), ctypes.byref(out)), "pyr_diag_layer")
+    return int(out.value)
 
 
 def decode_workspace_bytes(shape: PyrShape, w: int) -> int:

@@ -169,7 +169,10 @@ int pyr_attention(const void* q, const void* k, const void* v,
     if (info.uniform_len == 0 && shape->total_tokens > 0 && tile_map == nullptr) return PYR_ERR_WORKSPACE;
     pyr_shape s = *shape;
     s.max_seqlen = info.max_len;                 // (the caller's may be any upper bound: a grid made for it would hold tiles that are not there)
-    return pyr::launch_attention(q, k, v, seq_offsets_dev, seq_offsets_host, s, info.uniform_len,
+    pyr::AttentionChoice choice;
+    rc = pyr::choose_attention(s, seq_offsets_host, info.uniform_len, &choice);
+    if (rc != PYR_OK) return rc;
+    return pyr::launch_attention(choice, q, k, v, seq_offsets_dev, seq_offsets_host, s, info.uniform_len,
                                  scale_log2(softmax_scale, shape->head_dim), out, lse, tile_map, (hipStream_t)stream);
 }
 
@@ -315,13 +318,28 @@ int pyr_prefill_layer_fused(const void* q, const void* k, const void* v,
     pyr_shape s = *shape;
     s.max_seqlen = info.max_len;
 
-    // four launches (five for a ragged batch: the tile map): attention; the score pass; the selection, which also adds
-    // the partial sums of a score pass that was split; one gather for everything (a small batch's in the selection's launch)
-    rc = pyr::launch_attention(q, k, v, seq_offsets_dev, seq_offsets_host, s, info.uniform_len, c, out, lse, tile_map, st);
+    // four launches (five for a ragged batch: the tile map): attention; the score pass (in the same launch where the batch is small); the
+    // selection, which also adds the partial sums of a score pass that was split; one gather for everything (a small batch's in the selection's launch)
+    pyr::AttentionChoice choice;
+    pyr::DeviceInfo dev;
+    if (pyr::device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
+    rc = pyr::choose_attention(s, seq_offsets_host, info.uniform_len, &choice);
     if (rc != PYR_OK) return rc;
-    int groups = 1;
-    rc = pyr::launch_score_groups(q, k, lse, seq_offsets_dev, seq_offsets_host, s, info.min_len, w, c, row_weights_dev, scores, parts, &groups, st);
-    if (rc != PYR_OK) return rc;
+    const pyr::LayerPlan layer = pyr::plan_layer(s, seq_offsets_host, info.uniform_len, info.min_len, w, parts != nullptr, choice, dev);
+    int groups = layer.groups;
+    if (groups > 0) {
+        // (its walk finds the denominators itself, so no row statistics lie in front of the partial sums, and there is room for more of them)
+        if (groups > pyr::kMaxScoreGroups) parts = (float*)workspace;
+        rc = pyr::launch_layer(choice, groups, q, k, v, seq_offsets_dev, seq_offsets_host, s, info.uniform_len, w, c, row_weights_dev, out,
+                               groups > 1 ? parts : scores, st);
+        if (rc != PYR_OK) return rc;
+    } else {
+        groups = layer.strip.groups;
+        rc = pyr::launch_attention(choice, q, k, v, seq_offsets_dev, seq_offsets_host, s, info.uniform_len, c, out, lse, tile_map, st);
+        if (rc != PYR_OK) return rc;
+        rc = pyr::launch_score_groups(layer.strip, q, k, lse, seq_offsets_dev, seq_offsets_host, s, info.min_len, w, c, row_weights_dev, scores, parts, st);
+        if (rc != PYR_OK) return rc;
+    }
     pyr::GatherSources g{};
     if (k_out != nullptr) {
         const size_t kv_row = (size_t)shape->n_kv_heads * shape->head_dim * 2;
@@ -392,13 +410,29 @@ int pyr_diag_launches(const pyr_shape* shape, const int32_t* seq_offsets_host, i
     if (compute_units == 0 && pyr::device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
     pyr_shape s = *shape;
     s.max_seqlen = info.max_len;
-    int groups = route.score_groups;
+    int groups = pyr::layer_groups(s, seq_offsets_host, info.uniform_len, info.min_len, w, pyr::score_parts_bytes(*shape) != 0, dev);
+    if (groups == 0) groups = route.score_groups;
     if (generation != 0) groups = pyr::update_route(s, seq_offsets_host, info.min_len, w, dev, launches_out);
     else if (route.attention != 0) pyr::attention_tile_route(s, seq_offsets_host, info.uniform_len, route.attention, dev, launches_out);
     if (keep_len_host == nullptr) return PYR_OK;
     const pyr::SelectPlan plan = pyr::plan_select(groups, s.n_seqs, s.max_seqlen, max_kept, row_bytes / 16);
     launches_out->sums = plan.sums ? 1 : 0;
     launches_out->select_split = plan.split;
+    return PYR_OK;
+}
+
+int pyr_diag_layer(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t w, int32_t compute_units, int32_t xcds, int32_t* groups_out) {
+    pyr_route route;
+    const int rc = pyr_diag_route(shape, seq_offsets_host, w, compute_units, xcds, &route);
+    if (rc != PYR_OK) return rc;
+    if (groups_out == nullptr) return PYR_ERR_NULL;
+    BatchInfo info;
+    check_offsets(seq_offsets_host, shape->n_seqs, shape->total_tokens, shape->max_seqlen, &info);
+    pyr::DeviceInfo dev{0, compute_units, xcds};
+    if (compute_units == 0 && pyr::device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
+    pyr_shape s = *shape;
+    s.max_seqlen = info.max_len;
+    *groups_out = pyr::layer_groups(s, seq_offsets_host, info.uniform_len, info.min_len, w, pyr::score_parts_bytes(*shape) != 0, dev);
     return PYR_OK;
 }
 

@@ -854,9 +854,7 @@ int launch_attention_long(const void* q, const void* k, const void* v, const int
 // heads 6530 / 6630 / 7470, 32768 and 255 x 64 7240 / 8280 / 8960, 8192 and 500 x 100 850 / 840 / 1050; heads that do not divide over the
 // XCDs: 1 x 8192 on 32/4 heads 471 / 513 / 566, on 20/20 415 / 349 / 365.  d = 64: 64 x 2048 1550 / 1340 / 1770, 2 x 2500 on 8 heads
 // 54 / 34 / 26 - there this kernel never wins and is not built.
-// turn_out: of the kernel above, where it is chosen.
-int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, const DeviceInfo& dev, int* turn_out) {
-    *turn_out = 0;
+AttentionChoice pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, const DeviceInfo& dev) {
     const double kv_share = 1.0 + (double)s.n_kv_heads / s.n_q_heads;      // rows a query row's traffic comes with
     const double cus = dev.compute_units;
     double work0 = 0, work1 = 0, work2 = 0;
@@ -896,7 +894,7 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
                  b1 * len / 128 + tile1 * n1;
         work2 += a2 * (n1 * (n1 - 1) + steps + n1) / 2 + b2 * n1;
     }
-    if (max_len == 0) return 0;
+    if (max_len == 0) return AttentionChoice{0, 0, 0.0};
     const double heads = (double)s.n_q_heads * (uniform_len > 0 ? s.n_seqs : 1);
     const double steps = (max_len + 63) / 64;
     const double per_cu = s.head_dim == 128 ? 2 : 3;                       // workgroups of one group a compute unit holds
@@ -905,13 +903,14 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
     // (tiles of unequal length share fewer K/V rows, but fill each other's gaps)
     const double ragged1 = uniform_len > 0 ? 1.0 : s.head_dim == 128 ? 0.925 : 1.05, ragged2 = uniform_len > 0 ? 1.0 : 1.05;
     const double t1 = fmax(ragged1 * work1 * heads / (per_cu * cus), chain1), t2 = fmax(ragged2 * work2 * heads / cus, chain2);
-    if (s.head_dim != 128) return t2 < t1 ? 2 : 1;
+    if (s.head_dim != 128) return t2 < t1 ? AttentionChoice{2, 0, t2} : AttentionChoice{1, 0, t1};
+    int best_turn = 0;
     const double item = 1.37 * (steps + 4) + 12.2;                         // the longest item: first and last tile
     double t0;
     if (uniform_len > 0) {
         const int64_t list = (int64_t)s.n_seqs * items_of(max_len) * s.n_q_heads / xcds;
         const Turn turns = pick_turn(uniform_len, s.n_q_heads / s.n_kv_heads, list < slots ? (int)list : slots, list);
-        *turn_out = turns.turn;
+        best_turn = turns.turn;
         t0 = fmax(work0 / ((max_len + kBM - 1) / kBM) * turns.most, item);
     } else {                                                               // the longest list, and the item map's launch
         double run = 0, most = 0;
@@ -923,14 +922,14 @@ int pick_kernel(const pyr_shape& s, const int32_t* off, int32_t uniform_len, con
     }
     t0 += 3.0;
     if (s.n_kv_heads % dev.xccs != 0) t0 *= 0.865 + 0.09 * kv_share;       // one list for all XCDs
-    return t0 < t1 + 0.054 * chain1 && t0 < t2 ? 0 : t2 < t1 ? 2 : 1;        // (the last tiles of one group's grid run out unevenly)
+    if (t0 < t1 + 0.054 * chain1 && t0 < t2) return AttentionChoice{0, best_turn, t0};
+    return t2 < t1 ? AttentionChoice{2, 0, t2} : AttentionChoice{1, 0, t1};  // (the last tiles of one group's grid run out unevenly)
 }
 
 }  // namespace
 
 void attention_route(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t uniform_len, const DeviceInfo& dev, pyr_route* out) {
-    int turn = 0;
-    out->attention = pick_kernel(s, seq_offsets_host, uniform_len, dev, &turn);
+    out->attention = pick_kernel(s, seq_offsets_host, uniform_len, dev).kernel;
     if (out->attention != 0) {
         out->attention_listed = attention_tile_listed(s, seq_offsets_host, uniform_len) ? 1 : 0;
         return;
@@ -942,17 +941,26 @@ void attention_route(const pyr_shape& s, const int32_t* seq_offsets_host, int32_
     out->attention_items = (int32_t)((items * s.n_q_heads / xcds + slots - 1) / slots);
 }
 
-int launch_attention(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev,
+int layer_groups(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t uniform_len, int32_t min_seqlen, int32_t w, bool parts, const DeviceInfo& dev) {
+    return plan_layer(s, seq_offsets_host, uniform_len, min_seqlen, w, parts, pick_kernel(s, seq_offsets_host, uniform_len, dev), dev).groups;
+}
+
+int choose_attention(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t uniform_len, AttentionChoice* out) {
+    DeviceInfo dev;
+    if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
+    *out = pick_kernel(s, seq_offsets_host, uniform_len, dev);
+    return PYR_OK;
+}
+
+int launch_attention(const AttentionChoice& choice, const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev,
                      const int32_t* seq_offsets_host, const pyr_shape& shape, int32_t uniform_len, float scale_log2,
                      void* out, float* lse, int32_t* item_map, hipStream_t stream) {
     DeviceInfo dev;
     if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
-    int turn = 0;
-    const int which = pick_kernel(shape, seq_offsets_host, uniform_len, dev, &turn);
-    if (which == 0)
-        return launch_attention_long(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2, out, lse, item_map, turn,
+    if (choice.kernel == 0)
+        return launch_attention_long(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2, out, lse, item_map, choice.turn,
                                      dev, stream);
-    return launch_attention_tile(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2, out, lse, item_map, which,
+    return launch_attention_tile(q, k, v, seq_offsets_dev, seq_offsets_host, shape, uniform_len, scale_log2, out, lse, item_map, choice.kernel,
                                  stream);
 }
 

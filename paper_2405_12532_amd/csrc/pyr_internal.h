@@ -60,7 +60,13 @@ int launch_select_gather(const float* parts, int groups, int32_t total_tokens, f
                          const int32_t* keep_len_dev, int32_t n_seqs, int32_t max_seqlen, int32_t max_kept, int64_t n_kept, int32_t w,
                          int32_t* kept_idx, int32_t* out_offsets_dev, const GatherSources& sources, hipStream_t stream);
 
-int launch_attention(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev,
+// kernel 0: lists of 256-row tiles (attention.hip), whose place in them moves on by `turn`; 1, 2: attention_tile.hip with so many groups.
+struct AttentionChoice {
+    int kernel, turn;
+    double cost;                  // predicted microseconds
+};
+int choose_attention(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len, AttentionChoice* out);
+int launch_attention(const AttentionChoice& choice, const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev,
                      const int32_t* seq_offsets_host, const pyr_shape& shape, int32_t uniform_len, float scale_log2,
                      void* out, float* lse, int32_t* item_map, hipStream_t stream);
 
@@ -73,9 +79,11 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
 void attention_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len, const DeviceInfo& dev, pyr_route* out);
 void attention_tile_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len, int groups, const DeviceInfo& dev,
                           pyr_launches* out);
+int64_t attention_tiles(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len);      // 128-row tiles of a query head
 bool attention_tile_listed(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len);
 // (returns the rows of partial sums)
 int update_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, const DeviceInfo& dev, pyr_launches* out);
+int layer_groups(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len, int32_t min_seqlen, int32_t w, bool parts, const DeviceInfo& dev);
 void score_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, bool parts, const DeviceInfo& dev,
                  pyr_route* out);
 
@@ -84,15 +92,36 @@ int launch_score(const void* q, const void* k, const float* lse, const int32_t* 
                  const pyr_shape& shape, int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights,
                  float* scores, hipStream_t stream);
 
+// How a walk over K is cut up (score.hip): 32-key tiles of a range, wavefronts of a workgroup, workgroups a range's tasks are split over.
+struct StripPlan {
+    int range_tiles, waves, groups;
+    double cost;                  // predicted microseconds
+};
+
+// A prefill step's scores.  groups > 0: in the launch of the attention tiles (launch_layer), with so many rows of partial sums; 0: by a walk of
+// their own (launch_score_groups).  parts: whether the workspace has room for partial sums (score_parts_bytes()).
+struct LayerPlan {
+    int groups;
+    StripPlan strip;
+};
+LayerPlan plan_layer(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len, int32_t min_seqlen, int32_t w, bool parts,
+                     const AttentionChoice& choice, const DeviceInfo& dev);
+
 // The score pass with its small-batch extra (see score.hip): the tasks of a range split over several workgroups when the
-// grid is small.  *groups > 1 afterwards: `parts` (score_parts_bytes()) holds that many rows of total_tokens partial
-// sums and `scores` is not written yet (launch_select does it); *groups == 1: `scores` is complete.
-// parts == nullptr: never split.
+// grid is small.  plan.groups > 1: `parts` (score_parts_bytes()) then holds that many rows of total_tokens partial
+// sums and `scores` is not written yet (launch_select does it); else `scores` is complete.
 constexpr int kMaxScoreGroups = 16;
 size_t score_parts_bytes(const pyr_shape& shape);
-int launch_score_groups(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev,
+int launch_score_groups(const StripPlan& plan, const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev,
                         const int32_t* seq_offsets_host, const pyr_shape& shape, int32_t min_seqlen, int32_t w, float scale_log2,
-                        const float* row_weights, float* scores, float* parts, int* groups, hipStream_t stream);
+                        const float* row_weights, float* scores, float* parts, hipStream_t stream);
+
+// Attention tiles and the scores' one walk over K in one launch (layer.hip).  groups > 1: sums [groups, total_tokens]; 1: the scores themselves.
+// No row statistics are written.
+constexpr int layer_max_keys(int attention_groups) { return 1024 * attention_groups; }
+int launch_layer(const AttentionChoice& choice, int groups, const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev,
+                 const int32_t* seq_offsets_host, const pyr_shape& shape, int32_t uniform_len, int32_t w, float scale_log2,
+                 const float* row_weights, void* out, float* sums, hipStream_t stream);
 
 // Generation phase: the same scores from the window's own query buffer q_win [B, w, Hq, d]
 // (right-aligned), in one launch (launch_window) or three: row statistics per range of keys -> part, folded into lse_win

@@ -547,12 +547,6 @@ BatchCut cut_batch(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t 
     return cut;
 }
 
-// How a walk over K is cut up.
-struct StripPlan {
-    int range_tiles, waves, groups;
-    double cost;                 // microseconds
-};
-
 // The cut with the lowest cost, in microseconds, of two limits joined smoothly (the fourth root of the sum of fourth powers):
 // - The chain.  An engine's compute units take its workgroups in rounds.  A round takes 1.9 until its first tiles are there, then a
 //   wavefront goes through its tasks, each the range's tiles and the task's row blocks, one step after the other.  A step takes
@@ -707,15 +701,12 @@ size_t score_parts_bytes(const pyr_shape& s) {
     return blocks < 1024 ? (size_t)kMaxScoreGroups * s.total_tokens * sizeof(float) : 0;
 }
 
-int launch_score_groups(const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev,
+int launch_score_groups(const StripPlan& plan, const void* q, const void* k, const float* lse, const int32_t* seq_offsets_dev,
                         const int32_t* seq_offsets_host, const pyr_shape& s, int32_t min_seqlen, int32_t w, float scale_log2, const float* row_weights,
-                        float* scores, float* parts, int* groups, hipStream_t stream) {
-    *groups = 1;
+                        float* scores, float* parts, hipStream_t stream) {
     if (s.n_seqs == 0 || s.max_seqlen == 0) return PYR_OK;
     DeviceInfo dev;
     if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
-    const StripPlan plan = plan_strip(s, cut_batch(s, seq_offsets_host, min_seqlen), w, dev, 1, parts != nullptr ? kMaxScoreGroups : 1, true);
-    *groups = plan.groups;
     return launch_scores(q, k, lse, seq_offsets_dev, seq_offsets_host, s, min_seqlen, w, 0, scale_log2, row_weights, scores, parts, plan, dev,
                          stream);
 }
@@ -751,6 +742,58 @@ UpdatePlan plan_update(const pyr_shape& s, const BatchCut& cut, int32_t w, const
     const double folded = (double)s.n_seqs * w * s.n_q_heads * ((s.max_seqlen + 63) / 64);
     p.one_walk = p.window.waves > 0 && p.window.cost < line * (11.5 + 1.16 * p.stats.cost + 0.86 * p.scores.cost + 7.6e-6 * folded);
     return p;
+}
+
+// A prefill step's scores: by the strip walk behind the attention launch, or by one walk in the launch of the attention tiles (layer.hip), where the
+// windows' workgroups have the tiles' size, one or two groups of four wavefronts, and write a row of partial sums each.
+// The one walk saves a launch and its latency and reads K beside the tiles that read it too, but takes the tiles' compute units: it wins where batches
+// are small.  Both are predicted, in microseconds, from the attention's predicted time A and the strip walk's predicted C:
+// - apart: A + 0.66 C + 4.1;
+// - together: a workgroup takes 2.93 until its first tiles are there and then a task after the other, 0.43 and 0.88 per 32-key tile of a wavefront
+//   (query rows count as one), 0.825 of that at d = 64; 0.86 of what all of them take adds to A as a share of the chip; joined with the longest workgroup as in
+//   plan_strip.  A row of partial sums costs the selection 0.029.  At d = 64 five tiles a wavefront and more leave a compute unit
+//   room for two workgroups instead of three: 12 % more for the tiles.  Where tiles of two groups fill their rounds, three at most, so far that the windows
+//   open another: a tenth of A (1 x 2048 on 32 heads, two rounds exactly: 73.9 / 76.0).
+// Fitted to 1300 layers of random shapes (fifteen head shapes, w = 16...256, one sequence to 100, 32...2048 tokens, equal and ragged, with and without weights and
+// hidden rows), each timed apart and with up to nine numbers of rows on inputs that change from call to call; one launch is taken where it is predicted to save
+// 5 % of A, C and 10 us.  That chose it for 852 of them; over all 1300 the geometric mean of the time is 0.899 of that of the two launches (0.885 for
+// the best choice each time), and four were more than 2 % slower, 4 % at most (91 x 44 tokens on 8 heads, d = 64 20.6 / 21.5, 24 x 284 on 12, d = 64 36.2 / 37.4).
+// Two launches / one: 1 x 256 on 8 heads, d = 64 16.1 / 12.3, 1 x 473 on 32/8 heads, d = 64 19.7 / 15.8, 6 x 134 on 32/8 heads 25.8 / 20.7, 1 x 1058
+// on 40 heads 43.1 / 38.9; but 64 x 359 on 32 heads 385 / 399, 16 x 694 on 32/8 heads, d = 64 89.7 / 98.9.
+// Tried and taken back: the windows' workgroups behind the first rows of tiles, so that the longest tiles start first (within 1 %).
+LayerPlan plan_layer(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t uniform_len, int32_t min_seqlen, int32_t w, bool parts,
+                     const AttentionChoice& choice, const DeviceInfo& dev) {
+    LayerPlan plan{0, StripPlan{1, 1, 1, 0.0}};
+    if (s.n_seqs == 0 || s.max_seqlen == 0) return plan;
+    const BatchCut cut = cut_batch(s, seq_offsets_host, min_seqlen);
+    plan.strip = plan_strip(s, cut, w, dev, 1, parts ? kMaxScoreGroups : 1, true);
+    const int waves = 4 * choice.kernel, max_tiles = (s.max_seqlen + 31) / 32;
+    const int L = w < s.max_seqlen ? w : s.max_seqlen, tasks = s.n_q_heads * ((L + 31) / 32);
+    if (!parts || choice.kernel == 0 || s.max_seqlen > layer_max_keys(choice.kernel) || attention_tile_listed(s, seq_offsets_host, uniform_len)) return plan;
+    // (one dimension of workgroups, of which a launch takes 2^32 lanes)
+    if ((int64_t)s.n_seqs * (max_tiles + 3) / 4 * s.n_q_heads >= 1 << 20 || (int64_t)s.n_seqs * tasks >= 1 << 20) return plan;
+    const bool d64 = s.head_dim == 64;
+    const int wave_tiles = (max_tiles + waves - 1) / waves;
+    const double k = d64 ? 0.825 : 1.0, longest = 0.43 + 0.88 * k * (wave_tiles + 1), mean = 0.43 + 0.88 * k * (cut.tiles / s.n_seqs / waves + 1);
+    const double slots = (double)dev.compute_units * (choice.kernel == 2 ? 1 : d64 && wave_tiles <= 4 ? 3 : 2);
+    const double tiles = choice.cost * (d64 && choice.kernel == 1 && wave_tiles > 4 ? 1.12 : 1.0);
+    const int64_t places = attention_tiles(s, seq_offsets_host, uniform_len) * s.n_q_heads, cus = dev.compute_units;      // workgroups of the tiles
+    const int64_t spare = choice.kernel == 2 && places <= 3 * cus ? (places + cus - 1) / cus * cus - places : (int64_t)1 << 40;
+    double best = choice.cost + 0.66 * plan.strip.cost + 4.1 - 0.05 * (choice.cost + plan.strip.cost + 10.0);
+    // (the workspace has room for a row per query head where the row statistics would lie, and for the strip walk's rows behind them)
+    const int limit = tasks < s.n_q_heads + kMaxScoreGroups ? tasks : s.n_q_heads + kMaxScoreGroups;
+    for (int g = 1;; g = g < 8 ? 2 * g : g + 8) {
+        if (g > limit) g = limit;
+        const double own = 2.93 + (tasks + g - 1) / g * longest;
+        const double all = tiles + 0.86 * s.n_seqs * (g * 2.93 + tasks * mean) / slots;
+        const double cost = sqrt(sqrt(all * all * all * all + own * own * own * own)) + 0.029 * (g - 1) + (s.n_seqs * (int64_t)g > spare ? 0.1 * choice.cost : 0.0);
+        if (cost < best) {
+            best = cost;
+            plan.groups = g;
+        }
+        if (g == limit) break;
+    }
+    return plan;
 }
 
 void score_route(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, bool parts, const DeviceInfo& dev,

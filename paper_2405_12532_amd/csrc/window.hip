@@ -36,15 +36,7 @@ template <int D, int kTiles, bool kWeighted>
 __global__ __launch_bounds__(64 * kWindowWaves, 2) void window_kernel(WindowArgs a) {
     extern __shared__ __align__(1024) char smem[];
     int b, g;
-    const int id = (int)blockIdx.x;
-    if (a.xcds > 0) {
-        const int slot = id / a.xcds;
-        b = slot / a.groups * a.xcds + id % a.xcds;
-        g = slot % a.groups;
-    } else {
-        b = id / a.groups;
-        g = id % a.groups;
-    }
+    window_place(a, (int)blockIdx.x, &b, &g);
     window_scores<D, kTiles, kWeighted>(a, b, g, smem);
 }
 
@@ -130,8 +122,8 @@ WindowPlan plan_window(const pyr_shape& s, double tiles, int32_t w, int max_grou
     return best;
 }
 
-int launch_window(const void* q, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& s, bool equal, int32_t w, int32_t q_window,
-                  float scale_log2, const float* row_weights, float* sums, const WindowPlan& plan, const DeviceInfo& dev, hipStream_t stream) {
+WindowArgs window_args(const void* q, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& s, bool equal, int32_t w, int32_t q_window,
+                       float scale_log2, const float* row_weights, float* sums, int groups, const DeviceInfo& dev) {
     WindowArgs a{};
     a.q = (const uint16_t*)q;
     a.k = (const uint16_t*)k;
@@ -140,13 +132,19 @@ int launch_window(const void* q, const void* k, const int32_t* seq_offsets_dev, 
     a.n_q_heads = s.n_q_heads;
     a.n_kv_heads = s.n_kv_heads;
     a.w = w;
-    a.groups = plan.groups;
+    a.groups = groups;
     a.xcds = equal && s.n_seqs % dev.xccs == 0 ? dev.xccs : 0;
     a.q_window = q_window;
     a.c = scale_log2;
     a.row_weights = row_weights;
     a.sums = sums;
     a.total_tokens = s.total_tokens;
+    return a;
+}
+
+int launch_window(const void* q, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& s, bool equal, int32_t w, int32_t q_window,
+                  float scale_log2, const float* row_weights, float* sums, const WindowPlan& plan, const DeviceInfo& dev, hipStream_t stream) {
+    const WindowArgs a = window_args(q, k, seq_offsets_dev, s, equal, w, q_window, scale_log2, row_weights, sums, plan.groups, dev);
     const int64_t n = (int64_t)s.n_seqs * plan.groups;
     if (n >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
     return s.head_dim == 128 ? launch_window_d<128>(a, s.max_seqlen, (unsigned)n, plan.waves, stream) : launch_window_d<64>(a, s.max_seqlen, (unsigned)n, plan.waves, stream);

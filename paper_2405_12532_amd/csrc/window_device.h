@@ -45,11 +45,27 @@ struct WindowArgs {
     int32_t groups;                           // workgroups per sequence; workgroup g takes tasks g, g + groups, ...
     int32_t xcds;                             // > 0: equal lengths, a multiple of so many: a sequence's workgroups on one XCD
     int32_t q_window;                         // 0: q by packed row; else by (sequence, window slot)
+    int32_t by_kv_head;                       // tasks in turn over the KV heads; else query head after query head
     float c;
     const float* row_weights;
     float* sums;                              // [groups, total_tokens]
     int32_t total_tokens;
 };
+
+WindowArgs window_args(const void* q, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& s, bool equal, int32_t w, int32_t q_window,
+                       float scale_log2, const float* row_weights, float* sums, int groups, const DeviceInfo& dev);
+
+// Sequence and place in it of workgroup `id`.
+__device__ __forceinline__ void window_place(const WindowArgs& a, int id, int* b, int* g) {
+    if (a.xcds > 0) {
+        const int slot = id / a.xcds;
+        *b = slot / a.groups * a.xcds + id % a.xcds;
+        *g = slot % a.groups;
+    } else {
+        *b = id / a.groups;
+        *g = id % a.groups;
+    }
+}
 
 template <int D, int kTiles>
 constexpr int window_lds_bytes(int waves) {                      // of a wavefront: ring, weights, factors, key sums and moves; statistics
@@ -158,9 +174,20 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
     // The stream's next element: the query rows of a task, then its key tiles.  (The divisions once per task, not in front of every tile.)
     int left = n_my > 0 ? n_task_my : 0, at_e = 0, at_task = g, at_rb = 0;
     const char *at_q = nullptr, *at_k = nullptr;
+    auto task_place = [&](int task, int* h, int* rb) {
+        if (a.by_kv_head) {
+            const int r = task / a.n_kv_heads, of_group = r / n_rb;
+            *h = (task - r * a.n_kv_heads) * group + of_group;
+            *rb = r - of_group * n_rb;
+        } else {
+            *h = task / n_rb;
+            *rb = task - *h * n_rb;
+        }
+    };
     auto locate = [&]() {
-        const int h = __builtin_amdgcn_readfirstlane(at_task / n_rb);
-        at_rb = at_task - h * n_rb;
+        int h;
+        task_place(at_task, &h, &at_rb);
+        h = __builtin_amdgcn_readfirstlane(h);
         at_q = (const char*)(a.q + ((size_t)(q_row_base + 32 * at_rb) * a.n_q_heads + h) * D);
         at_k = (const char*)(a.k + ((size_t)(row0 + 32 * wave) * a.n_kv_heads + __builtin_amdgcn_readfirstlane(h / group)) * D);
     };
@@ -225,7 +252,8 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
     int behind = request(1);
     int slot = 0;
     for (int i = 0, task = g; i < n_task_my; ++i, task += a.groups) {
-        const int rb = task % n_rb;
+        int of_head, rb;
+        task_place(task, &of_head, &rb);
         const int q_lo = first_row + 32 * rb;         // sequence position of the block's first row
         f32x16 s[kTiles];                             // exponentials of the wavefront's tiles
         float l[16], omega = 1.f;                     // the lane's share of the rows' sums
