@@ -30,11 +30,11 @@ __global__ __launch_bounds__(1024) void tile_map_kernel(const int32_t* __restric
 }
 
 template <int D, int kGroups>
-int launch_tile(const TileArgs& a, dim3 grid, hipStream_t stream) {
+int launch_tile(const TileArgs& a, const NoFront& rest, dim3 grid, hipStream_t stream) {
     using T = TileLds<D, kGroups>;
     static std::atomic<uint64_t> lds_set{0};
     if (ensure_dynamic_lds((const void*)attention_tile_kernel<D, kGroups, NoFront>, T::kBytes, &lds_set) != PYR_OK) return PYR_ERR_LAUNCH;
-    hipLaunchKernelGGL((attention_tile_kernel<D, kGroups, NoFront>), grid, dim3(kGroups * 256), T::kBytes, stream, a, NoFront{});
+    hipLaunchKernelGGL((attention_tile_kernel<D, kGroups, NoFront>), grid, dim3(kGroups * 256), T::kBytes, stream, a, rest);
     return check_launch();
 }
 
@@ -138,7 +138,7 @@ void attention_tile_route(const pyr_shape& s, const int32_t* seq_offsets_host, i
 }
 
 int tile_args(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
-              const pyr_shape& s, int32_t uniform_len, float scale_log2, void* out, float* lse, const DeviceInfo& dev, TileArgs* args) {
+              const pyr_shape& s, int32_t uniform_len, float scale_log2, void* out, const DeviceInfo& dev, TileArgs* args) {
     TileArgs a{};
     a.q = (const uint16_t*)q;
     a.k = (const uint16_t*)k;
@@ -146,14 +146,12 @@ int tile_args(const void* q, const void* k, const void* v, const int32_t* seq_of
     a.seq_offsets = seq_offsets_dev;
     if ((int64_t)s.n_seqs * s.n_kv_heads >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
     a.n_seqs = s.n_seqs;
-    a.n_units = s.n_seqs * s.n_kv_heads;
     a.n_q_heads = s.n_q_heads;
     a.n_kv_heads = s.n_kv_heads;
     a.xcds = bound_xcds(s, seq_offsets_host, uniform_len, dev);
     a.uniform_len = uniform_len;
     a.c = scale_log2;
     a.out = (uint16_t*)out;
-    a.lse = lse;
     *args = a;
     return PYR_OK;
 }
@@ -171,23 +169,25 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
     DeviceInfo dev;
     if (device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
     TileArgs a;
-    int rc = tile_args(q, k, v, seq_offsets_dev, seq_offsets_host, s, uniform_len, scale_log2, out, lse, dev, &a);
+    int rc = tile_args(q, k, v, seq_offsets_dev, seq_offsets_host, s, uniform_len, scale_log2, out, dev, &a);
     if (rc != PYR_OK) return rc;
     const int tiles = (s.max_seqlen + kTileRows - 1) / kTileRows, head_group = s.n_q_heads / s.n_kv_heads;
+    NoFront rest{nullptr, lse, 0, 0};
     const auto launch = [&](dim3 grid) {
-        if (s.head_dim == 128) return groups == 2 ? launch_tile<128, 2>(a, grid, stream) : launch_tile<128, 1>(a, grid, stream);
-        return groups == 2 ? launch_tile<64, 2>(a, grid, stream) : launch_tile<64, 1>(a, grid, stream);
+        rest.tiles = (int32_t)grid.y;
+        if (s.head_dim == 128) return groups == 2 ? launch_tile<128, 2>(a, rest, grid, stream) : launch_tile<128, 1>(a, rest, grid, stream);
+        return groups == 2 ? launch_tile<64, 2>(a, rest, grid, stream) : launch_tile<64, 1>(a, rest, grid, stream);
     };
     // (sequence after sequence with the last tile first, the order a chunk of one sequence has)
     if (attention_tile_listed(s, seq_offsets_host, uniform_len)) {
         const int64_t listed = count_tiles(s, seq_offsets_host);
         hipLaunchKernelGGL(tile_map_kernel, dim3(1), dim3(1024), 0, stream, seq_offsets_dev, s.n_seqs, tile_map);
         rc = check_launch();
-        a.tile_map = tile_map;
+        rest.tile_map = tile_map;
         const int64_t x = (int64_t)(s.n_kv_heads + a.xcds - 1) / a.xcds * head_group * a.xcds;
         if (x * 256 * groups >= (int64_t)1 << 32) return PYR_ERR_UNSUPPORTED;
         for (int64_t first = 0; rc == PYR_OK && first < listed; first += kMaxGrid) {
-            a.first_tile = (int32_t)first;
+            rest.first_tile = (int32_t)first;
             rc = launch(dim3((unsigned)x, (unsigned)(listed - first < kMaxGrid ? listed - first : kMaxGrid)));
         }
         return rc;
@@ -195,7 +195,7 @@ int launch_attention_tile(const void* q, const void* k, const void* v, const int
     dim3 grid = tile_grid(s, seq_offsets_host, uniform_len, groups, dev, &a);
     for (int left = tiles; left > 0; left -= kMaxGrid) {         // (one launch below 8 million tokens a sequence)
         const int n = left < kMaxGrid ? left : kMaxGrid;
-        a.first_tile = left - n;
+        rest.first_tile = left - n;
         grid.y = (unsigned)n;
         rc = launch(grid);
         if (rc != PYR_OK) return rc;

@@ -34,23 +34,22 @@ struct TileLds {
     static constexpr int kBytes = kGroups * kGroupBytes > kMergeBytes ? kGroups * kGroupBytes : kMergeBytes;
 };
 
+// (Kernel arguments of 112 bytes and less, implicit ones - the grid's and the workgroup's size - among them, are 0.7 us less host time a launch
+// than longer ones, 2.8 / 3.5: so the grid's size is passed, and what does not go together does not travel together.)
 struct TileArgs {
     const uint16_t* q;
     const uint16_t* k;
     const uint16_t* v;
     const int32_t* seq_offsets;
-    const int32_t* tile_map;                      // the list of a ragged batch's tiles (prefix sums of tiles per sequence), or nullptr
-    int32_t n_seqs;
-    int32_t n_units, n_q_heads, n_kv_heads;       // unit: one KV head of one sequence
-    int32_t units_per_chunk, xcds, uniform_len, first_tile;
-    float c;
     uint16_t* out;
-    float* lse;
+    int32_t n_seqs, uniform_len, n_q_heads, n_kv_heads;
+    int32_t units_per_chunk, xcds;                // unit: one KV head of one sequence
+    float c;
 };
 
 // Launch arguments of a batch (attention_tile.hip), and the grid where its tiles are not listed (one launch below 8 million tokens a sequence).
 int tile_args(const void* q, const void* k, const void* v, const int32_t* seq_offsets_dev, const int32_t* seq_offsets_host,
-              const pyr_shape& s, int32_t uniform_len, float scale_log2, void* out, float* lse, const DeviceInfo& dev, TileArgs* args);
+              const pyr_shape& s, int32_t uniform_len, float scale_log2, void* out, const DeviceInfo& dev, TileArgs* args);
 dim3 tile_grid(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t uniform_len, int groups, const DeviceInfo& dev, TileArgs* a);
 
 // Grid: x = ((unit of the chunk's share of one XCD) * group + query head of the group) * xcds + xcd; y = query tile, the last
@@ -58,10 +57,13 @@ dim3 tile_grid(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t unif
 // inside a chunk the long tiles of all its units start first.
 // With a list (very unequal sequences, see the launch): x = (place * group + query head of the group) * xcds + xcd, where the
 // places are the KV heads of a sequence that one XCD serves; y = position in the list of all sequences' tiles.
-// Front: what the first `front.workgroups` workgroups of a one-dimensional grid do instead of a tile (layer.hip), or nothing.
+// Front: what the first `front.workgroups` workgroups of a one-dimensional grid do instead of a tile (layer.hip), or nothing, and the arguments that go with it.
 struct NoFront {
     static constexpr bool kAny = false;
     static constexpr int kWaves = 2;              // wavefronts of a SIMD to leave registers for
+    const int32_t* tile_map;                      // the list of a ragged batch's tiles (prefix sums of tiles per sequence), or nullptr
+    float* lse;
+    int32_t first_tile, tiles;                    // of the grid's y
 };
 template <int D, int kGroups, class Front>
 __global__ __launch_bounds__(kGroups * 256, Front::kWaves) void attention_tile_kernel(TileArgs a, Front front) {
@@ -79,10 +81,12 @@ __global__ __launch_bounds__(kGroups * 256, Front::kWaves) void attention_tile_k
     constexpr int kLine = 256 / kRowBytes;        // rows per 256-byte bank line (1 or 2)
     static_assert(2 * kInstr == NS, "one load instruction per slice of a group");
     extern __shared__ __attribute__((aligned(1024))) char smem[];
-    int grid_x = (int)blockIdx.x, grid_y = (int)blockIdx.y, grid_z = (int)blockIdx.z, tiles = (int)gridDim.y;
+    int grid_x = (int)blockIdx.x, grid_y = (int)blockIdx.y, grid_z = (int)blockIdx.z, tiles, first_tile = 0;
+    const int32_t* tile_map = nullptr;
+    float* lse = nullptr;
     if constexpr (Front::kAny) {
         if (grid_x < front.workgroups) {
-            front.run(grid_x, smem);
+            front.run(a, grid_x, smem);
             return;
         }
         const int place = grid_x - front.workgroups, row = place / front.grid_x;
@@ -90,6 +94,11 @@ __global__ __launch_bounds__(kGroups * 256, Front::kWaves) void attention_tile_k
         grid_x = place - row * front.grid_x;
         grid_z = row / tiles;
         grid_y = row - grid_z * tiles;
+    } else {
+        tiles = front.tiles;
+        first_tile = front.first_tile;
+        tile_map = front.tile_map;
+        lse = front.lse;
     }
 
     const int lane = threadIdx.x & 63;
@@ -101,28 +110,28 @@ __global__ __launch_bounds__(kGroups * 256, Front::kWaves) void attention_tile_k
     const int head_group = a.n_q_heads / a.n_kv_heads;
     const int xcd = grid_x % a.xcds, slot = grid_x / a.xcds;
     int b, kvh, q_tile;
-    if (a.tile_map != nullptr) {
+    if (tile_map != nullptr) {
         // The sequence: the last b with tile_map[b] <= position, found 64 candidates at a time (a binary search would be a chain of
         // a dozen loads in front of each tile).  [b, b + span) holds it; candidate lane l stands at b + l * step.
-        const int pos = a.first_tile + grid_y;
+        const int pos = first_tile + grid_y;
         b = 0;
         for (int span = a.n_seqs; span > 1;) {
             const int step = (span + 63) / 64;
             const int cand = b + lane * step;
-            const bool below = lane * step < span && a.tile_map[cand] <= pos;
+            const bool below = lane * step < span && tile_map[cand] <= pos;
             const int hits = __builtin_popcountll(__builtin_amdgcn_ballot_w64(below));
             b += (hits - 1) * step;               // (candidate 0 always is one)
             span = min(step, span - (hits - 1) * step);
         }
-        q_tile = a.tile_map[b + 1] - 1 - pos;
+        q_tile = tile_map[b + 1] - 1 - pos;
         kvh = (xcd + a.xcds - (int)((int64_t)b * a.n_kv_heads % a.xcds)) % a.xcds + slot / head_group * a.xcds;      // the XCDs take turns at the odd heads
         if (kvh >= a.n_kv_heads) return;          // (uniform over the workgroup, like the others)
     } else {
         const int unit = (grid_z * a.units_per_chunk + slot / head_group) * a.xcds + xcd;
-        if (unit >= a.n_units) return;
         b = unit / a.n_kv_heads;
+        if (b >= a.n_seqs) return;
         kvh = unit % a.n_kv_heads;
-        q_tile = a.first_tile + tiles - 1 - grid_y;
+        q_tile = first_tile + tiles - 1 - grid_y;
     }
     const int h = kvh * head_group + slot % head_group;
     int row0, S;
@@ -540,8 +549,8 @@ __global__ __launch_bounds__(kGroups * 256, Front::kWaves) void attention_tile_k
         for (int dt = 0; dt < kStoreTiles; ++dt)
 #pragma unroll
             for (int ap = 0; ap < 2; ++ap) *(u32x4*)(dst + 32 * dt + 16 * ap) = o16[dt][ap];
-        if (a.lse != nullptr && gl == 0 && grp == 0)
-            a.lse[(size_t)(row0 + qrow) * a.n_q_heads + h] = m_run * a.c + __builtin_amdgcn_logf(l_tot);
+        if (lse != nullptr && gl == 0 && grp == 0)
+            lse[(size_t)(row0 + qrow) * a.n_q_heads + h] = m_run * a.c + __builtin_amdgcn_logf(l_tot);
     }
 }
 

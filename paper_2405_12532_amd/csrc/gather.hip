@@ -40,12 +40,12 @@ __device__ __forceinline__ void copy_row(const u32x4* __restrict__ src, u32x4* _
 __global__ __launch_bounds__(kThreads) void gather_rows_kernel(
     const u32x4* __restrict__ src0, u32x4* __restrict__ dst0,
     const u32x4* __restrict__ src1, u32x4* __restrict__ dst1,
-    const int32_t* __restrict__ kept_idx, int64_t n_rows, int32_t chunks_per_row) {
+    const int32_t* __restrict__ kept_idx, int64_t n_rows, int32_t chunks_per_row, int32_t blocks) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const u32x4* __restrict__ src = blockIdx.y == 0 ? src0 : src1;
     u32x4* __restrict__ dst = blockIdx.y == 0 ? dst0 : dst1;
-    const int64_t wave_stride = (int64_t)gridDim.x * kWavesPerBlock;
+    const int64_t wave_stride = (int64_t)blocks * kWavesPerBlock;
     for (int64_t j = (int64_t)blockIdx.x * kWavesPerBlock + wave; j < n_rows; j += wave_stride) {
         copy_row(src + (int64_t)kept_idx[j] * chunks_per_row, dst + j * chunks_per_row, chunks_per_row, lane);
     }
@@ -53,21 +53,22 @@ __global__ __launch_bounds__(kThreads) void gather_rows_kernel(
 
 // Several sources gathered with one index list in ONE launch (K, V, the hidden rows, the position ids): at small
 // batch every launch costs about as much as the rows it moves (Appendix A.1 is about exactly this regime).
+// (Arguments of 112 bytes and less, the grid's size among them, which would bring the implicit ones along: 0.7 us less host time a launch.)
 // blockIdx.y picks the source; the last y, if pos is given, gathers the 4-byte position ids.
 __global__ __launch_bounds__(kThreads) void gather_multi_kernel(GatherSources g, const int32_t* __restrict__ kept_idx,
-                                                                int64_t n_rows) {
+                                                                int64_t n_rows, int32_t blocks) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int y = blockIdx.y;
     if (y >= g.n) {                    // position ids
-        for (int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x; j < n_rows; j += (int64_t)gridDim.x * kThreads)
+        for (int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x; j < n_rows; j += (int64_t)blocks * kThreads)
             g.pos_out[j] = g.pos[kept_idx[j]];
         return;
     }
     const u32x4* __restrict__ src = y == 0 ? g.src[0] : y == 1 ? g.src[1] : g.src[2];
     u32x4* __restrict__ dst = y == 0 ? g.dst[0] : y == 1 ? g.dst[1] : g.dst[2];
     const int32_t chunks_per_row = y == 0 ? g.chunks[0] : y == 1 ? g.chunks[1] : g.chunks[2];
-    const int64_t wave_stride = (int64_t)gridDim.x * kWavesPerBlock;
+    const int64_t wave_stride = (int64_t)blocks * kWavesPerBlock;
     for (int64_t j = (int64_t)blockIdx.x * kWavesPerBlock + wave; j < n_rows; j += wave_stride) {
         copy_row(src + (int64_t)kept_idx[j] * chunks_per_row, dst + j * chunks_per_row, chunks_per_row, lane);
     }
@@ -98,7 +99,7 @@ int launch_gather_multi(const GatherSources& g, const int32_t* kept_idx, int64_t
     int64_t blocks = (n_kept + kWavesPerBlock - 1) / kWavesPerBlock;
     if (blocks > kMaxBlocks) blocks = kMaxBlocks;
     dim3 grid((unsigned)blocks, (unsigned)(g.n + (g.pos != nullptr ? 1 : 0)), 1);
-    hipLaunchKernelGGL(gather_multi_kernel, grid, dim3(kThreads), 0, stream, g, kept_idx, n_kept);
+    hipLaunchKernelGGL(gather_multi_kernel, grid, dim3(kThreads), 0, stream, g, kept_idx, n_kept, (int32_t)blocks);
     return check_launch();
 }
 
@@ -111,7 +112,7 @@ int launch_gather(const void* src0, void* dst0, const void* src1, void* dst1, si
     dim3 grid((unsigned)blocks, src1 != nullptr ? 2 : 1, 1);
     hipLaunchKernelGGL(gather_rows_kernel, grid, dim3(kThreads), 0, stream,
                        (const u32x4*)src0, (u32x4*)dst0, (const u32x4*)src1, (u32x4*)dst1,
-                       kept_idx, n_kept, chunks);
+                       kept_idx, n_kept, chunks, (int32_t)blocks);
     return check_launch();
 }
 

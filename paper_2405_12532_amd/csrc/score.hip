@@ -72,16 +72,19 @@ struct StripArgs {
     const uint16_t* k;
     const float* lse;
     const int32_t* seq_offsets;
-    int32_t n_seqs, n_q_heads, n_kv_heads, w;
+    const float* row_weights;
+    union {                                   // (arguments of 112 bytes and less, implicit ones among them, are 0.7 us less host time a launch)
+        float* sums;                          // [groups, total_tokens]
+        float2* part;                         // kStats: [range, sequence, query head, window slot]
+    };
+    int32_t n_seqs, n_q_heads, n_kv_heads, w, total_tokens;
     int32_t range_tiles, ranges_per_seq;      // tiles of a range; ranges of the longest sequence
+    int32_t waves, groups;                    // of a workgroup; workgroups a range's tasks are split over (the grid's y)
     int32_t order, xcds, turn, head_step;     // order of the ranges over the workgroups, of the heads over the ranges
     int32_t q_window;                         // 0: q and lse by packed row; else by (sequence, window slot)
     float c;
-    const float* row_weights;
-    float* sums;                              // [gridDim.y, total_tokens]
-    int32_t total_tokens;
-    float2* part;                             // kStats: [range, sequence, query head, window slot]
 };
+static_assert(sizeof(StripArgs) <= 112, "short arguments");
 
 template <int D>
 constexpr int wave_lds_bytes(int range_tiles) { return kSlots * 32 * D * 2 + 2 * kRowArea + 256 * range_tiles; }
@@ -143,7 +146,7 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
     constexpr int kRowLoads = kMode == kStats ? 0 : kWeighted ? 2 : 1;      // ... of a task's denominators and weights
     extern __shared__ __align__(1024) char smem[];
 
-    const int lane = threadIdx.x & 63, waves = (int)(blockDim.x >> 6);
+    const int lane = threadIdx.x & 63, waves = a.waves;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int li = lane & 31, gl = lane >> 5;
     // ---- which sequence, which range (uniform over the workgroup)
@@ -195,7 +198,7 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
     const int pairs = (blocks + 1) / 2;
     // this workgroup's share of the tasks, dealt to its wavefronts one by one
     const int64_t n_tasks = (int64_t)a.n_kv_heads * pairs;
-    const int t_begin = (int)(n_tasks * blockIdx.y / gridDim.y), t_end = (int)(n_tasks * (blockIdx.y + 1) / gridDim.y);
+    const int t_begin = (int)(n_tasks * blockIdx.y / a.groups), t_end = (int)(n_tasks * (blockIdx.y + 1) / a.groups);
     const int n_my = max(0, (t_end - t_begin - wave + waves - 1) / waves);
     // Where the launcher asks for it (head_step != 0), neighbouring ranges start their walks head_step heads apart (a step of 8: at
     // two different heads of 16, four of 32; an odd step: at all of them): workgroups that run side by side then read different
@@ -428,7 +431,7 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
     const float norm = 1.0f / ((float)a.n_q_heads * weight_sum);
     __syncthreads();
     float* dst = a.sums + (size_t)blockIdx.y * a.total_tokens + row0 + key_base;
-    for (int x = threadIdx.x; x < 32 * n_tiles && key_base + x < S; x += blockDim.x) {
+    for (int x = threadIdx.x; x < 32 * n_tiles && key_base + x < S; x += 64 * waves) {
         const uint32_t at = lds0 + kSlots * kTileBytes + 2 * kRowArea + 256 * (x >> 5) + 4 * (x & 31);
         float sum = 0.f;
         for (int wv = 0; wv < waves; ++wv) {
@@ -638,10 +641,16 @@ int launch_strip(const void* q, const void* k, const float* lse, const int32_t* 
     a.k = (const uint16_t*)k;
     a.lse = lse;
     a.seq_offsets = seq_offsets_dev;
+    a.row_weights = row_weights;
+    if (kMode == kStats) a.part = part;
+    else a.sums = sums;
     a.n_seqs = s.n_seqs;
+    a.w = w;
+    a.total_tokens = s.total_tokens;
     a.n_q_heads = s.n_q_heads;
     a.n_kv_heads = s.n_kv_heads;
-    a.w = w;
+    a.groups = plan.groups;
+    a.waves = plan.waves;
     a.range_tiles = plan.range_tiles;
     a.ranges_per_seq = ((s.max_seqlen + 31) / 32 + plan.range_tiles - 1) / plan.range_tiles;
     // A whole sequence per XCD where that spreads the work evenly by construction (equal lengths, a multiple of the XCD
@@ -660,10 +669,6 @@ int launch_strip(const void* q, const void* k, const float* lse, const int32_t* 
     a.head_step = pick_head_step(s, plan.range_tiles);
     a.q_window = q_window;
     a.c = scale_log2;
-    a.row_weights = row_weights;
-    a.sums = sums;
-    a.total_tokens = s.total_tokens;
-    a.part = part;
     const int64_t n = a.order == kPacked ? ranges : (int64_t)s.n_seqs * a.ranges_per_seq;
     if (n >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)n, (unsigned)plan.groups, 1);

@@ -57,10 +57,40 @@ __global__ __launch_bounds__(kT) void select_topk_kernel(
 // length: whole calls, two launches / one with a wavefront per row / one (us): 203 x 55 tokens on 2/1 heads, d = 64 17.8 / 22.0 / 13.8, 16 x 370
 // 20.2 / 21.8 / 17.8, 1 x 64 on 32 heads, d = 128 17.9 / 16.7 / 15.3.  (Held
 // to 64 registers, as if a compute unit had more than one of these workgroups, it spills: 1 to 3 % on the whole call.)
+// Sources: GatherSources, or K and V alone, which leaves the arguments at 108 bytes (112 and less are 0.7 us less host time a launch).
+struct TwoSources {
+    const u32x4* src[2];
+    u32x4* dst[2];
+    int32_t row_chunks;                // of either
+    __device__ __forceinline__ int32_t all() const { return 2 * row_chunks; }
+    __device__ __forceinline__ int32_t piece(int32_t c, const u32x4** from, u32x4** to, int32_t* chunks) const {
+        const bool y = c >= row_chunks;
+        *from = y ? src[1] : src[0];
+        *to = y ? dst[1] : dst[0];
+        *chunks = row_chunks;
+        return y ? c - row_chunks : c;
+    }
+    __device__ __forceinline__ void position(int32_t, int64_t) const {}
+};
+struct AnySources {
+    GatherSources g;
+    __device__ __forceinline__ int32_t end1() const { return g.chunks[0] + (g.n > 1 ? g.chunks[1] : 0); }
+    __device__ __forceinline__ int32_t all() const { return end1() + (g.n > 2 ? g.chunks[2] : 0); }
+    __device__ __forceinline__ int32_t piece(int32_t c, const u32x4** from, u32x4** to, int32_t* chunks) const {      // its place in the row of its source
+        const int y = (c >= g.chunks[0]) + (c >= end1());
+        *from = y == 0 ? g.src[0] : y == 1 ? g.src[1] : g.src[2];
+        *to = y == 0 ? g.dst[0] : y == 1 ? g.dst[1] : g.dst[2];
+        *chunks = y == 0 ? g.chunks[0] : y == 1 ? g.chunks[1] : g.chunks[2];
+        return c - (y == 0 ? 0 : y == 1 ? g.chunks[0] : end1());
+    }
+    __device__ __forceinline__ void position(int32_t row, int64_t at) const {
+        if (g.pos != nullptr) g.pos_out[at] = g.pos[row];
+    }
+};
+template <class Sources>
 __global__ __launch_bounds__(kFusedLanes) void select_gather_kernel(
-    const float* __restrict__ parts, int32_t groups, int32_t total_tokens, float* scores,
-    const int32_t* __restrict__ seq_offsets, const int32_t* __restrict__ keep_len, int32_t w,
-    int32_t* __restrict__ kept_idx, int32_t* __restrict__ out_offsets, GatherSources g, int32_t split, int32_t room) {
+    const float* __restrict__ parts, float* scores, const int32_t* __restrict__ seq_offsets, const int32_t* __restrict__ keep_len,
+    int32_t* __restrict__ kept_idx, int32_t* __restrict__ out_offsets, Sources g, int32_t groups, int32_t total_tokens, int32_t w, int32_t split, int32_t room) {
     extern __shared__ int32_t rows[];
     __shared__ SelectShared<kFusedLanes> sh;
     const int b = (int)blockIdx.x / split, part = (int)blockIdx.x - b * split;
@@ -71,7 +101,7 @@ __global__ __launch_bounds__(kFusedLanes) void select_gather_kernel(
     constexpr int kAhead = 4;
     const int n = sink.hi - sink.lo;
     const int64_t first = (int64_t)sink.base + sink.lo;
-    const int32_t end0 = g.chunks[0], end1 = end0 + (g.n > 1 ? g.chunks[1] : 0), all = end1 + (g.n > 2 ? g.chunks[2] : 0);
+    const int32_t all = g.all();
     for (int i0 = threadIdx.x; i0 < n * all; i0 += kAhead * kFusedLanes) {
         u32x4 x[kAhead];
         u32x4* to[kAhead];
@@ -79,10 +109,11 @@ __global__ __launch_bounds__(kFusedLanes) void select_gather_kernel(
         for (int u = 0; u < kAhead; ++u) {
             const int i = i0 + u * kFusedLanes;
             if (i >= n * all) break;
-            const int j = i / all, c = i - j * all, y = (c >= end0) + (c >= end1);
-            const int32_t chunks = y == 0 ? g.chunks[0] : y == 1 ? g.chunks[1] : g.chunks[2], at = c - (y == 0 ? 0 : y == 1 ? end0 : end1);
-            const u32x4* src = y == 0 ? g.src[0] : y == 1 ? g.src[1] : g.src[2];
-            u32x4* dst = y == 0 ? g.dst[0] : y == 1 ? g.dst[1] : g.dst[2];
+            const int j = i / all;
+            const u32x4* src;
+            u32x4* dst;
+            int32_t chunks;
+            const int32_t at = g.piece(i - j * all, &src, &dst, &chunks);
             x[u] = __builtin_nontemporal_load(src + (int64_t)rows[j] * chunks + at);
             to[u] = dst + (first + j) * chunks + at;
         }
@@ -90,8 +121,7 @@ __global__ __launch_bounds__(kFusedLanes) void select_gather_kernel(
         for (int u = 0; u < kAhead; ++u)
             if (i0 + u * kFusedLanes < n * all) __builtin_nontemporal_store(x[u], to[u]);
     }
-    if (g.pos != nullptr)
-        for (int j = threadIdx.x; j < n; j += kFusedLanes) g.pos_out[first + j] = g.pos[rows[j]];
+    for (int j = threadIdx.x; j < n; j += kFusedLanes) g.position(rows[j], first + j);
 }
 
 template <int kT, KeySource kSource>
@@ -164,10 +194,14 @@ int launch_select_gather(const float* parts, int groups, int32_t total_tokens, f
                           overlap(out_offsets_dev, n_seqs + (int64_t)1, keep_len_dev, n_seqs);
     if (plan.split > 0 && !in_place) {
         const int32_t room = (max_kept + plan.split - 1) / plan.split;
-        hipLaunchKernelGGL(select_gather_kernel, dim3((unsigned)(plan.split * n_seqs)), dim3(kFusedLanes), (size_t)room * sizeof(int32_t), stream, parts,
-                           (int32_t)groups, total_tokens, scores, seq_offsets_dev, keep_len_dev, w, kept_idx, out_offsets_dev, g,
-                           (int32_t)plan.split, room);
-        return check_launch();
+        const auto launch = [&](auto sources) {
+            hipLaunchKernelGGL((select_gather_kernel<decltype(sources)>), dim3((unsigned)(plan.split * n_seqs)), dim3(kFusedLanes), (size_t)room * sizeof(int32_t),
+                               stream, parts, scores, seq_offsets_dev, keep_len_dev, kept_idx, out_offsets_dev, sources, (int32_t)groups, total_tokens, w,
+                               (int32_t)plan.split, room);
+            return check_launch();
+        };
+        if (g.n == 2 && g.chunks[0] == g.chunks[1] && g.pos == nullptr) return launch(TwoSources{{g.src[0], g.src[1]}, {g.dst[0], g.dst[1]}, g.chunks[0]});
+        return launch(AnySources{g});
     }
     const int rc = launch_select(parts, groups, total_tokens, scores, seq_offsets_dev, keep_len_dev, n_seqs, max_seqlen, w, kept_idx, out_offsets_dev, stream);
     return rc != PYR_OK ? rc : launch_gather_multi(g, kept_idx, n_kept, stream);

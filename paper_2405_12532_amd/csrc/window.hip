@@ -37,7 +37,7 @@ __global__ __launch_bounds__(64 * kWindowWaves, 2) void window_kernel(WindowArgs
     extern __shared__ __align__(1024) char smem[];
     int b, g;
     window_place(a, (int)blockIdx.x, &b, &g);
-    window_scores<D, kTiles, kWeighted>(a, b, g, smem);
+    window_scores<D, kTiles, kWeighted, false>(a, b, g, smem);
 }
 
 int window_bytes(bool d64, int tiles, int waves) {
@@ -122,29 +122,24 @@ WindowPlan plan_window(const pyr_shape& s, double tiles, int32_t w, int max_grou
     return best;
 }
 
-WindowArgs window_args(const void* q, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& s, bool equal, int32_t w, int32_t q_window,
-                       float scale_log2, const float* row_weights, float* sums, int groups, const DeviceInfo& dev) {
+int launch_window(const void* q, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& s, bool equal, int32_t w, int32_t q_window,
+                  float scale_log2, const float* row_weights, float* sums, const WindowPlan& plan, const DeviceInfo& dev, hipStream_t stream) {
     WindowArgs a{};
     a.q = (const uint16_t*)q;
     a.k = (const uint16_t*)k;
     a.seq_offsets = seq_offsets_dev;
-    a.n_seqs = s.n_seqs;
-    a.n_q_heads = s.n_q_heads;
-    a.n_kv_heads = s.n_kv_heads;
-    a.w = w;
-    a.groups = groups;
-    a.xcds = equal && s.n_seqs % dev.xccs == 0 ? dev.xccs : 0;
-    a.q_window = q_window;
-    a.c = scale_log2;
     a.row_weights = row_weights;
     a.sums = sums;
+    a.n_seqs = s.n_seqs;
+    a.w = w;
     a.total_tokens = s.total_tokens;
-    return a;
-}
-
-int launch_window(const void* q, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& s, bool equal, int32_t w, int32_t q_window,
-                  float scale_log2, const float* row_weights, float* sums, const WindowPlan& plan, const DeviceInfo& dev, hipStream_t stream) {
-    const WindowArgs a = window_args(q, k, seq_offsets_dev, s, equal, w, q_window, scale_log2, row_weights, sums, plan.groups, dev);
+    a.n_q_heads = s.n_q_heads;
+    a.n_kv_heads = s.n_kv_heads;
+    a.groups = plan.groups;
+    a.xcds = equal && s.n_seqs % dev.xccs == 0 ? dev.xccs : 0;
+    a.waves = plan.waves;
+    a.q_window = q_window;
+    a.c = scale_log2;
     const int64_t n = (int64_t)s.n_seqs * plan.groups;
     if (n >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
     return s.head_dim == 128 ? launch_window_d<128>(a, s.max_seqlen, (unsigned)n, plan.waves, stream) : launch_window_d<64>(a, s.max_seqlen, (unsigned)n, plan.waves, stream);

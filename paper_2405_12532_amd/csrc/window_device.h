@@ -41,19 +41,15 @@ struct WindowArgs {
     const uint16_t* q;
     const uint16_t* k;
     const int32_t* seq_offsets;
-    int32_t n_seqs, n_q_heads, n_kv_heads, w;
+    const float* row_weights;
+    float* sums;                              // [groups, total_tokens]
+    int32_t n_seqs, n_q_heads, n_kv_heads, w, total_tokens;
+    int32_t waves;                            // of a workgroup
     int32_t groups;                           // workgroups per sequence; workgroup g takes tasks g, g + groups, ...
     int32_t xcds;                             // > 0: equal lengths, a multiple of so many: a sequence's workgroups on one XCD
     int32_t q_window;                         // 0: q by packed row; else by (sequence, window slot)
-    int32_t by_kv_head;                       // tasks in turn over the KV heads; else query head after query head
     float c;
-    const float* row_weights;
-    float* sums;                              // [groups, total_tokens]
-    int32_t total_tokens;
 };
-
-WindowArgs window_args(const void* q, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& s, bool equal, int32_t w, int32_t q_window,
-                       float scale_log2, const float* row_weights, float* sums, int groups, const DeviceInfo& dev);
 
 // Sequence and place in it of workgroup `id`.
 __device__ __forceinline__ void window_place(const WindowArgs& a, int id, int* b, int* g) {
@@ -110,7 +106,8 @@ __device__ __forceinline__ float times_exp2(float v, float x, int up) {
 }
 
 // The tasks of workgroup g of sequence b; at most kWindowWaves wavefronts, S <= 32 * kTiles * wavefronts, window_lds_bytes<D, kTiles>(wavefronts) of LDS at smem.
-template <int D, int kTiles, bool kWeighted>
+// kByKvHead: the tasks in turn over the KV heads; else query head after query head.
+template <int D, int kTiles, bool kWeighted, bool kByKvHead>
 __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
     constexpr int kSteps = D / 16;
     constexpr int kChunks = D / 8;                  // 16-byte chunks per row
@@ -121,7 +118,7 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
     constexpr int kRowLoads = kWeighted ? 1 : 0;    // ... of a task's weights
 
     const int lane = threadIdx.x & 63;
-    const int waves = (int)(blockDim.x >> 6), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int waves = a.waves, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int li = lane & 31, gl = lane >> 5;
     const int row0 = a.seq_offsets[b], S = a.seq_offsets[b + 1] - row0;
     if (S <= 0) return;
@@ -175,7 +172,7 @@ __device__ void window_scores(const WindowArgs& a, int b, int g, char* smem) {
     int left = n_my > 0 ? n_task_my : 0, at_e = 0, at_task = g, at_rb = 0;
     const char *at_q = nullptr, *at_k = nullptr;
     auto task_place = [&](int task, int* h, int* rb) {
-        if (a.by_kv_head) {
+        if (kByKvHead) {
             const int r = task / a.n_kv_heads, of_group = r / n_rb;
             *h = (task - r * a.n_kv_heads) * group + of_group;
             *rb = r - of_group * n_rb;
