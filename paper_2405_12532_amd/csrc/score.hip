@@ -728,12 +728,11 @@ struct UpdatePlan {
 // per block: it wins where row blocks per KV head are few or sequences short.  Whole updates, two walks / one walk (us): 1 x 1024 rows on
 // 32 heads, w = 64 28.2 / 23.1, 4 x 1537 71.8 / 61, 5 x 1330 on 8 heads, d = 64, w = 128 27.1 / 22.2, 48 of 689 at most on 24 heads, w = 32
 // 135.6 / 100; but 18 x 826 on 64/8 heads, w = 16 55.8 / 74.5, 57 of 1066 at most on 32/8 heads, d = 64, w = 48 87 / 111.  Both costs
-// are predicted (the two walks' with the fold and the selection, to 10 %) and one walk is taken where it is 11.5 % lower, with four to eight row blocks
-// per KV head, where the prediction flatters it, 16 %.  1200 updates of random shapes whose predictions are 0.6 to 1.15 of each other, a line everywhere
-// at 0.885 / as it is (500 of them chose it, 700 others agree): the choice takes 0.8 / 0.9 % longer than the faster form in the mean, one walk throughout 1.1 %, two
-// 22 %; it takes one walk against two that are more than 3 % faster in 18 / 4 (10 x 793 rows on 40 heads, w = 100 115 / 127, 69 x 1518 on 32/8 heads, d = 64,
-// w = 32 145 / 159; now 5 % at most: 24 x 898...1054 on 8 heads, d = 64, w = 128 49.8 / 52.5) and keeps two against one that is faster by 25 % at most
-// (25 x 850...998 on 48/8 heads, w = 256 300 / 240).
+// are predicted (the two walks' with the fold and the selection, to 10 %) and one walk is taken where it is 8 % lower, 13 % with four to eight row blocks
+// per KV head, where the prediction flatters it, 11.5 % with more than sixteen.  Of 1200 updates of random shapes up to 2048 rows, each timed both ways, the choice takes
+// 0.5 % longer than the faster form in the mean (0.8 % with the lines 8 and 3 % lower that were drawn before the one walk's tasks went by KV head); it takes one walk
+// against two that are more than 3 % faster in 6 (42 x 215 at most on 32/8 heads, d = 64, w = 100 43 / 51) and keeps two against one that is more than 3 % faster
+// in 51, by 28 % at most (40 x 254...280 on 64/8 heads, w = 48 84 / 66, 4 x 841 on 64/8 heads, w = 128 46.5 / 36.9).
 UpdatePlan plan_update(const pyr_shape& s, const BatchCut& cut, int32_t w, const DeviceInfo& dev) {
     UpdatePlan p{};
     const size_t room = window_score_part_bytes(s, w), row = (size_t)s.total_tokens * sizeof(float);
@@ -743,7 +742,7 @@ UpdatePlan plan_update(const pyr_shape& s, const BatchCut& cut, int32_t w, const
     p.scores = plan_strip(s, cut, w, dev, 1, split, true);
     p.window = plan_window(s, cut.tiles, w, room / row < 1 ? 1 : room / row > 256 ? 256 : (int)(room / row), dev);
     const int blocks = s.n_q_heads / s.n_kv_heads * (((w < s.max_seqlen ? w : s.max_seqlen) + 31) / 32);
-    const double line = blocks >= 4 && blocks <= 8 ? 0.84 : 0.885;
+    const double line = blocks >= 4 && blocks <= 8 ? 0.87 : blocks <= 16 ? 0.92 : 0.885;
     const double folded = (double)s.n_seqs * w * s.n_q_heads * ((s.max_seqlen + 63) / 64);
     p.one_walk = p.window.waves > 0 && p.window.cost < line * (11.5 + 1.16 * p.stats.cost + 0.86 * p.scores.cost + 7.6e-6 * folded);
     return p;

@@ -32,12 +32,12 @@ __global__ __launch_bounds__(64 * kSumWaves) void sum_parts_kernel(const float* 
     scores[t] = x;
 }
 
-template <int D, int kTiles, bool kWeighted>
+template <int D, int kTiles, bool kWeighted, bool kByKvHead>
 __global__ __launch_bounds__(64 * kWindowWaves, 2) void window_kernel(WindowArgs a) {
     extern __shared__ __align__(1024) char smem[];
     int b, g;
     window_place(a, (int)blockIdx.x, &b, &g);
-    window_scores<D, kTiles, kWeighted, false>(a, b, g, smem);
+    window_scores<D, kTiles, kWeighted, kByKvHead>(a, b, g, smem);
 }
 
 int window_bytes(bool d64, int tiles, int waves) {
@@ -45,25 +45,40 @@ int window_bytes(bool d64, int tiles, int waves) {
     return tiles <= 2 ? of(std::integral_constant<int, 2>{}) : tiles <= 4 ? of(std::integral_constant<int, 4>{}) : of(std::integral_constant<int, 8>{});
 }
 
-template <int D, int kTiles, bool kWeighted>
+template <int D, int kTiles, bool kWeighted, bool kByKvHead>
 int launch_window_t(const WindowArgs& a, unsigned grid, int waves, hipStream_t stream) {
     static std::atomic<uint64_t> lds_set{0};
-    if (ensure_dynamic_lds((const void*)window_kernel<D, kTiles, kWeighted>, window_lds_bytes<D, kTiles>(kWindowWaves), &lds_set) != PYR_OK) return PYR_ERR_LAUNCH;
+    const void* kernel = (const void*)window_kernel<D, kTiles, kWeighted, kByKvHead>;
+    if (ensure_dynamic_lds(kernel, window_lds_bytes<D, kTiles>(kWindowWaves), &lds_set) != PYR_OK) return PYR_ERR_LAUNCH;
     const int lds = window_lds_bytes<D, kTiles>(waves);
-    hipLaunchKernelGGL((window_kernel<D, kTiles, kWeighted>), dim3(grid), dim3(64 * waves), lds, stream, a);
+    hipLaunchKernelGGL((window_kernel<D, kTiles, kWeighted, kByKvHead>), dim3(grid), dim3(64 * waves), lds, stream, a);
     return check_launch();
 }
 
+// The order of the tasks.  Where a sequence's workgroups are not on one XCD anyway, those of a KV head come together on one, or on few, if its
+// tasks are as many apart as there are KV heads, since workgroups go round robin over the XCDs; else every XCD fetches the keys of every head.  Short
+// sequences gain less than the divisions by the number of KV heads take (0.2 us), and more than sixteen row blocks per KV head find the keys in L2 either way.
+// Whole updates, query head after query head / by KV head (us): 1 x 1537 rows on 32 heads, w = 64 31.2 / 30.55, 4 x 1605 at most on 32/8, w = 64 37.3 / 30.5,
+// 4 x 1378 on 40 heads, w = 64 58.7 / 55.3, 28 x 345 on 8 heads, w = 100 31.5 / 29.1.  Of 460 updates by KV head, geometric means of the time: 256
+// tokens and more on 8, 24, 32 or 40 KV heads 0.95...0.98 (the worst 1.02), below 0.97...1.01; on 2, 4 or 12 from 768 tokens and four row blocks on
+// 0.94...0.98, else 0.99...1.015; 24 row blocks per KV head and more 1.00...1.02.  With a sequence's workgroups on one XCD 64 x 2048 901 / 1055.
+bool by_kv_head(const WindowArgs& a, int32_t max_seqlen, const DeviceInfo& dev) {
+    const int blocks = a.n_q_heads / a.n_kv_heads * (((a.w < max_seqlen ? a.w : max_seqlen) + 31) / 32);
+    const bool even = a.n_kv_heads % dev.xccs == 0;
+    return a.xcds == 0 && blocks >= (even ? 2 : 4) && blocks <= 16 && max_seqlen >= (even ? 256 : 768);
+}
+
 template <int D, int kTiles>
-int launch_window_w(const WindowArgs& a, unsigned grid, int waves, hipStream_t stream) {
-    return a.row_weights ? launch_window_t<D, kTiles, true>(a, grid, waves, stream) : launch_window_t<D, kTiles, false>(a, grid, waves, stream);
+int launch_window_w(const WindowArgs& a, unsigned grid, int waves, bool by_kv, hipStream_t stream) {
+    if (by_kv) return a.row_weights ? launch_window_t<D, kTiles, true, true>(a, grid, waves, stream) : launch_window_t<D, kTiles, false, true>(a, grid, waves, stream);
+    return a.row_weights ? launch_window_t<D, kTiles, true, false>(a, grid, waves, stream) : launch_window_t<D, kTiles, false, false>(a, grid, waves, stream);
 }
 
 template <int D>
-int launch_window_d(const WindowArgs& a, int32_t max_seqlen, unsigned grid, int waves, hipStream_t stream) {
+int launch_window_d(const WindowArgs& a, int32_t max_seqlen, unsigned grid, int waves, bool by_kv, hipStream_t stream) {
     const int tiles = (max_seqlen + 32 * waves - 1) / (32 * waves);
-    return tiles <= 2 ? launch_window_w<D, 2>(a, grid, waves, stream)
-         : tiles <= 4 ? launch_window_w<D, 4>(a, grid, waves, stream) : launch_window_w<D, 8>(a, grid, waves, stream);
+    return tiles <= 2 ? launch_window_w<D, 2>(a, grid, waves, by_kv, stream)
+         : tiles <= 4 ? launch_window_w<D, 4>(a, grid, waves, by_kv, stream) : launch_window_w<D, 8>(a, grid, waves, by_kv, stream);
 }
 
 }  // namespace
@@ -142,7 +157,9 @@ int launch_window(const void* q, const void* k, const int32_t* seq_offsets_dev, 
     a.c = scale_log2;
     const int64_t n = (int64_t)s.n_seqs * plan.groups;
     if (n >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
-    return s.head_dim == 128 ? launch_window_d<128>(a, s.max_seqlen, (unsigned)n, plan.waves, stream) : launch_window_d<64>(a, s.max_seqlen, (unsigned)n, plan.waves, stream);
+    const bool by_kv = by_kv_head(a, s.max_seqlen, dev);
+    return s.head_dim == 128 ? launch_window_d<128>(a, s.max_seqlen, (unsigned)n, plan.waves, by_kv, stream)
+                             : launch_window_d<64>(a, s.max_seqlen, (unsigned)n, plan.waves, by_kv, stream);
 }
 
 int launch_sum_parts(const float* parts, int groups, int32_t total_tokens, float* scores, hipStream_t stream) {

@@ -35,6 +35,13 @@ ONE_WALK = [
     ((1537, 1100), 9, 9, 64, 128),                              # ... fewer, but of many tokens
     ((200,) * 90, 16, 16, 64, 32),                              # several rounds of workgroups, several tasks each
 ]
+BY_KV_HEAD = [                                                  # tasks in turn over the KV heads (window.hip, by_kv_head), as many per workgroup as said
+    ((300, 290), 8, 8, 128, 33),                                # two row blocks a head; one task
+    ((700, 33, 0), 32, 8, 64, 32),                              # GQA 4
+    ((260,) * 50, 16, 8, 64, 40),                               # several
+    ((800,) * 5, 12, 4, 64, 40),                                # KV heads that do not divide over the XCDs; six row blocks each
+    ((1500, 5), 16, 8, 128, 128),                               # eight
+]
 TWO_WALKS = [
     ((2049,), 4, 4, 64, 16),                                    # a key too many
     ((120,) * 60, 32, 1, 128, 128),                             # many row blocks per KV head: one lane folds a row's one range
@@ -47,7 +54,7 @@ TWO_WALKS = [
 ]
 
 
-@pytest.mark.parametrize("lens,Hq,Hkv,d,w", ONE_WALK)
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w", ONE_WALK + BY_KV_HEAD)
 @pytest.mark.parametrize("weighted", [False, True])
 def test_one_walk(lib, lens, Hq, Hkv, d, w, weighted):
     assert route(lib, lens, Hq, Hkv, d, w).stats_waves == 0
