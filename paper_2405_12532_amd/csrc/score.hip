@@ -72,17 +72,18 @@ struct StripArgs {
     const uint16_t* k;
     const float* lse;
     const int32_t* seq_offsets;
+    int32_t n_seqs, group, n_kv_heads, w;     // (group: query heads per KV head)
+    int32_t range_tiles, ranges_per_seq;      // tiles of a range; ranges of the longest sequence
+    int32_t order, xcds, turn, head_step;     // order of the ranges over the workgroups, of the heads over the ranges
+    int32_t q_window;                         // 0: q and lse by packed row; else by (sequence, window slot)
+    float c;
     const float* row_weights;
     union {                                   // (arguments of 112 bytes and less, implicit ones among them, are 0.7 us less host time a launch)
         float* sums;                          // [groups, total_tokens]
         float2* part;                         // kStats: [range, sequence, query head, window slot]
     };
-    int32_t n_seqs, n_q_heads, n_kv_heads, w, total_tokens;
-    int32_t range_tiles, ranges_per_seq;      // tiles of a range; ranges of the longest sequence
+    int32_t total_tokens;
     int32_t waves, groups;                    // of a workgroup; workgroups a range's tasks are split over (the grid's y)
-    int32_t order, xcds, turn, head_step;     // order of the ranges over the workgroups, of the heads over the ranges
-    int32_t q_window;                         // 0: q and lse by packed row; else by (sequence, window slot)
-    float c;
 };
 static_assert(sizeof(StripArgs) <= 112, "short arguments");
 
@@ -91,7 +92,7 @@ constexpr int wave_lds_bytes(int range_tiles) { return kSlots * 32 * D * 2 + 2 *
 
 // A position in a wavefront's stream of tiles.  All fields wave-uniform.
 struct Cursor {
-    int left;        // tasks left, this one included
+    int task;        // number of the task among all
     int hd, pair;    // KV head (before the rotation) and row-block pair of the task
     int e;           // element of the task: its row blocks, then its key tiles
 };
@@ -178,11 +179,12 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
             left -= __builtin_amdgcn_readlane(incl, 63);
         }
     } else {
-        const int id = (int)blockIdx.x, slot = a.order == kSeqPerXcd ? id / a.xcds : id;
-        const int at = slot / a.ranges_per_seq;
-        b = a.order == kSeqPerXcd ? at * a.xcds + id % a.xcds : at;
+        const int id = (int)blockIdx.x, slot = a.order == kSeqPerXcd ? (int)((uint32_t)id / (uint32_t)a.xcds) : id;
+        const int at = (int)((uint32_t)slot / (uint32_t)a.ranges_per_seq);
+        b = a.order == kSeqPerXcd ? at * a.xcds + (id - slot * a.xcds) : at;
         if (b >= a.n_seqs) return;
-        range = (slot + a.turn * at) % a.ranges_per_seq;       // (the same ranges of the sequence, from its at-th on)
+        range = slot - at * a.ranges_per_seq;
+        if (a.turn) range = (int)((uint32_t)(range + at) % (uint32_t)a.ranges_per_seq);       // (the same ranges of the sequence, from its at-th on)
         row0 = a.seq_offsets[b];
         S = a.seq_offsets[b + 1] - row0;
     }
@@ -193,17 +195,18 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
     const int first_row = S - L;                      // local position of the first window row
     const int q_row_base = a.q_window ? b * a.w + (a.w - L) : row0 + first_row;   // row of q / lse holding the first window row
     const int n_rb = (L + 31) / 32;
-    const int group = a.n_q_heads / a.n_kv_heads;
+    const int group = a.group, n_q_heads = group * a.n_kv_heads;
     const int blocks = group * n_rb;                  // row blocks per KV head
     const int pairs = (blocks + 1) / 2;
-    // this workgroup's share of the tasks, dealt to its wavefronts one by one
-    const int64_t n_tasks = (int64_t)a.n_kv_heads * pairs;
-    const int t_begin = (int)(n_tasks * blockIdx.y / a.groups), t_end = (int)(n_tasks * (blockIdx.y + 1) / a.groups);
-    const int n_my = max(0, (t_end - t_begin - wave + waves - 1) / waves);
+    // This workgroup's share of the tasks, dealt to its wavefronts one by one.  (All that stands in front of the first load is the time of
+    // every workgroup: unsigned 32-bit divisions, and as few as can be, which the launcher's bounds allow: fewer than 2^26 tasks, kMaxScoreGroups
+    // shares.  With signed and 64-bit ones and two per row block, 8 x 352 on 64/8 heads, w = 32 15.2 us, now 14.6.)
+    const uint32_t n_tasks = (uint32_t)(a.n_kv_heads * pairs), groups = (uint32_t)a.groups;
+    const int t_begin = (int)(n_tasks * blockIdx.y / groups), t_end = (int)(n_tasks * (blockIdx.y + 1) / groups);
     // Where the launcher asks for it (head_step != 0), neighbouring ranges start their walks head_step heads apart (a step of 8: at
     // two different heads of 16, four of 32; an odd step: at all of them): workgroups that run side by side then read different
     // columns of their token rows, which spreads them over the memory channels when the rows are a power of two apart.
-    const int head_rot = (range * a.head_step) % a.n_kv_heads;
+    const int head_rot = a.head_step == 0 ? 0 : (int)((uint32_t)(range * a.head_step) % (uint32_t)a.n_kv_heads);
 
     // sum of the weights in use (fixed order: every lane strides over them, then a butterfly).
     // These are the only ordinary loads of the kernel and they are complete before the first
@@ -228,7 +231,7 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
     // ---- load side: lane -> (row inside an instruction's row group, physical chunk).  The LDS
     // slot of a lane is fixed by the instruction, so the swizzle picks the global chunk.
     const int ld_row = lane / kChunks, ld_chunk = lane % kChunks;
-    const uint32_t k_row_bytes = (uint32_t)a.n_kv_heads * kRowBytes, q_row_bytes = (uint32_t)a.n_q_heads * kRowBytes;
+    const uint32_t k_row_bytes = (uint32_t)a.n_kv_heads * kRowBytes, q_row_bytes = (uint32_t)n_q_heads * kRowBytes;
     auto load_tile = [&](const char* base, uint32_t row_bytes, int last_row, uint32_t to) {      // rows past the last re-read it
 #pragma unroll
         for (int i = 0; i < kTileLoads; ++i) {
@@ -248,7 +251,7 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
     auto kv_head = [&](const Cursor& cu) { const int h = cu.hd + head_rot; return h >= a.n_kv_heads ? h - a.n_kv_heads : h; };
     auto n_blk = [&](const Cursor& cu) { return min(2, blocks - 2 * cu.pair); };
     auto next_task = [&](Cursor& cu) {
-        --cu.left;
+        cu.task += waves;
         cu.pair += waves;
         while (cu.pair >= pairs) {
             cu.pair -= pairs;
@@ -257,21 +260,34 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
     };
     // Request the element at the cursor into ring slot `slot` and move on; returns the number of load
     // instructions issued (0: the stream has ended).
+    int of[2] = {0, 0}, rb[2] = {0, 0};               // the requested row blocks: query head of the KV head's, place in the window
     auto request = [&](Cursor& cu, int slot) -> int {
-        if (cu.left <= 0) return 0;
+        if (cu.task >= t_end) return 0;
         const uint32_t to = ring + slot * kTileBytes;
         const int kvh = kv_head(cu), nb = n_blk(cu);
         int n = kTileLoads;
         if (cu.e < nb) {
-            const int blk = 2 * cu.pair + cu.e;
-            const int h = kvh * group + blk / n_rb, rb = blk % n_rb;
+            int of_blk, rb_blk;
+            if (cu.e == 0) {
+                of_blk = (int)((uint32_t)(2 * cu.pair) / (uint32_t)n_rb);
+                rb_blk = 2 * cu.pair - of_blk * n_rb;
+                of[0] = of_blk;
+                rb[0] = rb_blk;
+            } else {                                  // the block behind it
+                const bool next = rb[0] + 1 == n_rb;
+                of_blk = next ? of[0] + 1 : of[0];
+                rb_blk = next ? 0 : rb[0] + 1;
+                of[1] = of_blk;
+                rb[1] = rb_blk;
+            }
+            const int h = kvh * group + of_blk;
             if (kMode != kStats) {
-                const uint32_t row = (uint32_t)min(li, L - 1 - 32 * rb), area = rows_at + cu.e * kRowArea;
-                lds_dma((const char*)(a.lse + (size_t)(q_row_base + 32 * rb) * a.n_q_heads + h), __umul24(row, (uint32_t)a.n_q_heads * 4), area, true);
-                if (kWeighted) lds_dma((const char*)(a.row_weights + (a.w - L) + 32 * rb), row * 4, area + 256, true);
+                const uint32_t row = (uint32_t)min(li, L - 1 - 32 * rb_blk), area = rows_at + cu.e * kRowArea;
+                lds_dma((const char*)(a.lse + (size_t)(q_row_base + 32 * rb_blk) * n_q_heads + h), __umul24(row, (uint32_t)n_q_heads * 4), area, true);
+                if (kWeighted) lds_dma((const char*)(a.row_weights + (a.w - L) + 32 * rb_blk), row * 4, area + 256, true);
                 n += kRowLoads;
             }
-            load_tile((const char*)(a.q + ((size_t)(q_row_base + 32 * rb) * a.n_q_heads + h) * D), q_row_bytes, L - 1 - 32 * rb, to);
+            load_tile((const char*)(a.q + ((size_t)(q_row_base + 32 * rb_blk) * n_q_heads + h) * D), q_row_bytes, L - 1 - 32 * rb_blk, to);
         } else {
             const int key = key_base + 32 * (cu.e - nb);
             const char* base = (const char*)(a.k + ((size_t)(row0 + key) * a.n_kv_heads + kvh) * D);
@@ -327,26 +343,24 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
                                : __builtin_amdgcn_mfma_f32_32x32x16_bf16(qv, kv, acc, 0, 0, 0);
     };
 
-    if (n_my == 0) {
+    if (t_begin + wave >= t_end) {
         for (int t = 0; t < n_tiles; ++t) *(lfloat_t)(uintptr_t)(sums_at + 256 * t + 4 * lane) = 0.f;
     } else {
-        Cursor now{n_my, 0, 0, 0};
-        {
-            const int first = t_begin + wave;
-            now.hd = first / pairs;
-            now.pair = first % pairs;
-        }
+        Cursor now{t_begin + wave, 0, 0, 0};
+        now.hd = (int)((uint32_t)now.task / (uint32_t)pairs);
+        now.pair = now.task - now.hd * pairs;
         Cursor ahead = now;
         request(ahead, 0);
         int behind = request(ahead, 1);
         int slot = 0;
         bool first_task = true;
-        for (; now.left > 0; next_task(now)) {
+        for (; now.task < t_end; next_task(now)) {
             const int kvh = kv_head(now), nb = n_blk(now);
             bf16x8 qf[2][kSteps];
             float nl[2][16];                          // minus the rows' denominators (log2 domain), weights included
             int q_lo[2];                              // sequence positions of the row blocks' first rows
-            const int rb0 = (2 * now.pair) % n_rb, rb1 = (2 * now.pair + 1) % n_rb;
+            // (the task's first two elements have been requested, no row block of the next task: it has a key tile at least)
+            const int rb0 = rb[0], rb1 = rb[1], of0 = of[0], of1 = of[1];
             q_lo[0] = first_row + 32 * rb0;
             q_lo[1] = first_row + 32 * rb1;
             wait_front(behind);
@@ -417,8 +431,8 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
                     const int rb = j ? rb1 : rb0;
                     if (gl == 0 && 32 * rb + li < L && key_base <= q_lo[j] + li) {      // every range that the fold reads for this row
                         const float total = l_run[j] * __builtin_amdgcn_exp2f(m_run[j] - m_all) + so * __builtin_amdgcn_exp2f(mo - m_all);
-                        const int h = kvh * group + (2 * now.pair + j) / n_rb, at = (a.w - L) + 32 * rb + li;
-                        a.part[(((size_t)range * a.n_seqs + b) * a.n_q_heads + h) * a.w + at] = make_float2(m_all, total);   // 32 rows: 256 consecutive bytes
+                        const int h = kvh * group + (j ? of1 : of0), at = (a.w - L) + 32 * rb + li;
+                        a.part[(((size_t)range * a.n_seqs + b) * n_q_heads + h) * a.w + at] = make_float2(m_all, total);   // 32 rows: 256 consecutive bytes
                     }
                 }
             }
@@ -428,7 +442,7 @@ __global__ __launch_bounds__(kMaxWaves * 64, D == 64 ? 3 : 2) void strip_kernel(
     if (kMode == kStats) return;
 
     // ---- the sums of the two half-wavefronts (16 window rows of a block each) and of the wavefronts, fixed order
-    const float norm = 1.0f / ((float)a.n_q_heads * weight_sum);
+    const float norm = 1.0f / ((float)n_q_heads * weight_sum);
     __syncthreads();
     float* dst = a.sums + (size_t)blockIdx.y * a.total_tokens + row0 + key_base;
     for (int x = threadIdx.x; x < 32 * n_tiles && key_base + x < S; x += 64 * waves) {
@@ -647,7 +661,7 @@ int launch_strip(const void* q, const void* k, const float* lse, const int32_t* 
     a.n_seqs = s.n_seqs;
     a.w = w;
     a.total_tokens = s.total_tokens;
-    a.n_q_heads = s.n_q_heads;
+    a.group = s.n_q_heads / s.n_kv_heads;
     a.n_kv_heads = s.n_kv_heads;
     a.groups = plan.groups;
     a.waves = plan.waves;
