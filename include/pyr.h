@@ -111,7 +111,8 @@ PYR_API int pyr_schedule_plan(int32_t S, int32_t w, int32_t n_layers, const int3
  *   out                dev bf16 [T,Hq,d], written
  *   lse                dev fp32 [T,Hq], written: log2 of the softmax denominator of
  *                      every row, in the scaled base-2 domain,
- *                      lse[i,h] = log2(sum_j 2^(scale*log2(e)*s_ij)); may be NULL
+ *                      lse[i,h] = log2(sum_j 2^(scale*log2(e)*s_ij)); may be NULL.  A logit of -inf is a
+ *                      key without weight; a row that has no other: -inf here, NaN in out
  *   tile_map           dev int32 [B+1] scratch, written (prefix sums of query
  *                      tiles per sequence); part of the workspace
  */

@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ seq_offsets, const int32_t* __restrict__ item_map,
     int32_t n_seqs, int32_t n_q_heads, int32_t n_kv_heads, int32_t uniform_len, int32_t xcds,
-    int32_t items_per_xcd, int32_t turn, float c, uint16_t* __restrict__ out, float* __restrict__ lse) {
+    int32_t items_per_xcd, int32_t turn, float c, float lowest, uint16_t* __restrict__ out, float* __restrict__ lse) {
     using T = Tile;
     constexpr int NS = D / 16;                    // MFMAs per group = k-steps of QK^T = V fragments of a half
     constexpr int kDTiles = D / 32;               // 32-row tiles of O^T
@@ -639,7 +639,7 @@ __global__ __launch_bounds__(kNW * 64, 2) void attention_kernel(
             const float nxt = r + 1 < 16 ? s0[r + 1] : s0[r];
             mx = fmaxf(fmaxf(mx, s0[r]), nxt);
         }
-        m_run = max_with_other_half(mx);          // key 0 is visible to every row: finite
+        m_run = fmaxf(max_with_other_half(mx), lowest);
         nmc = -m_run * c;
         ls0 = 0.f;
         fence();
@@ -834,7 +834,7 @@ int launch_attention_long(const void* q, const void* k, const void* v, const int
     hipLaunchKernelGGL(attention_kernel, dim3((unsigned)(slots * xcds)), dim3(kNW * 64), Tile::kLdsBytes, stream,
                        (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, seq_offsets_dev,
                        (const int32_t*)item_map, s.n_seqs, s.n_q_heads, s.n_kv_heads, uniform_len, xcds,
-                       items_per_xcd, turn, c, (uint16_t*)out, lse);
+                       items_per_xcd, turn, c, lowest_reference(c), (uint16_t*)out, lse);
     return check_launch();
 }
 

@@ -2,9 +2,16 @@
 // halves of a wavefront.
 #pragma once
 
+#include <math.h>
+
 #include "pyr_internal.h"
 
 namespace pyr {
+
+// The lowest exponent reference of a row.  A row's reference is the largest logit of its first 32 keys; where those are all -inf it is this, a finite
+// number, also times c, so that the row's sum is zero so far and not the NaN of -inf - -inf: the first key that can be seen outgrows it.  (Logits below
+// it, finite ones, have no finite product with c.)
+inline float lowest_reference(float c) { return -0x1.fffffcp127f / fmaxf(c, 1.0f); }
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;

@@ -151,6 +151,7 @@ int tile_args(const void* q, const void* k, const void* v, const int32_t* seq_of
     a.xcds = bound_xcds(s, seq_offsets_host, uniform_len, dev);
     a.uniform_len = uniform_len;
     a.c = scale_log2;
+    a.lowest = lowest_reference(scale_log2);
     a.out = (uint16_t*)out;
     *args = a;
     return PYR_OK;

@@ -44,7 +44,7 @@ struct TileArgs {
     uint16_t* out;
     int32_t n_seqs, uniform_len, n_q_heads, n_kv_heads;
     int32_t units_per_chunk, xcds;                // unit: one KV head of one sequence
-    float c;
+    float c, lowest;                              // factor of the logits; lowest_reference()
 };
 
 // Launch arguments of a batch (attention_tile.hip), and the grid where its tiles are not listed (one launch below 8 million tokens a sequence).
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(kGroups * 256, Front::kWaves) void attention_tile_k
         prime(fk0);
         qk_group(s0, no_e, fk0, fk1);
         mask_half(s0, 0, 0);
-        m_run = max_of(s0);                       // (group 0: the sequence's first key is visible to every row)
+        m_run = max_of(s0);
     }
     // The reference is the row's maximum over its first 32 keys, for both groups: a reference of its own would have the second
     // group depend on keys 64...95, which may all be masked by the caller (logits of -inf), and round its probabilities apart from the
@@ -418,6 +418,7 @@ __global__ __launch_bounds__(kGroups * 256, Front::kWaves) void attention_tile_k
         if (grp == 1 && n_my > 0) m_run = *ref;
     }
     if (n_my > 0) {
+        m_run = fmaxf(m_run, a.lowest);
         nmc = -m_run * a.c;
         ls0 = 0.f;
         fence();
@@ -511,7 +512,7 @@ __global__ __launch_bounds__(kGroups * 256, Front::kWaves) void attention_tile_k
         *stat(wave, 1) = l_tot;
         __syncthreads();
         const float m_oth = *stat(wave ^ 4, 0), l_oth = *stat(wave ^ 4, 1);
-        const float m_all = fmaxf(m_run, m_oth);  // (group 0 has the row's first key: finite)
+        const float m_all = fmaxf(m_run, m_oth);  // (finite: group 0 always has a tile)
         const float f_own = __builtin_amdgcn_exp2f((m_run - m_all) * a.c), f_oth = __builtin_amdgcn_exp2f((m_oth - m_all) * a.c);
         l_tot = l_tot * f_own + l_oth * f_oth;
         m_run = m_all;

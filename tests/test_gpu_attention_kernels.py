@@ -21,22 +21,24 @@ def _batch(lens, Hq, Hkv, d, seed):
     return [torch.randn((T, h, d), generator=gen, device="cuda").to(torch.bfloat16) for h in (Hq, Hkv, Hkv)]
 
 
-def _reference(q, k, v):
+def _reference(q, k, v, scale=None):
     """Causal attention of one sequence in float64: out [S, Hq, d], log2 of the denominators [S, Hq]."""
     S, Hq, d = q.shape
     Hkv = k.shape[1]
     g = Hq // Hkv
     qh = q.double().permute(1, 0, 2).reshape(Hkv, g * S, d).contiguous()
     kh, vh = k.double().permute(1, 2, 0).contiguous(), v.double().permute(1, 0, 2).contiguous()
-    x = (torch.bmm(qh, kh) / math.sqrt(d)).reshape(Hkv, g, S, S)
+    x = (torch.bmm(qh, kh) * (scale or 1 / math.sqrt(d))).reshape(Hkv, g, S, S)
     x.masked_fill_(torch.ones(S, S, dtype=torch.bool, device=q.device).triu(1), -math.inf)
     out = torch.bmm(torch.softmax(x, dim=3).reshape(Hkv, g * S, S), vh).reshape(Hq, S, d).permute(1, 0, 2)
     return out, (torch.logsumexp(x, dim=3) / math.log(2.0)).reshape(Hq, S).t()
 
 
-def _check(lib, lens, Hq, Hkv, d, seed=1, every=1, masked=()):
+def _check(lib, lens, Hq, Hkv, d, seed=1, every=1, masked=(), scale=None):
     """masked: positions of every sequence whose keys nobody may see, a logit of -inf by way of one head dimension."""
     q, k, v = _batch(lens, Hq, Hkv, d, seed)
+    if scale:
+        q *= 1 / (scale * math.sqrt(d))            # (the same logits)
     T = sum(lens)
     off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     if len(masked):
@@ -46,14 +48,20 @@ def _check(lib, lens, Hq, Hkv, d, seed=1, every=1, masked=()):
     off_h = torch.from_numpy(off)
     shape = lib.make_shape(len(lens), T, max(lens), Hq, Hkv, d)
     out, lse = torch.full_like(q, 7.0), torch.full((T, Hq), 7.0, dtype=torch.float32, device="cuda")
-    lib.attention(q, k, v, off_h.cuda(), off_h, shape, 0.0, out, lse, torch.empty(len(lens) + 1, dtype=torch.int32, device="cuda"))
+    lib.attention(q, k, v, off_h.cuda(), off_h, shape, scale or 0.0, out, lse, torch.empty(len(lens) + 1, dtype=torch.int32, device="cuda"))
     torch.cuda.synchronize()
     vmax = float(v.abs().max())
     for b in range(0, len(lens), every):
         r0, r1 = int(off[b]), int(off[b + 1])
         if r0 == r1:
             continue
-        o, den = _reference(q[r0:r1], k[r0:r1], v[r0:r1])
+        o, den = _reference(q[r0:r1], k[r0:r1], v[r0:r1], scale)
+        if 0 in masked:                            # rows that see none but masked keys have no output
+            blind = next(j for j in range(r1 - r0 + 1) if j not in masked)
+            assert bool(out[r0:r0 + blind].isnan().all()) and bool((lse[r0:r0 + blind] == -math.inf).all())
+            r0, o, den = r0 + blind, o[blind:], den[blind:]
+            if r0 >= r1:
+                continue
         # one rounding of the result to bf16, bf16 probabilities that sum to one, fp32 sums
         err = (out[r0:r1].double() - o).abs()
         assert bool((err <= 2.0 ** -8 * (o.abs() + vmax) + 1e-3).all()), (b, float(err.max()))
@@ -173,3 +181,14 @@ def test_masked_keys(lib, lens, Hq, Hkv, d, kernel):
     assert route(lib, lens, Hq, Hkv, d).attention == kernel
     masked = [*range(40, 200), *range(256, 288), *range(301, 700, 2)]
     _check(lib, lens, Hq, Hkv, d, masked=masked, every=max(1, len(lens) // 4))
+
+
+@pytest.mark.parametrize("first", [32, 70, 200])
+@pytest.mark.parametrize("lens,Hq,Hkv,d,kernel", MASKED_BATCHES)
+def test_masked_keys_in_front(lib, lens, Hq, Hkv, d, kernel, first):
+    """... and where they are all of a row's first 32 keys, which the exponent reference is taken from.  Also with a softmax scale whose
+    product with the lowest finite reference is no finite number."""
+    assert route(lib, lens, Hq, Hkv, d).attention == kernel
+    masked = [*range(first), *range(256, 288)]
+    for scale in (None, 1.0):
+        _check(lib, lens, Hq, Hkv, d, masked=masked, every=max(1, len(lens) // 4), scale=scale)
