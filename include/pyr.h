@@ -371,6 +371,15 @@ PYR_API int pyr_diag_launches(const pyr_shape* shape, const int32_t* seq_offsets
 PYR_API int pyr_diag_layer(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t w, int32_t compute_units, int32_t xcds,
                            int32_t* groups_out);
 
+/*
+ * Diagnostic, not part of the method: in which order the one walk of pyr_decode_update takes its tasks (a row block of a query head each).  Host
+ * only; launches nothing.
+ *   compute_units, xcds  as in pyr_diag_route
+ *   order_out            host, written: 0 query head after query head, 1 in turn over the KV heads; -1: a batch of two walks, or without tokens
+ */
+PYR_API int pyr_diag_update(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t w, int32_t compute_units, int32_t xcds,
+                            int32_t* order_out);
+
 #ifdef __cplusplus
 }
 #endif

@@ -67,6 +67,7 @@ _SIGNATURES = {
     "pyr_diag_route": (ctypes.c_int, [ctypes.POINTER(PyrShape), _VP, _I32, _I32, _I32, ctypes.POINTER(PyrRoute)]),
     "pyr_diag_launches": (ctypes.c_int, [ctypes.POINTER(PyrShape), _VP, _I32, _I32, _VP, _I64, _I32, _I32, ctypes.POINTER(PyrLaunches)]),
     "pyr_diag_layer": (ctypes.c_int, [ctypes.POINTER(PyrShape), _VP, _I32, _I32, _I32, ctypes.POINTER(_I32)]),
+    "pyr_diag_update": (ctypes.c_int, [ctypes.POINTER(PyrShape), _VP, _I32, _I32, _I32, ctypes.POINTER(_I32)]),
 }
 EXPORTS = tuple(_SIGNATURES)
 
@@ -270,6 +271,13 @@ def diag_layer(shape: PyrShape, seq_offsets_host, w: int, compute_units: int = 0
     """Rows of partial scores where a layer's attention and scores go in one launch, 0 where they go in two (host only)."""
     out = _I32(0)
     _check(load().pyr_diag_layer(ctypes.byref(shape), _ptr(seq_offsets_host), int(w), int(compute_units), int(xcds), ctypes.byref(out)), "pyr_diag_layer")
+    return int(out.value)
+
+
+def diag_update(shape: PyrShape, seq_offsets_host, w: int, compute_units: int = 0, xcds: int = 0) -> int:
+    """Order of the tasks of an update's one walk: 0 by query head, 1 by KV head; -1 where the update takes two walks (host only)."""
+    out = _I32(0)
+    _check(load().pyr_diag_update(ctypes.byref(shape), _ptr(seq_offsets_host), int(w), int(compute_units), int(xcds), ctypes.byref(out)), "pyr_diag_update")
     return int(out.value)
 
 

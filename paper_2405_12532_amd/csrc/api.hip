@@ -436,6 +436,23 @@ int pyr_diag_layer(const pyr_shape* shape, const int32_t* seq_offsets_host, int3
     return PYR_OK;
 }
 
+int pyr_diag_update(const pyr_shape* shape, const int32_t* seq_offsets_host, int32_t w, int32_t compute_units, int32_t xcds, int32_t* order_out) {
+    pyr_route route;
+    const int rc = pyr_diag_route(shape, seq_offsets_host, w, compute_units, xcds, &route);
+    if (rc != PYR_OK) return rc;
+    if (order_out == nullptr) return PYR_ERR_NULL;
+    BatchInfo info;
+    check_offsets(seq_offsets_host, shape->n_seqs, shape->total_tokens, shape->max_seqlen, &info);
+    pyr::DeviceInfo dev{0, compute_units, xcds};
+    if (compute_units == 0 && pyr::device_info(&dev) != PYR_OK) return PYR_ERR_LAUNCH;
+    *order_out = -1;
+    if (info.max_len == 0) return PYR_OK;
+    pyr_shape s = *shape;
+    s.max_seqlen = info.max_len;
+    *order_out = pyr::update_task_order(s, seq_offsets_host, info.min_len, w, dev);
+    return PYR_OK;
+}
+
 int pyr_decode_workspace_bytes(const pyr_shape* shape, int32_t w, size_t* bytes_out) {
     if (bytes_out == nullptr) return PYR_ERR_NULL;
     const int rc = check_shape(shape);

@@ -83,6 +83,7 @@ int64_t attention_tiles(const pyr_shape& shape, const int32_t* seq_offsets_host,
 bool attention_tile_listed(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len);
 // (returns the rows of partial sums)
 int update_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, const DeviceInfo& dev, pyr_launches* out);
+int update_task_order(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, const DeviceInfo& dev);      // as pyr_diag_update
 int layer_groups(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t uniform_len, int32_t min_seqlen, int32_t w, bool parts, const DeviceInfo& dev);
 void score_route(const pyr_shape& shape, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, bool parts, const DeviceInfo& dev,
                  pyr_route* out);
@@ -139,6 +140,7 @@ struct WindowPlan {
     double cost;                  // microseconds, selection included
 };
 WindowPlan plan_window(const pyr_shape& shape, double tiles, int32_t w, int max_groups, const DeviceInfo& dev);
+int window_task_order(const pyr_shape& shape, bool equal, int32_t w, const DeviceInfo& dev);      // 1: by KV head
 int launch_window(const void* q, const void* k, const int32_t* seq_offsets_dev, const pyr_shape& shape, bool equal, int32_t w,
                   int32_t q_window, float scale_log2, const float* row_weights, float* sums, const WindowPlan& plan, const DeviceInfo& dev,
                   hipStream_t stream);

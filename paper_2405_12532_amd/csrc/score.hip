@@ -847,6 +847,11 @@ int update_route(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t mi
     return update.scores.groups;
 }
 
+int update_task_order(const pyr_shape& s, const int32_t* seq_offsets_host, int32_t min_seqlen, int32_t w, const DeviceInfo& dev) {
+    const BatchCut cut = cut_batch(s, seq_offsets_host, min_seqlen);
+    return plan_update(s, cut, w, dev).one_walk ? window_task_order(s, cut.equal, w, dev) : -1;
+}
+
 size_t window_score_part_bytes(const pyr_shape& s, int32_t w) {
     const size_t ranges = ((size_t)s.max_seqlen + 63) / 64;           // (statistics ranges are at least 64 keys)
     return ranges * (size_t)s.n_seqs * (size_t)w * (size_t)s.n_q_heads * sizeof(float2);

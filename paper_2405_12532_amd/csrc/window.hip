@@ -55,6 +55,9 @@ int launch_window_t(const WindowArgs& a, unsigned grid, int waves, hipStream_t s
     return check_launch();
 }
 
+// Equal lengths, a multiple of the XCDs: a sequence's workgroups on one of them.
+bool seq_per_xcd(const pyr_shape& s, bool equal, const DeviceInfo& dev) { return equal && s.n_seqs % dev.xccs == 0; }
+
 // The order of the tasks.  Where a sequence's workgroups are not on one XCD anyway, those of a KV head come together on one, or on few, if its
 // tasks are as many apart as there are KV heads, since workgroups go round robin over the XCDs; else every XCD fetches the keys of every head.  Short
 // sequences gain less than the divisions by the number of KV heads take (0.2 us), and more than sixteen row blocks per KV head find the keys in L2 either way.
@@ -62,10 +65,10 @@ int launch_window_t(const WindowArgs& a, unsigned grid, int waves, hipStream_t s
 // 4 x 1378 on 40 heads, w = 64 58.7 / 55.3, 28 x 345 on 8 heads, w = 100 31.5 / 29.1.  Of 460 updates by KV head, geometric means of the time: 256
 // tokens and more on 8, 24, 32 or 40 KV heads 0.95...0.98 (the worst 1.02), below 0.97...1.01; on 2, 4 or 12 from 768 tokens and four row blocks on
 // 0.94...0.98, else 0.99...1.015; 24 row blocks per KV head and more 1.00...1.02.  With a sequence's workgroups on one XCD 64 x 2048 901 / 1055.
-bool by_kv_head(const WindowArgs& a, int32_t max_seqlen, const DeviceInfo& dev) {
-    const int blocks = a.n_q_heads / a.n_kv_heads * (((a.w < max_seqlen ? a.w : max_seqlen) + 31) / 32);
-    const bool even = a.n_kv_heads % dev.xccs == 0;
-    return a.xcds == 0 && blocks >= (even ? 2 : 4) && blocks <= 16 && max_seqlen >= (even ? 256 : 768);
+bool by_kv_head(const pyr_shape& s, bool equal, int32_t w, const DeviceInfo& dev) {
+    const int blocks = s.n_q_heads / s.n_kv_heads * (((w < s.max_seqlen ? w : s.max_seqlen) + 31) / 32);
+    const bool even = s.n_kv_heads % dev.xccs == 0;
+    return !seq_per_xcd(s, equal, dev) && blocks >= (even ? 2 : 4) && blocks <= 16 && s.max_seqlen >= (even ? 256 : 768);
 }
 
 template <int D, int kTiles>
@@ -151,16 +154,18 @@ int launch_window(const void* q, const void* k, const int32_t* seq_offsets_dev, 
     a.n_q_heads = s.n_q_heads;
     a.n_kv_heads = s.n_kv_heads;
     a.groups = plan.groups;
-    a.xcds = equal && s.n_seqs % dev.xccs == 0 ? dev.xccs : 0;
+    a.xcds = seq_per_xcd(s, equal, dev) ? dev.xccs : 0;
     a.waves = plan.waves;
     a.q_window = q_window;
     a.c = scale_log2;
     const int64_t n = (int64_t)s.n_seqs * plan.groups;
     if (n >= (int64_t)1 << 31) return PYR_ERR_UNSUPPORTED;
-    const bool by_kv = by_kv_head(a, s.max_seqlen, dev);
+    const bool by_kv = by_kv_head(s, equal, w, dev);
     return s.head_dim == 128 ? launch_window_d<128>(a, s.max_seqlen, (unsigned)n, plan.waves, by_kv, stream)
                              : launch_window_d<64>(a, s.max_seqlen, (unsigned)n, plan.waves, by_kv, stream);
 }
+
+int window_task_order(const pyr_shape& s, bool equal, int32_t w, const DeviceInfo& dev) { return by_kv_head(s, equal, w, dev) ? 1 : 0; }
 
 int launch_sum_parts(const float* parts, int groups, int32_t total_tokens, float* scores, hipStream_t stream) {
     hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)((total_tokens + (int64_t)63) / 64)), dim3(64 * kSumWaves), 0, stream, parts, (int32_t)groups,

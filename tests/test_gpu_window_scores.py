@@ -35,12 +35,24 @@ ONE_WALK = [
     ((1537, 1100), 9, 9, 64, 128),                              # ... fewer, but of many tokens
     ((200,) * 90, 16, 16, 64, 32),                              # several rounds of workgroups, several tasks each
 ]
-BY_KV_HEAD = [                                                  # tasks in turn over the KV heads (window.hip, by_kv_head), as many per workgroup as said
-    ((300, 290), 8, 8, 128, 33),                                # two row blocks a head; one task
-    ((700, 33, 0), 32, 8, 64, 32),                              # GQA 4
-    ((260,) * 50, 16, 8, 64, 40),                               # several
-    ((800,) * 5, 12, 4, 64, 40),                                # KV heads that do not divide over the XCDs; six row blocks each
-    ((1500, 5), 16, 8, 128, 128),                               # eight
+BY_KV_HEAD = [                                                  # tasks in turn over the KV heads (window.hip, by_kv_head) ..., tasks of a workgroup
+    ((300, 290), 8, 8, 128, 33, 2),                             # two row blocks a head
+    ((700, 33, 0), 32, 8, 64, 32, 1),                           # GQA 4
+    ((260,) * 50, 16, 8, 64, 40, 2),
+    ((800,) * 5, 12, 4, 64, 40, 2),                             # KV heads that do not divide over the XCDs; six row blocks each
+    ((1500, 5), 16, 8, 128, 128, 1),                            # eight
+    ((256, 200), 8, 8, 64, 64, 1),                              # the shortest
+    ((300,), 32, 8, 64, 128, 1),                                # sixteen row blocks
+    ((300,) * 7 + (299,), 8, 8, 64, 64, 1),                     # eight sequences, not equal
+    ((768,), 8, 4, 64, 64, 1),                                  # the shortest where KV heads do not divide over the XCDs, with four row blocks
+]
+BY_QUERY_HEAD = [                                               # ... on the other side of each limit
+    ((255, 200), 8, 8, 64, 64, 1),
+    ((300,), 8, 8, 64, 32, 1),                                  # one row block
+    ((300,), 40, 8, 64, 128, 1),                                # twenty
+    ((300,) * 8, 8, 8, 64, 64, 1),                              # equal: a sequence's workgroups on one XCD
+    ((767,), 8, 4, 64, 64, 1),
+    ((800,), 4, 4, 64, 96, 1),                                  # three
 ]
 TWO_WALKS = [
     ((2049,), 4, 4, 64, 16),                                    # a key too many
@@ -54,7 +66,20 @@ TWO_WALKS = [
 ]
 
 
-@pytest.mark.parametrize("lens,Hq,Hkv,d,w", ONE_WALK + BY_KV_HEAD)
+def task_order(lib, lens, Hq, Hkv, d, w, **device):
+    """Order of the one walk's tasks (-1: two walks), the most tasks of a workgroup."""
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32))
+    order = lib.diag_update(lib.make_shape(len(lens), int(sum(lens)), max(lens), Hq, Hkv, d), off, w, **device)
+    return order, -(-Hq * -(-min(w, max(lens)) // 32) // route(lib, lens, Hq, Hkv, d, w, **device).window_groups)
+
+
+@pytest.mark.parametrize("by_kv_head", [True, False])
+def test_order_of_the_tasks(lib, by_kv_head):
+    for *batch, tasks in BY_KV_HEAD if by_kv_head else BY_QUERY_HEAD:
+        assert task_order(lib, *batch) == (int(by_kv_head), tasks), batch
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w", ONE_WALK + [batch[:5] for batch in BY_KV_HEAD + BY_QUERY_HEAD])
 @pytest.mark.parametrize("weighted", [False, True])
 def test_one_walk(lib, lens, Hq, Hkv, d, w, weighted):
     assert route(lib, lens, Hq, Hkv, d, w).stats_waves == 0

@@ -58,7 +58,11 @@ def test_route_arguments():
         with pytest.raises(binding.PyrError):
             binding.diag_launches(*args)
     assert lib.pyr_diag_launches(ctypes.byref(shape), off.data_ptr(), 16, 0, None, 0, 256, 8, None) == -1
+    with pytest.raises(binding.PyrError):
+        binding.diag_update(shape, off, 0, 256, 8)
+    assert lib.pyr_diag_update(ctypes.byref(shape), off.data_ptr(), 16, 256, 8, None) == -1
     empty = binding.make_shape(0, 0, 0, 4, 2, 64)
+    assert binding.diag_update(empty, torch.zeros(1, dtype=torch.int32), 16, 256, 8) == -1
     assert binding.diag_launches(empty, torch.zeros(1, dtype=torch.int32), 16, 1, None, 0, 256, 8).attention_units == 0
     assert binding.diag_route(empty, torch.zeros(1, dtype=torch.int32), 16, 256, 8).score_tiles == 0
 
@@ -90,6 +94,10 @@ def test_generation_walks():
         assert r.stats_waves == r.stats_tiles == r.stats_groups == 0, batch
     for batch in window.TWO_WALKS:
         assert route(binding, *batch, **MI355X).stats_waves > 0, batch
+        assert window.task_order(binding, *batch, **MI355X)[0] == -1, batch
+    for batches, order in ((window.BY_KV_HEAD, 1), (window.BY_QUERY_HEAD, 0)):
+        for *batch, tasks in batches:
+            assert window.task_order(binding, *batch, **MI355X) == (order, tasks), batch
     # measured, two walks / one (us): 115 / 127, 66 / 71, 145 / 159, and with other numbers of row blocks per KV head 34 / 31, 1073 / 900
     for *batch, walks in (((793,) * 10, 40, 40, 128, 100, 2), ((300,) * 52, 64, 8, 128, 32, 2), ((1518,) * 69, 32, 8, 64, 32, 2),
                           ((1537,), 32, 32, 128, 64, 1), ((2048,) * 64, 32, 32, 128, 64, 1)):
