@@ -1,11 +1,12 @@
-"""The merged layer step (pyr_prefill_layer_fused: attention, score pass with the KV heads split over workgroups
-at small batch, selection, one gather for K, V, hidden rows and position ids) against the
+"""The merged layer step (pyr_prefill_layer_fused: attention and score pass, in one launch or two, the latter's tasks split over
+workgroups at small batch, selection, one gather for K, V, hidden rows and position ids) against the
 oracle and against the same step through the separate entry points."""
 import numpy as np
 import pytest
 
 from paper_2405_12532_amd import synth
 from tests import parity
+from tests.routes import route
 from tests.test_gpu_layer import run_and_check, sample_rows
 
 pytestmark = pytest.mark.gpu
@@ -46,20 +47,32 @@ def separate_calls(lib, x, wl, pos):
                 hidden_out=lib.to_host_bits(hid_out), pos_out=pos_out.cpu().numpy())
 
 
-@pytest.mark.parametrize("lens,Hq,Hkv,d,w", [
-    ((2048,), 32, 32, 128, 64),               # one prompt at the 7B head shape: 16 head groups
-    ((1000,), 32, 32, 128, 64),               # ... a shorter one, its last key block ragged
-    ((700, 33, 1000), 16, 8, 128, 64),        # ragged, GQA 2: 4 head groups
-    ((256,), 8, 8, 64, 16),                   # the smallest workload's shape: 4 head groups
-    ((5000, 300), 8, 4, 64, 32),              # a long and a short sequence, 2 head groups
-    ((300, 0, 120), 4, 4, 64, 16),            # an empty sequence
-    ((900,) * 40, 8, 8, 128, 64),             # enough key blocks for the chip: one head group
-    ((2048,) * 20, 8, 8, 128, 64),            # ... with longer sequences
-    ((300,) * 8, 8, 8, 64, 32),               # equal lengths, eight sequences: a sequence per XCD, 2 head groups
-    ((130,) * 16, 4, 2, 128, 64),             # ... GQA 2, three key blocks each, the last one ragged
-    ((1100,) * 24, 16, 16, 64, 64),           # ... one head group
-])
-def test_fused_step_equals_the_separate_calls(lib, lens, Hq, Hkv, d, w):
+FUSED = [                                     # ..., rows of partial scores of attention and scores in one launch (0: two), and of a walk of their own
+    ((2048,), 32, 32, 128, 64, 0, 4),         # one prompt at the 7B head shape
+    ((1000,), 32, 32, 128, 64, 32, 4),        # ... a shorter one, its last tile ragged
+    ((700, 33, 1000), 16, 8, 128, 64, 16, 4),     # ragged, GQA 2
+    ((256,), 8, 8, 64, 16, 8, 2),             # the smallest workload's shape
+    ((5000, 300), 8, 4, 64, 32, 0, 1),        # a long and a short sequence
+    ((300, 0, 120), 4, 4, 64, 16, 4, 1),      # an empty sequence
+    ((900,) * 40, 8, 8, 128, 64, 0, 1),       # enough keys for the chip: nothing is split
+    ((2048,) * 20, 8, 8, 128, 64, 0, 1),      # ... with longer sequences
+    ((300,) * 8, 8, 8, 64, 32, 8, 2),         # equal lengths, eight sequences
+    ((130,) * 16, 4, 2, 128, 64, 8, 1),       # ... GQA 2
+    ((1100,) * 24, 16, 16, 64, 64, 0, 2),     # ... a sequence per XCD
+    ((2500, 130, 40), 12, 4, 64, 96, 0, 4),   # ragged, nine row blocks per KV head
+    ((2060,), 40, 40, 128, 64, 0, 8),         # KV heads not a power of two
+    ((64,) * 60, 40, 40, 128, 64, 0, 4),      # many short ones
+]
+
+
+def kinds(lib, lens, Hq, Hkv, d, w, **device):
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32))
+    return lib.diag_layer(lib.make_shape(len(lens), sum(lens), max(lens), Hq, Hkv, d), off, w, **device), route(lib, lens, Hq, Hkv, d, w, **device).score_groups
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w,merged,split", FUSED)
+def test_fused_step_equals_the_separate_calls(lib, lens, Hq, Hkv, d, w, merged, split):
+    assert kinds(lib, lens, Hq, Hkv, d, w) == (merged, split)
     wl = synth.shrunk(synth.workload("cfg2"), lens, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, w=w, hidden_dim=256)
     x = parity.inputs(wl, lib)
     pos = np.random.default_rng(2).integers(0, 1 << 28, sum(lens)).astype(np.int32)
@@ -98,7 +111,7 @@ def test_single_long_prompt_against_the_oracle(lib):
 
 
 def test_fused_step_twice_on_one_workspace(lib):
-    """The arrival counters are left at zero: a second step on the same workspace, without clearing it, is right."""
+    """Nothing in the workspace has to be cleared: steps on one, filled with garbage at first, are the same."""
     wl = synth.shrunk(synth.workload("cfg2"), (1000, 700), n_q_heads=8, n_kv_heads=8, head_dim=64, w=32, hidden_dim=64)
     x = parity.inputs(wl, lib)
     q, k, v = (lib.to_device_bf16(x[n]) for n in ("q", "k", "v"))

@@ -82,13 +82,13 @@ def test_many_short_sequences(lib):
 
 
 @pytest.mark.parametrize("lens,Hq,Hkv,d,w", [
-    ((300,) * 8, 8, 8, 64, 32),                 # 2 head groups
-    ((130,) * 16, 4, 2, 128, 64),               # GQA 2, the last key block ragged
-    ((1100,) * 8, 8, 4, 64, 64),                # longer, 18 key blocks each
+    ((300,) * 8, 8, 8, 64, 32),                 # attention and scores in one launch
+    ((130,) * 16, 4, 2, 128, 64),               # ... GQA 2, the last key tile ragged
+    ((1100,) * 8, 8, 4, 64, 64),                # longer, in two
 ])
 def test_equal_lengths_in_multiples_of_eight(lib, lens, Hq, Hkv, d, w):
-    """Batches of equal lengths and a multiple of eight sequences: the score pass keeps a sequence's key blocks on
-    one XCD (another workgroup-to-block map than any ragged batch gets) and rotates the walk over the heads."""
+    """Batches of equal lengths and a multiple of eight sequences: a score walk of its own keeps a sequence's ranges on
+    one XCD (another map of workgroups than any ragged batch gets)."""
     wl = synth.shrunk(synth.workload("cfg2"), lens, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, w=w, hidden_dim=128)
     run_and_check(lib, wl)
 

@@ -30,10 +30,46 @@ SHAPES = [
 ]
 
 
+def _one_launch(lib, lens, Hq, Hkv, d, w, **device):
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32))
+    return lib.diag_layer(lib.make_shape(len(lens), sum(lens), max(lens), Hq, Hkv, d), off, w, **device)
+
+
 @pytest.mark.parametrize("lens,Hq,Hkv,d,w", SHAPES)
 @pytest.mark.parametrize("weighted", [False, True])
 def test_prefill_scores(lib, lens, Hq, Hkv, d, w, weighted):
+    """A layer of these takes its scores in the attention's launch (the strip walk by itself: tests/test_gpu_layer_launch.py)."""
+    assert _one_launch(lib, lens, Hq, Hkv, d, w) > 0
     rw = np.linspace(0.0, 1.0, w, dtype=np.float32) if weighted and w > 1 else None      # (the first weight is zero)
+    res, ref, _ = test_gpu_layer.run_and_check(lib, _wl(lens, Hq, Hkv, d, w), row_weights=rw)
+    np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
+
+
+def _spread(n, lo, hi, seed):
+    return tuple(int(x) for x in np.random.default_rng(seed).integers(lo, hi + 1, size=n))
+
+
+SPLIT = [                                                       # layers whose strip walk is split: order of the ranges, workgroups of a range
+    ((2100, 33, 700), 16, 8, 128, 64, COUNTED, 2),
+    ((2500, 130), 12, 4, 64, 96, COUNTED, 4),                   # nine row blocks per KV head: pairs span query heads, one is left over
+    ((2300,), 5, 5, 64, 100, EQUAL, 2),                         # five KV heads; four row blocks, the last of four rows
+    ((2060,), 40, 40, 128, 64, EQUAL, 8),                       # rows not a power of two apart
+    ((64,) * 60, 40, 40, 128, 64, EQUAL, 4),                    # many short ones
+    ((300,) * 14, 64, 8, 128, 100, EQUAL, 16),                  # as many workgroups as there can be
+    ((64,) * 64, 32, 32, 64, 16, SEQ_PER_XCD, 4),
+    ((520,) * 16, 2, 1, 128, 300, SEQ_PER_XCD, 2),              # twenty row blocks of one KV head, whose share no workgroup begins at
+    (_spread(200, 1, 100, 6), 12, 4, 64, 100, PLACES, 2),
+    (_spread(200, 1, 100, 6), 40, 40, 64, 64, PLACES, 2),
+    (_spread(150, 1, 150, 6), 2, 1, 128, 256, PLACES, 2),       # windows longer than the sequences
+]
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w,order,groups", SPLIT)
+@pytest.mark.parametrize("weighted", [False, True])
+def test_split_walk_of_a_layer(lib, lens, Hq, Hkv, d, w, order, groups, weighted):
+    r = route(lib, lens, Hq, Hkv, d, w)
+    assert (_one_launch(lib, lens, Hq, Hkv, d, w), r.score_order, r.score_groups) == (0, order, groups)
+    rw = np.linspace(0.25, 1.0, w, dtype=np.float32) if weighted else None
     res, ref, _ = test_gpu_layer.run_and_check(lib, _wl(lens, Hq, Hkv, d, w), row_weights=rw)
     np.testing.assert_allclose(res["scores"], ref["scores"], rtol=SCORE_RTOL, atol=1e-12)
 
@@ -58,7 +94,7 @@ def test_loose_max_seqlen(lib):
     split this batch into partial sums where there is room for them, may not do so there.  The guard behind the workspace stays
     as it was."""
     lens, H, d, w = LOOSE
-    assert route(lib, lens, H, H, d, w).score_groups > 1
+    assert route(lib, lens, H, H, d, w).score_groups > 1 and _one_launch(lib, lens, H, H, d, w) == 0
     wl = _wl(lens, H, H, d, w)
     x = parity.inputs(wl, lib, want_hidden=False)
     q, k, v = (lib.to_device_bf16(x[n]) for n in ("q", "k", "v"))
@@ -83,29 +119,32 @@ def test_loose_max_seqlen(lib):
     np.testing.assert_allclose(results[0], results[1], rtol=2e-6, atol=1e-12)
 
 
-def _spread(n, lo, hi, seed):
-    return tuple(int(x) for x in np.random.default_rng(seed).integers(lo, hi + 1, size=n))
-
-
-ORDERS = [
-    ((900,) * 7, 4, 4, 64, 32, EQUAL),                          # as many ranges in every sequence, not a multiple of the XCDs
-    ((380, 370, 384, 361), 4, 2, 128, 16, EQUAL),               # ... of lengths that differ
-    ((0, 700, 0, 0, 33, 1), 4, 2, 128, 32, COUNTED),            # counted by the workgroup: empty sequences in front and between
-    (_spread(64, 1, 400, 1), 2, 2, 64, 16, COUNTED),            # one round of the count
-    (_spread(65, 1, 400, 2) + (0,), 2, 1, 128, 16, COUNTED),    # two
-    (_spread(255, 0, 300, 3) + (600,), 2, 2, 64, 16, COUNTED),  # four, the last sequence the longest
-    (_spread(257, 0, 300, 4), 2, 2, 64, 16, PLACES),            # places for every sequence
-    (_spread(129, 1, 250, 5), 2, 2, 128, 16, PLACES),           # ... more than 128 short ones
-    ((700,) * 7, 2, 2, 64, 400, EQUAL),                         # half a sequence in the window: each starts at another range
-    ((520,) * 16, 2, 1, 128, 300, SEQ_PER_XCD),                 # ... on one XCD each
+ORDERS = [                                                      # order of the score walk's ranges, whether a layer takes its scores in the attention's launch
+    ((900,) * 7, 4, 4, 64, 32, EQUAL, True),                    # as many ranges in every sequence, not a multiple of the XCDs
+    ((380, 370, 384, 361), 4, 2, 128, 16, EQUAL, True),         # ... of lengths that differ
+    ((0, 700, 0, 0, 33, 1), 4, 2, 128, 32, COUNTED, True),      # counted by the workgroup: empty sequences in front and between
+    (_spread(64, 1, 400, 1), 2, 2, 64, 16, COUNTED, True),      # one round of the count
+    (_spread(65, 1, 400, 2) + (0,), 2, 1, 128, 16, COUNTED, True),    # two
+    (_spread(255, 0, 300, 3) + (600,), 2, 2, 64, 16, COUNTED, False), # four, the last sequence the longest
+    (_spread(257, 0, 300, 4), 2, 2, 64, 16, PLACES, False),     # places for every sequence
+    (_spread(129, 1, 250, 5), 2, 2, 128, 16, PLACES, True),     # ... more than 128 short ones
+    ((700,) * 7, 2, 2, 64, 400, EQUAL, True),                   # half a sequence in the window: each starts at another range
+    ((520,) * 16, 2, 1, 128, 300, SEQ_PER_XCD, False),          # ... on one XCD each
+    ((2100,) * 3, 2, 1, 64, 16, EQUAL, False),                  # too long for one launch
+    ((2100, 2098, 2112), 4, 2, 128, 33, EQUAL, False),
+    ((2100,) * 8, 2, 1, 64, 16, SEQ_PER_XCD, False),
+    ((0, 2100, 0, 0, 33, 1), 4, 2, 128, 32, COUNTED, False),
+    (_spread(64, 1, 400, 1) + (0, 2100), 2, 2, 64, 16, COUNTED, False),
+    (_spread(257, 0, 300, 4) + (2100,), 2, 2, 64, 16, PLACES, False),
 ]
 
 
-@pytest.mark.parametrize("lens,Hq,Hkv,d,w,order", ORDERS)
-def test_order_of_the_ranges(lib, lens, Hq, Hkv, d, w, order):
-    """Every range is taken by exactly one workgroup, whichever way the grid is laid out: scores of the prefill step; and the cache update of
-    the same batches, which these lengths send through one walk (test_order_of_the_updates_ranges has the two walks)."""
-    assert route(lib, lens, Hq, Hkv, d, w).score_order == order
+@pytest.mark.parametrize("lens,Hq,Hkv,d,w,order,one", ORDERS)
+def test_order_of_the_ranges(lib, lens, Hq, Hkv, d, w, order, one):
+    """Every range is taken by exactly one workgroup, whichever way the grid is laid out: scores of the prefill step, where it does not take
+    them in the attention's launch (the score walk of all of these by itself: tests/test_gpu_layer_launch.py); and the cache update of
+    the same batches (test_order_of_the_updates_ranges has its two walks)."""
+    assert (route(lib, lens, Hq, Hkv, d, w).score_order, _one_launch(lib, lens, Hq, Hkv, d, w) > 0) == (order, one)
     wl = _wl(lens, Hq, Hkv, d, w)
     for run in (test_gpu_layer.run_and_check, test_gpu_decode.run_and_check):
         res, ref, _ = run(lib, wl)

@@ -31,8 +31,12 @@ def test_attention_kernels():
 
 
 def test_score_walks():
-    for lens, Hq, Hkv, d, w, order in ranges.ORDERS:
-        assert route(binding, lens, Hq, Hkv, d, w, **MI355X).score_order == order, (len(lens), d, w)
+    for *batch, order, one in ranges.ORDERS:
+        assert (route(binding, *batch, **MI355X).score_order, ranges._one_launch(binding, *batch, **MI355X) > 0) == (order, one), (len(batch[0]), batch[1:])
+    for *batch, order, groups in ranges.SPLIT:
+        r = route(binding, *batch, **MI355X)
+        assert (ranges._one_launch(binding, *batch, **MI355X), r.score_order, r.score_groups) == (0, order, groups), (len(batch[0]), batch[1:])
+    assert all(ranges._one_launch(binding, *batch, **MI355X) > 0 for batch in ranges.SHAPES)
     for *batch, stats, scores in ranges.UPDATE_ORDERS:
         r = launches(binding, *batch, generation=True, **MI355X)
         assert (r.stats_order, r.window_order) == (stats, scores), (len(batch[0]), batch[1:], r.stats_order, r.window_order)
@@ -102,6 +106,12 @@ def test_generation_walks():
     for *batch, walks in (((793,) * 10, 40, 40, 128, 100, 2), ((300,) * 52, 64, 8, 128, 32, 2), ((1518,) * 69, 32, 8, 64, 32, 2),
                           ((1537,), 32, 32, 128, 64, 1), ((2048,) * 64, 32, 32, 128, 64, 1)):
         assert (route(binding, *batch, **MI355X).stats_waves > 0) == (walks == 2), batch
+
+
+def test_fused_steps():
+    from tests import test_gpu_fused as fused
+    for *batch, merged, split in fused.FUSED:
+        assert fused.kinds(binding, *batch, **MI355X) == (merged, split), batch
 
 
 def test_selection_and_gather():
