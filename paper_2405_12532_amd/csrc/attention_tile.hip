@@ -32,6 +32,7 @@ __global__ __launch_bounds__(1024) void tile_map_kernel(const int32_t* __restric
 template <int D, int kGroups>
 int launch_tile(const TileArgs& a, const NoFront& rest, dim3 grid, hipStream_t stream) {
     using T = TileLds<D, kGroups>;
+    static_assert(sizeof(TileArgs) + sizeof(NoFront) <= 112, "short arguments");
     static std::atomic<uint64_t> lds_set{0};
     if (ensure_dynamic_lds((const void*)attention_tile_kernel<D, kGroups, NoFront>, T::kBytes, &lds_set) != PYR_OK) return PYR_ERR_LAUNCH;
     hipLaunchKernelGGL((attention_tile_kernel<D, kGroups, NoFront>), grid, dim3(kGroups * 256), T::kBytes, stream, a, rest);

@@ -72,6 +72,7 @@ struct TwoSources {
     }
     __device__ __forceinline__ void position(int32_t, int64_t) const {}
 };
+static_assert(6 * sizeof(void*) + sizeof(TwoSources) + 5 * sizeof(int32_t) <= 112, "short arguments");
 struct AnySources {
     GatherSources g;
     __device__ __forceinline__ int32_t end1() const { return g.chunks[0] + (g.n > 1 ? g.chunks[1] : 0); }

@@ -50,6 +50,7 @@ struct WindowArgs {
     int32_t q_window;                         // 0: q by packed row; else by (sequence, window slot)
     float c;
 };
+static_assert(sizeof(WindowArgs) <= 112, "short arguments");
 
 // Sequence and place in it of workgroup `id`.
 __device__ __forceinline__ void window_place(const WindowArgs& a, int id, int* b, int* g) {
