@@ -15,7 +15,10 @@ namespace {
 template <int D, int kGroups, int kTiles, bool kWeighted>
 struct WindowFront {
     static constexpr bool kAny = true;
-    static constexpr int kWaves = D == 64 && kGroups == 1 && kTiles < 8 ? 3 : 2;      // (as many tiles a compute unit as without it, where they fit)
+    // As many tiles a compute unit as without it.  At d = 64 with four tiles a wavefront that holds the kernel to 168 registers, two to four of which
+    // wait in scratch memory: 30 such layers take 7 % longer (0.93 to 1.16) with two workgroups a compute unit and none there.  (d = 128, eight
+    // tiles a wavefront: one to four with 256 registers.  Their accesses make the counted waits for a walk's tiles stricter, never shorter.)
+    static constexpr int kWaves = D == 64 && kGroups == 1 && kTiles < 8 ? 3 : 2;
     const float* row_weights;
     float* sums;                                      // [groups, total_tokens]
     int32_t w, total_tokens, groups;

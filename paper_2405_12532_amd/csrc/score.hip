@@ -746,7 +746,9 @@ struct UpdatePlan {
 // per KV head, where the prediction flatters it, 11.5 % with more than sixteen.  Of 1200 updates of random shapes up to 2048 rows, each timed both ways, the choice takes
 // 0.5 % longer than the faster form in the mean (0.8 % with the lines 8 and 3 % lower that were drawn before the one walk's tasks went by KV head); it takes one walk
 // against two that are more than 3 % faster in 6 (42 x 215 at most on 32/8 heads, d = 64, w = 100 43 / 51) and keeps two against one that is more than 3 % faster
-// in 51, by 28 % at most (40 x 254...280 on 64/8 heads, w = 48 84 / 66, 4 x 841 on 64/8 heads, w = 128 46.5 / 36.9).
+// in 51, by 28 % at most (40 x 254...280 on 64/8 heads, w = 48 84 / 66, 4 x 841 on 64/8 heads, w = 128 46.5 / 36.9).  The lines stand where a batch's tasks go
+// by query head too (window.hip, by_kv_head): 400 such updates between these lines and those take 0.918 of the two walks' time by one, 0.91 to 0.94 by
+// the limit of that rule that keeps them out; 21 are more than 3 % slower, 16 % at most (48 x 75 on 64/8 heads, w = 48 45.6 / 52.9, 53 x 479 on 32/4, w = 16 50.7 / 57.4).
 UpdatePlan plan_update(const pyr_shape& s, const BatchCut& cut, int32_t w, const DeviceInfo& dev) {
     UpdatePlan p{};
     const size_t room = window_score_part_bytes(s, w), row = (size_t)s.total_tokens * sizeof(float);
@@ -771,7 +773,9 @@ UpdatePlan plan_update(const pyr_shape& s, const BatchCut& cut, int32_t w, const
 //   (query rows count as one), 0.825 of that at d = 64; 0.86 of what all of them take adds to A as a share of the chip; joined with the longest workgroup as in
 //   plan_strip.  A row of partial sums costs the selection 0.029.  At d = 64 five tiles a wavefront and more leave a compute unit
 //   room for two workgroups instead of three: 12 % more for the tiles.  Where tiles of two groups fill their rounds, three at most, so far that the windows
-//   open another: a tenth of A (1 x 2048 on 32 heads, two rounds exactly: 73.9 / 76.0).
+//   open another: a tenth of A.  Two launches / one on both sides of two rounds, 512 tiles: 1 x 1900 on 32 heads (480) 68.5 / 65.7, 1 x 1920 68.8 / 65.9,
+//   1 x 1985 (512) 72.2 / 73.9, 1 x 2048 74.2 / 75.6 (lengths between get tiles of one group, which go up to 1024 keys here); on 32/8 heads 1 x 1920 61.8 / 58.4, 1 x 2048 66.1 / 67.3.  A single round does not mind (1 x 1024 on 32 heads,
+//   256 tiles 42.4 / 36.0), but 1 x 2048 on 16 heads is kept apart by the term: 55.7 / 49.4.
 // Fitted to 1300 layers of random shapes (fifteen head shapes, w = 16...256, one sequence to 100, 32...2048 tokens, equal and ragged, with and without weights and
 // hidden rows), each timed apart and with up to nine numbers of rows on inputs that change from call to call; one launch is taken where it is predicted to save
 // 5 % of A, C and 10 us.  That chose it for 852 of them; over all 1300 the geometric mean of the time is 0.899 of that of the two launches (0.885 for
